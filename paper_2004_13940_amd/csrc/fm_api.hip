@@ -6,6 +6,8 @@
 #include <string.h>
 
 #include <algorithm>
+#include <mutex>
+#include <utility>
 
 #include "fm_internal.h"
 
@@ -22,25 +24,147 @@ int fm_fail(fm_matrix* m, int code, const char* fmt, ...)
     return code;
 }
 
+// Device blocks that handles have given back, kept for the next handle.  A scoring service makes and destroys a handle
+// per batch of requests and a build makes and frees gigabytes of scratch: mapping and unmapping that memory cost 8 ms
+// of the 60 ms that opening a data set of 4.9e7 entries took.  Blocks come back idle (see fm_dev_free), so any thread
+// and stream may take them.  Bounded to POOL_CAP per process; all of it goes back to the driver when an allocation
+// fails.  Requests up to POOL_MIN are left to the runtime, which hands them out of its own chunks in under a microsecond.
+namespace {
+constexpr size_t POOL_MIN = size_t(1) << 20;
+constexpr size_t POOL_CAP = size_t(4) << 30;
+constexpr size_t POOL_PINNED_CAP = 32;  // pinned scalar blocks
+
+struct PoolBlock {
+    void* p;
+    size_t bytes;
+    int device;
+};
+std::mutex g_pool_lock;
+std::vector<PoolBlock> g_pool;  // oldest first
+size_t g_pool_bytes = 0;
+std::vector<std::pair<int, void*>> g_pinned;
+
+// Sizes are rounded so that a block fits the next request of about the same size: to 1/16 of the power of two below.
+size_t pool_round(size_t bytes)
+{
+    size_t unit = size_t(1) << 16;
+    while (unit * 32 <= bytes) unit <<= 1;
+    return (bytes + unit - 1) / unit * unit;
+}
+
+void pool_drain()
+{
+    std::vector<PoolBlock> all;
+    {
+        std::lock_guard<std::mutex> g(g_pool_lock);
+        all.swap(g_pool);
+        g_pool_bytes = 0;
+    }
+    for (const PoolBlock& b : all) (void)hipFree(b.p);
+}
+
+void* pool_take(size_t bytes, int device)
+{
+    std::lock_guard<std::mutex> g(g_pool_lock);
+    for (size_t i = g_pool.size(); i-- > 0;)
+        if (g_pool[i].bytes == bytes && g_pool[i].device == device) {
+            void* p = g_pool[i].p;
+            g_pool.erase(g_pool.begin() + (ptrdiff_t)i);
+            g_pool_bytes -= bytes;
+            return p;
+        }
+    return nullptr;
+}
+
+void pool_give(void* p, size_t bytes, int device)
+{
+    std::vector<void*> evicted;
+    {
+        std::lock_guard<std::mutex> g(g_pool_lock);
+        if (bytes > POOL_CAP) {
+            evicted.push_back(p);
+        } else {
+            while (g_pool_bytes + bytes > POOL_CAP) {
+                evicted.push_back(g_pool.front().p);
+                g_pool_bytes -= g_pool.front().bytes;
+                g_pool.erase(g_pool.begin());
+            }
+            g_pool.push_back({p, bytes, device});
+            g_pool_bytes += bytes;
+        }
+    }
+    for (void* q : evicted) (void)hipFree(q);
+}
+}  // namespace
+
 int fm_dev_alloc(fm_matrix* m, void** p, size_t bytes)
 {
     *p = nullptr;
     if (bytes == 0) bytes = 16;
-    hipError_t e = hipMalloc(p, bytes);
-    if (e != hipSuccess) {
-        (void)hipGetLastError();
-        return fm_fail(m, FM_ENOMEM, "hipMalloc of %zu bytes failed: %s", bytes, hipGetErrorString(e));
+    const bool pooled = bytes > POOL_MIN;
+    const size_t want = pooled ? pool_round(bytes) : bytes;
+    if (pooled) *p = pool_take(want, m->device);
+    if (*p == nullptr) {
+        hipError_t e = hipMalloc(p, want);
+        if (e != hipSuccess) {  // what the pool holds may be what is missing
+            (void)hipGetLastError();
+            pool_drain();
+            e = hipMalloc(p, want);
+        }
+        if (e != hipSuccess) {
+            (void)hipGetLastError();
+            return fm_fail(m, FM_ENOMEM, "hipMalloc of %zu bytes failed: %s", bytes, hipGetErrorString(e));
+        }
     }
-    m->allocs.push_back(*p);
+    m->allocs.push_back({*p, pooled ? want : 0});
     return FM_OK;
 }
 
+// No work that uses the block may be in flight on any stream: it may be handed to another handle at once.
 void fm_dev_free(fm_matrix* m, void* p)
 {
     if (p == nullptr) return;
-    auto it = std::find(m->allocs.begin(), m->allocs.end(), p);
-    if (it != m->allocs.end()) m->allocs.erase(it);
-    (void)hipFree(p);
+    size_t bytes = 0;
+    for (size_t i = m->allocs.size(); i-- > 0;)
+        if (m->allocs[i].p == p) {
+            bytes = m->allocs[i].pool_bytes;
+            m->allocs.erase(m->allocs.begin() + (ptrdiff_t)i);
+            break;
+        }
+    if (bytes > 0)
+        pool_give(p, bytes, m->device);
+    else
+        (void)hipFree(p);
+}
+
+static int pinned_alloc(fm_matrix* m)
+{
+    {
+        std::lock_guard<std::mutex> g(g_pool_lock);
+        for (size_t i = g_pinned.size(); i-- > 0;)
+            if (g_pinned[i].first == m->device) {
+                m->h_scal = (double*)g_pinned[i].second;
+                g_pinned.erase(g_pinned.begin() + (ptrdiff_t)i);
+                return FM_OK;
+            }
+    }
+    if (hipHostMalloc((void**)&m->h_scal, FM_PINNED_DOUBLES * sizeof(double)) == hipSuccess) return FM_OK;
+    (void)hipGetLastError();
+    m->h_scal = nullptr;
+    return fm_fail(m, FM_ENOMEM, "pinned allocation failed");
+}
+
+static void pinned_free(fm_matrix* m)
+{
+    if (m->h_scal == nullptr) return;
+    {
+        std::lock_guard<std::mutex> g(g_pool_lock);
+        if (g_pinned.size() < POOL_PINNED_CAP) {
+            g_pinned.push_back({m->device, m->h_scal});
+            return;
+        }
+    }
+    (void)hipHostFree(m->h_scal);
 }
 
 ProfScope::ProfScope(fm_matrix* m_, hipStream_t st_, int id_) : m(m_), st(st_), id(id_)
@@ -104,13 +228,20 @@ extern "C" const char* fm_last_error(const fm_matrix* m) { return m != nullptr ?
 extern "C" int fm_destroy(fm_matrix* m)
 {
     if (m == nullptr) return FM_OK;
+    int current = -1;  // the blocks go back idle: wait for the device they are on
+    const bool elsewhere = hipGetDevice(&current) == hipSuccess && current != m->device;
+    if (elsewhere) (void)hipSetDevice(m->device);
     (void)hipDeviceSynchronize();
     fm_drop_graph(m);
     if (m->gstream != nullptr) (void)hipStreamDestroy(m->gstream);
     if (m->g_in != nullptr) (void)hipEventDestroy(m->g_in);
     if (m->g_out != nullptr) (void)hipEventDestroy(m->g_out);
-    for (void* p : m->allocs) (void)hipFree(p);
-    if (m->h_scal != nullptr) (void)hipHostFree(m->h_scal);
+    for (const FmAlloc& a : m->allocs)
+        if (a.pool_bytes > 0)
+            pool_give(a.p, a.pool_bytes, m->device);
+        else
+            (void)hipFree(a.p);
+    pinned_free(m);
     if (m->side1 != nullptr) (void)hipStreamDestroy(m->side1);
     if (m->side2 != nullptr) (void)hipStreamDestroy(m->side2);
     for (hipEvent_t e : {m->ev_fork, m->ev_join1, m->ev_join2})
@@ -120,7 +251,26 @@ extern "C" int fm_destroy(fm_matrix* m)
         (void)hipEventDestroy(r.b);
     }
     for (hipEvent_t e : m->prof_pool) (void)hipEventDestroy(e);
+    if (elsewhere) (void)hipSetDevice(current);
     delete m;
+    return FM_OK;
+}
+
+// The first violation of the CSR rules in row order, for the message (the check itself runs on the device).
+static int first_csr_error(int64_t N, int64_t D, int64_t nnz, const int64_t* rowptr, const int32_t* col)
+{
+    for (int64_t i = 0; i < N; ++i) {
+        const int64_t b = rowptr[i], e = rowptr[i + 1];
+        if (e < b || e > nnz) return fm_fail(nullptr, FM_EUNSORTED, "rowptr not monotone at row %lld", (long long)i);
+        for (int64_t t = b; t < e; ++t) {
+            const int64_t c = col[t];
+            if (c < 0 || c >= D)
+                return fm_fail(nullptr, FM_ERANGE, "column %lld of row %lld outside [0,%lld)", (long long)c,
+                               (long long)i, (long long)D);
+            if (t > b && col[t - 1] >= c)
+                return fm_fail(nullptr, FM_EUNSORTED, "columns of row %lld not strictly ascending", (long long)i);
+        }
+    }
     return FM_OK;
 }
 
@@ -134,39 +284,34 @@ extern "C" int fm_build_csr(int64_t N, int64_t D, int64_t nnz, const int64_t* ro
     if (N >= (1LL << 31) || D >= (1LL << 31) || nnz >= (1LL << 32))
         return fm_fail(nullptr, FM_ERANGE, "N, D must be < 2^31 and nnz < 2^32");
     if (rowptr[0] != 0 || rowptr[N] != nnz) return fm_fail(nullptr, FM_EUNSORTED, "rowptr[0] != 0 or rowptr[N] != nnz");
-    for (int64_t i = 0; i < N; ++i) {
-        const int64_t b = rowptr[i], e = rowptr[i + 1];
-        if (e < b || e > nnz) return fm_fail(nullptr, FM_EUNSORTED, "rowptr not monotone at row %lld", (long long)i);
-        for (int64_t t = b; t < e; ++t) {
-            const int64_t c = col[t];
-            if (c < 0 || c >= D)
-                return fm_fail(nullptr, FM_ERANGE, "column %lld of row %lld outside [0,%lld)", (long long)c,
-                               (long long)i, (long long)D);
-            if (t > b && col[t - 1] >= c)
-                return fm_fail(nullptr, FM_EUNSORTED, "columns of row %lld not strictly ascending", (long long)i);
-        }
-    }
     hipStream_t st = (hipStream_t)hip_stream;
     fm_matrix* m = new (std::nothrow) fm_matrix();
     if (m == nullptr) return fm_fail(nullptr, FM_ENOMEM, "out of host memory");
     m->N = N;
     m->D = D;
     m->nnz = nnz;
-    int rc = FM_OK;
+    int rc = hipGetDevice(&m->device) == hipSuccess ? FM_OK : fm_fail(m, FM_EHIP, "no current device");
     auto up = [&](void** d, const void* h, size_t bytes) -> int {
         FM_TRY(fm_dev_alloc(m, d, bytes));
         if (bytes > 0) FM_HIP(m, hipMemcpyAsync(*d, h, bytes, hipMemcpyHostToDevice, st));
         return FM_OK;
     };
-    rc = up((void**)&m->rowptr, rowptr, (size_t)(N + 1) * sizeof(int64_t));
+    if (rc == FM_OK) rc = up((void**)&m->rowptr, rowptr, (size_t)(N + 1) * sizeof(int64_t));
     if (rc == FM_OK) rc = up((void**)&m->col, col, (size_t)nnz * sizeof(int32_t));
     if (rc == FM_OK) rc = up((void**)&m->val, val, (size_t)nnz * sizeof(float));
     if (rc == FM_OK) rc = fm_dev_alloc(m, (void**)&m->scal, (8 + FM_REDUCE_TMP) * sizeof(double));
-    if (rc == FM_OK && hipHostMalloc((void**)&m->h_scal, 8 * sizeof(double)) != hipSuccess)
-        rc = fm_fail(m, FM_ENOMEM, "pinned allocation failed");
-    if (rc == FM_OK && hipStreamSynchronize(st) != hipSuccess) rc = fm_fail(m, FM_EHIP, "upload failed");
+    if (rc == FM_OK) rc = pinned_alloc(m);
+    bool valid = false;
+    if (rc == FM_OK) rc = fm_check_csr(m, st, &valid);  // waits for the uploads
+    if (!valid) {  // also where a step failed: what is wrong with the matrix itself is reported first
+        const int bad = first_csr_error(N, D, nnz, rowptr, col);
+        if (bad != FM_OK) {
+            fm_destroy(m);  // g_build_error holds the message
+            return bad;
+        }
+        if (rc == FM_OK) rc = fm_fail(m, FM_EHIP, "the matrix changed while it was uploaded");
+    }
     if (rc == FM_OK) rc = fm_noalloc_init_device(m);  // set-up for fm_forward_noalloc on this device
-    if (rc == FM_OK) rc = fm_dense_detect(m, st);
     if (rc != FM_OK) {
         g_build_error = m->err;
         fm_destroy(m);
@@ -365,6 +510,7 @@ void fm_drop_graph(fm_matrix* m)
 void fm_drop_workspace(fm_matrix* m)
 {
     fm_drop_graph(m);
+    if (m->wsK != 0) (void)hipDeviceSynchronize();  // the blocks go back idle
     for (void* p : {(void*)m->aux, (void*)m->dV, (void*)m->dwn, (void*)m->part, (void*)m->row_part})
         fm_dev_free(m, p);
     m->aux = m->dV = m->part = m->row_part = nullptr;

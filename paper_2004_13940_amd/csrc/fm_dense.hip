@@ -22,15 +22,6 @@ constexpr int FM_DENSE_CHUNKS = 4096;  // row chunks (one wavefront each) of the
 
 __device__ __forceinline__ int c_row(int v, int lane) { return 8 * (v / 4) + 4 * (lane / 32) + (v % 4); }
 
-// bad[0] = 1 unless rowptr[i] == i * D and col[e] == e % D everywhere
-__global__ void k_dense_check(const int64_t* __restrict__ rowptr, const int32_t* __restrict__ col, int64_t N, int64_t D,
-                              int32_t* __restrict__ bad)
-{
-    const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (e < N * D && col[e] != (int32_t)(e % D)) bad[0] = 1;
-    if (e <= N && rowptr[e] != e * D) bad[0] = 1;
-}
-
 // Forward pass over 32 rows per wavefront.  DB = D / 32, KB = K / 32.
 // LDS: w (D floats), squared row norms of V (D floats), then one tile of 32 x S floats per wavefront,
 // S = max(D, K) + 1 (odd: the column-wise reads of the tile spread over the banks).
@@ -270,29 +261,6 @@ __global__ void k_dense_index(int64_t D, int64_t nchunks, int32_t* __restrict__ 
 }
 
 }  // namespace
-
-int fm_dense_detect(fm_matrix* m, hipStream_t st)
-{
-    m->is_dense = false;
-    const int64_t N = m->N, D = m->D;
-    if (N <= 0 || D <= 0 || D > 0x7fffffffLL / 2 || m->nnz != N * D) return FM_OK;
-    int32_t* bad = nullptr;
-    FM_TRY(fm_dev_alloc(m, (void**)&bad, sizeof(int32_t)));
-    int32_t h_bad = 1;
-    hipError_t e = hipMemsetAsync(bad, 0, sizeof(int32_t), st);
-    if (e == hipSuccess) {
-        const int64_t n = m->nnz > N + 1 ? m->nnz : N + 1;
-        hipLaunchKernelGGL(k_dense_check, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st,
-                           (const int64_t*)m->rowptr, (const int32_t*)m->col, N, D, bad);
-        e = hipGetLastError();
-    }
-    if (e == hipSuccess) e = hipMemcpyAsync(&h_bad, bad, sizeof(int32_t), hipMemcpyDeviceToHost, st);
-    if (e == hipSuccess) e = hipStreamSynchronize(st);
-    fm_dev_free(m, bad);
-    if (e != hipSuccess) return fm_fail(m, FM_EHIP, "dense check failed: %s", hipGetErrorString(e));
-    m->is_dense = h_bad == 0;
-    return FM_OK;
-}
 
 // D and K in {32, 64}: the tiles are 32 wide and the accumulators of both kernels stay in registers
 bool fm_dense_shape_ok(const fm_matrix* m, int32_t K)

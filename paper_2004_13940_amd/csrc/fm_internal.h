@@ -71,6 +71,15 @@ enum fm_kernel_id {
     FMK_COUNT
 };
 
+// What one workgroup of the CSR check found, written straight to pinned host memory.
+struct FmCheck {
+    int64_t bad;        // pointers not monotone or outside [0, nnz], or a column outside [0, D)
+    int64_t descents;   // entries whose column is not above that of the entry before, minus those that open a row
+    int64_t not_dense;  // row i does not start at i * D
+};
+constexpr int FM_CHECK_BLOCKS = 512;
+constexpr size_t FM_PINNED_DOUBLES = 8 + FM_CHECK_BLOCKS * sizeof(FmCheck) / sizeof(double);
+
 // Work items for columns longer than `seg` entries (of one matrix, or of all strata
 // concatenated).  Offsets in item_beg are global offsets into the entry arrays.  Items of
 // a column are numbered consecutively (long_first); partial sums live at the item id.
@@ -105,6 +114,11 @@ struct LongIndex {
 struct ProfRec {
     int id;
     hipEvent_t a, b;
+};
+
+struct FmAlloc {
+    void* p;
+    size_t pool_bytes;  // size of a block that goes back to the pool; 0: to the runtime
 };
 
 struct fm_matrix {
@@ -175,7 +189,7 @@ struct fm_matrix {
     float* part = nullptr;      // [max items * part_stride(K)] partial sums of the items, see fm_part_stride
     float* row_part = nullptr;  // [2 * row blocks]: loss, sum r
     double* scal = nullptr;     // device scalars: 0 loss, 1 sum r, 2 |w|^2, 3 |V|^2
-    double* h_scal = nullptr;   // pinned mirror
+    double* h_scal = nullptr;   // pinned: 8 doubles that mirror scal, then one FmCheck per workgroup of k_check_csr
     bool aux_full = false;      // a, q valid (not only G, r)
     bool aux_held = false;      // the aggregate rows hold the result of a pass (fm_get_aux may read them)
     // side streams so that the LDS-bound and the memory-bound column kernels overlap
@@ -198,7 +212,8 @@ struct fm_matrix {
     int64_t prof_launches[FMK_COUNT] = {0};
     double prof_ms[FMK_COUNT] = {0};
     // bookkeeping
-    std::vector<void*> allocs;
+    int device = 0;  // the device the handle was created on
+    std::vector<FmAlloc> allocs;
     std::string err;
 };
 
@@ -241,6 +256,8 @@ struct ProfScope {
 };
 
 // ---- build (fm_build.hip) ----
+// Checks the uploaded CSR arrays on the device and sets is_dense; waits for the stream.
+int fm_check_csr(fm_matrix* m, hipStream_t st, bool* valid);
 int fm_scan_exclusive_i64(fm_matrix* m, int64_t* d, int64_t n, hipStream_t st);
 int fm_sort_by_key_u32(fm_matrix* m, uint32_t* keys, uint32_t* idx, uint32_t* keys_alt, uint32_t* idx_alt,
                        int64_t n, int bits, hipStream_t st, bool* result_in_alt);
@@ -285,7 +302,6 @@ int fm_noalloc_init_device(fm_matrix* m);
 int fm_pack_aux(fm_matrix* m, const float* r, const float* G, hipStream_t st);  // packed layout only
 int fm_to_half(fm_matrix* m, const float* x, _Float16* out, int64_t n, hipStream_t st);  // round to nearest even
 // dense matrices (fm_dense.hip)
-int fm_dense_detect(fm_matrix* m, hipStream_t st);           // sets is_dense
 bool fm_dense_shape_ok(const fm_matrix* m, int32_t K);       // the dense kernels exist for this D and K
 int fm_dense_build_index(fm_matrix* m, hipStream_t st);      // ldense, dense_chunk_rows, dense_chunks
 int fm_launch_rows_dense(fm_matrix* m, const RowArgs& A, hipStream_t st);

@@ -1,0 +1,65 @@
+"""Building a handle on the GPU machine: the checks of the uploaded CSR arrays, and blocks reused from handle to handle."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+def _csr(N, D, per_row):
+    rowptr = np.arange(N + 1, dtype=np.int64) * per_row
+    col = (np.arange(N)[:, None] % (D - per_row) + np.arange(per_row)[None, :]).astype(np.int32).ravel()
+    return rowptr, col, np.ones(N * per_row, np.float32)
+
+
+@pytest.mark.parametrize("N", [1, 300, 200_003])  # one workgroup, a few, every workgroup with several rounds
+@pytest.mark.parametrize("where", [0, -1])
+@pytest.mark.parametrize("what,code", [("ok", 0), ("equal", -3), ("descending", -3), ("negative", -4), ("too large", -4),
+                                       ("pointer", -3)])
+def test_csr_rules_on_the_device(N, where, what, code):
+    from paper_2004_13940_amd import binding as B
+    D, k = 50, 3
+    rowptr, col, val = _csr(N, D, k)
+    i = 0 if where == 0 else N - 1
+    if what == "equal":
+        col[i * k + 1] = col[i * k]
+    elif what == "descending":
+        col[i * k + 2] = col[i * k]
+    elif what == "negative":
+        col[i * k] = -1
+    elif what == "too large":
+        col[i * k + 2] = D
+    elif what == "pointer":
+        if N == 1:
+            pytest.skip("one row: both pointers are checked on the host")
+        rowptr[i if i > 0 else 1] = N * k + 1
+    if code == 0:
+        B.Matrix(N, D, rowptr, col, val).close()
+        return
+    with pytest.raises(B.FMError) as e:
+        B.Matrix(N, D, rowptr, col, val)
+    assert e.value.code == code and (what == "pointer" or f" {i} " in str(e.value))
+
+
+def test_handles_one_after_the_other_reuse_blocks_with_their_own_content():
+    """Blocks above the pool's smallest size come back with an older handle's content."""
+    import torch
+    from paper_2004_13940_amd import binding as B
+    rng = np.random.default_rng(5)
+    N, D, k, K = 40_000, 3_000, 12, 16
+    w0, w = torch.zeros(1, device="cuda"), torch.from_numpy(rng.standard_normal(D).astype(np.float32)).cuda()
+    V = torch.zeros(D * K, device="cuda")
+    for shift in range(3):
+        rowptr, col, val = _csr(N, D, k)
+        val = (val * (1 + shift) + rng.random(N * k).astype(np.float32)).astype(np.float32)
+        m = B.Matrix(N, D, rowptr, col, val)
+        m.fm_build_csc()
+        p = B.make_params(K, B.FM_LOSS_SQUARED, 0.0, 0.0, 0.1)
+        a = torch.empty(N, device="cuda")
+        m.fm_forward(p, None, w0, w, V, a=a)
+        want = (val.reshape(N, k).astype(np.float64) * w.cpu().numpy().astype(np.float64)[col.reshape(N, k)]).sum(1)
+        got = a.cpu().numpy()
+        assert np.max(np.abs(got - want)) <= 1e-5 * np.max(np.abs(want))
+        colptr, row, cval = m.fm_get_csc()
+        order = np.argsort(col, kind="stable")
+        assert np.array_equal(row, np.repeat(np.arange(N), k)[order]) and np.array_equal(cval, val[order])
+        m.close()
