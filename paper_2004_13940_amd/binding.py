@@ -45,21 +45,36 @@ EXPORTS = ["fm_build_csr", "fm_build_csc", "fm_partition", "fm_partition_placed"
 FM_OPT_AUX_PLANAR, FM_OPT_SIDE_STREAMS, FM_OPT_LAZY_REG, FM_OPT_GRAPH, FM_OPT_DENSE_ROWS = 0, 1, 2, 3, 4
 
 _lib = None
+_torch = None
 
 
 def load() -> ctypes.CDLL:
     """Load the shared library; raises if it has not been built."""
-    global _lib
+    global _lib, _torch
     if _lib is None:
         if not os.path.exists(LIB_PATH):
             raise FileNotFoundError(f"{LIB_PATH} is missing: run `python -m paper_2004_13940_amd.build` "
                                     "(there is no CPU fallback)")
         # PyTorch ships its own HIP runtime under the same soname; it must be the one this
         # library binds to, so that streams and device pointers of torch tensors are valid here
-        import torch  # noqa: F401
+        import torch
         lib = ctypes.CDLL(LIB_PATH)
         for name in EXPORTS:
             getattr(lib, name).restype = ctypes.c_int
+        # arguments converted by ctypes from plain integers, without an object for each
+        vp, i32, i64 = ctypes.c_void_p, ctypes.c_int32, ctypes.c_int64
+        for name, types in {
+                "fm_build_csr": [i64] * 3 + [vp] * 5, "fm_build_csc": [vp] * 2, "fm_partition": [vp, i32, vp],
+                "fm_partition_placed": [vp, i32, vp, vp], "fm_partition_batches": [vp, i32, vp],
+                "fm_get_csc": [vp] * 4, "fm_get_block_index": [vp] * 4, "fm_get_stratum_nnz": [vp, i32, vp],
+                "fm_get_stratum_csr": [vp, i32] + [vp] * 3, "fm_get_stratum_csc": [vp, i32] + [vp] * 3,
+                "fm_get_batch_csc": [vp, i32] + [vp] * 3, "fm_forward": [vp] * 13, "fm_forward_noalloc": [vp] * 13,
+                "fm_evaluate": [vp] * 8, "fm_gradient": [vp] * 10, "fm_sgd_epoch": [vp] * 8,
+                "fm_minibatch_epoch": [vp] * 8, "fm_stratified_epoch": [vp] * 8, "fm_stratified_begin": [vp] * 7,
+                "fm_stratified_step": [vp, vp, i32] + [vp] * 5, "fm_stratified_end": [vp] * 4, "fm_get_aux": [vp] * 6,
+                "fm_profile_read": [vp] * 3, "fm_destroy": [vp]}.items():
+            getattr(lib, name).argtypes = types
+        _torch = torch
         lib.fm_last_error.restype = ctypes.c_char_p
         lib.fm_last_error.argtypes = [ctypes.c_void_p]
         lib.fm_profile_kernel_name.restype = ctypes.c_char_p
@@ -68,26 +83,25 @@ def load() -> ctypes.CDLL:
 
 
 def _vp(x):
-    """void* of a torch tensor (device), a numpy array (host) or None."""
+    """Address of a torch tensor (device) or a numpy array (host), or None."""
     if x is None:
-        return ctypes.c_void_p(None)
+        return None
     if isinstance(x, np.ndarray):
-        return ctypes.c_void_p(x.ctypes.data)
-    return ctypes.c_void_p(x.data_ptr())
+        return x.ctypes.data
+    return x.data_ptr()
 
 
 def _stream(stream):
     if stream is None:
-        import torch
-        stream = torch.cuda.current_stream()
-    return ctypes.c_void_p(stream.cuda_stream)
+        c = _torch._C  # the handle of torch.cuda.current_stream() without building the object
+        return c._cuda_getCurrentRawStream(c._cuda_getDevice())
+    return stream.cuda_stream
 
 
 def _dev(t, n, what):
-    import torch
     if t is None:
         return
-    if not (isinstance(t, torch.Tensor) and t.is_cuda and t.dtype == torch.float32 and t.is_contiguous()):
+    if not (isinstance(t, _torch.Tensor) and t.is_cuda and t.dtype is _torch.float32 and t.is_contiguous()):
         raise TypeError(f"{what} must be a contiguous float32 CUDA tensor")
     if t.numel() != n:
         raise ValueError(f"{what} has {t.numel()} elements, expected {n}")
@@ -221,7 +235,7 @@ class Matrix:
         loss = ctypes.c_double(0.0)
         self._check(load().fm_forward(self._h, ctypes.byref(p), _vp(y), _vp(w0), _vp(w), _vp(V), _vp(yhat),
                                       _vp(a), _vp(G), _vp(q), _vp(r),
-                                      ctypes.byref(loss) if want_loss else ctypes.c_void_p(None), _stream(stream)))
+                                      ctypes.byref(loss) if want_loss else None, _stream(stream)))
         return loss.value if want_loss else None
 
     def fm_forward_noalloc(self, p: fm_params, y, w0, w, V, yhat=None, a=None, G=None, q=None, r=None,
@@ -249,7 +263,7 @@ class Matrix:
         _dev(y, N, "y"); _dev(w0, 1, "w0"); _dev(w, D, "w"); _dev(V, D * K, "V")
         obj = (ctypes.c_double * 2)(0.0, 0.0)
         self._check(fn(self._h, ctypes.byref(p), _vp(y), _vp(w0), _vp(w), _vp(V),
-                       obj if want_objective else ctypes.c_void_p(None), _stream(stream)))
+                       obj if want_objective else None, _stream(stream)))
         return (obj[0], obj[1]) if want_objective else None
 
     def fm_sgd_epoch(self, p, y, w0, w, V, want_objective=False, stream=None):

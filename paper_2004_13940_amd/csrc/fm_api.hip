@@ -575,9 +575,10 @@ static void fill_long(const fm_matrix* m, ColArgs& A, const LongIndex& li, int32
     A.tile_rows = li.tile_rows;
     A.ntiles = strat ? 0 : li.ntiles;
     A.tile_ptr = li.tile_ptr;
-    A.lin_mode = 0;
-    A.vlong = strat ? nullptr : li.vlong;
-    A.nvlong = strat ? 0 : li.nvlong;
+    const int64_t v0 = strat && !li.h_vlong_off.empty() ? li.h_vlong_off[s] : 0;
+    const int64_t v1 = strat ? (li.h_vlong_off.empty() ? 0 : li.h_vlong_off[s + 1]) : li.nvlong;
+    A.vlong = li.vlong != nullptr ? li.vlong + v0 : nullptr;
+    A.nvlong = v1 - v0;
     A.vlong_items = m->tune.vlong;
     const int64_t s0 = strat ? li.h_short_off[s] : 0, s1 = strat ? li.h_short_off[s + 1] : li.nshort;
     A.short_col = li.short_col != nullptr ? li.short_col + s0 : nullptr;
@@ -621,6 +622,36 @@ static int half_copy(fm_matrix* m, const fm_params* p, const float* V, const _Fl
     return FM_OK;
 }
 
+// (loss, multiplier) pairs a forward pass over N rows leaves: one per row block of the sparse kernel, one per 32 rows
+// of the dense one
+static int64_t forward_pairs(const fm_matrix* m, const fm_params* p)
+{
+    return !p->half_gather && fm_dense_shape_ok(m, p->K) ? (m->N + 31) / 32 : fm_rows_grid(m->N, p->K);
+}
+
+// The sums over n pairs (or, single, n multipliers `stride` floats apart) as an epilogue.
+static void set_epilogue(fm_matrix* m, FmEpilogue& E, const float* x, int64_t n, int64_t stride, bool single)
+{
+    memset(&E, 0, sizeof(E));
+    E.on = 1;
+    E.x = x;
+    E.n = n;
+    E.stride = stride;
+    E.single = single ? 1 : 0;
+    E.nsums = fm_epi_nsums(n);
+    E.sums = m->scal + 8;
+    E.scal = m->scal;
+}
+
+// After the last kernel of a call with an objective: its two terms from the figures in pinned memory.
+static int read_objective(fm_matrix* m, const fm_params* p, double* objective, hipStream_t st)
+{
+    FM_HIP(m, hipStreamSynchronize(st));
+    objective[0] = (double)p->loss_scale * m->h_scal[0];
+    objective[1] = 0.5 * (double)p->lambda_w * m->h_scal[2] + 0.5 * (double)p->lambda_v * m->h_scal[3];
+    return FM_OK;
+}
+
 // mode 0: caller arrays (dense); 1: handle's aggregate rows, G and r; 2: handle's rows, G r a q
 static int run_forward(fm_matrix* m, const fm_params* p, const float* y, const float* w0, const float* w,
                        const float* V, float* yhat, float* a, float* G, float* q, float* r, int mode, bool want_sums,
@@ -655,11 +686,20 @@ static int run_forward(fm_matrix* m, const fm_params* p, const float* y, const f
     FM_TRY(half_copy(m, p, V, &A.Vh, st));
     const bool dense = A.Vh == nullptr && fm_dense_shape_ok(m, p->K);
     if (dense) A.dense_D = (int32_t)m->D;
-    FM_TRY(fm_launch_rows(m, A, false, st));
-    // one (loss, multiplier) pair per row block of the sparse kernel, per 32 rows of the dense one
-    const int64_t pairs = dense ? (m->N + 31) / 32 : fm_rows_grid(m->N, p->K);
-    if (A.row_part != nullptr) FM_TRY(fm_reduce_pairs(m, m->row_part, pairs, m->scal + 0, st));
-    return FM_OK;
+    return fm_launch_rows(m, A, false, st);  // the pairs stay in m->row_part
+}
+
+// Forward at the parameters as they stand, the sums and the objective: what the epochs with several steps report.
+static int objective_pass(fm_matrix* m, const fm_params* p, const float* y, const float* w0, const float* w, const float* V,
+                          int mode, double* objective, hipStream_t st)
+{
+    FM_TRY(run_forward(m, p, y, w0, w, V, nullptr, nullptr, nullptr, nullptr, nullptr, mode, true, st));
+    FmEpilogue E;
+    set_epilogue(m, E, m->row_part, forward_pairs(m, p), 0, false);
+    FM_TRY(fm_reg_partials(m, w, m->D, V, m->D * (int64_t)p->K, &E.regs, &E.nregs, st));
+    E.host = m->h_scal;
+    FM_TRY(fm_run_epilogue(m, E, st));
+    return read_objective(m, p, objective, st);
 }
 
 extern "C" int fm_forward(fm_matrix* m, const fm_params* p, const float* y, const float* w0, const float* w,
@@ -679,7 +719,7 @@ extern "C" int fm_forward(fm_matrix* m, const fm_params* p, const float* y, cons
     }
     FM_TRY(run_forward(m, p, y, w0, w, V, yhat, a, G, q, r, 0, loss_sum != nullptr, st));
     if (loss_sum != nullptr) {
-        FM_HIP(m, hipMemcpyAsync(m->h_scal, m->scal, 2 * sizeof(double), hipMemcpyDeviceToHost, st));
+        FM_TRY(fm_reduce_pairs(m, m->row_part, forward_pairs(m, p), m->h_scal, st));
         FM_HIP(m, hipStreamSynchronize(st));
         *loss_sum = m->h_scal[0];
     }
@@ -698,7 +738,7 @@ extern "C" int fm_evaluate(fm_matrix* m, const fm_params* p, const float* y, con
     FM_TRY(ensure_ws(m, p->K));
     metrics[0] = metrics[1] = metrics[2] = 0.0;
     if (m->N == 0) return FM_OK;
-    // the scores go to the start of the aggregate storage, which holds nothing afterwards
+    // the sums per row block go to the start of the aggregate storage, which holds nothing afterwards
     m->aux_held = false;
     m->aux_full = false;
     RowArgs A;
@@ -712,25 +752,21 @@ extern "C" int fm_evaluate(fm_matrix* m, const fm_params* p, const float* y, con
     A.w = w;
     A.V = V;
     A.y = y;
-    A.yhat = m->aux;
     A.gs = p->K;
     A.ss = 1;
-    A.row_part = m->row_part;
+    A.eval_part = reinterpret_cast<double*>(m->aux);
     A.loss = p->loss;
     A.s = 1.f;
     FM_TRY(half_copy(m, p, V, &A.Vh, st));
     const bool dense = A.Vh == nullptr && fm_dense_shape_ok(m, p->K);
     if (dense) A.dense_D = (int32_t)m->D;
     FM_TRY(fm_launch_rows(m, A, false, st));
-    FM_TRY(fm_reduce_pairs(m, m->row_part, dense ? (m->N + 31) / 32 : fm_rows_grid(m->N, p->K), m->scal + 0, st));
-    FM_TRY(fm_reduce_eval(m, m->aux, y, m->N, 0, m->scal + 4, st));
-    FM_TRY(fm_reduce_eval(m, m->aux, y, m->N, 1, m->scal + 5, st));
-    FM_HIP(m, hipMemcpyAsync(m->h_scal, m->scal, 6 * sizeof(double), hipMemcpyDeviceToHost, st));
+    FM_TRY(fm_reduce_eval(m, A.eval_part, forward_pairs(m, p), m->h_scal, m->scal + 8, st));
     FM_HIP(m, hipStreamSynchronize(st));
     const double n = (double)m->N;
     metrics[0] = m->h_scal[0] / n;
-    metrics[1] = sqrt(m->h_scal[4] / n);
-    metrics[2] = m->h_scal[5] / n;
+    metrics[1] = sqrt(m->h_scal[1] / n);
+    metrics[2] = m->h_scal[2] / n;
     return FM_OK;
 }
 
@@ -761,6 +797,10 @@ static void base_col_args(fm_matrix* m, const fm_params* p, ColArgs& A)
     A.N = m->N;
     A.part = m->part;
     A.ps = fm_part_stride(p->K);
+    // Aggregates that do not fit the memory-side cache: rows that are gathered once do not push others out of the L2.
+    const int64_t aux_bytes = fm_aux_floats(m, p->K) * (int64_t)sizeof(float);
+    A.nt = aux_bytes > (int64_t(256) << 20) ? 1 : 0;
+    A.big = aux_bytes > FM_BUF_BYTES ? 1 : 0;
 }
 
 extern "C" int fm_gradient(fm_matrix* m, const fm_params* p, const float* r, const float* G, const float* w,
@@ -774,13 +814,14 @@ extern "C" int fm_gradient(fm_matrix* m, const fm_params* p, const float* r, con
     FM_TRY(fm_check_vec_aligned(m, {G, V, grad_V}));
     hipStream_t st = (hipStream_t)hip_stream;
     FM_TRY(ensure_ws(m, p->K));
-    if (grad_w0 != nullptr) {
-        FM_TRY(fm_reduce_sum(m, r, m->N, 1, false, m->scal + 1, st));
-        FM_TRY(fm_bias_step(m, nullptr, m->scal + 1, 0.f, grad_w0, st));
-    }
-    if (m->D == 0 || (grad_w == nullptr && grad_V == nullptr)) return FM_OK;
+    FmEpilogue E;
+    set_epilogue(m, E, r, m->N, 1, true);
+    E.grad_w0 = grad_w0;
+    if (m->D == 0 || (grad_w == nullptr && grad_V == nullptr))
+        return grad_w0 != nullptr ? fm_run_epilogue(m, E, st) : FM_OK;
     ColArgs A;
     base_col_args(m, p, A);
+    if (grad_w0 != nullptr) A.epi = E;
     A.ptr = m->colptr;
     A.row = m->crow;
     A.val = m->cval;
@@ -830,10 +871,6 @@ extern "C" int fm_sgd_epoch(fm_matrix* m, const fm_params* p, const float* y, fl
     // steps 1-3: G, r, loss and sum r
     FM_TRY(run_forward(m, p, y, w0, w, V, nullptr, nullptr, nullptr, nullptr, nullptr, 1, true, st));
     m->aux_full = false;
-    if (objective != nullptr) {  // regulariser at the parameters the epoch starts from
-        FM_TRY(fm_reduce_sum(m, w, m->D, 1, true, m->scal + 2, st));
-        FM_TRY(fm_reduce_sum(m, V, m->D * (int64_t)p->K, 1, true, m->scal + 3, st));
-    }
     // steps 4-5 fused: gradient of every column and the step on w, V
     ColArgs A;
     base_col_args(m, p, A);
@@ -849,15 +886,17 @@ extern "C" int fm_sgd_epoch(fm_matrix* m, const fm_params* p, const float* y, fl
     A.w = w;
     A.V = V;
     full_long(m, p, A);
-    FM_TRY(fm_launch_cols(m, A, true, st));
-    if (p->update_w0) FM_TRY(fm_bias_step(m, w0, m->scal + 1, p->eta, nullptr, st));
-    if (objective != nullptr) {
-        FM_HIP(m, hipMemcpyAsync(m->h_scal, m->scal, 4 * sizeof(double), hipMemcpyDeviceToHost, st));
-        FM_HIP(m, hipStreamSynchronize(st));
-        objective[0] = (double)p->loss_scale * m->h_scal[0];
-        objective[1] = 0.5 * (double)p->lambda_w * m->h_scal[2] + 0.5 * (double)p->lambda_v * m->h_scal[3];
+    if (p->update_w0 || objective != nullptr) {
+        set_epilogue(m, A.epi, m->row_part, forward_pairs(m, p), 0, false);
+        if (p->update_w0) A.epi.w0 = w0;
+        A.epi.eta = p->eta;
+        if (objective != nullptr) {  // regulariser at the parameters the epoch starts from
+            FM_TRY(fm_reg_partials(m, w, m->D, V, m->D * (int64_t)p->K, &A.epi.regs, &A.epi.nregs, st));
+            A.epi.host = m->h_scal;
+        }
     }
-    return FM_OK;
+    FM_TRY(fm_launch_cols(m, A, true, st));
+    return objective != nullptr ? read_objective(m, p, objective, st) : FM_OK;
 }
 
 // ------------------------------------------------------- stratified epoch ----
@@ -969,6 +1008,17 @@ extern "C" int fm_stratified_step(fm_matrix* m, const fm_params* p, int32_t s, c
     return stratified_step(m, p, s, y, w0, w, V, false, (hipStream_t)hip_stream);
 }
 
+// The bias step from the multipliers as they stand in the aggregate rows.
+static int stratified_bias_step(fm_matrix* m, const fm_params* p, float* w0, hipStream_t st)
+{
+    const FmAux x = fm_aux_layout(m, p->K);
+    FmEpilogue E;
+    set_epilogue(m, E, x.r, m->N, x.ss, true);
+    E.w0 = w0;
+    E.eta = p->eta;
+    return fm_run_epilogue(m, E, st);
+}
+
 extern "C" int fm_stratified_end(fm_matrix* m, const fm_params* p, float* w0, void* hip_stream)
 {
     if (m == nullptr) return FM_EINVAL;
@@ -977,9 +1027,7 @@ extern "C" int fm_stratified_end(fm_matrix* m, const fm_params* p, float* w0, vo
     if (w0 == nullptr) return fm_fail(m, FM_EINVAL, "w0 must not be NULL");
     hipStream_t st = (hipStream_t)hip_stream;
     if (p->update_w0) {
-        const FmAux x = fm_aux_layout(m, p->K);
-        FM_TRY(fm_reduce_sum(m, x.r, m->N, x.ss, false, m->scal + 1, st));
-        FM_TRY(fm_bias_step(m, w0, m->scal + 1, p->eta, nullptr, st));
+        FM_TRY(stratified_bias_step(m, p, w0, st));
     }
     return FM_OK;
 }
@@ -997,9 +1045,7 @@ static int enqueue_stratified_epoch(fm_matrix* m, const fm_params* p, const floa
         FM_TRY(fm_launch_cols_flush(m, F, st));
     }
     if (p->update_w0) {
-        const FmAux x = fm_aux_layout(m, p->K);
-        FM_TRY(fm_reduce_sum(m, x.r, m->N, x.ss, false, m->scal + 1, st));
-        FM_TRY(fm_bias_step(m, w0, m->scal + 1, p->eta, nullptr, st));
+        FM_TRY(stratified_bias_step(m, p, w0, st));
     }
     return FM_OK;
 }
@@ -1093,16 +1139,7 @@ extern "C" int fm_stratified_epoch(fm_matrix* m, const fm_params* p, const float
     if (!done) FM_TRY(enqueue_stratified_epoch(m, p, y, w0, w, V, lazy, st));
     m->aux_full = true;
     m->aux_held = true;
-    if (objective != nullptr) {
-        FM_TRY(run_forward(m, p, y, w0, w, V, nullptr, nullptr, nullptr, nullptr, nullptr, 2, true, st));
-        FM_TRY(fm_reduce_sum(m, w, m->D, 1, true, m->scal + 2, st));
-        FM_TRY(fm_reduce_sum(m, V, m->D * (int64_t)p->K, 1, true, m->scal + 3, st));
-        FM_HIP(m, hipMemcpyAsync(m->h_scal, m->scal, 4 * sizeof(double), hipMemcpyDeviceToHost, st));
-        FM_HIP(m, hipStreamSynchronize(st));
-        objective[0] = (double)p->loss_scale * m->h_scal[0];
-        objective[1] = 0.5 * (double)p->lambda_w * m->h_scal[2] + 0.5 * (double)p->lambda_v * m->h_scal[3];
-    }
-    return FM_OK;
+    return objective != nullptr ? objective_pass(m, p, y, w0, w, V, 2, objective, st) : FM_OK;
 }
 
 // ------------------------------------------------------- mini-batch epoch ----
@@ -1159,8 +1196,6 @@ extern "C" int fm_minibatch_epoch(fm_matrix* m, const fm_params* p, const float*
             R.s = p->loss_scale;
             FM_TRY(half_copy(m, p, V, &R.Vh, st));  // the factors as they stand
             FM_TRY(fm_launch_rows(m, R, false, st));
-            if (R.row_part != nullptr)
-                FM_TRY(fm_reduce_pairs(m, m->row_part, fm_rows_grid(nb, p->K), m->scal + 0, st));
         }
         // steps 4-5 over the batch's rows: gradient and step of every column that has entries there
         ColArgs A;
@@ -1175,24 +1210,19 @@ extern "C" int fm_minibatch_epoch(fm_matrix* m, const fm_params* p, const float*
         A.rs = x.ss;
         A.packed = fm_cols_packed_mode(m, p->K);
         fill_long(m, A, m->lbatch, b, true);
+        if (p->update_w0 && nb > 0) {
+            set_epilogue(m, A.epi, m->row_part, fm_rows_grid(nb, p->K), 0, false);
+            A.epi.w0 = w0;
+            A.epi.eta = p->eta;
+        }
         FM_TRY(fm_launch_cols(m, A, true, st));
-        if (p->update_w0 && nb > 0) FM_TRY(fm_bias_step(m, w0, m->scal + 1, p->eta, nullptr, st));
     }
     if (lazy) {
         ColArgs F;
         col_args(m->B, F);
         FM_TRY(fm_launch_cols_flush(m, F, st));
     }
-    if (objective != nullptr) {
-        FM_TRY(run_forward(m, p, y, w0, w, V, nullptr, nullptr, nullptr, nullptr, nullptr, 1, true, st));
-        FM_TRY(fm_reduce_sum(m, w, m->D, 1, true, m->scal + 2, st));
-        FM_TRY(fm_reduce_sum(m, V, m->D * (int64_t)p->K, 1, true, m->scal + 3, st));
-        FM_HIP(m, hipMemcpyAsync(m->h_scal, m->scal, 4 * sizeof(double), hipMemcpyDeviceToHost, st));
-        FM_HIP(m, hipStreamSynchronize(st));
-        objective[0] = (double)p->loss_scale * m->h_scal[0];
-        objective[1] = 0.5 * (double)p->lambda_w * m->h_scal[2] + 0.5 * (double)p->lambda_v * m->h_scal[3];
-    }
-    return FM_OK;
+    return objective != nullptr ? objective_pass(m, p, y, w0, w, V, 1, objective, st) : FM_OK;
 }
 
 extern "C" int fm_get_aux(const fm_matrix* m, float* a, float* G, float* q, float* r, void* hip_stream)
@@ -1245,7 +1275,7 @@ extern "C" int fm_set_tuning(fm_matrix* m, int32_t seg, int32_t panel, int32_t h
     if (m == nullptr) return FM_EINVAL;
     if (m->has_csc) return fm_fail(m, FM_ESTATE, "fm_set_tuning must come before fm_build_csc");
     FmTune& t = m->tune;
-    if (seg > 0) t.seg = t.seg_strat = seg < 16 ? 16 : seg;
+    if (seg > 0) t.seg = seg < 16 ? 16 : seg;
     if (panel > 0) t.panel = panel < 64 ? 64 : panel;
     if (heavy_per_panel > 0) t.heavy_per_panel = heavy_per_panel;
     if (vlong > 0) t.vlong = vlong;

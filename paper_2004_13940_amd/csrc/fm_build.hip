@@ -742,6 +742,23 @@ static int build_short_list(fm_matrix* m, const int64_t* ptr, const int32_t* ids
     return FM_OK;
 }
 
+// Columns with very many items get a workgroup each in the finish step: their list, stratum by stratum.
+static int build_vlong_list(fm_matrix* m, const std::vector<int64_t>& h_first, LongIndex* out)
+{
+    std::vector<int32_t> h_vlong;
+    out->h_vlong_off.assign(out->h_long_off.size(), 0);
+    for (size_t s = 0; s + 1 < out->h_long_off.size(); ++s) {
+        for (int64_t lc = out->h_long_off[s]; lc < out->h_long_off[s + 1]; ++lc)
+            if (h_first[(size_t)lc + 1] - h_first[(size_t)lc] > m->tune.vlong) h_vlong.push_back((int32_t)lc);
+        out->h_vlong_off[s + 1] = (int64_t)h_vlong.size();
+    }
+    out->nvlong = (int64_t)h_vlong.size();
+    if (out->nvlong == 0) return FM_OK;
+    FM_TRY(fm_dev_alloc(m, (void**)&out->vlong, h_vlong.size() * sizeof(int32_t)));
+    FM_HIP(m, hipMemcpy(out->vlong, h_vlong.data(), h_vlong.size() * sizeof(int32_t), hipMemcpyHostToDevice));
+    return FM_OK;
+}
+
 int fm_build_long_index(fm_matrix* m, const int64_t* ptr, const int32_t* ids, int64_t ncols_total,
                         const std::vector<int64_t>& h_bounds, int32_t nstrata, LongIndex* out, hipStream_t st)
 {
@@ -755,22 +772,7 @@ int fm_build_long_index(fm_matrix* m, const int64_t* ptr, const int32_t* ids, in
     int64_t *tl = nullptr, *ti = nullptr;
     FM_TRY(fm_dev_alloc(m, (void**)&tl, (size_t)(ntiles + 1) * sizeof(int64_t)));
     FM_TRY(fm_dev_alloc(m, (void**)&ti, (size_t)(ntiles + 1) * sizeof(int64_t)));
-    // Item length.  The launches of one stratum are small: when full-length items would leave a
-    // stratum with too few of them to fill the chip, they are halved (more groups to spread over,
-    // at the price of more partial sums); fm_set_tuning overrides this.
-    int seg = m->tune.seg_strat;
-    if (seg <= 0) {
-        seg = m->tune.seg;
-        FM_HIP(m, hipMemsetAsync(ti, 0, (size_t)(ntiles + 1) * sizeof(int64_t), st));
-        FM_HIP(m, hipMemsetAsync(tl, 0, (size_t)(ntiles + 1) * sizeof(int64_t), st));
-        hipLaunchKernelGGL(k_long_count, dim3((unsigned)ntiles), dim3(LI_T), 0, st, ptr, ncols_total, seg, tl, ti);
-        FM_HIP(m, hipGetLastError());
-        FM_TRY(fm_scan_exclusive_i64(m, ti, ntiles + 1, st));
-        int64_t n_full = 0;
-        FM_HIP(m, hipMemcpyAsync(&n_full, ti + ntiles, sizeof(int64_t), hipMemcpyDeviceToHost, st));
-        FM_HIP(m, hipStreamSynchronize(st));
-        if (n_full / nstrata < 12288 && seg > 128) seg = 128;
-    }
+    const int seg = m->tune.seg > 0 ? m->tune.seg : fm_item_length(m->nnz / nstrata);
     FM_TRY(build_short_list(m, ptr, ids, ncols_total, h_bounds, nstrata, seg, true, out, st));
     FM_HIP(m, hipMemsetAsync(tl, 0, (size_t)(ntiles + 1) * sizeof(int64_t), st));
     FM_HIP(m, hipMemsetAsync(ti, 0, (size_t)(ntiles + 1) * sizeof(int64_t), st));
@@ -810,6 +812,7 @@ int fm_build_long_index(fm_matrix* m, const int64_t* ptr, const int32_t* ids, in
             out->h_item_off[s] = h_first[(size_t)k];
         }
         fm_dev_free(m, vcol);
+        FM_TRY(build_vlong_list(m, h_first, out));
     }
     fm_dev_free(m, tl);
     fm_dev_free(m, ti);
@@ -826,6 +829,16 @@ static void free_long_index(fm_matrix* m, LongIndex* li)
     *li = LongIndex();
 }
 
+// Entries per item when nobody has set it: a run is a serial chain of rounds of 16 entries, so items are as short as
+// still fills the chip (8 groups of 8 lanes per wavefront, 16 wavefronts on each of 256 compute units) once over; below
+// 32 the partial sums (one row per item) would cost as much as the entries, above 256 nothing is gained.
+int fm_item_length(int64_t entries)
+{
+    int seg = 32;
+    while (seg < 256 && entries / (2 * seg) >= 8 * 16 * 256) seg *= 2;
+    return seg;
+}
+
 // Shape of the LDS tiles for N rows and latent size K (K = 0: not known yet).  Explicit settings win;
 // else two tiles must fit the LDS of a compute unit (1024 rows only while [G | r] of a row is at most
 // 17 floats) and the tile shrinks with the matrix.  Larger tiles mean fewer items, hence fewer partial sums to write and read back.
@@ -834,12 +847,14 @@ void fm_tile_shape(const fm_matrix* m, int32_t K, int* tile_rows, int* tile_min,
     const FmTune& T = m->tune;
     const int64_t N = m->N;
     // one workgroup works on one tile: tall matrices take big tiles (fewer items, hence fewer partial
-    // sums), short ones small tiles (enough workgroups to fill the chip)
+    // sums), shorter ones small tiles (enough workgroups to fill the chip), and below 2^17 rows none: their aggregate
+    // rows stay in the caches anyway, and one launch over short items (text-like workload, 5e4 rows: epoch 146 -> 68 us)
+    // beats three kernels on three streams
     int rows = 512, dense = 8, seg = 256;
     if (K > 0 && K % 4 == 0 && K <= 16 && N >= (int64_t(1) << 21)) {
         rows = 1024, dense = 12, seg = 512;
     } else if (N < (int64_t(1) << 17)) {
-        rows = 128, dense = 2, seg = 128;
+        rows = 128, dense = 0, seg = 128;
     } else if (N < (int64_t(1) << 18)) {
         rows = 256, dense = 4, seg = 256;
     }
@@ -853,11 +868,12 @@ int fm_build_full_index(fm_matrix* m, int32_t K, hipStream_t st)
     LongIndex* out = &m->lfull;
     free_long_index(m, out);
     FmTune T = m->tune;
+    if (T.seg <= 0) T.seg = fm_item_length(m->nnz);
     fm_tile_shape(m, K, &T.tile, &T.tile_min, &T.tile_seg);
     m->lfull_shape[0] = T.tile;
     m->lfull_shape[1] = T.tile_min;
     m->lfull_shape[2] = T.tile_seg;
-    FM_TRY(build_short_list(m, m->colptr, nullptr, m->D, {0, m->D}, 1, m->tune.seg, false, out, st));
+    FM_TRY(build_short_list(m, m->colptr, nullptr, m->D, {0, m->D}, 1, T.seg, false, out, st));
     out->nlong = out->nitems = 0;
     out->h_long_off.assign(2, 0);
     out->h_item_off.assign(2, 0);
@@ -973,19 +989,11 @@ int fm_build_full_index(fm_matrix* m, int32_t K, hipStream_t st)
     fm_dev_free(m, k0);
     fm_dev_free(m, k1);
     fm_dev_free(m, d_off);
-    // 4. columns with very many items get a workgroup each in the finish step
-    std::vector<int32_t> h_vlong;
-    for (int64_t lc = 0; lc < nlong; ++lc)
-        if (h_first[(size_t)lc + 1] - h_first[(size_t)lc] > T.vlong) h_vlong.push_back((int32_t)lc);
-    out->nvlong = (int64_t)h_vlong.size();
-    if (out->nvlong > 0) {
-        FM_TRY(fm_dev_alloc(m, (void**)&out->vlong, h_vlong.size() * sizeof(int32_t)));
-        FM_HIP(m, hipMemcpy(out->vlong, h_vlong.data(), h_vlong.size() * sizeof(int32_t), hipMemcpyHostToDevice));
-    }
     out->nlong = nlong;
     out->nitems = nitems;
     out->h_long_off[1] = nlong;
     out->h_item_off[1] = nitems;
+    FM_TRY(build_vlong_list(m, h_first, out));
     fm_dev_free(m, vcol);
     fm_dev_free(m, tl);
     fm_dev_free(m, ti);

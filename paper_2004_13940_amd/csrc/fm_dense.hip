@@ -121,12 +121,15 @@ __global__ __launch_bounds__(FM_BLOCK) void k_rows_dense(const RowArgs A)
     const float a_i = a_part + __shfl_xor(a_part, 32, FM_WAVE);
     const float q_i = q_part + __shfl_xor(q_part, 32, FM_WAVE);
     pair += __shfl_xor(pair, 32, FM_WAVE);
-    float l_i = 0.f, r_i = 0.f;
+    float l_i = 0.f, r_i = 0.f, yh = 0.f, y_i = 0.f;
     if (half == 0 && lo < nrows) {
         const int64_t row = row0 + lo;
-        const float yh = A.w0[0] + a_i + 0.5f * (pair - q_i);
+        yh = A.w0[0] + a_i + 0.5f * (pair - q_i);
         if (A.yhat != nullptr) A.yhat[row] = yh;
-        if (A.y != nullptr) loss_and_multiplier(A.loss, A.s, yh, A.y[row], l_i, r_i);
+        if (A.y != nullptr) {
+            y_i = A.y[row];
+            loss_and_multiplier(A.loss, A.s, yh, y_i, l_i, r_i);
+        }
         if (A.a != nullptr) A.a[row * A.ss] = a_i;
         if (A.q != nullptr) A.q[row * A.ss] = q_i;
         if (A.y != nullptr && A.r != nullptr) A.r[row * A.ss] = r_i;
@@ -146,6 +149,7 @@ __global__ __launch_bounds__(FM_BLOCK) void k_rows_dense(const RowArgs A)
             A.row_part[2 * tid + 1] = rs;
         }
     }
+    if (A.eval_part != nullptr) fm_eval_wave(half == 0 && lo < nrows, yh, y_i, l_i, lane, A.eval_part + 3 * tid);
     __builtin_amdgcn_wave_barrier();  // the next tile overwrites the LDS tile
     }  // tiles of this wavefront
 }

@@ -4,7 +4,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
-#include "fm.h"
+#include "fm_internal.h"
 
 #include <type_traits>
 
@@ -37,25 +37,6 @@ __device__ __forceinline__ void fm_load_vec(const _Float16* __restrict__ p, floa
         v[0] = (float)t.x; v[1] = (float)t.y;
     } else {
         v[0] = (float)*p;
-    }
-}
-
-// Same load with the non-temporal hint: the line is not kept in L2 ahead of lines that
-// were loaded normally.  Used on the column side for rows that will not be gathered again
-// soon, so that they do not push a panel's rows out of the 4 MB L2 of the XCD.
-typedef float fm_v4f __attribute__((ext_vector_type(4)));
-typedef float fm_v2f __attribute__((ext_vector_type(2)));
-template <int VEC>
-__device__ __forceinline__ void fm_load_vec_nt(const float* __restrict__ p, float (&v)[VEC])
-{
-    if constexpr (VEC == 4) {
-        const fm_v4f t = __builtin_nontemporal_load(reinterpret_cast<const fm_v4f*>(p));
-        v[0] = t.x; v[1] = t.y; v[2] = t.z; v[3] = t.w;
-    } else if constexpr (VEC == 2) {
-        const fm_v2f t = __builtin_nontemporal_load(reinterpret_cast<const fm_v2f*>(p));
-        v[0] = t.x; v[1] = t.y;
-    } else {
-        v[0] = __builtin_nontemporal_load(p);
     }
 }
 
@@ -110,6 +91,21 @@ __device__ __forceinline__ void loss_and_multiplier(int32_t loss, float s, float
             l = -mg + log1pf(e);
             r = -s * y / (1.f + e);
         }
+    }
+}
+
+// What fm_evaluate counts, over the lanes with `has`: sum of losses, of squared errors, number of correct signs
+// (a score of 0 counts as +1).  Written to out[0..2] by lane 0.
+__device__ __forceinline__ void fm_eval_wave(bool has, float yh, float y, float l, int lane, double* out)
+{
+    const double d = has ? (double)yh - (double)y : 0.0;
+    const float ls = fm_wave_sum(has ? l : 0.f);
+    const double sq = fm_wave_sum(d * d);
+    const int ok = __popcll(__ballot(has && (yh >= 0.f ? 1.f : -1.f) == y));
+    if (lane == 0) {
+        out[0] = (double)ls;
+        out[1] = sq;
+        out[2] = (double)ok;
     }
 }
 
@@ -197,8 +193,7 @@ __device__ __forceinline__ void fm_gather_slots(const IX& ix, const MU& mu, cons
     });
 }
 
-// The common inner loop of the row and the column kernels.  A group of L lanes walks
-// the entries [beg,end) of one sparse row (or column): idx[e] names a row of `src`
+// The inner loop of the row kernels.  A group of L lanes walks the entries [beg,end) of one sparse row: idx[e] names a row of `src`
 // (`stride` floats apart) and val[e] its coefficient.  Lane `sub` of the group
 //   * loads entry e+sub of every L-entry slot (coalesced) and calls
 //       m = own(index, value)      -- per-entry work of that lane, linear in the value;
@@ -268,107 +263,180 @@ __device__ __forceinline__ void fm_gather_accumulate(const int32_t* __restrict__
     }
 }
 
-// Column-side variant for packed aggregate rows [G_0..G_{K-1} | r | a | q | pad] whose [G | r] lies
-// inside one 128-byte line: a group of L lanes, one lane wider than the latent values need, reads
-// the row with a single request, and lane rl = K/VEC picks up r for the others.
-// Per entry (row i, value x):
-//   acc[z] += x r_i G_i[kb+z]     on the latent lanes,
-//   gw += x r_i, s2 += x^2 r_i    on the scalar lane (the others keep 0).
-template <int VEC, int L, bool NT, int S, int MAXB = 16, class IX, class XV>
-__device__ __forceinline__ void fm_gather_slots_packed(const IX& ix, const XV& xv, const float* __restrict__ src,
-                                                       int64_t stride, int kb, int rl, bool scalar_lane,
-                                                       float (&acc)[VEC], float& gw, float& s2)
+// Largest value over the 64 lanes, as a wave-uniform number (a scalar register: branches on it do not diverge).
+__device__ __forceinline__ int fm_wave_max(int v)
 {
-    constexpr int B = S < MAXB ? S : MAXB;
-    fm_static_for<0, S / B>([&](auto bc) {
-        constexpr int B0 = decltype(bc)::value * B;
-        float g[B][VEC];
-        float xt[B];
-        fm_static_for<0, B>([&](auto sc) {
-            constexpr int s = B0 + decltype(sc)::value;
-            constexpr int u = s / L, T = s % L;
-            const int it = fm_bcast_i<L, T>(ix[u]);
-            xt[s - B0] = fm_bcast_f<L, T>(xv[u]);
-            if constexpr (NT)
-                fm_load_vec_nt<VEC>(src + (int64_t)it * stride + kb, g[s - B0]);
-            else
-                fm_load_vec<VEC>(src + (int64_t)it * stride + kb, g[s - B0]);
-        });
 #pragma unroll
-        for (int s = 0; s < B; ++s) {
-            const float r = __shfl(g[s][0], rl, L);
-            const float m = xt[s] * r;
+    for (int o = 32; o > 0; o >>= 1) {
+        const int t = __shfl_xor(v, o, 64);
+        v = t > v ? t : v;
+    }
+    return __builtin_amdgcn_readfirstlane(v);
+}
+
+// How a walk addresses the rows it gathers.  BUF, BUF_NT: byte offsets of 32 bits from one buffer descriptor (arrays of
+// up to FM_BUF_BYTES): one address register per gather instead of two, and an offset of FM_BUF_NONE is out of range,
+// which reads zero without a request to memory, so slots without an entry cost nothing.  PTR: 64-bit addresses for
+// larger arrays; slots without an entry repeat the run's last one.
+enum { FM_ADDR_BUF = 0, FM_ADDR_BUF_NT = 1, FM_ADDR_PTR = 2 };
+constexpr uint32_t FM_BUF_NONE = (uint32_t)FM_BUF_BYTES;  // + the offset inside a row (at most 1 KB) does not wrap
+
+template <int VEC, bool NT>
+__device__ __forceinline__ void fm_buf_load(__amdgpu_buffer_rsrc_t rs, uint32_t off, float (&v)[VEC])
+{
+    constexpr int AUX = NT ? 2 : 0;
+    typedef int i4 __attribute__((ext_vector_type(4)));
+    typedef int i2 __attribute__((ext_vector_type(2)));
+    if constexpr (VEC == 4) {
+        const i4 t = __builtin_amdgcn_raw_buffer_load_b128(rs, (int)off, 0, AUX);
+        v[0] = __int_as_float(t.x); v[1] = __int_as_float(t.y); v[2] = __int_as_float(t.z); v[3] = __int_as_float(t.w);
+    } else if constexpr (VEC == 2) {
+        const i2 t = __builtin_amdgcn_raw_buffer_load_b64(rs, (int)off, 0, AUX);
+        v[0] = __int_as_float(t.x); v[1] = __int_as_float(t.y);
+    } else {
+        v[0] = __int_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs, (int)off, 0, AUX));
+    }
+}
+
+// What a walk adds up per entry with multiplier m and gathered row g:
+//   SUM     acc += m g
+//   PACKED  rows are [G | r | ..], lane rl holds r in its first float; acc += x r G on the latent lanes,
+//           gw += x r and s2 += x^2 r on lane rl
+enum { FM_WALK_SUM = 0, FM_WALK_PACKED = 1 };
+
+// S slots of a round from slot S0 on: all loads, then all sums in entry order.
+template <int VEC, int L, int KIND, int ADDR, int S, int S0, class IX, class MU>
+__device__ __forceinline__ void fm_slots(const IX& ix, const MU& mu, __amdgpu_buffer_rsrc_t rs, const float* __restrict__ src,
+                                         int64_t stride, int kb, int rl, bool scalar_lane, float (&acc)[VEC], float& gw,
+                                         float& s2)
+{
+    float g[S][VEC];
+    float xt[S];
+    fm_static_for<0, S>([&](auto sc) {
+        constexpr int s = decltype(sc)::value;
+        constexpr int u = (S0 + s) / L, T = (S0 + s) % L;
+        const int it = fm_bcast_i<L, T>(ix[u]);
+        xt[s] = fm_bcast_f<L, T>(mu[u]);
+        if constexpr (ADDR == FM_ADDR_PTR)
+            fm_load_vec<VEC>(src + (int64_t)it * stride + kb, g[s]);
+        else
+            fm_buf_load<VEC, ADDR == FM_ADDR_BUF_NT>(rs, (uint32_t)it + (uint32_t)(kb * (int)sizeof(float)), g[s]);
+    });
+#pragma unroll
+    for (int s = 0; s < S; ++s) {
+        if constexpr (KIND == FM_WALK_PACKED) {
+            const float m = xt[s] * __shfl(g[s][0], rl, L);
 #pragma unroll
             for (int z = 0; z < VEC; ++z) acc[z] += m * g[s][z];
             if (scalar_lane) {
                 gw += m;
                 s2 += xt[s] * m;
             }
+        } else {
+#pragma unroll
+            for (int z = 0; z < VEC; ++z) acc[z] += xt[s] * g[s][z];
         }
-    });
+    }
 }
 
-// kb: the caller clamps it so that lanes past the scalars re-read the row's last VEC floats
-// (they discard their acc).
-template <int VEC, int L, bool NT>
-__device__ __forceinline__ void fm_col_accumulate_packed(const int32_t* __restrict__ idx, const float* __restrict__ val,
-                                                         int64_t beg, int64_t end, const float* __restrict__ src,
-                                                         int64_t stride, int sub, int kb, int rl, float (&acc)[VEC],
-                                                         float& gw, float& s2)
+// The inner loop of the column kernels.  Every group of L lanes walks its own run [beg,end) of one column, all groups of
+// the wavefront in step: a round takes the next C entries of every run (16; L for wider groups), in batches of SMAX or
+// four slots by the longest run left, so the choice is a scalar branch, and a group whose run is over sits the round
+// out.  The indices of the next round are loaded while the gathers of this one are on their way: a round costs one
+// memory latency, not two.  Columns of a few entries are what a stratum or a batch consists of; with a slot loop and a
+// four-at-a-time tail per group a column of 15 entries took six round trips, here it takes two.
+// SMAX = 8 rather than 16: 101 registers instead of 146, five wavefronts per SIMD instead of three (mini-batch epoch of
+// the click-style workload, 2.5e6 rows: 4.53 -> 4.20 ms); 4 for groups of 16 (80 registers; with 16 it is 163, and the
+// gradient of the hashed workload takes 2.88 instead of 2.53 ms).
+//   own(index, value) -> multiplier: the work of the lane that holds the entry
+template <int VEC, int L, int KIND, int ADDR, class Own>
+__device__ __forceinline__ void fm_walk(const int32_t* __restrict__ idx, const float* __restrict__ val, int64_t beg,
+                                        int64_t end, const float* __restrict__ src, int64_t stride, int sub, int kb, int rl,
+                                        float (&acc)[VEC], float& gw, float& s2, Own&& own)
 {
-    constexpr int CH = FmChunk<L>::CH;
+    constexpr int SMAX = L == 16 ? 4 : 8;
+    constexpr int C = L < 16 ? 16 : L;
+    constexpr int U = C / L;
+    const int len = (int)(end - beg);
+    int left = fm_wave_max(len);
+    if (left <= 0) return;
+    const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(src), 0, (int)FM_BUF_NONE, 0x20000);
+    const uint32_t row_bytes = (uint32_t)stride * (uint32_t)sizeof(float);
     const bool scalar_lane = sub == rl;
-    int64_t e = beg;
-    for (; e + L * CH <= end; e += L * CH) {
-        int ix[CH];
-        float xv[CH];
+    const int32_t* __restrict__ ip = idx + beg;
+    const float* __restrict__ vp = val + beg;
+    int ix[U], raw[U];
+    float mu[U];
+    auto fetch = [&](int at, int (&i)[U], float (&x)[U]) {
 #pragma unroll
-        for (int u = 0; u < CH; ++u) {
-            const int64_t my = e + u * L + sub;
-            ix[u] = idx[my];
-            xv[u] = val[my];
+        for (int u = 0; u < U; ++u) {
+            const int t = at + u * L + sub;
+            i[u] = -1;
+            x[u] = 0.f;
+            if (t < len) {
+                i[u] = ip[t];
+                x[u] = vp[t];
+            } else if (ADDR == FM_ADDR_PTR && len > 0) {
+                i[u] = ip[len - 1];
+            }
         }
-        fm_gather_slots_packed<VEC, L, NT, CH * L>(ix, xv, src, stride, kb, rl, scalar_lane, acc, gw, s2);
-    }
-    for (; e < end; e += L) {
-        const int64_t want = e + sub;
-        const bool has = want < end;
-        const int64_t my = has ? want : end - 1;
-        int ix[1];
-        float xv[1];
-        ix[0] = idx[my];
-        xv[0] = has ? val[my] : 0.f;
-        if constexpr (L <= 4) {
-            fm_gather_slots_packed<VEC, L, NT, L>(ix, xv, src, stride, kb, rl, scalar_lane, acc, gw, s2);
-        } else {
-            // wide groups: only the entries that exist, four gathers at a time
-            const int nv = (int)((end - e) < L ? (end - e) : L);
-            for (int t0 = 0; t0 < nv; t0 += 4) {
-                float g[4][VEC];
-                float xt[4];
+    };
+    fetch(0, raw, mu);
+    for (int at = 0;; at += C, left -= C) {
+        int in[U];
+        float mn[U];
+        const bool more = left > C;
+        if (more) fetch(at + C, in, mn);
 #pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    const int t = t0 + u < nv ? t0 + u : nv - 1;
-                    const int it = __shfl(ix[0], t, L);
-                    const float x = __shfl(xv[0], t, L);
-                    xt[u] = t0 + u < nv ? x : 0.f;
-                    if constexpr (NT)
-                        fm_load_vec_nt<VEC>(src + (int64_t)it * stride + kb, g[u]);
-                    else
-                        fm_load_vec<VEC>(src + (int64_t)it * stride + kb, g[u]);
-                }
-#pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    const float r = __shfl(g[u][0], rl, L);
-                    const float m = xt[u] * r;
-#pragma unroll
-                    for (int z = 0; z < VEC; ++z) acc[z] += m * g[u][z];
-                    if (scalar_lane) {
-                        gw += m;
-                        s2 += xt[u] * m;
-                    }
+        for (int u = 0; u < U; ++u) {
+            if constexpr (ADDR == FM_ADDR_PTR) {
+                ix[u] = raw[u] < 0 ? 0 : raw[u];  // only where the run is empty: its group sits the round out
+                if (at + u * L + sub < len) mu[u] = own(raw[u], mu[u]);
+            } else {
+                ix[u] = (int)FM_BUF_NONE;
+                if (raw[u] >= 0) {
+                    mu[u] = own(raw[u], mu[u]);
+                    ix[u] = (int)((uint32_t)raw[u] * row_bytes);
                 }
             }
+        }
+        if (at < len) {
+            if constexpr (L <= 16) {
+                if (left > 4 && SMAX == 8) {
+                    fm_slots<VEC, L, KIND, ADDR, 8, 0>(ix, mu, rs, src, stride, kb, rl, scalar_lane, acc, gw, s2);
+                    if (left > 8)
+                        fm_slots<VEC, L, KIND, ADDR, 8, 8>(ix, mu, rs, src, stride, kb, rl, scalar_lane, acc, gw, s2);
+                } else {
+                    fm_slots<VEC, L, KIND, ADDR, 4, 0>(ix, mu, rs, src, stride, kb, rl, scalar_lane, acc, gw, s2);
+                    if constexpr (SMAX < 8) {
+                        if (left > 4)
+                            fm_slots<VEC, L, KIND, ADDR, 4, 4>(ix, mu, rs, src, stride, kb, rl, scalar_lane, acc, gw, s2);
+                        if (left > 8)
+                            fm_slots<VEC, L, KIND, ADDR, 4, 8>(ix, mu, rs, src, stride, kb, rl, scalar_lane, acc, gw, s2);
+                        if (left > 12)
+                            fm_slots<VEC, L, KIND, ADDR, 4, 12>(ix, mu, rs, src, stride, kb, rl, scalar_lane, acc, gw, s2);
+                    }
+                }
+            } else {
+                // one or two runs per wavefront: eight entries at a time, broadcast through the LDS crossbar
+                const int nv = left < C ? left : C;
+                for (int t0 = 0; t0 < nv; t0 += 8) {
+                    int i8[8];
+                    float x8[8];
+#pragma unroll
+                    for (int u = 0; u < 8; ++u) {  // t0 + u < L: L is a multiple of eight
+                        i8[u] = __shfl(ix[0], t0 + u, L);
+                        x8[u] = __shfl(mu[0], t0 + u, L);
+                    }
+                    fm_slots<VEC, 1, KIND, ADDR, 8, 0>(i8, x8, rs, src, stride, kb, rl, scalar_lane, acc, gw, s2);
+                }
+            }
+        }
+        if (!more) break;
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            raw[u] = in[u];
+            mu[u] = mn[u];
         }
     }
 }

@@ -22,15 +22,14 @@ constexpr int FM_XCDS = 8;                // L2 domains; workgroup b runs on XCD
 // Tunables of the column-side work decomposition, per handle (fm_set_tuning, fm_set_tile_tuning;
 // tile, tile_min < 0, tile_seg: 0 or negative = chosen per latent size, see fm_tile_shape).
 struct FmTune {
-    int seg = 256;             // entries per work item of a long column
+    int seg = 0;               // entries per work item of a long column; 0: by the number of entries, fm_item_length
     int panel = 32768;         // rows per panel of the L2-blocked traversal of heavy columns
     int heavy_per_panel = 16;  // a column is heavy if it averages at least this many entries per panel
-    int vlong = 512;           // columns with more items than this are finished by a whole workgroup
+        int vlong = 128;           // columns with more items than this are finished by a whole workgroup
     int min_panels = 8 * 8;    // the panel order is used only for matrices with at least this many panels
     int tile = 0;              // rows per LDS tile of the kernel for dense-ish columns
     int tile_min = -1;         // a column is dense-ish if it averages this many entries per tile (0: none)
     int tile_seg = 0;          // entries per item inside a tile
-    int seg_strat = 0;         // `seg` of the per-stratum and per-batch matrices (fm_set_tuning sets both); 0: automatic
 };
 
 // Per-handle switches between code paths that compute the same thing (fm_set_option).
@@ -53,6 +52,8 @@ struct fm_matrix;
 bool fm_aux_packed(const fm_matrix* m, int32_t K);
 // floats per row of partial sums [acc_0..acc_{K-1} | gw | s2 | pad]: a multiple of 32 (128 bytes)
 inline int64_t fm_part_stride(int32_t K) { return ((int64_t)K + 2 + 31) / 32 * 32; }
+// Arrays up to this size are gathered through a buffer descriptor with offsets of 32 bits (see fm_walk)
+constexpr int64_t FM_BUF_BYTES = 0xFFFFF000LL;
 // How the column kernels read the aggregate rows (ColArgs::packed).
 enum { FM_PLANAR = 0, FM_PACKED_LANE = 1 };
 int fm_cols_packed_mode(const fm_matrix* m, int32_t K);
@@ -109,6 +110,7 @@ struct LongIndex {
     int64_t* tile_ptr = nullptr;    // [ntiles+1] positions in `order`
     int32_t* vlong = nullptr;       // [nvlong] indices into long_col of columns with > vlong items
     int64_t nvlong = 0;
+    std::vector<int64_t> h_vlong_off;  // per stratum: where its part of vlong starts (the full matrix: all of it)
 };
 
 struct ProfRec {
@@ -268,6 +270,7 @@ int fm_build_long_index(fm_matrix* m, const int64_t* ptr, const int32_t* ids, in
 // lfull, with the panel order of heavy columns and the LDS tiles shaped for latent size K (0: unknown)
 int fm_build_full_index(fm_matrix* m, int32_t K, hipStream_t st);
 void fm_tile_shape(const fm_matrix* m, int32_t K, int* tile_rows, int* tile_min, int* tile_seg);
+int fm_item_length(int64_t entries);  // of a launch over so many entries
 int fm_ensure_lazy(fm_matrix* m);  // allocates lazy_last on first use
 
 // ---- pass kernels (fm_rows.hip / fm_cols.hip / fm_reduce.hip) ----
@@ -288,6 +291,7 @@ struct RowArgs {
     int64_t ss;         // floats between consecutive rows of r, a, q (1, or the aggregate row stride)
     int32_t whole_rows; // forward into packed aggregate rows: write r, a, q and the padding with G
     float* row_part;    // nullable: [2*gridDim] loss and sum r per block
+    double* eval_part;  // nullable: [3*gridDim] sums of losses, squared errors and correct signs per block
     int32_t dense_D;      // forward: > 0 when `val` is a dense row-major N x dense_D matrix (col is then not read)
     const int32_t* rows;  // nullable: the launch covers rows[0..N) instead of rows 0..N-1, and
                           // rowptr[k], rowptr[k+1] bound the entries of rows[k]
@@ -308,6 +312,32 @@ int fm_launch_rows_dense(fm_matrix* m, const RowArgs& A, hipStream_t st);
 struct ColArgs;
 int fm_launch_cols_dense(fm_matrix* m, const ColArgs& A, hipStream_t st);  // partial sums only; the finish kernels follow
 int fm_unpack_aux(fm_matrix* m, float* a, float* G, float* q, float* r, hipStream_t st);
+
+// What is left of an epoch when the columns have stepped: the sums over the examples, the bias step and the figures of
+// the objective.  One workgroup, which rides along with the last column kernel.
+struct FmEpilogue {
+    int32_t on;
+    const float* x;        // raw values, one pair (loss, multiplier) per row block or, with single, one multiplier per row
+    int64_t n, stride;
+    int32_t single;
+    double* sums;          // [2 * nsums] partial pairs of x, written by the kernel before (nsums == 0: x is read as it is)
+    int32_t nsums;
+    const double* regs;    // nullable: [2 * nregs] partial pairs (|w|^2, |V|^2)
+    int32_t nregs;
+    float* w0;             // nullable: takes the bias step
+    float eta;
+    float* grad_w0;        // nullable
+    double* scal;          // device: loss, sum of the multipliers
+    double* host;          // nullable, pinned: loss, sum of the multipliers, |w|^2, |V|^2
+};
+constexpr int FM_EPI_DIRECT = 2048;  // values the epilogue sums itself; above, workgroups of the kernel before do
+constexpr int FM_EPI_CHUNK = 4096;   // ... one for so many values
+inline int fm_epi_nsums(int64_t n)
+{
+    if (n <= FM_EPI_DIRECT) return 0;
+    const int64_t nb = (n + FM_EPI_CHUNK - 1) / FM_EPI_CHUNK;
+    return (int)(nb < 512 ? nb : 512);
+}
 
 struct ColArgs {
     int64_t D;
@@ -366,8 +396,11 @@ struct ColArgs {
     int64_t list_mid[FM_XCDS];
     int64_t tile_rows, ntiles;     // dense-ish columns: items sorted by row tile, after the lists
     const int64_t* tile_ptr;
-    int32_t lin_mode;              // k_cols_long: take positions lin_base.. of `order` in sequence
-    int64_t lin_base, lin_count;
+    int64_t lin_base, lin_count;   // positions of `order` that are taken in sequence (tile items that are not staged)
+    int64_t blk_lists, blk_lin, blk_short;  // workgroups of k_cols per role, in this order; then epi.nsums for the sums
+    int32_t nt;                    // gathers of rows that are not used again soon carry the non-temporal hint
+    int32_t big;                   // the gathered array is larger than FM_BUF_BYTES
+    FmEpilogue epi;
     const int32_t* vlong;          // nullable: long columns finished by a whole workgroup
     int64_t nvlong;
     int32_t vlong_items;           // threshold that defines vlong
@@ -378,14 +411,17 @@ int fm_launch_cols(fm_matrix* m, const ColArgs& A, bool update, hipStream_t st);
 // takes the postponed regulariser steps of every column up to stratum A.s (exclusive)
 int fm_launch_cols_flush(fm_matrix* m, const ColArgs& A, hipStream_t st);
 
+constexpr int FM_REG_PAIRS = 512;      // partial pairs of fm_reg_partials
 constexpr int FM_REDUCE_TMP = 2048;  // doubles of stage-1 scratch a reduction may use
 // tmp: FM_REDUCE_TMP doubles of device scratch, or nullptr for the handle's own
 int fm_reduce_pairs(fm_matrix* m, const float* part, int64_t nblocks, double* out2, hipStream_t st,
                     double* tmp = nullptr);
-int fm_reduce_sum(fm_matrix* m, const float* x, int64_t n, int64_t stride, bool square, double* out1, hipStream_t st);
-int fm_reduce_eval(fm_matrix* m, const float* yhat, const float* y, int64_t n, int what, double* out1, hipStream_t st);
+// |w|^2 and |V|^2 as nregs partial pairs of doubles in the handle's scratch
+int fm_reg_partials(fm_matrix* m, const float* w, int64_t nw, const float* V, int64_t nV, const double** regs, int32_t* nregs,
+                    hipStream_t st);
+int fm_reduce_eval(fm_matrix* m, const double* part, int64_t n, double* out3, double* tmp, hipStream_t st);
+int fm_run_epilogue(fm_matrix* m, const FmEpilogue& E, hipStream_t st);  // as kernels of its own
 int fm_fill_i32(fm_matrix* m, int32_t* x, int64_t n, int32_t v, hipStream_t st);
-int fm_bias_step(fm_matrix* m, float* w0, const double* rsum, float eta, float* grad_w0_out, hipStream_t st);
 
 // lanes per row/column group and floats per lane for a given K; false if K unsupported
 bool fm_shape_for_K(int32_t K, int* vec, int* lanes);

@@ -91,6 +91,7 @@ __global__ __launch_bounds__(FM_BLOCK) void k_rows(const RowArgs A)
     }
 
     float l_i = 0.f, r_i = 0.f;
+    [[maybe_unused]] float yh_i = 0.f, y_i = 0.f;
     if constexpr (MODE != MODE_REFRESH) {
         float pair = 0.f;
 #pragma unroll
@@ -102,7 +103,11 @@ __global__ __launch_bounds__(FM_BLOCK) void k_rows(const RowArgs A)
         if (valid) {
             if (sub == 0) {
                 if (A.yhat != nullptr) A.yhat[row] = yh;
-                if (A.y != nullptr) loss_and_multiplier(A.loss, A.s, yh, A.y[row], l_i, r_i);
+                if (A.y != nullptr) {
+                    yh_i = yh;
+                    y_i = A.y[row];
+                    loss_and_multiplier(A.loss, A.s, yh, y_i, l_i, r_i);
+                }
             }
             if (A.G != nullptr && kact) fm_store_vec<VEC>(A.G + row * A.gs + kbase, acc);
             if (A.whole_rows) {
@@ -174,6 +179,19 @@ __global__ __launch_bounds__(FM_BLOCK) void k_rows(const RowArgs A)
             }
             A.row_part[2 * (int64_t)blockIdx.x] = t0;
             A.row_part[2 * (int64_t)blockIdx.x + 1] = t1;
+        }
+    }
+    if constexpr (MODE != MODE_REFRESH) {
+        if (A.eval_part != nullptr) {  // sums of losses, squared errors and correct signs of the block's rows
+            __shared__ double she[3 * FM_WAVES];
+            fm_eval_wave(valid && sub == 0, yh_i, y_i, l_i, lane, she + 3 * wave);
+            __syncthreads();
+            if (threadIdx.x < 3) {
+                double t = 0.0;
+#pragma unroll
+                for (int wv = 0; wv < FM_WAVES; ++wv) t += she[3 * wv + threadIdx.x];
+                A.eval_part[3 * (int64_t)blockIdx.x + threadIdx.x] = t;
+            }
         }
     }
 }

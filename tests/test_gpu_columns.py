@@ -1,0 +1,46 @@
+"""The column kernels at the edges of their rounds and items, against the oracle."""
+import numpy as np
+import pytest
+
+from oracle import fm_oracle as O
+
+from helpers import assert_close, dev_params, to_dev
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("K", [1, 2, 4, 12, 16, 28, 32, 60, 100, 256])  # every lane count, packed and planar rows
+def test_columns_of_every_length_around_the_rounds_and_the_item(K):
+    """Column j holds j entries, j = 0..100: rounds of 4, 8 and 16 entries, one and several items, all lengths mixed
+    inside a wavefront; one column stores every row (summed by a whole workgroup)."""
+    import torch
+    from paper_2004_13940_amd import binding as B
+    rng = np.random.default_rng(7000 + K)
+    N, D = 6000, 102
+    mask = np.zeros((N, D), bool)
+    for j in range(101):
+        mask[rng.choice(N, j, replace=False), j] = True
+    mask[:, 101] = True
+    rowptr = np.concatenate([[0], np.cumsum(mask.sum(1))]).astype(np.int64)
+    col = np.nonzero(mask)[1].astype(np.int32)
+    val = rng.standard_normal(len(col)).astype(np.float32)
+    r = (rng.standard_normal(N) / N).astype(np.float32)
+    G = rng.standard_normal((N, K)).astype(np.float32)
+    w = (rng.standard_normal(D) * 0.1).astype(np.float32)
+    V = (rng.standard_normal((D, K)) * 0.1).astype(np.float32)
+    print("columns of every length", K, len(col), flush=True)
+    m = B.Matrix(N, D, rowptr, col, val)
+    m.fm_build_csc()
+    p = B.make_params(K, O.LOSS_SQUARED, 0.01, 0.02, 0.1)
+    _, d_w, d_V = dev_params(np.float32(0), w, V)
+    g0 = torch.full((1,), float("nan"), device="cuda")
+    gw = torch.full((D,), float("nan"), device="cuda")
+    gV = torch.full((D * K,), float("nan"), device="cuda")
+    m.fm_gradient(p, to_dev(r), to_dev(G.ravel()), d_w, d_V, g0, gw, gV)
+    torch.cuda.synchronize()
+    X = O.make_matrix(N, D, rowptr, col, val)
+    wg0, wgw, wgV = O.gradient(X, r, G, w, V, 0.01, 0.02)
+    assert abs(g0.item() - wg0) <= 1e-5 * np.abs(r).sum()
+    assert_close(gw.cpu().numpy(), wgw, "grad_w")
+    assert_close(gV.cpu().numpy().reshape(D, K), wgV, "grad_V")
+    m.close()
