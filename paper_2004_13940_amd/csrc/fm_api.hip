@@ -535,7 +535,8 @@ static int ensure_ws(fm_matrix* m, int32_t K)
         }
     }
     const size_t D = (size_t)m->D;
-    FM_TRY(fm_dev_alloc(m, (void**)&m->aux, (size_t)std::max<int64_t>(fm_aux_floats(m, K), 1) * sizeof(float)));
+    // fm_evaluate leaves three doubles per row block there: more than the aggregates of a single row with K <= 2 take
+    FM_TRY(fm_dev_alloc(m, (void**)&m->aux, (size_t)std::max<int64_t>(fm_aux_floats(m, K), 6) * sizeof(float)));
     const int64_t items = std::max<int64_t>(std::max<int64_t>(m->lfull.nitems, m->lstrat.nitems),
                                             std::max<int64_t>(m->lbatch.nitems, m->ldense.nitems));
     FM_TRY(fm_dev_alloc(m, (void**)&m->part,

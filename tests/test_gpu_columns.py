@@ -44,3 +44,33 @@ def test_columns_of_every_length_around_the_rounds_and_the_item(K):
     assert_close(gw.cpu().numpy(), wgw, "grad_w")
     assert_close(gV.cpu().numpy().reshape(D, K), wgV, "grad_V")
     m.close()
+
+
+@pytest.mark.parametrize("N,K", [(1, 1), (1, 2), (2, 1), (5, 3), (17, 64), (300, 4), (1, 256)])
+def test_evaluation_of_a_few_rows(N, K):
+    """The row kernel leaves three doubles per block of rows for the metrics: at the smallest N and K they take more room
+    than the aggregates do.  Another K follows on the same handle, which lays its storage out anew."""
+    from paper_2004_13940_amd import binding as B
+    rng = np.random.default_rng(7100 + 10 * N + K)
+    D = 6
+    mask = rng.random((N, D)) < 0.6
+    rowptr = np.concatenate([[0], np.cumsum(mask.sum(1))]).astype(np.int64)
+    col = np.nonzero(mask)[1].astype(np.int32)
+    val = rng.standard_normal(len(col)).astype(np.float32)
+    y = np.where(rng.random(N) < 0.5, 1.0, -1.0).astype(np.float32)
+    X = O.make_matrix(N, D, rowptr, col, val)
+    m = B.Matrix(N, D, rowptr, col, val)
+    for k in (K, 1):
+        print("evaluation of a few rows", N, k, flush=True)
+        w = (rng.standard_normal(D) * 0.3).astype(np.float32)
+        V = (rng.standard_normal((D, k)) * 0.3).astype(np.float32)
+        got = m.fm_evaluate(B.make_params(k, O.LOSS_LOGISTIC), to_dev(y), *dev_params(np.float32(0.1), w, V))
+        yh = O.forward(X, float(np.float32(0.1)), w, V)[3]
+        loss = O.loss_multiplier(O.LOSS_LOGISTIC, 1.0, yh, y)[0].mean()
+        rmse = np.sqrt(np.mean((yh - y) ** 2))
+        assert abs(got["mean_loss"] - loss) <= 1e-5 * loss
+        assert abs(got["rmse"] - rmse) <= 1e-5 * rmse
+        sure = np.abs(yh) > 1e-5
+        right = (np.sign(yh) == y)[sure].sum() / N
+        assert right - 1e-9 <= got["accuracy"] <= right + (~sure).sum() / N + 1e-9
+    m.close()
