@@ -93,6 +93,8 @@ def _vp(x):
 
 def _stream(stream):
     if stream is None:
+        if not _torch.cuda.is_initialized():  # False in a forked child too, where this raises
+            _torch.cuda.init()
         c = _torch._C  # the handle of torch.cuda.current_stream() without building the object
         return c._cuda_getCurrentRawStream(c._cuda_getDevice())
     return stream.cuda_stream
