@@ -348,18 +348,18 @@ __device__ __forceinline__ void fm_slots(const IX& ix, const MU& mu, __amdgpu_bu
 // SMAX = 8 rather than 16: 101 registers instead of 146, five wavefronts per SIMD instead of three (mini-batch epoch of
 // the click-style workload, 2.5e6 rows: 4.53 -> 4.20 ms); 4 for groups of 16 (80 registers; with 16 it is 163, and the
 // gradient of the hashed workload takes 2.88 instead of 2.53 ms).
+// C and SMAX can be set lower for runs that are mostly shorter than a round (the refresh of a stratum).
 //   own(index, value) -> multiplier: the work of the lane that holds the entry
-template <int VEC, int L, int KIND, int ADDR, class Own>
+constexpr int fm_walk_round(int L) { return L < 16 ? 16 : L; }
+constexpr int fm_walk_slots(int L) { return L == 16 ? 4 : 8; }
+template <int VEC, int L, int KIND, int ADDR, int C = fm_walk_round(L), int SMAX = fm_walk_slots(L), class Own>
 __device__ __forceinline__ void fm_walk(const int32_t* __restrict__ idx, const float* __restrict__ val, int64_t beg,
                                         int64_t end, const float* __restrict__ src, int64_t stride, int sub, int kb, int rl,
                                         float (&acc)[VEC], float& gw, float& s2, Own&& own)
 {
-    constexpr int SMAX = L == 16 ? 4 : 8;
-    constexpr int C = L < 16 ? 16 : L;
     constexpr int U = C / L;
+    static_assert(C % 4 == 0 && C % L == 0 && (L > 16 || SMAX == 4 || C == 16), "rounds of whole batches");
     const int len = (int)(end - beg);
-    int left = fm_wave_max(len);
-    if (left <= 0) return;
     const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(src), 0, (int)FM_BUF_NONE, 0x20000);
     const uint32_t row_bytes = (uint32_t)stride * (uint32_t)sizeof(float);
     const bool scalar_lane = sub == rl;
@@ -381,7 +381,11 @@ __device__ __forceinline__ void fm_walk(const int32_t* __restrict__ idx, const f
             }
         }
     };
+    // On its way while the longest run is found, six steps across the wavefront: mini-batch epoch of the click-style
+    // workload, 2.5e6 rows: 4.23 -> 3.96 ms.
     fetch(0, raw, mu);
+    int left = fm_wave_max(len);
+    if (left <= 0) return;
     for (int at = 0;; at += C, left -= C) {
         int in[U];
         float mn[U];
@@ -402,15 +406,22 @@ __device__ __forceinline__ void fm_walk(const int32_t* __restrict__ idx, const f
         }
         if (at < len) {
             if constexpr (L <= 16) {
-                if (left > 4 && SMAX == 8) {
-                    fm_slots<VEC, L, KIND, ADDR, 8, 0>(ix, mu, rs, src, stride, kb, rl, scalar_lane, acc, gw, s2);
-                    if (left > 8)
-                        fm_slots<VEC, L, KIND, ADDR, 8, 8>(ix, mu, rs, src, stride, kb, rl, scalar_lane, acc, gw, s2);
-                } else {
+                bool done = false;
+                if constexpr (SMAX == 8) {
+                    if (left > 4) {
+                        done = true;
+                        fm_slots<VEC, L, KIND, ADDR, 8, 0>(ix, mu, rs, src, stride, kb, rl, scalar_lane, acc, gw, s2);
+                        if (left > 8)
+                            fm_slots<VEC, L, KIND, ADDR, 8, 8>(ix, mu, rs, src, stride, kb, rl, scalar_lane, acc, gw, s2);
+                    }
+                }
+                if (!done) {
                     fm_slots<VEC, L, KIND, ADDR, 4, 0>(ix, mu, rs, src, stride, kb, rl, scalar_lane, acc, gw, s2);
-                    if constexpr (SMAX < 8) {
+                    if constexpr (SMAX < 8 && C > 4) {
                         if (left > 4)
                             fm_slots<VEC, L, KIND, ADDR, 4, 4>(ix, mu, rs, src, stride, kb, rl, scalar_lane, acc, gw, s2);
+                    }
+                    if constexpr (SMAX < 8 && C > 8) {
                         if (left > 8)
                             fm_slots<VEC, L, KIND, ADDR, 4, 8>(ix, mu, rs, src, stride, kb, rl, scalar_lane, acc, gw, s2);
                         if (left > 12)
