@@ -986,6 +986,7 @@ static int stratified_step(fm_matrix* m, const fm_params* p, int32_t s, const fl
     }
     R.w0 = w0;
     R.V = m->dV;
+    R.big = m->D * (int64_t)p->K * (int64_t)sizeof(float) > FM_BUF_BYTES ? 1 : 0;
     R.dwn = m->dwn;
     R.y = y;
     aux_outputs(m, p->K, R, true);

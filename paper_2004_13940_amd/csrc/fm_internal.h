@@ -292,6 +292,7 @@ struct RowArgs {
     int32_t whole_rows; // forward into packed aggregate rows: write r, a, q and the padding with G
     float* row_part;    // nullable: [2*gridDim] loss and sum r per block
     double* eval_part;  // nullable: [3*gridDim] sums of losses, squared errors and correct signs per block
+    int32_t big;          // refresh: dV is larger than FM_BUF_BYTES
     int32_t dense_D;      // forward: > 0 when `val` is a dense row-major N x dense_D matrix (col is then not read)
     const int32_t* rows;  // nullable: the launch covers rows[0..N) instead of rows 0..N-1, and
                           // rowptr[k], rowptr[k+1] bound the entries of rows[k]

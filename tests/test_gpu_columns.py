@@ -1,10 +1,10 @@
-"""The column kernels at the edges of their rounds and items, against the oracle."""
+"""The column and row kernels at the edges of their rounds and items, against the oracle."""
 import numpy as np
 import pytest
 
 from oracle import fm_oracle as O
 
-from helpers import assert_close, dev_params, to_dev
+from helpers import assert_close, dev_params, run_stratified_epochs, to_dev
 
 pytestmark = pytest.mark.gpu
 
@@ -64,7 +64,7 @@ def test_evaluation_of_a_few_rows(N, K):
         print("evaluation of a few rows", N, k, flush=True)
         w = (rng.standard_normal(D) * 0.3).astype(np.float32)
         V = (rng.standard_normal((D, k)) * 0.3).astype(np.float32)
-        got = m.fm_evaluate(B.make_params(k, O.LOSS_LOGISTIC), to_dev(y), *dev_params(np.float32(0.1), w, V))
+        got = m.fm_evaluate(B.make_params(k, O.LOSS_LOGISTIC, 0.0, 0.0, 0.1), to_dev(y), *dev_params(np.float32(0.1), w, V))
         yh = O.forward(X, float(np.float32(0.1)), w, V)[3]
         loss = O.loss_multiplier(O.LOSS_LOGISTIC, 1.0, yh, y)[0].mean()
         rmse = np.sqrt(np.mean((yh - y) ** 2))
@@ -73,4 +73,35 @@ def test_evaluation_of_a_few_rows(N, K):
         sure = np.abs(yh) > 1e-5
         right = (np.sign(yh) == y)[sure].sum() / N
         assert right - 1e-9 <= got["accuracy"] <= right + (~sure).sum() / N + 1e-9
+    m.close()
+
+
+@pytest.mark.parametrize("K", [1, 2, 6, 16, 28, 32, 60, 64, 128])  # every lane count of the row kernels, K that idles lanes
+@pytest.mark.parametrize("P", [1, 3])
+def test_refresh_of_rows_of_every_length_around_the_rounds(K, P):
+    """Row i holds i mod 40 entries, so that a stratum's rows end in every place of a round, rows without entries among
+    them; aggregates, multipliers and parameters after every stratum."""
+    from types import SimpleNamespace
+    from paper_2004_13940_amd import binding as B
+    rng = np.random.default_rng(7200 + 10 * K + P)
+    N, D = 403, 61
+    mask = np.zeros((N, D), bool)
+    for i in range(N):
+        mask[i, rng.choice(D, i % 40, replace=False)] = True
+    rowptr = np.concatenate([[0], np.cumsum(mask.sum(1))]).astype(np.int64)
+    col = np.nonzero(mask)[1].astype(np.int32)
+    wl = SimpleNamespace(N=N, D=D, K=K, rowptr=rowptr, col=col, val=(rng.random(len(col)) + 0.2).astype(np.float32),
+                         y=np.where(rng.random(N) < 0.5, 1.0, -1.0).astype(np.float32), w0=np.float32(0.1),
+                         w=(rng.standard_normal(D) * 0.2).astype(np.float32),
+                         V=(rng.standard_normal((D, K)) * 0.2 / np.sqrt(K)).astype(np.float32), loss=O.LOSS_LOGISTIC,
+                         lambda_w=0.01, lambda_v=0.02, eta=0.5, loss_scale=1.0 / N, update_w0=1)
+    print("refresh of rows of every length", K, P, flush=True)
+    X = O.make_matrix(N, D, rowptr, col, wl.val)
+    m = B.Matrix(N, D, rowptr, col, wl.val)
+    m.fm_build_csc()
+    m.fm_partition(P)
+    p = B.make_params(K, wl.loss, wl.lambda_w, wl.lambda_v, wl.eta, wl.loss_scale, 1)
+    dev = (*dev_params(wl.w0, wl.w, wl.V), to_dev(wl.y))
+    host = (float(wl.w0), wl.w.astype(np.float64), wl.V.astype(np.float64))
+    run_stratified_epochs(B, wl, m, p, X, dev, host, 1, check_strata=True)
     m.close()
