@@ -570,7 +570,10 @@ __device__ __forceinline__ void add_partials(const ColArgs& A, int64_t first, in
 // items each (group g adds items g, g+NG, ... in fp64, the group totals are then added in ascending g by group 0, which
 // finishes the column).  The workgroups after them: one wavefront per long column, the listed ones left out (group g adds
 // items g, g+R, ..., then a fixed butterfly).  The last workgroup, if epi.on: the sums over the examples and the bias step.
-template <int VEC, int L, bool UPDATE>
+// WAVES false: no column is left for a wavefront (a matrix that stores every column), so there are at most a few hundred
+// workgroups, one per compute unit, and what counts is the serial chain: all registers go to it (1e6 rows of 64 columns,
+// K=32: 29 us; the kernel for both kinds, held to 112 registers, takes 43).
+template <int VEC, int L, bool UPDATE, bool WAVES>
 __global__ __launch_bounds__(FM_BLOCK) void k_cols_finish(const ColArgs A)
 {
     constexpr int R = FM_WAVE / L;
@@ -607,7 +610,8 @@ __global__ __launch_bounds__(FM_BLOCK) void k_cols_finish(const ColArgs A)
 #pragma unroll
             for (int z = 0; z < VEC; ++z) tot[z] = 0.0;
             double tg = 0.0, ts = 0.0;
-#pragma unroll 4  // in full it takes every register of the wavefront, and the other kinds of workgroup pay for it
+            constexpr int UNROLL = WAVES ? 4 : NG;  // in full it takes every register, and wavefronts with a column pay for it
+#pragma unroll UNROLL
             for (int g = 0; g < NG; ++g) {
 #pragma unroll
                 for (int z = 0; z < VEC; ++z) tot[z] += sh[(g * L + sub) * VEC + z];
@@ -622,6 +626,7 @@ __global__ __launch_bounds__(FM_BLOCK) void k_cols_finish(const ColArgs A)
         }
         return;
     }
+    if constexpr (WAVES) {
     const int lane = threadIdx.x & (FM_WAVE - 1);
     const int wave = threadIdx.x / FM_WAVE;
     const int grp = lane / L;
@@ -646,6 +651,7 @@ __global__ __launch_bounds__(FM_BLOCK) void k_cols_finish(const ColArgs A)
         for (int z = 0; z < VEC; ++z) accf[z] = (float)acc[z];
         finish_column<VEC, L, UPDATE>(A, j, sub, kbase, kact, accf, (float)gw, (float)s2,
                                       load_column<VEC, UPDATE>(A, j, sub, kbase, kact));
+    }
     }
 }
 
@@ -850,10 +856,17 @@ int launch_cols_t(fm_matrix* m, const ColArgs& A, bool update, hipStream_t st)
     const int64_t g3 = A.nvlong + by_wave + (Am.epi.on ? 1 : 0);
     if (g3 > 0) {
         ProfScope ps(m, st, FMK_COLS_FINISH);
-        if (update)
-            hipLaunchKernelGGL((k_cols_finish<VEC, L, true>), dim3((unsigned)g3), dim3(FM_BLOCK), 0, st, Am);
+        auto launch = [&](auto waves) {
+            constexpr bool W = decltype(waves)::value;
+            if (update)
+                hipLaunchKernelGGL((k_cols_finish<VEC, L, true, W>), dim3((unsigned)g3), dim3(FM_BLOCK), 0, st, Am);
+            else
+                hipLaunchKernelGGL((k_cols_finish<VEC, L, false, W>), dim3((unsigned)g3), dim3(FM_BLOCK), 0, st, Am);
+        };
+        if (by_wave > 0 || A.nvlong == 0)
+            launch(std::true_type{});
         else
-            hipLaunchKernelGGL((k_cols_finish<VEC, L, false>), dim3((unsigned)g3), dim3(FM_BLOCK), 0, st, Am);
+            launch(std::false_type{});
         FM_HIP(m, hipGetLastError());
     }
     // a stratum or batch whose steps are taken at once: every column that had entries has marked itself by now
