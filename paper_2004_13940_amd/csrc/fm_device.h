@@ -381,11 +381,13 @@ __device__ __forceinline__ void fm_walk(const int32_t* __restrict__ idx, const f
             }
         }
     };
-    // On its way while the longest run is found, six steps across the wavefront: mini-batch epoch of the click-style
-    // workload, 2.5e6 rows: 4.23 -> 3.96 ms.
-    fetch(0, raw, mu);
+    // Short rounds: the first indices are on their way while the longest run is found, six steps across the wavefront.
+    // Not for the columns: mini-batch click epoch 4.23 -> 3.96 ms, but full click epoch 7.37 -> 7.59 ms.
+    constexpr bool EARLY = C < 16;
+    if constexpr (EARLY) fetch(0, raw, mu);
     int left = fm_wave_max(len);
     if (left <= 0) return;
+    if constexpr (!EARLY) fetch(0, raw, mu);
     for (int at = 0;; at += C, left -= C) {
         int in[U];
         float mn[U];
