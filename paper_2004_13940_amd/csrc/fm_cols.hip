@@ -566,19 +566,34 @@ __device__ __forceinline__ void add_partials(const ColArgs& A, int64_t first, in
     }
 }
 
+// Sum over the wavefront's groups; lanes with equal `sub` hold the same latent slice.  Fixed butterfly order.
+template <int VEC, int L>
+__device__ __forceinline__ void add_groups(double (&acc)[VEC], double& gw, double& s2)
+{
+#pragma unroll
+    for (int o = L; o < FM_WAVE; o <<= 1) {
+#pragma unroll
+        for (int z = 0; z < VEC; ++z) acc[z] += __shfl_xor(acc[z], o, FM_WAVE);
+        gw += __shfl_xor(gw, o, FM_WAVE);
+        s2 += __shfl_xor(s2, o, FM_WAVE);
+    }
+}
+
 // The long columns from their partial sums, one launch.  Workgroups 0..nvlong-1: one column of more than vlong_items
-// items each (group g adds items g, g+NG, ... in fp64, the group totals are then added in ascending g by group 0, which
-// finishes the column).  The workgroups after them: one wavefront per long column, the listed ones left out (group g adds
-// items g, g+R, ..., then a fixed butterfly).  The last workgroup, if epi.on: the sums over the examples and the bias step.
-// WAVES false: no column is left for a wavefront (a matrix that stores every column), so there are at most a few hundred
-// workgroups, one per compute unit, and what counts is the serial chain: all registers go to it (1e6 rows of 64 columns,
-// K=32: 29 us; the kernel for both kinds, held to 112 registers, takes 43).
-template <int VEC, int L, bool UPDATE, bool WAVES>
+// items each (group g of the workgroup adds items g, g+NG, ... in fp64, every wavefront adds its groups by the butterfly,
+// and the first group adds the wavefronts and finishes the column).  The workgroups after them: one wavefront per long
+// column, the listed ones left out.  The last workgroup, if epi.on: the sums over the examples and the bias step.
+// What bounds it is the serial chain of loads of a column, not registers: the same 108 for every lane count.  One group
+// adding all NG group totals from LDS, unrolled, spilled below 8 lanes (epoch of 49,990 x 22, K=4: 109.6 us, now 34.5).
+template <int VEC, int L, bool UPDATE>
 __global__ __launch_bounds__(FM_BLOCK) void k_cols_finish(const ColArgs A)
 {
     constexpr int R = FM_WAVE / L;
     constexpr int NG = FM_BLOCK / L;  // groups per workgroup
-    __shared__ double sh[FM_BLOCK * VEC + 2 * NG];
+    constexpr int S = L * VEC + 2;    // doubles per wavefront
+    __shared__ double sh[FM_WAVES * S];
+    const int lane = threadIdx.x & (FM_WAVE - 1);
+    const int wave = threadIdx.x / FM_WAVE;
     const int sub = threadIdx.x & (L - 1);
     const int kbase = sub * VEC;
     const bool kact = kbase < A.K;
@@ -591,68 +606,45 @@ __global__ __launch_bounds__(FM_BLOCK) void k_cols_finish(const ColArgs A)
         fm_epi_final<FM_BLOCK>(A.epi, sh);
         return;
     }
+    int64_t lc;
     if (b < A.nvlong) {
-        const int grp = threadIdx.x / L;
-        const int64_t lc = A.vlong[b];
-        const int64_t j = A.long_col[lc];
-        const int64_t first = A.long_first[lc], last = A.long_first[lc + 1];
-        add_partials<VEC>(A, first + grp, last, NG, kbase, kact, acc, gw, s2);
-        double* sh_gs = sh + FM_BLOCK * VEC;
+        lc = A.vlong[b];
+        add_partials<VEC>(A, A.long_first[lc] + threadIdx.x / L, A.long_first[lc + 1], NG, kbase, kact, acc, gw, s2);
+        add_groups<VEC, L>(acc, gw, s2);
+        double* mine = sh + wave * S;
+        if (lane < L) {
 #pragma unroll
-        for (int z = 0; z < VEC; ++z) sh[(grp * L + sub) * VEC + z] = acc[z];
-        if (sub == 0) {
-            sh_gs[2 * grp] = gw;
-            sh_gs[2 * grp + 1] = s2;
+            for (int z = 0; z < VEC; ++z) mine[kbase + z] = acc[z];
+            if (sub == 0) {
+                mine[L * VEC] = gw;
+                mine[L * VEC + 1] = s2;
+            }
         }
         __syncthreads();
-        if (grp == 0) {
-            double tot[VEC];
+        if (threadIdx.x >= L) return;
 #pragma unroll
-            for (int z = 0; z < VEC; ++z) tot[z] = 0.0;
-            double tg = 0.0, ts = 0.0;
-            constexpr int UNROLL = WAVES ? 4 : NG;  // in full it takes every register, and wavefronts with a column pay for it
-#pragma unroll UNROLL
-            for (int g = 0; g < NG; ++g) {
+        for (int w = 1; w < FM_WAVES; ++w) {  // wavefront 0 is the one that adds
 #pragma unroll
-                for (int z = 0; z < VEC; ++z) tot[z] += sh[(g * L + sub) * VEC + z];
-                tg += sh_gs[2 * g];
-                ts += sh_gs[2 * g + 1];
-            }
-            float accf[VEC];
-#pragma unroll
-            for (int z = 0; z < VEC; ++z) accf[z] = (float)tot[z];
-            finish_column<VEC, L, UPDATE>(A, j, sub, kbase, kact, accf, (float)tg, (float)ts,
-                                          load_column<VEC, UPDATE>(A, j, sub, kbase, kact));
+            for (int z = 0; z < VEC; ++z) acc[z] += sh[w * S + kbase + z];
+            gw += sh[w * S + L * VEC];
+            s2 += sh[w * S + L * VEC + 1];
         }
-        return;
+    } else {
+        const int64_t rel = (b - A.nvlong) * FM_WAVES + wave;
+        if (rel >= A.nlong) return;  // whole wavefront leaves together
+        lc = A.long_base + rel;
+        const int64_t first = A.long_first[lc], last = A.long_first[lc + 1];
+        if (A.nvlong > 0 && last - first > A.vlong_items) return;
+        add_partials<VEC>(A, first + lane / L, last, R, kbase, kact, acc, gw, s2);
+        add_groups<VEC, L>(acc, gw, s2);
+        if (lane >= L) return;
     }
-    if constexpr (WAVES) {
-    const int lane = threadIdx.x & (FM_WAVE - 1);
-    const int wave = threadIdx.x / FM_WAVE;
-    const int grp = lane / L;
-    const int64_t rel = (b - A.nvlong) * FM_WAVES + wave;
-    if (rel >= A.nlong) return;  // whole wavefront leaves together
-    const int64_t lc = A.long_base + rel;
-    const int64_t first = A.long_first[lc], last = A.long_first[lc + 1];
-    if (A.nvlong > 0 && last - first > A.vlong_items) return;
     const int64_t j = A.long_col[lc];
-    add_partials<VEC>(A, first + grp, last, R, kbase, kact, acc, gw, s2);
-    // combine the R groups: lanes with equal `sub` hold the same latent slice
+    float accf[VEC];
 #pragma unroll
-    for (int o = L; o < FM_WAVE; o <<= 1) {
-#pragma unroll
-        for (int z = 0; z < VEC; ++z) acc[z] += __shfl_xor(acc[z], o, FM_WAVE);
-        gw += __shfl_xor(gw, o, FM_WAVE);
-        s2 += __shfl_xor(s2, o, FM_WAVE);
-    }
-    if (grp == 0) {
-        float accf[VEC];
-#pragma unroll
-        for (int z = 0; z < VEC; ++z) accf[z] = (float)acc[z];
-        finish_column<VEC, L, UPDATE>(A, j, sub, kbase, kact, accf, (float)gw, (float)s2,
-                                      load_column<VEC, UPDATE>(A, j, sub, kbase, kact));
-    }
-    }
+    for (int z = 0; z < VEC; ++z) accf[z] = (float)acc[z];
+    finish_column<VEC, L, UPDATE>(A, j, sub, kbase, kact, accf, (float)gw, (float)s2,
+                                  load_column<VEC, UPDATE>(A, j, sub, kbase, kact));
 }
 
 // LDS-staged kernel for the tile items; false if the tile does not fit in LDS for this K
@@ -856,17 +848,10 @@ int launch_cols_t(fm_matrix* m, const ColArgs& A, bool update, hipStream_t st)
     const int64_t g3 = A.nvlong + by_wave + (Am.epi.on ? 1 : 0);
     if (g3 > 0) {
         ProfScope ps(m, st, FMK_COLS_FINISH);
-        auto launch = [&](auto waves) {
-            constexpr bool W = decltype(waves)::value;
-            if (update)
-                hipLaunchKernelGGL((k_cols_finish<VEC, L, true, W>), dim3((unsigned)g3), dim3(FM_BLOCK), 0, st, Am);
-            else
-                hipLaunchKernelGGL((k_cols_finish<VEC, L, false, W>), dim3((unsigned)g3), dim3(FM_BLOCK), 0, st, Am);
-        };
-        if (by_wave > 0 || A.nvlong == 0)
-            launch(std::true_type{});
+        if (update)
+            hipLaunchKernelGGL((k_cols_finish<VEC, L, true>), dim3((unsigned)g3), dim3(FM_BLOCK), 0, st, Am);
         else
-            launch(std::false_type{});
+            hipLaunchKernelGGL((k_cols_finish<VEC, L, false>), dim3((unsigned)g3), dim3(FM_BLOCK), 0, st, Am);
         FM_HIP(m, hipGetLastError());
     }
     // a stratum or batch whose steps are taken at once: every column that had entries has marked itself by now

@@ -46,6 +46,33 @@ def test_columns_of_every_length_around_the_rounds_and_the_item(K):
     m.close()
 
 
+@pytest.mark.parametrize("K", [1, 2, 4, 8, 24, 64, 128, 256])  # every lane count of the finish
+def test_table_whose_columns_are_all_summed_by_a_workgroup(K):
+    """Every column has more items than a wavefront sums (128 of 32 entries), as in a table of some thousand rows."""
+    import torch
+    from paper_2004_13940_amd import binding as B
+    rng = np.random.default_rng(7050 + K)
+    N, D = 4200, 5
+    rowptr, col = np.arange(N + 1, dtype=np.int64) * D, np.tile(np.arange(D, dtype=np.int32), N)
+    val = rng.standard_normal(N * D).astype(np.float32)
+    y = rng.standard_normal(N).astype(np.float32)
+    w = (rng.standard_normal(D) * 0.1).astype(np.float32)
+    V = (rng.standard_normal((D, K)) * 0.1).astype(np.float32)
+    print("columns summed by a workgroup", K, flush=True)
+    m = B.Matrix(N, D, rowptr, col, val)
+    m.fm_build_csc()
+    d_w0, d_w, d_V = dev_params(np.float32(0.1), w, V)
+    m.fm_sgd_epoch(B.make_params(K, O.LOSS_SQUARED, 0.01, 0.02, 0.5, 1.0 / N), to_dev(y), d_w0, d_w, d_V)
+    torch.cuda.synchronize()
+    X = O.make_matrix(N, D, rowptr, col, val)
+    w0_o, w_o, V_o, _ = O.full_epoch(X, y, float(np.float32(0.1)), w, V, loss=O.LOSS_SQUARED, s=1.0 / N, lambda_w=0.01,
+                                     lambda_v=0.02, eta=0.5, update_w0=True)
+    assert_close(d_w.cpu().numpy(), w_o, "w")
+    assert_close(d_V.cpu().numpy().reshape(D, K), V_o, "V")
+    assert abs(d_w0.item() - w0_o) <= 1e-5 * max(abs(w0_o), 0.1)
+    m.close()
+
+
 @pytest.mark.parametrize("N,K", [(1, 1), (1, 2), (2, 1), (5, 3), (17, 64), (300, 4), (1, 256)])
 def test_evaluation_of_a_few_rows(N, K):
     """The row kernel leaves three doubles per block of rows for the metrics: at the smallest N and K they take more room

@@ -1,0 +1,50 @@
+"""What the compiler gave the kernels of the built library: read from the metadata note of its gfx950 code objects."""
+import os
+import struct
+
+import msgpack
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+LIB = os.path.join(ROOT, "paper_2004_13940_amd", "libfm_mi355x.so")
+EM_AMDGPU, NT_AMDGPU_METADATA = 224, 32
+
+
+def _notes(obj):
+    """Descriptors of the AMDGPU metadata notes of one ELF64 code object."""
+    shoff, = struct.unpack_from("<Q", obj, 0x28)
+    shentsize, shnum = struct.unpack_from("<HH", obj, 0x3A)
+    for i in range(shnum):
+        typ, = struct.unpack_from("<I", obj, shoff + i * shentsize + 4)
+        off, size = struct.unpack_from("<QQ", obj, shoff + i * shentsize + 0x18)
+        at = off
+        while typ == 7 and at < off + size:
+            namesz, descsz, kind = struct.unpack_from("<III", obj, at)
+            desc = at + 12 + (namesz + 3) // 4 * 4
+            if kind == NT_AMDGPU_METADATA and obj[at + 12:at + 12 + 6] == b"AMDGPU":
+                yield msgpack.unpackb(obj[desc:desc + descsz])
+            at = desc + (descsz + 3) // 4 * 4
+
+
+@pytest.fixture(scope="module")
+def kernels():
+    if not os.path.exists(LIB):
+        from paper_2004_13940_amd import build
+        build.build()
+    data = open(LIB, "rb").read()
+    found, at = {}, data.find(b"\x7fELF", 1)
+    while at >= 0:
+        if data[at + 4] == 2 and struct.unpack_from("<H", data, at + 18)[0] == EM_AMDGPU:
+            for note in _notes(memoryview(data)[at:].tobytes() if at else data):
+                for k in note["amdhsa.kernels"]:
+                    found[k[".name"]] = k
+        at = data.find(b"\x7fELF", at + 1)
+    assert len(found) > 250, "kernels of the library"
+    return found
+
+
+def test_no_kernel_spills(kernels):
+    """Every instantiation is reached by some K: registers that spill to scratch memory make the small ones, which have
+    the most lane groups to a workgroup, many times slower."""
+    spilled = {n: k[".private_segment_fixed_size"] for n, k in kernels.items() if k[".private_segment_fixed_size"] > 0}
+    assert spilled == {}
