@@ -21,7 +21,6 @@ namespace {
 
 // Accumulate one run of entries [beg,end) of a column into acc/gw/s2 (per-lane
 // partials for gw, s2; complete sums for acc's latent slice).  All groups of the wavefront call it together.
-// once: the gathered rows are not used again soon.
 template <int VEC, int L, int PACKED, int ADDR>
 __device__ __forceinline__ void walk_column(const ColArgs& A, int64_t beg, int64_t end, int sub, int kbase, bool kact,
                                             float (&acc)[VEC], float& gw, float& s2)
@@ -35,21 +34,26 @@ __device__ __forceinline__ void walk_column(const ColArgs& A, int64_t beg, int64
         const float* __restrict__ r = A.r;
         const int64_t rs = A.rs;
         float unused = 0.f;
-        fm_walk<VEC, L, FM_WALK_SUM, ADDR>(A.row, A.val, beg, end, A.G, A.gs, sub, kact ? kbase : 0, 0, acc, unused, unused,
-                                           [&](int i, float x) {
-                                               const float xr = x * r[(int64_t)i * rs];
-                                               gw += xr;
-                                               s2 += x * xr;
-                                               return xr;
-                                           });
+        auto own = [&](int i, float x) {
+            const float xr = x * r[(int64_t)i * rs];
+            gw += xr;
+            s2 += x * xr;
+            return xr;
+        };
+        if constexpr (L >= FM_WIDE_GROUP)
+            fm_walk_wide<VEC, L>(A.row, A.val, beg, end, A.G, A.gs, sub, kact ? kbase : 0, acc, own);
+        else
+            fm_walk<VEC, L, FM_WALK_SUM, ADDR>(A.row, A.val, beg, end, A.G, A.gs, sub, kact ? kbase : 0, 0, acc, unused, unused,
+                                               own);
     }
 }
 
+// once: the gathered rows are not used again soon
 template <int VEC, int L, int PACKED>
 __device__ __forceinline__ void accumulate_entries(const ColArgs& A, bool once, int64_t beg, int64_t end, int sub, int kbase,
                                                    bool kact, float (&acc)[VEC], float& gw, float& s2)
 {
-    if (A.big)
+    if (L >= FM_WIDE_GROUP || A.big)
         walk_column<VEC, L, PACKED, FM_ADDR_PTR>(A, beg, end, sub, kbase, kact, acc, gw, s2);
     else if (once && A.nt)
         walk_column<VEC, L, PACKED, FM_ADDR_BUF_NT>(A, beg, end, sub, kbase, kact, acc, gw, s2);
@@ -865,14 +869,18 @@ int launch_cols_t(fm_matrix* m, const ColArgs& A, bool update, hipStream_t st)
 template <int VEC, int PACKED>
 int launch_cols_v(fm_matrix* m, int lanes, const ColArgs& A, bool update, hipStream_t st)
 {
+    if constexpr (PACKED == FM_PLANAR) {  // a packed row, K <= 28, takes two to eight lanes
+        switch (lanes) {
+            case 1: return launch_cols_t<VEC, 1, PACKED>(m, A, update, st);
+            case 16: return launch_cols_t<VEC, 16, PACKED>(m, A, update, st);
+            case 32: return launch_cols_t<VEC, 32, PACKED>(m, A, update, st);
+            case 64: return launch_cols_t<VEC, 64, PACKED>(m, A, update, st);
+        }
+    }
     switch (lanes) {
-        case 1: return launch_cols_t<VEC, 1, PACKED>(m, A, update, st);
         case 2: return launch_cols_t<VEC, 2, PACKED>(m, A, update, st);
         case 4: return launch_cols_t<VEC, 4, PACKED>(m, A, update, st);
         case 8: return launch_cols_t<VEC, 8, PACKED>(m, A, update, st);
-        case 16: return launch_cols_t<VEC, 16, PACKED>(m, A, update, st);
-        case 32: return launch_cols_t<VEC, 32, PACKED>(m, A, update, st);
-        case 64: return launch_cols_t<VEC, 64, PACKED>(m, A, update, st);
     }
     return fm_fail(m, FM_EINVAL, "unsupported lane count %d", lanes);
 }

@@ -263,6 +263,58 @@ __device__ __forceinline__ void fm_gather_accumulate(const int32_t* __restrict__
     }
 }
 
+// From this many lanes on a group walks alone (fm_walk_wide), below it in step with its wavefront's other groups
+// (fm_walk).  Rounds in step for 16 lanes and more kept one to four runs per wavefront apart at the price of 78 to 102
+// registers, six or four wavefronts per SIMD where eight fit: 2e6 hashed rows over 2e7 permuted columns, K=64, gradient
+// 11.53 ms in step, 10.10 alone; stratified epoch over 128 strata 76.4 and 64.2 ms; text-like
+// workload with K=64 stratified 1.10 and 1.08, K=22 1.11 and 1.04, epochs 135.8 and 134.7 us, 96.7 and 93.2 us.
+constexpr int FM_WIDE_GROUP = 16;
+
+// The inner loop of the column kernels and of the refresh for wide groups (K > 32, or K > 16 where it is not a multiple of
+// four, or odd from 9 on).  A group walks its run [beg,end) L entries to a round, four gathers at a time, at most 64
+// registers in all.  Latency-bound: the indices of the next round are on their way during this one, and the gathers of a
+// round are issued before the multipliers (own's own loads) are waited for.
+template <int VEC, int L, class Own>
+__device__ __forceinline__ void fm_walk_wide(const int32_t* __restrict__ idx, const float* __restrict__ val, int64_t beg,
+                                             int64_t end, const float* __restrict__ src, int64_t stride, int sub, int kb,
+                                             float (&acc)[VEC], Own&& own)
+{
+    const int len = (int)(end - beg);
+    if (len <= 0) return;
+    const int32_t* __restrict__ ip = idx + beg;
+    const float* __restrict__ vp = val + beg;
+    const float* __restrict__ sp = src + kb;
+    int ix = ip[sub < len ? sub : len - 1];
+    float mu = sub < len ? vp[sub] : 0.f;
+    for (int at = 0;;) {
+        const int nv = len - at < L ? len - at : L;
+        const int i = ix;
+        float x = mu;
+        at += L;
+        const int t = at + sub < len ? at + sub : len - 1;
+        if (at < len) {  // the next round's indices are on their way during this one
+            ix = ip[t];
+            mu = at + sub < len ? vp[t] : 0.f;
+        }
+        x = own(i, x);
+        for (int t0 = 0; t0 < nv; t0 += 4) {
+            float g[4][VEC];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const int it = __shfl(i, t0 + u < nv ? t0 + u : nv - 1, L);
+                fm_load_vec<VEC>(sp + (int64_t)it * stride, g[u]);
+            }
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const float m = __shfl(x, t0 + u, L);  // 0 where the run is over
+#pragma unroll
+                for (int z = 0; z < VEC; ++z) acc[z] += m * g[u][z];
+            }
+        }
+        if (at >= len) break;
+    }
+}
+
 // Largest value over the 64 lanes, as a wave-uniform number (a scalar register: branches on it do not diverge).
 __device__ __forceinline__ int fm_wave_max(int v)
 {
@@ -339,26 +391,24 @@ __device__ __forceinline__ void fm_slots(const IX& ix, const MU& mu, __amdgpu_bu
     }
 }
 
-// The inner loop of the column kernels.  Every group of L lanes walks its own run [beg,end) of one column, all groups of
-// the wavefront in step: a round takes the next C entries of every run (16; L for wider groups), in batches of SMAX or
-// four slots by the longest run left, so the choice is a scalar branch, and a group whose run is over sits the round
-// out.  The indices of the next round are loaded while the gathers of this one are on their way: a round costs one
-// memory latency, not two.  Columns of a few entries are what a stratum or a batch consists of; with a slot loop and a
-// four-at-a-time tail per group a column of 15 entries took six round trips, here it takes two.
-// SMAX = 8 rather than 16: 101 registers instead of 146, five wavefronts per SIMD instead of three (mini-batch epoch of
-// the click-style workload, 2.5e6 rows: 4.53 -> 4.20 ms); 4 for groups of 16 (80 registers; with 16 it is 163, and the
-// gradient of the hashed workload takes 2.88 instead of 2.53 ms).
-// C and SMAX can be set lower for runs that are mostly shorter than a round (the refresh of a stratum).
+// The inner loop of the column kernels and of the refresh for groups of up to eight lanes.  Every group of L lanes walks
+// its own run [beg,end) of one column, all groups of the wavefront in step: a round takes the next C entries of every run,
+// in batches of SMAX or four slots by the longest run left, so the choice is a scalar branch, and a group whose run is
+// over sits the round out.  The indices of the next round are loaded while the gathers of this one are on their way: a
+// round costs one memory latency, not two.  Columns of a few entries are what a stratum or a batch consists of; with a
+// slot loop and a four-at-a-time tail per group a column of 15 entries took six round trips, here it takes two.
+// SMAX = 8 rather than 16 in the columns: 103 registers instead of 146 at eight lanes of a packed row, four wavefronts per
+// SIMD instead of three (mini-batch epoch of the click-style workload, 2.5e6 rows: 4.53 -> 4.20 ms).
+// The refresh of a stratum, whose runs are mostly shorter than a round, takes rounds of four or eight in fours.
 //   own(index, value) -> multiplier: the work of the lane that holds the entry
-constexpr int fm_walk_round(int L) { return L < 16 ? 16 : L; }
-constexpr int fm_walk_slots(int L) { return L == 16 ? 4 : 8; }
-template <int VEC, int L, int KIND, int ADDR, int C = fm_walk_round(L), int SMAX = fm_walk_slots(L), class Own>
+template <int VEC, int L, int KIND, int ADDR, int C = 16, int SMAX = 8, class Own>
 __device__ __forceinline__ void fm_walk(const int32_t* __restrict__ idx, const float* __restrict__ val, int64_t beg,
                                         int64_t end, const float* __restrict__ src, int64_t stride, int sub, int kb, int rl,
                                         float (&acc)[VEC], float& gw, float& s2, Own&& own)
 {
     constexpr int U = C / L;
-    static_assert(C % 4 == 0 && C % L == 0 && (L > 16 || SMAX == 4 || C == 16), "rounds of whole batches");
+    static_assert(L < FM_WIDE_GROUP && C % L == 0 && ((SMAX == 8 && C == 16) || (SMAX == 4 && (C == 4 || C == 8))),
+                  "rounds of whole batches");
     const int len = (int)(end - beg);
     const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(src), 0, (int)FM_BUF_NONE, 0x20000);
     const uint32_t row_bytes = (uint32_t)stride * (uint32_t)sizeof(float);
@@ -407,41 +457,20 @@ __device__ __forceinline__ void fm_walk(const int32_t* __restrict__ idx, const f
             }
         }
         if (at < len) {
-            if constexpr (L <= 16) {
-                bool done = false;
-                if constexpr (SMAX == 8) {
-                    if (left > 4) {
-                        done = true;
-                        fm_slots<VEC, L, KIND, ADDR, 8, 0>(ix, mu, rs, src, stride, kb, rl, scalar_lane, acc, gw, s2);
-                        if (left > 8)
-                            fm_slots<VEC, L, KIND, ADDR, 8, 8>(ix, mu, rs, src, stride, kb, rl, scalar_lane, acc, gw, s2);
-                    }
+            bool done = false;
+            if constexpr (SMAX == 8) {
+                if (left > 4) {
+                    done = true;
+                    fm_slots<VEC, L, KIND, ADDR, 8, 0>(ix, mu, rs, src, stride, kb, rl, scalar_lane, acc, gw, s2);
+                    if (left > 8)
+                        fm_slots<VEC, L, KIND, ADDR, 8, 8>(ix, mu, rs, src, stride, kb, rl, scalar_lane, acc, gw, s2);
                 }
-                if (!done) {
-                    fm_slots<VEC, L, KIND, ADDR, 4, 0>(ix, mu, rs, src, stride, kb, rl, scalar_lane, acc, gw, s2);
-                    if constexpr (SMAX < 8 && C > 4) {
-                        if (left > 4)
-                            fm_slots<VEC, L, KIND, ADDR, 4, 4>(ix, mu, rs, src, stride, kb, rl, scalar_lane, acc, gw, s2);
-                    }
-                    if constexpr (SMAX < 8 && C > 8) {
-                        if (left > 8)
-                            fm_slots<VEC, L, KIND, ADDR, 4, 8>(ix, mu, rs, src, stride, kb, rl, scalar_lane, acc, gw, s2);
-                        if (left > 12)
-                            fm_slots<VEC, L, KIND, ADDR, 4, 12>(ix, mu, rs, src, stride, kb, rl, scalar_lane, acc, gw, s2);
-                    }
-                }
-            } else {
-                // one or two runs per wavefront: eight entries at a time, broadcast through the LDS crossbar
-                const int nv = left < C ? left : C;
-                for (int t0 = 0; t0 < nv; t0 += 8) {
-                    int i8[8];
-                    float x8[8];
-#pragma unroll
-                    for (int u = 0; u < 8; ++u) {  // t0 + u < L: L is a multiple of eight
-                        i8[u] = __shfl(ix[0], t0 + u, L);
-                        x8[u] = __shfl(mu[0], t0 + u, L);
-                    }
-                    fm_slots<VEC, 1, KIND, ADDR, 8, 0>(i8, x8, rs, src, stride, kb, rl, scalar_lane, acc, gw, s2);
+            }
+            if (!done) {
+                fm_slots<VEC, L, KIND, ADDR, 4, 0>(ix, mu, rs, src, stride, kb, rl, scalar_lane, acc, gw, s2);
+                if constexpr (SMAX == 4 && C == 8) {
+                    if (left > 4)
+                        fm_slots<VEC, L, KIND, ADDR, 4, 4>(ix, mu, rs, src, stride, kb, rl, scalar_lane, acc, gw, s2);
                 }
             }
         }

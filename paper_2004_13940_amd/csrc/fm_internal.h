@@ -52,7 +52,8 @@ struct fm_matrix;
 bool fm_aux_packed(const fm_matrix* m, int32_t K);
 // floats per row of partial sums [acc_0..acc_{K-1} | gw | s2 | pad]: a multiple of 32 (128 bytes)
 inline int64_t fm_part_stride(int32_t K) { return ((int64_t)K + 2 + 31) / 32 * 32; }
-// Arrays up to this size are gathered through a buffer descriptor with offsets of 32 bits (see fm_walk)
+// Arrays up to this size are gathered through a buffer descriptor with offsets of 32 bits (see fm_walk; wide groups use
+// 64-bit addresses at any size)
 constexpr int64_t FM_BUF_BYTES = 0xFFFFF000LL;
 // How the column kernels read the aggregate rows (ColArgs::packed).
 enum { FM_PLANAR = 0, FM_PACKED_LANE = 1 };

@@ -77,18 +77,21 @@ __global__ __launch_bounds__(FM_BLOCK) void k_rows(const RowArgs A)
         const float2* __restrict__ dwn = A.dwn;
         float unused = 0.f;
         // A row has few entries inside one stratum (1 to 4 where it has any): rounds as short as the group allows, four
-        // gathers at a time, so that few registers are in use and many rows in flight, and a slot without an entry is no
-        // request (BUF addressing).  Missing entries used to repeat the last one: three of four requests of a row with
-        // one entry (stratified epoch of the click-style workload, 1e7 rows, 64 strata: 39.0 -> 37.5 ms).
-        constexpr int ROUND = L < 4 ? 4 : L;
-        constexpr int ADDR = MODE == MODE_REFRESH ? FM_ADDR_BUF : FM_ADDR_PTR;
-        fm_walk<VEC, L, FM_WALK_SUM, ADDR, ROUND, 4>(A.col, A.val, beg, end, A.V, K, sub, kb, 0, acc, unused, unused,
-                                                     [&](int c, float x) {
-                                                         const float2 d = dwn[c];
-                                                         a_acc += d.x * x;
-                                                         q_acc += d.y * (x * x);
-                                                         return x;
-                                                     });
+        // gathers at a time, so that few registers are in use and many rows in flight; for groups of up to eight lanes a
+        // slot without an entry is no request (BUF addressing).  Missing entries used to repeat the last one: three of
+        // four requests of a row with one entry (stratified epoch of the click-style workload, 1e7 rows, 64 strata:
+        // 39.0 -> 38.5 ms).
+        auto own = [&](int c, float x) {
+            const float2 d = dwn[c];
+            a_acc += d.x * x;
+            q_acc += d.y * (x * x);
+            return x;
+        };
+        if constexpr (L >= FM_WIDE_GROUP)
+            fm_walk_wide<VEC, L>(A.col, A.val, beg, end, A.V, K, sub, kb, acc, own);
+        else
+            fm_walk<VEC, L, FM_WALK_SUM, MODE == MODE_REFRESH ? FM_ADDR_BUF : FM_ADDR_PTR, L < 4 ? 4 : L, 4>(
+                A.col, A.val, beg, end, A.V, K, sub, kb, 0, acc, unused, unused, own);
     }
     if (!kact) {  // idle lanes of a group wider than K/VEC worked on a valid but foreign slice
 #pragma unroll
@@ -210,8 +213,9 @@ int launch_rows_t(fm_matrix* m, const RowArgs& A, bool refresh, hipStream_t st)
     if (grid <= 0) return FM_OK;
     if (grid > 0x7fffffffLL) return fm_fail(m, FM_ERANGE, "row grid too large");
     ProfScope ps(m, st, refresh ? FMK_ROWS_REFRESH : FMK_ROWS_FORWARD);
+    constexpr int BIG = L < FM_WIDE_GROUP ? MODE_REFRESH_BIG : MODE_REFRESH;  // wide groups use 64-bit addresses throughout
     if (refresh && A.big) {
-        hipLaunchKernelGGL((k_rows<VEC, L, MODE_REFRESH_BIG>), dim3((unsigned)grid), dim3(FM_BLOCK), 0, st, A);
+        hipLaunchKernelGGL((k_rows<VEC, L, BIG>), dim3((unsigned)grid), dim3(FM_BLOCK), 0, st, A);
     } else if (refresh) {
         hipLaunchKernelGGL((k_rows<VEC, L, MODE_REFRESH>), dim3((unsigned)grid), dim3(FM_BLOCK), 0, st, A);
     } else if (A.Vh != nullptr) {

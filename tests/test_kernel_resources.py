@@ -1,5 +1,6 @@
 """What the compiler gave the kernels of the built library: read from the metadata note of its gfx950 code objects."""
 import os
+import re
 import struct
 
 import msgpack
@@ -48,3 +49,12 @@ def test_no_kernel_spills(kernels):
     the most lane groups to a workgroup, many times slower."""
     spilled = {n: k[".private_segment_fixed_size"] for n, k in kernels.items() if k[".private_segment_fixed_size"] > 0}
     assert spilled == {}
+
+
+def test_wide_groups_leave_room_for_eight_wavefronts(kernels):
+    """Columns and refresh with 16 lanes to a group and more (K > 32) have few runs per wavefront and are bound by latency:
+    up to 64 of the 512 registers per lane of a SIMD, so that eight wavefronts fit."""
+    wide = {n: k[".vgpr_count"] for n, k in kernels.items()
+            if re.search(r"k_colsILi[124]ELi(16|32|64)E|k_rowsILi[124]ELi(16|32|64)ELi1E", n)}
+    assert len(wide) == 27, sorted(wide)
+    assert {n: v for n, v in wide.items() if v > 64} == {}
