@@ -568,9 +568,9 @@ static void fill_long(const fm_matrix* m, ColArgs& A, const LongIndex& li, int32
     A.item_col = li.item_col;
     A.item_beg = li.item_beg;
     A.item_len = li.item_len;
-    A.order = strat ? nullptr : li.order;
-    A.ord_beg = li.ord_beg;
-    A.ord_len = li.ord_len;
+    A.order = li.order != nullptr ? li.order + i0 : nullptr;  // a stratum or batch: one sequence, list_off is zero
+    A.ord_beg = li.ord_beg != nullptr ? li.ord_beg + i0 : nullptr;
+    A.ord_len = li.ord_len != nullptr ? li.ord_len + i0 : nullptr;
     for (int x = 0; x <= FM_XCDS; ++x) A.list_off[x] = li.list_off[x];
     for (int x = 0; x < FM_XCDS; ++x) A.list_mid[x] = li.list_mid[x];
     A.tile_rows = li.tile_rows;

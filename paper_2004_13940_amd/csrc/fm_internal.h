@@ -100,7 +100,8 @@ struct LongIndex {
     int32_t* short_len = nullptr;   // entries of every listed column (the full matrix has its colptr)
     std::vector<int64_t> h_short_off;
     // processing order of the full matrix: FM_XCDS lists of item ids, list x walked by the
-    // workgroups that run on XCD x, heavy columns panel by panel (order == nullptr: id order)
+    // workgroups that run on XCD x, heavy columns panel by panel; of strata and batches: by first row inside each
+    // (then all list offsets are 0 and item_beg, item_len are given back); order == nullptr: id order
     uint32_t* order = nullptr;      // [nitems]
     int64_t* ord_beg = nullptr;     // [nitems] item_beg / item_len in processing order
     int32_t* ord_len = nullptr;
@@ -266,7 +267,7 @@ int fm_sort_by_key_u32(fm_matrix* m, uint32_t* keys, uint32_t* idx, uint32_t* ke
                        int64_t n, int bits, hipStream_t st, bool* result_in_alt);
 // ptr[c], ptr[c+1] bound the entries of list position c = 0..ncols_total-1; ids[c] is its column;
 // h_bounds[s] (nstrata+1 values) is the first list position of stratum s
-int fm_build_long_index(fm_matrix* m, const int64_t* ptr, const int32_t* ids, int64_t ncols_total,
+int fm_build_long_index(fm_matrix* m, const int64_t* ptr, const int32_t* ids, const int32_t* row, int64_t ncols_total,
                         const std::vector<int64_t>& h_bounds, int32_t nstrata, LongIndex* out, hipStream_t st);
 // lfull, with the panel order of heavy columns and the LDS tiles shaped for latent size K (0: unknown)
 int fm_build_full_index(fm_matrix* m, int32_t K, hipStream_t st);
@@ -391,14 +392,14 @@ struct ColArgs {
     const int32_t* item_len;
     int64_t nlong, nitems;        // counts of this launch
     int64_t long_base, item_base;  // first long column / first item of this launch (absolute ids)
-    const uint32_t* order;         // nullable: item ids in processing order, FM_XCDS lists
+    const uint32_t* order;         // nullable: item ids in processing order, FM_XCDS lists and what follows them
     const int64_t* ord_beg;        // with order: item_beg / item_len in processing order
     const int32_t* ord_len;
     int64_t list_off[FM_XCDS + 1];
     int64_t list_mid[FM_XCDS];
     int64_t tile_rows, ntiles;     // dense-ish columns: items sorted by row tile, after the lists
     const int64_t* tile_ptr;
-    int64_t lin_base, lin_count;   // positions of `order` that are taken in sequence (tile items that are not staged)
+    int64_t lin_base, lin_count;   // positions of `order` that are taken in sequence (tile items that are not staged; all of a stratum or batch)
     int64_t blk_lists, blk_lin, blk_short;  // workgroups of k_cols per role, in this order; then epi.nsums for the sums
     int32_t nt;                    // gathers of rows that are not used again soon carry the non-temporal hint
     int32_t big;                   // the gathered array is larger than FM_BUF_BYTES

@@ -132,3 +132,40 @@ def test_refresh_of_rows_of_every_length_around_the_rounds(K, P):
     host = (float(wl.w0), wl.w.astype(np.float64), wl.V.astype(np.float64))
     run_stratified_epochs(B, wl, m, p, X, dev, host, 1, check_strata=True)
     m.close()
+
+
+@pytest.mark.parametrize("N,P,K", [(65_535, 3, 8), (65_536, 3, 8), (70_001, 600, 16), (70_001, 600, 32), (66_000, 1, 4)])
+def test_items_of_strata_and_batches_in_row_order(N, P, K):
+    """Columns that are full, start late or end early, so that their items interleave by row; from 65,536 rows on they are
+    worked on in that order; with 600 strata of 70,001 rows a stratum and a row no longer fit the sort key together and
+    rows are taken in units of eight."""
+    from types import SimpleNamespace
+    from paper_2004_13940_amd import binding as B
+    from test_gpu_parity import _run_minibatch_epochs
+    rng = np.random.default_rng(7400 + N + K)
+    D = max(P, 7)
+    mask = rng.random((N, D)) < 2.0 / D
+    for j, lo, hi in ((0, 0, N), (D // 3, 0, N), (D // 2, N // 3, N), (D - 2, 0, N // 2), (D - 1, 0, N)):
+        mask[lo:hi, j] = True
+    rowptr = np.concatenate([[0], np.cumsum(mask.sum(1))]).astype(np.int64)
+    col = np.nonzero(mask)[1].astype(np.int32)
+    wl = SimpleNamespace(N=N, D=D, K=K, P=P, rowptr=rowptr, col=col, val=rng.standard_normal(len(col)).astype(np.float32),
+                         y=np.where(rng.random(N) < 0.5, 1.0, -1.0).astype(np.float32), w0=np.float32(0.1),
+                         w=(rng.standard_normal(D) * 0.2).astype(np.float32),
+                         V=(rng.standard_normal((D, K)) * 0.2 / np.sqrt(K)).astype(np.float32), loss=O.LOSS_LOGISTIC,
+                         lambda_w=0.01, lambda_v=0.02, eta=0.5, loss_scale=1.0 / N, update_w0=1, name="row order",
+                         nnz=len(col))
+    print("items in row order", N, P, K, flush=True)
+    X = O.make_matrix(N, D, rowptr, col, wl.val)
+    m = B.Matrix(N, D, rowptr, col, wl.val)
+    m.fm_set_tuning(seg=16)
+    m.fm_build_csc()
+    m.fm_partition(P)
+    p = B.make_params(K, wl.loss, wl.lambda_w, wl.lambda_v, wl.eta, wl.loss_scale, 1)
+    dev = (*dev_params(wl.w0, wl.w, wl.V), to_dev(wl.y))
+    host = (float(wl.w0), wl.w.astype(np.float64), wl.V.astype(np.float64))
+    run_stratified_epochs(B, wl, m, p, X, dev, host, 1)
+    m.close()
+    wl.lambda_w = wl.lambda_v = 1e-5  # a batch is scored before its columns take their postponed regulariser steps
+    m2, _, _ = _run_minibatch_epochs(B, wl, P, 1, update_w0=True, setup=lambda h: h.fm_set_tuning(seg=16))
+    m2.close()
