@@ -843,13 +843,9 @@ int launch_cols_t(fm_matrix* m, const ColArgs& A, bool update, hipStream_t st)
             FM_HIP(m, hipStreamWaitEvent(st, m->ev_join1, 0));
         }
     }
-    if (dense && A.epi.on) {
-        FM_TRY(fm_run_epilogue(m, A.epi, st));
-        Am.epi.on = 0;
-    }
     // nothing left for single wavefronts when every long column is on the list of the very long ones
     const int64_t by_wave = A.nvlong == A.nlong ? 0 : (A.nlong + FM_WAVES - 1) / FM_WAVES;
-    const int64_t g3 = A.nvlong + by_wave + (Am.epi.on ? 1 : 0);
+    const int64_t g3 = A.nvlong + by_wave + (A.epi.on ? 1 : 0);
     if (g3 > 0) {
         ProfScope ps(m, st, FMK_COLS_FINISH);
         if (update)

@@ -10,6 +10,7 @@
 //   A: lane l holds A[l % 32][l / 32];   B: lane l holds B[l / 32][l % 32];
 //   C: register v of lane l holds C[8 * (v / 4) + 4 * (l / 32) + v % 4][l % 32].
 #include "fm_device.h"
+#include "fm_epilogue.h"
 #include "fm_internal.h"
 
 namespace {
@@ -157,15 +158,23 @@ __global__ __launch_bounds__(FM_BLOCK) void k_rows_dense(const RowArgs A)
 // Partial sums of every column over one chunk of rows per wavefront: for column j and latent k
 //   acc = sum_i x_ij r_i G_ik,  gw = sum_i x_ij r_i,  s2 = sum_i x_ij^2 r_i      (eqs. updates_w, updates_v),
 // two rows per matrix-core step (row parity = the contraction index).  Stored as the row
-// [acc | gw | s2] of item j * nchunks + c, which the finish kernels add in fp64 in item order.
+// [acc | gw | s2] of item j * nchunks + c, which the finish kernels add in fp64 in item order.  The first epi.nsums
+// workgroups, if epi.on, add up the examples instead, as in k_cols; as launches of their own between this kernel and the
+// finish they took 13 us of the 216 us of a full-gradient epoch of 1e6 x 64, K=32 (two launches on the critical path).
 template <int DB, int KB>
 __global__ __launch_bounds__(FM_BLOCK) void k_cols_dense(const ColArgs A)
 {
     constexpr int D = DB * DT, K = KB * DT;
+    const int sums = A.epi.on ? A.epi.nsums : 0;
+    if ((int)blockIdx.x < sums) {
+        __shared__ double sh[FM_WAVES];
+        fm_epi_partial<FM_BLOCK>(A.epi, (int)blockIdx.x, sh);
+        return;
+    }
     const int lane = threadIdx.x & (FM_WAVE - 1);
     const int wave = threadIdx.x / FM_WAVE;
     const int half = lane / 32, lo = lane % 32;
-    const int64_t c = (int64_t)blockIdx.x * FM_WAVES + wave;
+    const int64_t c = (int64_t)(blockIdx.x - sums) * FM_WAVES + wave;
     if (c >= A.nchunks) return;
     const int64_t beg = c * A.chunk_rows;
     const int64_t end = (beg + A.chunk_rows) < A.N ? (beg + A.chunk_rows) : A.N;
@@ -246,7 +255,7 @@ int launch_rows_dense_t(fm_matrix* m, const RowArgs& A, hipStream_t st)
 template <int DB, int KB>
 int launch_cols_dense_t(fm_matrix* m, const ColArgs& A, hipStream_t st)
 {
-    const int64_t grid = (A.nchunks + FM_WAVES - 1) / FM_WAVES;
+    const int64_t grid = (A.nchunks + FM_WAVES - 1) / FM_WAVES + (A.epi.on ? A.epi.nsums : 0);
     if (grid > 0x7fffffffLL) return fm_fail(m, FM_ERANGE, "chunk grid too large");
     hipLaunchKernelGGL((k_cols_dense<DB, KB>), dim3((unsigned)grid), dim3(FM_BLOCK), 0, st, A);
     FM_HIP(m, hipGetLastError());
