@@ -755,6 +755,12 @@ int launch_flush(fm_matrix* m, const ColArgs& A, hipStream_t st)
     return fm_fail(m, FM_EINVAL, "unsupported K=%d", A.K);
 }
 
+// From so many floats of V on the empty columns run beside the others, which are bound by latency while those stream
+// (gradient of 4e5 hashed rows, D = 4e6, K=64: 2525 -> 2480 us; of 2e6 rows, D = 2e7: 14.27 -> 14.11 ms).  Below, the fork
+// and the join cost more than they give (1e5 rows, D = 1e6: 603 -> 607 us), and so does a third kernel beside the LDS-staged one
+// (click-style epoch, 1e7 rows: 7.31 -> 7.98 ms).
+constexpr int64_t FM_EMPTY_BESIDE = int64_t(1) << 27;
+
 template <int VEC, int L, int PACKED>
 int launch_cols_t(fm_matrix* m, const ColArgs& A, bool update, hipStream_t st)
 {
@@ -806,6 +812,14 @@ int launch_cols_t(fm_matrix* m, const ColArgs& A, bool update, hipStream_t st)
             }
         }
         Am.blk_short = (A.nshort + per - 1) / per;
+        // empty columns of the full matrix: regulariser only (a stratum's wait for the marks, below); nothing to launch
+        // when every column of the matrix is listed as short or long
+        const bool empty = need_empty && A.ptr != nullptr && A.D > 0 && A.nshort + A.nlong < A.D;
+        const bool beside = empty && !side && A.D * (int64_t)A.K >= FM_EMPTY_BESIDE && !m->prof && fm_side_streams(m);
+        if (beside) {
+            FM_HIP(m, hipEventRecord(m->ev_fork, st));
+            FM_HIP(m, hipStreamWaitEvent(m->side2, m->ev_fork, 0));
+        }
         auto launch = [&](const ColArgs& B, hipStream_t q) -> int {
             const int64_t grid = B.blk_lists + B.blk_lin + B.blk_short + (B.epi.on ? B.epi.nsums : 0);
             if (grid > 0x7fffffffLL) return fm_fail(m, FM_ERANGE, "column grid too large");
@@ -834,10 +848,11 @@ int launch_cols_t(fm_matrix* m, const ColArgs& A, bool update, hipStream_t st)
         } else {
             FM_TRY(launch(Am, st));
         }
-        // empty columns of the full matrix: regulariser only (a stratum's wait for the marks, below)
-        // (nothing to launch when every column of the matrix is listed as short or long)
-        if (need_empty && A.ptr != nullptr && A.D > 0 && A.nshort + A.nlong < A.D)
-            FM_TRY((launch_empty<VEC>(m, A, update, st)));
+        if (empty) FM_TRY((launch_empty<VEC>(m, A, update, beside ? m->side2 : st)));
+        if (beside) {
+            FM_HIP(m, hipEventRecord(m->ev_join2, m->side2));
+            FM_HIP(m, hipStreamWaitEvent(st, m->ev_join2, 0));
+        }
         if (side) {
             FM_HIP(m, hipEventRecord(m->ev_join1, m->side1));
             FM_HIP(m, hipStreamWaitEvent(st, m->ev_join1, 0));

@@ -169,3 +169,51 @@ def test_items_of_strata_and_batches_in_row_order(N, P, K):
     wl.lambda_w = wl.lambda_v = 1e-5  # a batch is scored before its columns take their postponed regulariser steps
     m2, _, _ = _run_minibatch_epochs(B, wl, P, 1, update_w0=True, setup=lambda h: h.fm_set_tuning(seg=16))
     m2.close()
+
+
+@pytest.mark.parametrize("D", [(1 << 19) - 1, 1 << 19])  # K = 256: empty columns behind the others and, from 2^27 floats, beside them
+def test_empty_columns_of_a_large_factor_matrix(D):
+    """Nearly all columns are empty.  Their gradient is lambda v and their step v (1 - eta lambda), exactly as rounded; the
+    caller's next work on the same stream sees all of it."""
+    import torch
+    from paper_2004_13940_amd import binding as B
+    rng = np.random.default_rng(7500 + D)
+    N, K, lw, lv, eta = 300, 256, 0.01, 0.02, 0.5
+    cols = np.sort(np.concatenate([[0, D - 1], rng.choice(np.arange(1, D - 1), 38, replace=False)])).astype(np.int32)
+    mask = rng.random((N, 40)) < 0.4
+    mask[0] = True  # every listed column has an entry
+    mask[:, 7] = True
+    rowptr = np.concatenate([[0], np.cumsum(mask.sum(1))]).astype(np.int64)
+    sub = np.nonzero(mask)[1].astype(np.int32)
+    val = rng.standard_normal(len(sub)).astype(np.float32)
+    r = (rng.standard_normal(N) / N).astype(np.float32)
+    G = rng.standard_normal((N, K)).astype(np.float32)
+    w, V = torch.rand(D, device="cuda"), torch.rand(D * K, device="cuda")
+    print("empty columns", D, flush=True)
+    m = B.Matrix(N, D, rowptr, cols[sub], val)
+    m.fm_build_csc()
+    p = B.make_params(K, O.LOSS_SQUARED, lw, lv, eta, 1.0 / N)
+    at = torch.from_numpy(cols.astype(np.int64)).cuda()
+    rest = torch.ones(D, dtype=torch.bool, device="cuda")
+    rest[at] = False
+    X = O.make_matrix(N, 40, rowptr, sub, val)
+    _, wgw, wgV = O.gradient(X, r, G, w[at].cpu().numpy(), V.view(D, K)[at].cpu().numpy(), lw, lv)
+    d_r, d_G, g0 = to_dev(r), to_dev(G.ravel()), torch.empty(1, device="cuda")
+    for _ in range(3):
+        gw, gV = torch.full((D,), float("nan"), device="cuda"), torch.full((D * K,), float("nan"), device="cuda")
+        m.fm_gradient(p, d_r, d_G, w, V, g0, gw, gV)
+        gw, gV = gw * 1.0, gV.view(D, K) * 1.0
+        assert torch.equal(gw[rest], w[rest] * lw) and torch.equal(gV[rest], V.view(D, K)[rest] * lv)
+        assert_close(gw[at].cpu().numpy(), wgw, "grad_w")
+        assert_close(gV[at].cpu().numpy(), wgV, "grad_V")
+    del gw, gV
+    y, w1, V1, w0 = to_dev(rng.standard_normal(N)), w.clone(), V.clone(), torch.zeros(1, device="cuda")
+    m.fm_sgd_epoch(p, y, w0, w1, V1)
+    w2, V2 = w1 * 1.0, V1.view(D, K) * 1.0
+    fw, fv = (float(np.float32(1) - np.float32(eta) * np.float32(x)) for x in (lw, lv))
+    assert torch.equal(w2[rest], w[rest] * fw) and torch.equal(V2[rest], V.view(D, K)[rest] * fv)
+    w0o, wo, Vo, _ = O.full_epoch(X, y.cpu().numpy(), 0.0, w[at].cpu().numpy(), V.view(D, K)[at].cpu().numpy(),
+                                  loss=O.LOSS_SQUARED, s=1.0 / N, lambda_w=lw, lambda_v=lv, eta=eta, update_w0=True)
+    assert_close(w2[at].cpu().numpy(), wo, "w")
+    assert_close(V2[at].cpu().numpy(), Vo, "V")
+    m.close()
