@@ -290,7 +290,12 @@ int fm_set_tuning(fm_matrix* m, int32_t seg, int32_t panel, int32_t heavy_per_pa
  * min_per_tile < 0 keeps the current value. */
 int fm_set_tile_tuning(fm_matrix* m, int32_t tile_rows, int32_t min_per_tile, int32_t tile_seg);
 
+/* Device memory in blocks of more than 1 MB that fm_destroy and the build calls give up is kept for the next handle on
+ * the same device, at most 4 GiB per process; it goes back to the driver when an allocation of this library fails.
+ * fm_trim gives all of it back at once, for programs whose other allocators need it.  It frees device memory, so it
+ * must not be called while a stream is being captured; open handles are not touched. */
 int fm_destroy(fm_matrix* m);
+int fm_trim(void);
 const char* fm_last_error(const fm_matrix* m); /* m may be NULL: last build error of this thread */
 
 #ifdef __cplusplus

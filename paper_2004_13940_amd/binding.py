@@ -41,7 +41,7 @@ EXPORTS = ["fm_build_csr", "fm_build_csc", "fm_partition", "fm_partition_placed"
            "fm_sgd_epoch", "fm_minibatch_epoch", "fm_stratified_epoch", "fm_stratified_begin", "fm_stratified_step",
            "fm_stratified_end", "fm_get_aux", "fm_profile_enable", "fm_profile_kernels",
            "fm_profile_kernel_name", "fm_profile_read", "fm_set_option", "fm_set_tuning", "fm_set_tile_tuning", "fm_destroy",
-           "fm_last_error"]
+           "fm_trim", "fm_last_error"]
 FM_OPT_AUX_PLANAR, FM_OPT_SIDE_STREAMS, FM_OPT_LAZY_REG, FM_OPT_GRAPH, FM_OPT_DENSE_ROWS = 0, 1, 2, 3, 4
 
 _lib = None
@@ -107,6 +107,11 @@ def _dev(t, n, what):
         raise TypeError(f"{what} must be a contiguous float32 CUDA tensor")
     if t.numel() != n:
         raise ValueError(f"{what} has {t.numel()} elements, expected {n}")
+
+
+def fm_trim():
+    """Give the device memory that closed handles left in the library's pool back to the driver."""
+    load().fm_trim()
 
 
 def make_params(K, loss, lambda_w, lambda_v, eta, loss_scale=1.0, update_w0=1, reg_full_per_cell=0,

@@ -28,7 +28,7 @@ int fm_fail(fm_matrix* m, int code, const char* fmt, ...)
 // per batch of requests and a build makes and frees gigabytes of scratch: mapping and unmapping that memory cost 8 ms
 // of the 60 ms that opening a data set of 4.9e7 entries took.  Blocks come back idle (see fm_dev_free), so any thread
 // and stream may take them.  Bounded to POOL_CAP per process; all of it goes back to the driver when an allocation
-// fails.  Requests up to POOL_MIN are left to the runtime, which hands them out of its own chunks in under a microsecond.
+// fails or the program calls fm_trim.  Requests up to POOL_MIN are left to the runtime, which hands them out of its own chunks in under a microsecond.
 namespace {
 constexpr size_t POOL_MIN = size_t(1) << 20;
 constexpr size_t POOL_CAP = size_t(4) << 30;
@@ -97,6 +97,7 @@ void pool_give(void* p, size_t bytes, int device)
 }
 }  // namespace
 
+// On the device the handle was created on, which need not be the current one: a block returns to that device's list.
 int fm_dev_alloc(fm_matrix* m, void** p, size_t bytes)
 {
     *p = nullptr;
@@ -105,12 +106,16 @@ int fm_dev_alloc(fm_matrix* m, void** p, size_t bytes)
     const size_t want = pooled ? pool_round(bytes) : bytes;
     if (pooled) *p = pool_take(want, m->device);
     if (*p == nullptr) {
+        int current = m->device;
+        const bool elsewhere = hipGetDevice(&current) == hipSuccess && current != m->device;
+        if (elsewhere) (void)hipSetDevice(m->device);
         hipError_t e = hipMalloc(p, want);
         if (e != hipSuccess) {  // what the pool holds may be what is missing
             (void)hipGetLastError();
             pool_drain();
             e = hipMalloc(p, want);
         }
+        if (elsewhere) (void)hipSetDevice(current);
         if (e != hipSuccess) {
             (void)hipGetLastError();
             return fm_fail(m, FM_ENOMEM, "hipMalloc of %zu bytes failed: %s", bytes, hipGetErrorString(e));
@@ -135,6 +140,18 @@ void fm_dev_free(fm_matrix* m, void* p)
         pool_give(p, bytes, m->device);
     else
         (void)hipFree(p);
+}
+
+extern "C" int fm_trim(void)
+{
+    pool_drain();
+    std::vector<std::pair<int, void*>> pinned;
+    {
+        std::lock_guard<std::mutex> g(g_pool_lock);
+        pinned.swap(g_pinned);
+    }
+    for (const auto& b : pinned) (void)hipHostFree(b.second);
+    return FM_OK;
 }
 
 static int pinned_alloc(fm_matrix* m)

@@ -63,3 +63,27 @@ def test_handles_one_after_the_other_reuse_blocks_with_their_own_content():
         order = np.argsort(col, kind="stable")
         assert np.array_equal(row, np.repeat(np.arange(N), k)[order]) and np.array_equal(cval, val[order])
         m.close()
+
+
+def test_trim_gives_the_blocks_of_closed_handles_back():
+    """What a closed handle leaves is kept for the next one until fm_trim; an open handle goes on working."""
+    import torch
+    from paper_2004_13940_amd import binding as B
+    N, D, k, K = 400_000, 3_000, 12, 16
+    y, w0, w = torch.ones(N, device="cuda"), torch.zeros(1, device="cuda"), torch.zeros(D, device="cuda")
+    V = torch.full((D * K,), 0.01, device="cuda")
+    p = B.make_params(K, B.FM_LOSS_SQUARED, 0.0, 0.0, 0.1, 1.0 / N)
+    kept = B.Matrix(500, D, *_csr(500, D, k))
+    before = kept.fm_evaluate(p, y[:500].clone(), w0, w, V)
+    B.fm_trim()
+    torch.cuda.synchronize()
+    free = torch.cuda.mem_get_info()[0]
+    m = B.Matrix(N, D, *_csr(N, D, k))
+    m.fm_build_csc()
+    m.fm_sgd_epoch(p, y, w0.clone(), w.clone(), V.clone())
+    m.close()
+    assert torch.cuda.mem_get_info()[0] < free - (64 << 20)  # the matrix, its transpose and the aggregates
+    B.fm_trim()
+    assert torch.cuda.mem_get_info()[0] >= free - (8 << 20)  # the runtime keeps chunks of its own
+    assert kept.fm_evaluate(p, y[:500].clone(), w0, w, V) == before
+    kept.close()
