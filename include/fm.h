@@ -259,13 +259,16 @@ int fm_profile_read(fm_matrix* m, int64_t* launches /*HOST nk*/, double* total_m
  *   FM_OPT_DENSE_ROWS    1 (default): a matrix in which every row stores all D columns (D and K in
  *                        {32, 64}) takes dense kernels on the matrix cores for fm_forward, fm_gradient and
  *                        fm_sgd_epoch (G = XV and X^T(r.G) as fp32 contractions; the column indices are not
- *                        read); 0: the sparse kernels, as for every other matrix. */
+ *                        read); 0: the sparse kernels, as for every other matrix.
+ *   FM_OPT_WIDE_ADDRESSES  1: the rows that the column kernels and the refresh gather are addressed with 64
+ *                        bits, as they are when they take more than 4 GB; 0 (default): only then. */
 typedef enum {
     FM_OPT_AUX_PLANAR = 0,
     FM_OPT_SIDE_STREAMS = 1,
     FM_OPT_LAZY_REG = 2,
     FM_OPT_GRAPH = 3,
-    FM_OPT_DENSE_ROWS = 4
+    FM_OPT_DENSE_ROWS = 4,
+    FM_OPT_WIDE_ADDRESSES = 5
 } fm_option;
 int fm_set_option(fm_matrix* m, int32_t option /*fm_option*/, int32_t value);
 

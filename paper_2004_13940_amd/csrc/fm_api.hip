@@ -818,7 +818,7 @@ static void base_col_args(fm_matrix* m, const fm_params* p, ColArgs& A)
     // Aggregates that do not fit the memory-side cache: rows that are gathered once do not push others out of the L2.
     const int64_t aux_bytes = fm_aux_floats(m, p->K) * (int64_t)sizeof(float);
     A.nt = aux_bytes > (int64_t(256) << 20) ? 1 : 0;
-    A.big = aux_bytes > FM_BUF_BYTES ? 1 : 0;
+    A.big = aux_bytes > FM_BUF_BYTES || m->opt.wide_addresses ? 1 : 0;
 }
 
 extern "C" int fm_gradient(fm_matrix* m, const fm_params* p, const float* r, const float* G, const float* w,
@@ -1003,7 +1003,7 @@ static int stratified_step(fm_matrix* m, const fm_params* p, int32_t s, const fl
     }
     R.w0 = w0;
     R.V = m->dV;
-    R.big = m->D * (int64_t)p->K * (int64_t)sizeof(float) > FM_BUF_BYTES ? 1 : 0;
+    R.big = m->D * (int64_t)p->K * (int64_t)sizeof(float) > FM_BUF_BYTES || m->opt.wide_addresses ? 1 : 0;
     R.dwn = m->dwn;
     R.y = y;
     aux_outputs(m, p->K, R, true);
@@ -1279,6 +1279,10 @@ extern "C" int fm_set_option(fm_matrix* m, int32_t option, int32_t value)
             return FM_OK;
         case FM_OPT_DENSE_ROWS:
             m->opt.dense_rows = value != 0;
+            return FM_OK;
+        case FM_OPT_WIDE_ADDRESSES:
+            m->opt.wide_addresses = value != 0;
+            fm_drop_graph(m);
             return FM_OK;
         case FM_OPT_GRAPH:
             if (value < 0 || value > 2) return fm_fail(m, FM_EINVAL, "graph mode %d outside 0..2", value);

@@ -39,6 +39,7 @@ struct FmOptions {
     bool lazy_reg = true;      // regulariser-only steps of a stratified or mini-batch epoch are postponed
     int graph = 1;             // stratified epoch from a captured graph: 0 never, 1 when launch-bound, 2 always
     bool dense_rows = true;    // matrices that store every column in every row take the dense (MFMA) kernels
+    bool wide_addresses = false;  // gathers take 64-bit addresses at any size
 };
 
 // Where the handle keeps the aggregates.  Packed (when [G | r] fits one 128-byte line: K % 4 == 0,

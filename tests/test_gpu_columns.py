@@ -4,7 +4,7 @@ import pytest
 
 from oracle import fm_oracle as O
 
-from helpers import assert_close, dev_params, run_stratified_epochs, to_dev
+from helpers import assert_close, dev_params, run_full_epochs, run_stratified_epochs, to_dev
 
 pytestmark = pytest.mark.gpu
 
@@ -217,3 +217,97 @@ def test_empty_columns_of_a_large_factor_matrix(D):
     assert_close(w2[at].cpu().numpy(), wo, "w")
     assert_close(V2[at].cpu().numpy(), Vo, "V")
     m.close()
+
+
+@pytest.mark.parametrize("side_streams", [0, 1])
+@pytest.mark.parametrize("K,planar", [(4, 0), (4, 1), (8, 0), (12, 0), (12, 1), (16, 0), (16, 1), (20, 1), (28, 0), (60, 0),
+                                      (64, 0), (128, 0), (132, 0), (256, 0)])  # every lane count, K that idles lanes
+def test_columns_staged_in_tiles(K, planar, side_streams):
+    """Dense-ish columns beside sparse ones over five tiles of 64 rows and a ragged one, through the LDS-staged kernel on the
+    launch stream or on its own; whole epochs one after the other, so that each needs the last one's step."""
+    from types import SimpleNamespace
+    from paper_2004_13940_amd import binding as B
+    rng = np.random.default_rng(7600 + K)
+    N, D = 5 * 64 + 37, 45
+    mask = rng.random((N, D)) < 0.02
+    mask[:, 3] = True
+    mask[:, 20] = rng.random(N) < 0.5
+    mask[:, 21] = rng.random(N) < 0.15
+    mask[64:128, 20] = False  # a dense-ish column without entries in one tile
+    mask[:, 40] = rng.random(N) < 0.9
+    mask[:, 30] = False
+    rowptr = np.concatenate([[0], np.cumsum(mask.sum(1))]).astype(np.int64)
+    col = np.nonzero(mask)[1].astype(np.int32)
+    wl = SimpleNamespace(N=N, D=D, K=K, rowptr=rowptr, col=col, val=rng.standard_normal(len(col)).astype(np.float32),
+                         y=np.where(rng.random(N) < 0.5, 1.0, -1.0).astype(np.float32), w0=np.float32(0.1),
+                         w=(rng.standard_normal(D) * 0.2).astype(np.float32),
+                         V=(rng.standard_normal((D, K)) * 0.2 / np.sqrt(K)).astype(np.float32), loss=O.LOSS_LOGISTIC,
+                         lambda_w=0.01, lambda_v=0.02, eta=0.5, loss_scale=1.0 / N, update_w0=1)
+
+    def setup(m):
+        m.fm_set_tuning(seg=16)
+        m.fm_set_tile_tuning(tile_rows=64, min_per_tile=4, tile_seg=16)
+        m.fm_set_option(B.FM_OPT_AUX_PLANAR, planar)
+        m.fm_set_option(B.FM_OPT_SIDE_STREAMS, side_streams)
+
+    print("columns staged in tiles", K, planar, side_streams, flush=True)
+    m, p, _, dev, _ = run_full_epochs(B, wl, 3, setup=setup)
+    m.fm_profile_enable(True)
+    m.fm_sgd_epoch(p, dev[3], *dev[:3])
+    assert m.fm_profile_read()["cols_tile"][0] == 1
+    m.close()
+
+
+@pytest.mark.parametrize("K", [1, 2, 3, 4, 8, 12, 16, 28, 32])  # every lane count below 16, packed and planar rows
+def test_columns_and_refresh_with_64_bit_addresses(K, monkeypatch):
+    """The same matrices through the form of the walk that large arrays take: slots without an entry read the run's last row
+    again, empty runs row 0, and neither may count."""
+    from paper_2004_13940_amd import binding as B
+    build = B.Matrix.fm_build_csc
+
+    def wide(m, *a, **k):
+        m.fm_set_option(B.FM_OPT_WIDE_ADDRESSES, 1)
+        build(m, *a, **k)
+
+    monkeypatch.setattr(B.Matrix, "fm_build_csc", wide)
+    test_columns_of_every_length_around_the_rounds_and_the_item(K)
+    for P in (1, 3):
+        test_refresh_of_rows_of_every_length_around_the_rounds(K, P)
+
+
+# packed rows of 128 bytes, the aggregates 4,096 bytes below 4 GiB and less, and more; the caller's G of 128 bytes a row,
+# where the aggregates of 140 bytes a row decide
+@pytest.mark.parametrize("N,K", [(33_554_300, 16), (33_554_500, 16), (30_678_300, 32), (30_678_400, 32)])
+def test_gathers_at_offsets_of_two_to_four_gigabytes(N, K):
+    """Columns whose entries lie in the first and the last rows and around 2 GiB: 32-bit offsets into the buffer up to its
+    largest size, 64-bit addresses above."""
+    import torch
+    from paper_2004_13940_amd import binding as B
+    rng = np.random.default_rng(7700 + K)
+    edges = [0, 1, (1 << 24) - 2, (1 << 24) - 1, 1 << 24, (1 << 24) + 1, N - 2, N - 1]
+    rows = np.unique(np.concatenate([edges, rng.choice(N, 300, replace=False)]))
+    D = 5
+    mask = rng.random((len(rows), D)) < 0.6
+    mask[:, 0] = True
+    counts = np.zeros(N, np.int64)
+    counts[rows] = mask.sum(1)
+    rowptr = np.concatenate([[0], np.cumsum(counts)]).astype(np.int64)
+    sub = np.nonzero(mask)
+    val = rng.standard_normal(len(sub[0])).astype(np.float32)
+    gen = torch.Generator(device="cuda").manual_seed(K)
+    G, r = torch.randn(N * K, generator=gen, device="cuda"), torch.randn(N, generator=gen, device="cuda")
+    w = (rng.standard_normal(D) * 0.1).astype(np.float32)
+    V = (rng.standard_normal((D, K)) * 0.1).astype(np.float32)
+    print("offsets of gigabytes", N, K, flush=True)
+    m = B.Matrix(N, D, rowptr, sub[1].astype(np.int32), val)
+    m.fm_build_csc()
+    _, d_w, d_V = dev_params(np.float32(0), w, V)
+    gw, gV = torch.full((D,), float("nan"), device="cuda"), torch.full((D * K,), float("nan"), device="cuda")
+    m.fm_gradient(B.make_params(K, O.LOSS_SQUARED, 0.01, 0.02, 0.1), r, G, d_w, d_V, None, gw, gV)
+    at = torch.from_numpy(rows).cuda()
+    X = O.make_matrix(len(rows), D, np.concatenate([[0], np.cumsum(mask.sum(1))]).astype(np.int64), sub[1].astype(np.int32), val)
+    _, wgw, wgV = O.gradient(X, r[at].cpu().numpy(), G.view(N, K)[at].cpu().numpy(), w, V, 0.01, 0.02)
+    assert_close(gw.cpu().numpy(), wgw, "grad_w")
+    assert_close(gV.cpu().numpy().reshape(D, K), wgV, "grad_V")
+    m.close()
+    B.fm_trim()
