@@ -45,7 +45,21 @@ def csrc_sha256():
     return h.hexdigest()
 
 
-def algorithmic_bytes(N, D, K, counts, seg=256, tile_rows=512, tile_min=8, tile_seg=256):
+def column_classes(N, K, nnz):
+    """(seg, tile_rows, tile_min, tile_seg) by the rules of the library (fm_item_length, fm_tile_shape)."""
+    seg = 32
+    while seg < 256 and nnz // (2 * seg) >= 8 * 16 * 256:
+        seg *= 2
+    if K % 4 == 0 and K <= 16 and N >= 1 << 21:
+        return seg, 1024, 12, 512
+    if N < 1 << 17:
+        return seg, 128, 0, 128
+    if N < 1 << 18:
+        return seg, 256, 4, 256
+    return seg, 512, 8, 256
+
+
+def algorithmic_bytes(N, D, K, counts):
     """Bytes each kernel must move if every array is streamed once and every gather is served
     from cache (fp32 values, int32 indices, int64 pointers).  Columns are classed as the library
     classes them: dense-ish (>= tile_min entries per row tile on average) -> cols_tile; all others
@@ -54,6 +68,9 @@ def algorithmic_bytes(N, D, K, counts, seg=256, tile_rows=512, tile_min=8, tile_
     between the two accumulation kernels in proportion to the entries they process."""
     import numpy as np
     nnz = int(counts.sum())
+    seg, tile_rows, tile_min, tile_seg = column_classes(N, K, nnz)
+    if K % 4 != 0 or tile_rows * (K + 1) * 4 > 72 * 1024:
+        tile_min = 0  # the tile does not fit: such items are part of cols
     ntiles = (N + tile_rows - 1) // tile_rows
     tile_thr = max(tile_min * ntiles, seg + 1) if ntiles >= 2 and tile_min > 0 else np.iinfo(np.int64).max
     short = counts <= seg

@@ -244,7 +244,7 @@ const char* fm_profile_kernel_name(int32_t k);
 int fm_profile_read(fm_matrix* m, int64_t* launches /*HOST nk*/, double* total_ms /*HOST nk*/);
 
 /* Switches between code paths that compute the same thing, per handle; tests run every one of them
- * against the oracle.  Results do not depend on them beyond fp32 rounding.
+ * against the oracle.  Results do not depend on them beyond fp32 rounding, except as FM_OPT_LAZY_REG says.
  *   FM_OPT_AUX_PLANAR    1: the handle keeps the aggregates planar (G [N x K], then r, a, q) for every
  *                        K; 0 (default): as packed rows [G | r | a | q | pad] when [G | r] fits one
  *                        128-byte line (K % 4 == 0, K <= 28).  Changing it drops the aggregates held.
@@ -252,7 +252,10 @@ int fm_profile_read(fm_matrix* m, int64_t* launches /*HOST nk*/, double* total_m
  *                        internal streams; 0: everything on the caller's stream.
  *   FM_OPT_LAZY_REG      1 (default): fm_stratified_epoch and fm_minibatch_epoch postpone the
  *                        regulariser-only steps of columns without entries in a cell or batch; 0: every
- *                        column takes its step in every stratum or batch.
+ *                        column takes its step in every stratum or batch.  A mini-batch scores its rows
+ *                        before their columns have taken the steps they postponed, so there the two
+ *                        differ by the part eta lambda of the parameters that those steps are, in the
+ *                        scores, not only by rounding.
  *   FM_OPT_GRAPH         fm_stratified_epoch replayed from a captured HIP graph: 0 never, 1 (default)
  *                        when there are 32 strata or more, or 16 and strata small enough for the launches
  *                        to dominate, 2 always.

@@ -909,8 +909,9 @@ void fm_tile_shape(const fm_matrix* m, int32_t K, int* tile_rows, int* tile_min,
     const int64_t N = m->N;
     // one workgroup works on one tile: tall matrices take big tiles (fewer items, hence fewer partial
     // sums), shorter ones small tiles (enough workgroups to fill the chip), and below 2^17 rows none: their aggregate
-    // rows stay in the caches anyway, and one launch over short items (text-like workload, 5e4 rows: epoch 146 -> 68 us)
-    // beats three kernels on three streams
+    // rows stay in the caches anyway, and one launch over short items beats three kernels on three streams.  Epochs in us
+    // without tiles and with tiles of 128 rows, at 8,000 / 30,000 / 120,000 rows: click-like K=16 30, 43, 124 and 71, 74,
+    // 129; text-like K=16 33, 46, 213 and 76, 88, 196; table of 22 columns, K=16 18, 26, 48 and 43, 43, 61
     int rows = 512, dense = 8, seg = 256;
     if (K > 0 && K % 4 == 0 && K <= 16 && N >= (int64_t(1) << 21)) {
         rows = 1024, dense = 12, seg = 512;

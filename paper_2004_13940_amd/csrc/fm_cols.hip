@@ -8,9 +8,9 @@
 //   grad_V_jk = gV_jk - s2_j v_jk + rho lambda_v v_jk
 //
 // A group of L lanes owns one column (lane `sub` holds VEC latent dimensions).
-// Columns longer than `seg` entries are cut into items: k_cols skips them, k_cols_long
-// writes one partial sum per item, and the finish kernels add the partials of a column
-// in a fixed order, so results are bit-reproducible from run to run.  Items of heavy
+// Columns longer than `seg` entries are cut into items: k_cols finishes the shorter ones and
+// writes one partial sum per item, and k_cols_finish adds the partials of a column in a
+// fixed order, so results are bit-reproducible from run to run.  Items of heavy
 // columns are cut at row-panel boundaries and handed out panel by panel, one panel at a
 // time per XCD, so that the gathered rows of G stay in that XCD's L2.
 #include "fm_device.h"

@@ -25,7 +25,9 @@ struct FmTune {
     int seg = 0;               // entries per work item of a long column; 0: by the number of entries, fm_item_length
     int panel = 32768;         // rows per panel of the L2-blocked traversal of heavy columns
     int heavy_per_panel = 16;  // a column is heavy if it averages at least this many entries per panel
-        int vlong = 128;           // columns with more items than this are finished by a whole workgroup
+    int vlong = 128;           // columns with more items than this are finished by a whole workgroup (128 against 512,
+                               // items of 128: mini-batch click epoch K=32 1.63 and 1.67 ms, stratified table K=64 934
+                               // and 959 us, hashed epoch K=64 2.50 and 2.48 ms)
     int min_panels = 8 * 8;    // the panel order is used only for matrices with at least this many panels
     int tile = 0;              // rows per LDS tile of the kernel for dense-ish columns
     int tile_min = -1;         // a column is dense-ish if it averages this many entries per tile (0: none)
@@ -66,11 +68,11 @@ enum fm_kernel_id {
     FMK_ROWS_FORWARD = 0,
     FMK_ROWS_REFRESH,
     FMK_COLS,
-    FMK_COLS_LONG,
+    FMK_COLS_LONG,  // dense matrices only: items of long columns are part of FMK_COLS
     FMK_COLS_TILE,
     FMK_COLS_FINISH,
     FMK_REDUCE,
-    FMK_BIAS,
+    FMK_BIAS,  // no launch of its own any more; the name stays in the list that callers read
     FMK_COUNT
 };
 
