@@ -219,6 +219,38 @@ def test_empty_columns_of_a_large_factor_matrix(D):
     m.close()
 
 
+def test_gradient_that_forks_for_its_empty_columns_replays_from_a_graph():
+    """A caller may capture the call: the fork onto the side stream and the join are part of the graph."""
+    import torch
+    from paper_2004_13940_amd import binding as B
+    rng = np.random.default_rng(7550)
+    N, D, K = 200, 1 << 19, 256
+    col = np.sort(rng.choice(D, (N, 6)), axis=1).astype(np.int32) // 6 * 6 + np.arange(6, dtype=np.int32)
+    rowptr, val = np.arange(N + 1, dtype=np.int64) * 6, rng.standard_normal(N * 6).astype(np.float32)
+    m = B.Matrix(N, D + 6, rowptr, col.ravel(), val)
+    m.fm_build_csc()
+    D += 6
+    p = B.make_params(K, O.LOSS_SQUARED, 0.01, 0.02, 0.5, 1.0 / N)
+    w, V, r, G = (torch.rand(n, device="cuda") for n in (D, D * K, N, N * K))
+    g0, gw, gV = torch.empty(1, device="cuda"), torch.empty(D, device="cuda"), torch.empty(D * K, device="cuda")
+    print("gradient from a graph", flush=True)
+    m.fm_gradient(p, r, G, w, V, g0, gw, gV)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        m.fm_gradient(p, r, G, w, V, g0, gw, gV)
+    for _ in range(4):
+        r.add_(0.5)
+        m.fm_gradient(p, r, G, w, V, g0, gw, gV)
+        want = g0.clone(), gw.clone(), gV.clone()
+        for t in (g0, gw, gV):
+            t.fill_(float("nan"))
+        graph.replay()
+        assert torch.equal(g0, want[0]) and torch.equal(gw, want[1]) and torch.equal(gV, want[2])
+    torch.cuda.synchronize()
+    m.close()
+
+
 @pytest.mark.parametrize("side_streams", [0, 1])
 @pytest.mark.parametrize("K,planar", [(4, 0), (4, 1), (8, 0), (12, 0), (12, 1), (16, 0), (16, 1), (20, 1), (28, 0), (60, 0),
                                       (64, 0), (128, 0), (132, 0), (256, 0)])  # every lane count, K that idles lanes
