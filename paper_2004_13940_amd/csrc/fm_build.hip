@@ -782,7 +782,7 @@ static int build_vlong_list(fm_matrix* m, const std::vector<int64_t>& h_first, L
 // at 1e6 rows with items of 256 entries, 3.10 with items of 64, 3.60 and 3.52 at 1.2e6 rows; by row it takes 2.17 and 2.45.
 // Mini-batch epoch of the click-style workload (2.5e6 rows): 4.17 -> 3.60 ms.  Below 2^16 rows the aggregates are found in
 // a cache in any order (text-like workload, 5e4 rows, 32 strata: 847 us both ways; table of 1e5 rows, K=32: 276 -> 250 us)
-// and a partition is spared the sort (0.35 ms of the 2 ms that the tiny workload takes to open).
+// and a partition is spared the sort.
 constexpr int64_t FM_ROW_ORDER_MIN = 1 << 16;
 static int order_by_row(fm_matrix* m, const int32_t* row, int32_t nstrata, LongIndex* out, hipStream_t st)
 {
