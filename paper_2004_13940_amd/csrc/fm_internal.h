@@ -294,7 +294,7 @@ struct RowArgs {
     float *yhat, *a, *G, *q, *r;  // forward: nullable outputs ; refresh: in/out aggregates
     int64_t gs;         // floats between consecutive rows of G
     int64_t ss;         // floats between consecutive rows of r, a, q (1, or the aggregate row stride)
-    int32_t whole_rows; // forward into packed aggregate rows: write r, a, q and the padding with G
+    int32_t whole_rows; // packed aggregate rows: r, a, q move as one float4 (forward: and the padding is written with them)
     float* row_part;    // nullable: [2*gridDim] loss and sum r per block
     double* eval_part;  // nullable: [3*gridDim] sums of losses, squared errors and correct signs per block
     int32_t big;          // refresh: dV is larger than FM_BUF_BYTES
