@@ -308,14 +308,14 @@ extern "C" int fm_build_csr(int64_t N, int64_t D, int64_t nnz, const int64_t* ro
     m->D = D;
     m->nnz = nnz;
     int rc = hipGetDevice(&m->device) == hipSuccess ? FM_OK : fm_fail(m, FM_EHIP, "no current device");
-    auto up = [&](void** d, const void* h, size_t bytes) -> int {
-        FM_TRY(fm_dev_alloc(m, d, bytes));
+    auto up = [&](void** d, const void* h, size_t bytes, size_t pad) -> int {
+        FM_TRY(fm_dev_alloc(m, d, bytes + pad));
         if (bytes > 0) FM_HIP(m, hipMemcpyAsync(*d, h, bytes, hipMemcpyHostToDevice, st));
         return FM_OK;
     };
-    if (rc == FM_OK) rc = up((void**)&m->rowptr, rowptr, (size_t)(N + 1) * sizeof(int64_t));
-    if (rc == FM_OK) rc = up((void**)&m->col, col, (size_t)nnz * sizeof(int32_t));
-    if (rc == FM_OK) rc = up((void**)&m->val, val, (size_t)nnz * sizeof(float));
+    if (rc == FM_OK) rc = up((void**)&m->rowptr, rowptr, (size_t)(N + 1) * sizeof(int64_t), 0);
+    if (rc == FM_OK) rc = up((void**)&m->col, col, (size_t)nnz * sizeof(int32_t), FM_ENTRY_PAD * sizeof(int32_t));
+    if (rc == FM_OK) rc = up((void**)&m->val, val, (size_t)nnz * sizeof(float), FM_ENTRY_PAD * sizeof(float));
     if (rc == FM_OK) rc = fm_dev_alloc(m, (void**)&m->scal, (8 + FM_REDUCE_TMP) * sizeof(double));
     if (rc == FM_OK) rc = pinned_alloc(m);
     bool valid = false;
@@ -685,6 +685,7 @@ static int run_forward(fm_matrix* m, const fm_params* p, const float* y, const f
     A.w0 = w0;
     A.w = w;
     A.V = V;
+    A.big = fm_rows_big(m, p->K);
     A.y = y;
     A.yhat = yhat;
     if (mode == 0) {
@@ -769,6 +770,7 @@ extern "C" int fm_evaluate(fm_matrix* m, const fm_params* p, const float* y, con
     A.w0 = w0;
     A.w = w;
     A.V = V;
+    A.big = fm_rows_big(m, p->K);
     A.y = y;
     A.gs = p->K;
     A.ss = 1;
@@ -1003,7 +1005,7 @@ static int stratified_step(fm_matrix* m, const fm_params* p, int32_t s, const fl
     }
     R.w0 = w0;
     R.V = m->dV;
-    R.big = m->D * (int64_t)p->K * (int64_t)sizeof(float) > FM_BUF_BYTES || m->opt.wide_addresses ? 1 : 0;
+    R.big = fm_rows_big(m, p->K);
     R.dwn = m->dwn;
     R.y = y;
     aux_outputs(m, p->K, R, true);
@@ -1204,6 +1206,7 @@ extern "C" int fm_minibatch_epoch(fm_matrix* m, const fm_params* p, const float*
             R.w0 = w0;
             R.w = w;
             R.V = V;
+            R.big = fm_rows_big(m, p->K);
             R.y = y + r0;
             R.G = x.G + r0 * x.gs;
             R.gs = x.gs;

@@ -447,8 +447,8 @@ __global__ __launch_bounds__(LI_T) void k_short_list(const int64_t* __restrict__
         if (len > 0 && len <= seg) {
             short_col[pos] = ids != nullptr ? ids[c] : (int32_t)c;
             short_vcol[pos] = c;
-            if (short_beg != nullptr) short_beg[pos] = ptr[c];
-            if (short_len != nullptr) short_len[pos] = (int32_t)len;
+            short_beg[pos] = ptr[c];
+            short_len[pos] = (int32_t)len;
             ++pos;
         }
     }
@@ -710,11 +710,10 @@ int fm_sort_by_key_u32(fm_matrix* m, uint32_t* keys, uint32_t* idx, uint32_t* ke
 
 // List of the non-empty columns with at most `seg` entries.  ptr[c], ptr[c+1] bound the entries of list
 // position c, ids[c] is its column (nullptr: c itself); per stratum when nstrata > 1: h_bounds[s] is the
-// first position of stratum s and h_short_off[s] where it starts in the short list.  with_extent: also
-// the first entry and the length of every listed column (needed when ptr is not indexed by column).
+// first position of stratum s and h_short_off[s] where it starts in the short list.  Every listed column comes with its
+// first entry and its length, so that a kernel asks for all three at once.
 static int build_short_list(fm_matrix* m, const int64_t* ptr, const int32_t* ids, int64_t ncols_total,
-                            const std::vector<int64_t>& h_bounds, int32_t nstrata, int seg, bool with_extent,
-                            LongIndex* out, hipStream_t st)
+                            const std::vector<int64_t>& h_bounds, int32_t nstrata, int seg, LongIndex* out, hipStream_t st)
 {
     out->nshort = 0;
     out->h_short_off.assign(nstrata + 1, 0);
@@ -733,10 +732,8 @@ static int build_short_list(fm_matrix* m, const int64_t* ptr, const int32_t* ids
     if (n > 0) {
         int64_t *vcol = nullptr, *d_off = nullptr, *d_bounds = nullptr;
         FM_TRY(fm_dev_alloc(m, (void**)&out->short_col, (size_t)n * sizeof(int32_t)));
-        if (with_extent) {
-            FM_TRY(fm_dev_alloc(m, (void**)&out->short_beg, (size_t)n * sizeof(int64_t)));
-            FM_TRY(fm_dev_alloc(m, (void**)&out->short_len, (size_t)n * sizeof(int32_t)));
-        }
+        FM_TRY(fm_dev_alloc(m, (void**)&out->short_beg, (size_t)n * sizeof(int64_t)));
+        FM_TRY(fm_dev_alloc(m, (void**)&out->short_len, (size_t)n * sizeof(int32_t)));
         FM_TRY(fm_dev_alloc(m, (void**)&vcol, (size_t)n * sizeof(int64_t)));
         FM_TRY(fm_dev_alloc(m, (void**)&d_off, (size_t)(nstrata + 1) * sizeof(int64_t)));
         FM_TRY(fm_dev_alloc(m, (void**)&d_bounds, (size_t)(nstrata + 1) * sizeof(int64_t)));
@@ -833,7 +830,7 @@ int fm_build_long_index(fm_matrix* m, const int64_t* ptr, const int32_t* ids, co
     FM_TRY(fm_dev_alloc(m, (void**)&tl, (size_t)(ntiles + 1) * sizeof(int64_t)));
     FM_TRY(fm_dev_alloc(m, (void**)&ti, (size_t)(ntiles + 1) * sizeof(int64_t)));
     const int seg = m->tune.seg > 0 ? m->tune.seg : fm_item_length(m->nnz / nstrata);
-    FM_TRY(build_short_list(m, ptr, ids, ncols_total, h_bounds, nstrata, seg, true, out, st));
+    FM_TRY(build_short_list(m, ptr, ids, ncols_total, h_bounds, nstrata, seg, out, st));
     FM_HIP(m, hipMemsetAsync(tl, 0, (size_t)(ntiles + 1) * sizeof(int64_t), st));
     FM_HIP(m, hipMemsetAsync(ti, 0, (size_t)(ntiles + 1) * sizeof(int64_t), st));
     hipLaunchKernelGGL(k_long_count, dim3((unsigned)ntiles), dim3(LI_T), 0, st, ptr, ncols_total, seg, tl, ti);
@@ -935,7 +932,7 @@ int fm_build_full_index(fm_matrix* m, int32_t K, hipStream_t st)
     m->lfull_shape[0] = T.tile;
     m->lfull_shape[1] = T.tile_min;
     m->lfull_shape[2] = T.tile_seg;
-    FM_TRY(build_short_list(m, m->colptr, nullptr, m->D, {0, m->D}, 1, T.seg, false, out, st));
+    FM_TRY(build_short_list(m, m->colptr, nullptr, m->D, {0, m->D}, 1, T.seg, out, st));
     out->nlong = out->nitems = 0;
     out->h_long_off.assign(2, 0);
     out->h_item_off.assign(2, 0);
@@ -1069,8 +1066,8 @@ extern "C" int fm_build_csc(fm_matrix* m, void* hip_stream)
     if (m->has_csc) return FM_OK;
     const int64_t n = m->nnz;
     FM_TRY(fm_dev_alloc(m, (void**)&m->colptr, (size_t)(m->D + 1) * sizeof(int64_t)));
-    FM_TRY(fm_dev_alloc(m, (void**)&m->crow, (size_t)(n > 0 ? n : 1) * sizeof(int32_t)));
-    FM_TRY(fm_dev_alloc(m, (void**)&m->cval, (size_t)(n > 0 ? n : 1) * sizeof(float)));
+    FM_TRY(fm_dev_alloc(m, (void**)&m->crow, (size_t)(n + FM_ENTRY_PAD) * sizeof(int32_t)));
+    FM_TRY(fm_dev_alloc(m, (void**)&m->cval, (size_t)(n + FM_ENTRY_PAD) * sizeof(float)));
     if (n == 0) {
         FM_HIP(m, hipMemsetAsync(m->colptr, 0, (size_t)(m->D + 1) * sizeof(int64_t), st));
     } else {
@@ -1129,8 +1126,8 @@ static int build_strata_side(fm_matrix* m, bool by_rows, hipStream_t st, StrataS
     const float* val = by_rows ? m->val : m->cval;
     out->h_ent_off.assign(P + 1, 0);
     out->h_list_off.assign(P + 1, 0);
-    FM_TRY(fm_dev_alloc(m, (void**)&out->ind, (size_t)(n > 0 ? n : 1) * sizeof(int32_t)));
-    FM_TRY(fm_dev_alloc(m, (void**)&out->val, (size_t)(n > 0 ? n : 1) * sizeof(float)));
+    FM_TRY(fm_dev_alloc(m, (void**)&out->ind, (size_t)(n + FM_ENTRY_PAD) * sizeof(int32_t)));
+    FM_TRY(fm_dev_alloc(m, (void**)&out->val, (size_t)(n + FM_ENTRY_PAD) * sizeof(float)));
     if (n == 0) {
         FM_TRY(fm_dev_alloc(m, (void**)&out->nz_major, sizeof(int32_t)));
         FM_TRY(fm_dev_alloc(m, (void**)&out->nz_beg, sizeof(int64_t)));

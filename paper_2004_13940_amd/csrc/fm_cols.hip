@@ -19,46 +19,71 @@
 
 namespace {
 
-// Accumulate one run of entries [beg,end) of a column into acc/gw/s2 (per-lane
-// partials for gw, s2; complete sums for acc's latent slice).  All groups of the wavefront call it together.
+// The multiplier of an entry of planar aggregates: x r, with r an array of its own.
+struct OwnMultiplier {
+    struct T {
+        float r[1];
+    };
+    FmOwnArray<1> r;
+    float gw, s2;  // this lane's entries
+    template <int ADDR>
+    __device__ __forceinline__ T load(int i) const
+    {
+        T t;
+        r.template get<ADDR>(i, t.r);
+        return t;
+    }
+    __device__ __forceinline__ float use(T t, float x)
+    {
+        const float xr = x * t.r[0];
+        gw += xr;
+        s2 += x * xr;
+        return xr;
+    }
+};
+
+// Sums of the run of `len` entries from beg on: acc, this lane's latent slice; gw, s2 on every lane of the group.  All
+// groups of the wavefront call it together.
 template <int VEC, int L, int PACKED, int ADDR>
-__device__ __forceinline__ void walk_column(const ColArgs& A, int64_t beg, int64_t end, int sub, int kbase, bool kact,
+__device__ __forceinline__ void walk_column(const ColArgs& A, int64_t beg, int len, int sub, int kbase, bool kact,
                                             float (&acc)[VEC], float& gw, float& s2)
 {
     if constexpr (PACKED == FM_PACKED_LANE) {
-        // every lane reads inside the row: lanes past the scalars re-read its last VEC floats
-        const int last = (int)A.gs - VEC;
-        fm_walk<VEC, L, FM_WALK_PACKED, ADDR>(A.row, A.val, beg, end, A.G, A.gs, sub, kbase < last ? kbase : last,
-                                              A.K / VEC, acc, gw, s2, [](int, float x) { return x; });
-    } else {
+        // lanes past the latent ones, at least the last of the group, read the scalars [r | a | q | pad]
+        fm_walk<VEC, L, FM_WALK_PACKED, ADDR>(A.row, A.val, beg, len, A.G, A.gs, sub, kact ? kbase : A.K, acc, gw, s2,
+                                              FmOwnNone());
+    } else if constexpr (L >= FM_WIDE_GROUP) {
         const float* __restrict__ r = A.r;
         const int64_t rs = A.rs;
-        float unused = 0.f;
-        auto own = [&](int i, float x) {
+        float g = 0.f, s = 0.f;
+        fm_walk_wide<VEC, L>(A.row, A.val, beg, beg + len, A.G, A.gs, sub, kact ? kbase : 0, acc, [&](int i, float x) {
             const float xr = x * r[(int64_t)i * rs];
-            gw += xr;
-            s2 += x * xr;
+            g += xr;
+            s += x * xr;
             return xr;
-        };
-        if constexpr (L >= FM_WIDE_GROUP)
-            fm_walk_wide<VEC, L>(A.row, A.val, beg, end, A.G, A.gs, sub, kact ? kbase : 0, acc, own);
-        else
-            fm_walk<VEC, L, FM_WALK_SUM, ADDR>(A.row, A.val, beg, end, A.G, A.gs, sub, kact ? kbase : 0, 0, acc, unused, unused,
-                                               own);
+        });
+        gw = fm_group_sum<L>(g);
+        s2 = fm_group_sum<L>(s);
+    } else {
+        OwnMultiplier own{FmOwnArray<1>(A.r, A.rs), 0.f, 0.f};
+        float unused = 0.f;
+        fm_walk<VEC, L, FM_WALK_SUM, ADDR>(A.row, A.val, beg, len, A.G, A.gs, sub, kact ? kbase : 0, acc, unused, unused, own);
+        gw = fm_group_sum<L>(own.gw);
+        s2 = fm_group_sum<L>(own.s2);
     }
 }
 
 // once: the gathered rows are not used again soon
 template <int VEC, int L, int PACKED>
-__device__ __forceinline__ void accumulate_entries(const ColArgs& A, bool once, int64_t beg, int64_t end, int sub, int kbase,
+__device__ __forceinline__ void accumulate_entries(const ColArgs& A, bool once, int64_t beg, int len, int sub, int kbase,
                                                    bool kact, float (&acc)[VEC], float& gw, float& s2)
 {
     if (L >= FM_WIDE_GROUP || A.big)
-        walk_column<VEC, L, PACKED, FM_ADDR_PTR>(A, beg, end, sub, kbase, kact, acc, gw, s2);
+        walk_column<VEC, L, PACKED, FM_ADDR_PTR>(A, beg, len, sub, kbase, kact, acc, gw, s2);
     else if (once && A.nt)
-        walk_column<VEC, L, PACKED, FM_ADDR_BUF_NT>(A, beg, end, sub, kbase, kact, acc, gw, s2);
+        walk_column<VEC, L, PACKED, FM_ADDR_BUF_NT>(A, beg, len, sub, kbase, kact, acc, gw, s2);
     else
-        walk_column<VEC, L, PACKED, FM_ADDR_BUF>(A, beg, end, sub, kbase, kact, acc, gw, s2);
+        walk_column<VEC, L, PACKED, FM_ADDR_BUF>(A, beg, len, sub, kbase, kact, acc, gw, s2);
 }
 
 // The class of column j that decides which row block it meets in which stratum: its column block in
@@ -131,28 +156,29 @@ __device__ __forceinline__ void catch_up_factors(const ColArgs& A, int32_t qb, i
                  pow_int((double)step_factor(A.rho_big, A.lambda_w, A.eta), n_big));
 }
 
-// What the step of column j needs from memory besides the data sums; loaded early by the
-// kernels that can, so that it overlaps the gathers.
+// What the step of column j needs besides the data sums; asked for early, so that it overlaps the gathers.  Every lane
+// loads (an inactive slice: the first), no branch: nothing has to be waited for before the entries are asked for.
 template <int VEC>
 struct ColState {
     float v[VEC];
     float w;
+    float rho;   // share of the regulariser
+    int32_t qb;  // class of the column
     int32_t t0;  // first stratum whose step the column has not taken yet
 };
 
 template <int VEC, bool UPDATE>
-__device__ __forceinline__ ColState<VEC> load_column(const ColArgs& A, int64_t j, int sub, int kbase, bool kact)
+__device__ __forceinline__ ColState<VEC> load_column(const ColArgs& A, int64_t j, int kbase, bool kact)
 {
     ColState<VEC> c;
-#pragma unroll
-    for (int z = 0; z < VEC; ++z) c.v[z] = 0.f;
-    c.w = 0.f;
+    fm_load_vec<VEC>(A.V + j * A.K + (kact ? kbase : 0), c.v);
+    c.w = A.w[j];
     c.t0 = A.s;
-    if (kact) fm_load_vec<VEC>(A.V + j * A.K + kbase, c.v);
-    if (sub == 0) c.w = A.w[j];
     if constexpr (UPDATE) {
         if (A.lazy_last != nullptr) c.t0 = A.lazy_last[j];
     }
+    c.qb = column_class(A, j);
+    c.rho = reg_share(A, c.qb, A.s);
     return c;
 }
 
@@ -163,10 +189,9 @@ __device__ __forceinline__ void finish_column(const ColArgs& A, int64_t j, int s
                                               const float (&acc)[VEC], float gw, float s2, ColState<VEC> c)
 {
     const int K = A.K;
-    const int32_t qb = column_class(A, j);
-    const float rho = reg_share(A, qb, A.s);
+    const float rho = c.rho;
     float fv = 1.f, fw = 1.f;
-    if (c.t0 < A.s) catch_up_factors(A, qb, c.t0, A.s, fv, fw);  // postponed regulariser-only steps
+    if (c.t0 < A.s) catch_up_factors(A, c.qb, c.t0, A.s, fv, fw);  // postponed regulariser-only steps
     float dn = 0.f;
     if (kact) {
         float g[VEC];
@@ -257,70 +282,66 @@ __global__ __launch_bounds__(FM_BLOCK) void k_cols(const ColArgs A)
     const int kbase = sub * VEC;
     const bool kact = kbase < A.K;
     int64_t b = blockIdx.x;
+    const int64_t blk_items = A.blk_lists + A.blk_lin;
+    if (b >= blk_items + A.blk_short) {
+        __shared__ double sh[FM_WAVES];
+        fm_epi_partial<FM_BLOCK>(A.epi, (int)(b - blk_items - A.blk_short), sh);
+        return;
+    }
+    const bool items = b < blk_items;
     float acc[VEC];
 #pragma unroll
     for (int z = 0; z < VEC; ++z) acc[z] = 0.f;
     float gw = 0.f, s2 = 0.f;
-    if (b < A.blk_lists + A.blk_lin) {
-        int64_t it = -1, beg = 0, end = 0;
-        bool again = true;  // item of a heavy column inside a panel: its rows are gathered again soon
+    int64_t id = -1, beg = 0;  // item or column
+    int len = 0;
+    bool once = true;
+    ColState<VEC> c = {};
+    if (items) {
         if (b >= A.blk_lists) {
             const int64_t rel = (b - A.blk_lists) * (FM_WAVES * R) + slot;
+            once = false;
             if (rel < A.lin_count) {
                 const int64_t pos = A.lin_base + rel;
-                it = A.order[pos];
+                id = A.order[pos];
                 beg = A.ord_beg[pos];
-                end = beg + A.ord_len[pos];
+                len = A.ord_len[pos];
             }
         } else if (A.order != nullptr) {
             const int x = (int)(b % FM_XCDS);
-            const int64_t pos = A.list_off[x] + (b / FM_XCDS) * (FM_WAVES * R) + slot;
-            if (pos < A.list_off[x + 1]) {
-                it = A.order[pos];
-                beg = A.ord_beg[pos];
-                end = beg + A.ord_len[pos];
+            const int64_t first = A.list_off[x] + (b / FM_XCDS) * (FM_WAVES * R);
+            once = first >= A.list_mid[x];  // not an item of a heavy column inside a panel: those gather their rows again soon
+            if (first + slot < A.list_off[x + 1]) {
+                id = A.order[first + slot];
+                beg = A.ord_beg[first + slot];
+                len = A.ord_len[first + slot];
             }
-            again = A.list_off[x] + (b / FM_XCDS) * (FM_WAVES * R) < A.list_mid[x];  // uniform in the workgroup
         } else {
             const int64_t pos = b * (FM_WAVES * R) + slot;
             if (pos < A.nitems) {
-                it = A.item_base + pos;
-                beg = A.item_beg[it];
-                end = beg + A.item_len[it];
-            }
-            again = false;
-        }
-        accumulate_entries<VEC, L, PACKED>(A, !again, beg, end, sub, kbase, kact, acc, gw, s2);
-        gw = fm_group_sum<L>(gw);
-        s2 = fm_group_sum<L>(s2);
-        if (it >= 0) store_partial<VEC, L>(A, it, sub, kbase, kact, acc, gw, s2);
-        return;
-    }
-    b -= A.blk_lists + A.blk_lin;
-    if (b < A.blk_short) {
-        const int64_t pos = b * (FM_WAVES * R) + slot;
-        const bool valid = pos < A.nshort;
-        int64_t j = 0, beg = 0, end = 0;
-        if (valid) {
-            j = A.short_col[pos];
-            if (A.ptr != nullptr) {
-                beg = A.ptr[j];
-                end = A.ptr[j + 1];
-            } else {
-                beg = A.short_beg[pos];
-                end = beg + A.short_len[pos];
+                id = A.item_base + pos;
+                beg = A.item_beg[id];
+                len = A.item_len[id];
             }
         }
-        // the column's own values do not depend on the gathers: fetch them first
-        const ColState<VEC> c = load_column<VEC, UPDATE>(A, j, sub, kbase, kact && valid);
-        accumulate_entries<VEC, L, PACKED>(A, true, beg, end, sub, kbase, kact, acc, gw, s2);
-        gw = fm_group_sum<L>(gw);
-        s2 = fm_group_sum<L>(s2);
-        if (valid) finish_column<VEC, L, UPDATE>(A, j, sub, kbase, kact, acc, gw, s2, c);
-        return;
+    } else {
+        const int64_t pos = (b - blk_items) * (FM_WAVES * R) + slot;
+        const int64_t p = pos < A.nshort ? pos : A.nshort - 1;
+        const int64_t j = A.short_col[p];
+        beg = A.short_beg[p];
+        len = A.short_len[p];
+        c = load_column<VEC, UPDATE>(A, j, kbase, kact);
+        if (pos < A.nshort)
+            id = j;
+        else
+            len = 0;
     }
-    __shared__ double sh[FM_WAVES];
-    fm_epi_partial<FM_BLOCK>(A.epi, (int)(b - A.blk_short), sh);
+    accumulate_entries<VEC, L, PACKED>(A, once, beg, len, sub, kbase, kact, acc, gw, s2);
+    if (id < 0) return;
+    if (items)
+        store_partial<VEC, L>(A, id, sub, kbase, kact, acc, gw, s2);
+    else
+        finish_column<VEC, L, UPDATE>(A, id, sub, kbase, kact, acc, gw, s2, c);
 }
 
 // Columns with nothing stored (in this matrix or stratum) only feel the regulariser; one group
@@ -366,7 +387,7 @@ __global__ __launch_bounds__(FM_BLOCK) void k_cols_empty(const ColArgs A)
 #pragma unroll
             for (int z = 0; z < VEC; ++z) acc[z] = 0.f;
             finish_column<VEC, LE, false>(A, j[u], sub, kbase, kact, acc, 0.f, 0.f,
-                                          load_column<VEC, false>(A, j[u], sub, kbase, kact));
+                                          load_column<VEC, false>(A, j[u], kbase, kact));
         }
     } else {
         float v[U][VEC];
@@ -574,12 +595,12 @@ __device__ __forceinline__ void add_partials(const ColArgs& A, int64_t first, in
 template <int VEC, int L>
 __device__ __forceinline__ void add_groups(double (&acc)[VEC], double& gw, double& s2)
 {
+    if constexpr (L < FM_WAVE) {
 #pragma unroll
-    for (int o = L; o < FM_WAVE; o <<= 1) {
-#pragma unroll
-        for (int z = 0; z < VEC; ++z) acc[z] += __shfl_xor(acc[z], o, FM_WAVE);
-        gw += __shfl_xor(gw, o, FM_WAVE);
-        s2 += __shfl_xor(s2, o, FM_WAVE);
+        for (int z = 0; z < VEC; ++z) acc[z] += fm_xor_lane<L>(acc[z]);
+        gw += fm_xor_lane<L>(gw);
+        s2 += fm_xor_lane<L>(s2);
+        add_groups<VEC, 2 * L>(acc, gw, s2);
     }
 }
 
@@ -610,9 +631,12 @@ __global__ __launch_bounds__(FM_BLOCK) void k_cols_finish(const ColArgs A)
         fm_epi_final<FM_BLOCK>(A.epi, sh);
         return;
     }
-    int64_t lc;
+    int64_t lc, j;
+    ColState<VEC> c;  // asked for ahead of the partial sums
     if (b < A.nvlong) {
         lc = A.vlong[b];
+        j = A.long_col[lc];
+        c = load_column<VEC, UPDATE>(A, j, kbase, kact);
         add_partials<VEC>(A, A.long_first[lc] + threadIdx.x / L, A.long_first[lc + 1], NG, kbase, kact, acc, gw, s2);
         add_groups<VEC, L>(acc, gw, s2);
         double* mine = sh + wave * S;
@@ -639,16 +663,16 @@ __global__ __launch_bounds__(FM_BLOCK) void k_cols_finish(const ColArgs A)
         lc = A.long_base + rel;
         const int64_t first = A.long_first[lc], last = A.long_first[lc + 1];
         if (A.nvlong > 0 && last - first > A.vlong_items) return;
+        j = A.long_col[lc];
+        c = load_column<VEC, UPDATE>(A, j, kbase, kact);
         add_partials<VEC>(A, first + lane / L, last, R, kbase, kact, acc, gw, s2);
         add_groups<VEC, L>(acc, gw, s2);
         if (lane >= L) return;
     }
-    const int64_t j = A.long_col[lc];
     float accf[VEC];
 #pragma unroll
     for (int z = 0; z < VEC; ++z) accf[z] = (float)acc[z];
-    finish_column<VEC, L, UPDATE>(A, j, sub, kbase, kact, accf, (float)gw, (float)s2,
-                                  load_column<VEC, UPDATE>(A, j, sub, kbase, kact));
+    finish_column<VEC, L, UPDATE>(A, j, sub, kbase, kact, accf, (float)gw, (float)s2, c);
 }
 
 // LDS-staged kernel for the tile items; false if the tile does not fit in LDS for this K

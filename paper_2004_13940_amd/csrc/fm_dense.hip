@@ -129,7 +129,7 @@ __global__ __launch_bounds__(FM_BLOCK) void k_rows_dense(const RowArgs A)
         if (A.yhat != nullptr) A.yhat[row] = yh;
         if (A.y != nullptr) {
             y_i = A.y[row];
-            loss_and_multiplier(A.loss, A.s, yh, y_i, l_i, r_i);
+            loss_and_multiplier(A.loss, A.s, yh, y_i, A.row_part != nullptr || A.eval_part != nullptr, l_i, r_i);
         }
         if (A.a != nullptr) A.a[row * A.ss] = a_i;
         if (A.q != nullptr) A.q[row * A.ss] = q_i;

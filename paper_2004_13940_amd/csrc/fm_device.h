@@ -52,13 +52,47 @@ __device__ __forceinline__ void fm_store_vec(float* __restrict__ p, const float 
     }
 }
 
+// Value held by the lane whose number differs in bit X (a power of two below 64).  Inside 16 lanes by DPP, which has
+// neither the address arithmetic of ds_bpermute nor a wait on the LDS crossbar behind it.
+template <int X>
+__device__ __forceinline__ int fm_xor_lane(int v)
+{
+    if constexpr (X == 1) {
+        return __builtin_amdgcn_mov_dpp(v, 0xB1 /* quad_perm [1,0,3,2] */, 0xf, 0xf, true);
+    } else if constexpr (X == 2) {
+        return __builtin_amdgcn_mov_dpp(v, 0x4E /* quad_perm [2,3,0,1] */, 0xf, 0xf, true);
+    } else if constexpr (X == 4) {
+        // quads 0 and 2 of a row of 16 take the quad after them, then quads 1 and 3 the one before them
+        const int x = __builtin_amdgcn_update_dpp(v, v, 0x104 /* row_shl:4 */, 0xf, 0x5, false);
+        return __builtin_amdgcn_update_dpp(x, v, 0x114 /* row_shr:4 */, 0xf, 0xa, false);
+    } else if constexpr (X == 8) {
+        return __builtin_amdgcn_mov_dpp(v, 0x128 /* row_ror:8 */, 0xf, 0xf, true);
+    } else if constexpr (X == 16) {
+        return __builtin_amdgcn_ds_swizzle(v, (16 << 10) | 0x1f);
+    } else {
+        return __shfl_xor(v, X, 64);
+    }
+}
+template <int X>
+__device__ __forceinline__ float fm_xor_lane(float v)
+{
+    return __int_as_float(fm_xor_lane<X>(__float_as_int(v)));
+}
+template <int X>
+__device__ __forceinline__ double fm_xor_lane(double v)
+{
+    return __hiloint2double(fm_xor_lane<X>(__double2hiint(v)), fm_xor_lane<X>(__double2loint(v)));
+}
+
 // Sum over the L lanes of a group (L a power of two, groups aligned to L lanes);
 // every lane of the group receives the total.  Fixed butterfly order.
 template <int L, typename T>
 __device__ __forceinline__ T fm_group_sum(T v)
 {
-#pragma unroll
-    for (int o = L / 2; o > 0; o >>= 1) v += __shfl_xor(v, o, L);
+    if constexpr (L > 1) {
+        v += fm_xor_lane<L / 2>(v);
+        return fm_group_sum<L / 2>(v);
+    }
     return v;
 }
 
@@ -66,31 +100,42 @@ __device__ __forceinline__ T fm_group_sum(T v)
 template <typename T>
 __device__ __forceinline__ T fm_wave_sum(T v)
 {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-    return v;
+    return fm_group_sum<FM_WAVE>(v);
 }
 
-// Loss value and multiplier for one example (cases after eq. updates_v; the loss
-// constants make the printed multiplier the exact derivative).  expf only ever sees
-// a non-positive argument.
-__device__ __forceinline__ void loss_and_multiplier(int32_t loss, float s, float yh, float y, float& l, float& r)
+// Largest of the values of a wavefront's groups (the L lanes of a group hold the same one), as a wave-uniform number (a
+// scalar register: branches on it do not diverge).
+template <int L>
+__device__ __forceinline__ int fm_wave_max(int v)
 {
+    static_assert(L <= 16, "groups inside a row of 16 lanes");
+    auto take = [&](int t) { v = t > v ? t : v; };
+    if constexpr (L <= 1) take(fm_xor_lane<1>(v));
+    if constexpr (L <= 2) take(fm_xor_lane<2>(v));
+    if constexpr (L <= 4) take(__builtin_amdgcn_mov_dpp(v, 0x141 /* row_half_mirror */, 0xf, 0xf, true));
+    if constexpr (L <= 8) take(__builtin_amdgcn_mov_dpp(v, 0x140 /* row_mirror */, 0xf, 0xf, true));
+    const int a = __builtin_amdgcn_readlane(v, 0), b = __builtin_amdgcn_readlane(v, 16);
+    const int c = __builtin_amdgcn_readlane(v, 32), d = __builtin_amdgcn_readlane(v, 48);
+    const int ab = a > b ? a : b, cd = c > d ? c : d;
+    return ab > cd ? ab : cd;
+}
+
+// Multiplier of one example, and its loss where `want` (uniform) says that somebody reads it: the logarithm is most of
+// the instructions (cases after eq. updates_v; the loss constants make the printed multiplier the exact derivative).
+// expf only ever sees a non-positive argument.
+__device__ __forceinline__ void loss_and_multiplier(int32_t loss, float s, float yh, float y, bool want, float& l, float& r)
+{
+    l = 0.f;
     if (loss == FM_LOSS_SQUARED) {
         const float d = yh - y;
-        l = 0.5f * d * d;
+        if (want) l = 0.5f * d * d;
         r = s * d;
     } else {
         const float mg = y * yh;
-        if (mg > 0.f) {
-            const float e = expf(-mg);
-            l = log1pf(e);
-            r = -s * y * e / (1.f + e);
-        } else {
-            const float e = expf(mg);
-            l = -mg + log1pf(e);
-            r = -s * y / (1.f + e);
-        }
+        const float e = expf(mg > 0.f ? -mg : mg);
+        const float sy = -s * y;
+        r = (mg > 0.f ? sy * e : sy) / (1.f + e);
+        if (want) l = (mg > 0.f ? 0.f : -mg) + log1pf(e);
     }
 }
 
@@ -111,9 +156,18 @@ __device__ __forceinline__ void fm_eval_wave(bool has, float yh, float y, float 
 
 // Block b of the floor split of n items into P blocks that holds index i:
 // b = floor(((i+1) P - 1) / n)   (inverse of the bound floor(b n / P)).
+// The quotient in fp64, at most one off (both terms below 2^51), and put right: a division of 64-bit integers is a hundred
+// instructions.
 __device__ __forceinline__ int32_t fm_block_of(int64_t i, int64_t n, int32_t P)
 {
-    return (int32_t)(((i + 1) * (int64_t)P - 1) / n);
+    const int64_t x = (i + 1) * (int64_t)P - 1;
+    int32_t b = (int32_t)((double)x * (1.0 / (double)n));
+    const int64_t rest = x - (int64_t)b * n;
+    if (rest < 0)
+        --b;
+    else if (rest >= n)
+        ++b;
+    return b;
 }
 
 // Compile-time loop: f(std::integral_constant<int, I>) for I = 0..N-1.
@@ -315,17 +369,6 @@ __device__ __forceinline__ void fm_walk_wide(const int32_t* __restrict__ idx, co
     }
 }
 
-// Largest value over the 64 lanes, as a wave-uniform number (a scalar register: branches on it do not diverge).
-__device__ __forceinline__ int fm_wave_max(int v)
-{
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-        const int t = __shfl_xor(v, o, 64);
-        v = t > v ? t : v;
-    }
-    return __builtin_amdgcn_readfirstlane(v);
-}
-
 // How a walk addresses the rows it gathers.  BUF, BUF_NT: byte offsets of 32 bits from one buffer descriptor (arrays of
 // up to FM_BUF_BYTES): one address register per gather instead of two, and an offset of FM_BUF_NONE is out of range,
 // which reads zero without a request to memory, so slots without an entry cost nothing.  PTR: 64-bit addresses for
@@ -350,127 +393,222 @@ __device__ __forceinline__ void fm_buf_load(__amdgpu_buffer_rsrc_t rs, uint32_t 
     }
 }
 
-// What a walk adds up per entry with multiplier m and gathered row g:
-//   SUM     acc += m g
-//   PACKED  rows are [G | r | ..], lane rl holds r in its first float; acc += x r G on the latent lanes,
-//           gw += x r and s2 += x^2 r on lane rl
-enum { FM_WALK_SUM = 0, FM_WALK_PACKED = 1 };
+// What a walk adds up per entry with value x and gathered row g:
+//   SUM     acc += m g with the multiplier m that `own` makes of x
+//   PACKED  rows are [G | r | ..] and the last lane of a group holds r in its first float; acc += x r G on the latent
+//           lanes, gw += x r and s2 += x^2 r on every lane
+//   SCORE   acc += x g, s2 += x^2 g^2
+enum { FM_WALK_SUM = 0, FM_WALK_PACKED = 1, FM_WALK_SCORE = 2 };
 
-// S slots of a round from slot S0 on: all loads, then all sums in entry order.
-template <int VEC, int L, int KIND, int ADDR, int S, int S0, class IX, class MU>
-__device__ __forceinline__ void fm_slots(const IX& ix, const MU& mu, __amdgpu_buffer_rsrc_t rs, const float* __restrict__ src,
-                                         int64_t stride, int kb, int rl, bool scalar_lane, float (&acc)[VEC], float& gw,
-                                         float& s2)
-{
-    float g[S][VEC];
-    float xt[S];
-    fm_static_for<0, S>([&](auto sc) {
-        constexpr int s = decltype(sc)::value;
-        constexpr int u = (S0 + s) / L, T = (S0 + s) % L;
-        const int it = fm_bcast_i<L, T>(ix[u]);
-        xt[s] = fm_bcast_f<L, T>(mu[u]);
-        if constexpr (ADDR == FM_ADDR_PTR)
-            fm_load_vec<VEC>(src + (int64_t)it * stride + kb, g[s]);
-        else
-            fm_buf_load<VEC, ADDR == FM_ADDR_BUF_NT>(rs, (uint32_t)it + (uint32_t)(kb * (int)sizeof(float)), g[s]);
-    });
+// Per-entry work of the lane that holds the entry, besides the gathered row: load() asks for what the entry's index names
+// (a slot without an entry, index < 0, gets zeros), use() takes it and returns the multiplier.  Two steps, so that what it
+// asks for and the gathers of the round are on their way together.
+struct FmOwnNone {
+    struct T {};
+    template <int ADDR>
+    __device__ __forceinline__ T load(int) const { return T(); }
+    __device__ __forceinline__ float use(T, float x) const { return x; }
+};
+
+// An array of W floats per index, read by load(): through a buffer descriptor, or with 64-bit addresses.
+template <int W>
+struct FmOwnArray {
+    const float* p;
+    uint32_t stride;  // floats
+    __amdgpu_buffer_rsrc_t rs;
+    __device__ __forceinline__ FmOwnArray(const float* p_, int64_t stride_)
+        : p(p_), stride((uint32_t)stride_),
+          rs(__builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(p_), 0, (int)FM_BUF_NONE, 0x20000))
+    {
+    }
+    template <int ADDR>
+    __device__ __forceinline__ void get(int i, float (&v)[W]) const
+    {
+        if constexpr (ADDR == FM_ADDR_PTR) {
 #pragma unroll
-    for (int s = 0; s < S; ++s) {
-        if constexpr (KIND == FM_WALK_PACKED) {
-            const float m = xt[s] * __shfl(g[s][0], rl, L);
-#pragma unroll
-            for (int z = 0; z < VEC; ++z) acc[z] += m * g[s][z];
-            if (scalar_lane) {
-                gw += m;
-                s2 += xt[s] * m;
-            }
+            for (int z = 0; z < W; ++z) v[z] = 0.f;
+            if (i >= 0) fm_load_vec<W>(p + (int64_t)i * stride, v);
         } else {
-#pragma unroll
-            for (int z = 0; z < VEC; ++z) acc[z] += xt[s] * g[s][z];
+            fm_buf_load<W, false>(rs, i >= 0 ? (uint32_t)i * (stride * (uint32_t)sizeof(float)) : FM_BUF_NONE, v);
         }
+    }
+};
+
+// One gathered row slice, from fp32 or half-precision rows.
+template <int VEC, bool NT>
+__device__ __forceinline__ void fm_buf_row(__amdgpu_buffer_rsrc_t rs, uint32_t off, float (&v)[VEC], const float*)
+{
+    fm_buf_load<VEC, NT>(rs, off, v);
+}
+template <int VEC, bool NT>
+__device__ __forceinline__ void fm_buf_row(__amdgpu_buffer_rsrc_t rs, uint32_t off, float (&v)[VEC], const _Float16*)
+{
+    static_assert(VEC == 4, "half rows come four at a time");
+    typedef int i2 __attribute__((ext_vector_type(2)));
+    const i2 t = __builtin_amdgcn_raw_buffer_load_b64(rs, (int)off, 0, NT ? 2 : 0);
+    const fm_h4 h = __builtin_bit_cast(fm_h4, t);
+    v[0] = (float)h.x; v[1] = (float)h.y; v[2] = (float)h.z; v[3] = (float)h.w;
+}
+
+// N consecutive entries at once; the arrays of entries are padded by FM_ENTRY_PAD, so that a load that begins inside a run
+// stays inside its array.  Entries lie at any multiple of four bytes.
+template <int N, typename T>
+__device__ __forceinline__ void fm_load_entries(const T* __restrict__ p, T (&v)[N])
+{
+    static_assert(N - 1 <= FM_ENTRY_PAD, "loads past the end of a run");
+    if constexpr (N >= 4) {
+        typedef T t4 __attribute__((ext_vector_type(4), aligned(4)));
+#pragma unroll
+        for (int i = 0; i < N; i += 4) {
+            const t4 t = *reinterpret_cast<const t4*>(p + i);
+            v[i] = t.x; v[i + 1] = t.y; v[i + 2] = t.z; v[i + 3] = t.w;
+        }
+    } else if constexpr (N == 2) {
+        typedef T t2 __attribute__((ext_vector_type(2), aligned(4)));
+        const t2 t = *reinterpret_cast<const t2*>(p);
+        v[0] = t.x; v[1] = t.y;
+    } else {
+        v[0] = *p;
     }
 }
 
-// The inner loop of the column kernels and of the refresh for groups of up to eight lanes.  Every group of L lanes walks
-// its own run [beg,end) of one column, all groups of the wavefront in step: a round takes the next C entries of every run,
-// in batches of SMAX or four slots by the longest run left, so the choice is a scalar branch, and a group whose run is
-// over sits the round out.  The indices of the next round are loaded while the gathers of this one are on their way: a
-// round costs one memory latency, not two.  Columns of a few entries are what a stratum or a batch consists of; with a
+// S slots of a round from slot S0 on (a lane holds U consecutive ones): the gathers ...
+template <int VEC, int L, int ADDR, int S, int S0, int U, class SRC>
+__device__ __forceinline__ void fm_slot_loads(const int (&ix)[U], __amdgpu_buffer_rsrc_t rs, const SRC* __restrict__ src,
+                                              int64_t stride, int kb, float (&g)[S][VEC])
+{
+    fm_static_for<0, S>([&](auto sc) {
+        constexpr int s = decltype(sc)::value;
+        constexpr int u = (S0 + s) % U, T = (S0 + s) / U;
+        const int it = fm_bcast_i<L, T>(ix[u]);
+        if constexpr (ADDR == FM_ADDR_PTR)
+            fm_load_vec<VEC>(src + (int64_t)it * stride + kb, g[s]);
+        else
+            fm_buf_row<VEC, ADDR == FM_ADDR_BUF_NT>(rs, (uint32_t)it + (uint32_t)(kb * (int)sizeof(SRC)), g[s], src);
+    });
+}
+
+// ... and the sums in entry order.
+template <int VEC, int L, int KIND, int S, int S0, int U>
+__device__ __forceinline__ void fm_slot_sums(const float (&mu)[U], const float (&g)[S][VEC], float (&acc)[VEC], float& gw, float& s2)
+{
+    fm_static_for<0, S>([&](auto sc) {
+        constexpr int s = decltype(sc)::value;
+        constexpr int u = (S0 + s) % U, T = (S0 + s) / U;
+        const float x = fm_bcast_f<L, T>(mu[u]);
+        if constexpr (KIND == FM_WALK_PACKED) {
+            const float m = x * fm_bcast_f<L, L - 1>(g[s][0]);
+#pragma unroll
+            for (int z = 0; z < VEC; ++z) acc[z] += m * g[s][z];
+            gw += m;
+            s2 += x * m;
+        } else {
+#pragma unroll
+            for (int z = 0; z < VEC; ++z) {
+                acc[z] += x * g[s][z];
+                if constexpr (KIND == FM_WALK_SCORE) s2 += (x * x) * (g[s][z] * g[s][z]);
+            }
+        }
+    });
+}
+
+// The inner loop of the kernels for groups of up to eight lanes.  Every group of L lanes walks
+// its own run [beg,end) of one row or column, all groups of the wavefront in step: a round takes the next C entries of
+// every run, in batches of SMAX or four slots by the longest run left, so the choice is a scalar branch, and a group whose
+// run is over sits the round out.  The indices of the next round are loaded while the gathers of this one are on their way,
+// and so is what the holder of an entry asks for (own): a round costs one memory latency, not three.  Columns of a few
+// entries are what a stratum or a batch consists of; with a
 // slot loop and a four-at-a-time tail per group a column of 15 entries took six round trips, here it takes two.
-// SMAX = 8 rather than 16 in the columns: 103 registers instead of 146 at eight lanes of a packed row, four wavefronts per
-// SIMD instead of three (mini-batch epoch of the click-style workload, 2.5e6 rows: 4.53 -> 4.20 ms).
+// A lane loads the U = C / L entries of a round that it holds at once: the L1 stalls on every further request for a line
+// that is still on its way, and entry by entry a round of four lanes made four of them (click-style scores, 2.5e6 rows,
+// K=16: 806 -> 721 us with this change alone; 1e5 text-like rows, K=8: 79.9 -> 64.9).  Against the row kernel's own loop,
+// without rounds in step, index prefetch or wide loads: 775 -> 721 and 78.6 -> 64.9 us.
+// SMAX = 8 rather than 16: few registers, more wavefronts (mini-batch epoch of the click-style workload, 2.5e6 rows:
+// 4.53 -> 4.20 ms).
 // The refresh of a stratum, whose runs are mostly shorter than a round, takes rounds of four or eight in fours.
-//   own(index, value) -> multiplier: the work of the lane that holds the entry
-template <int VEC, int L, int KIND, int ADDR, int C = 16, int SMAX = 8, class Own>
+// kb: offset of the lane's slice in a row, valid for every lane.
+template <int VEC, int L, int KIND, int ADDR, int C = 16, int SMAX = 8, class Own, class SRC>
 __device__ __forceinline__ void fm_walk(const int32_t* __restrict__ idx, const float* __restrict__ val, int64_t beg,
-                                        int64_t end, const float* __restrict__ src, int64_t stride, int sub, int kb, int rl,
+                                        int len, const SRC* __restrict__ src, int64_t stride, int sub, int kb,
                                         float (&acc)[VEC], float& gw, float& s2, Own&& own)
 {
     constexpr int U = C / L;
     static_assert(L < FM_WIDE_GROUP && C % L == 0 && ((SMAX == 8 && C == 16) || (SMAX == 4 && (C == 4 || C == 8))),
                   "rounds of whole batches");
-    const int len = (int)(end - beg);
-    const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(src), 0, (int)FM_BUF_NONE, 0x20000);
-    const uint32_t row_bytes = (uint32_t)stride * (uint32_t)sizeof(float);
-    const bool scalar_lane = sub == rl;
+    const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<SRC*>(src), 0, (int)FM_BUF_NONE, 0x20000);
+    const uint32_t row_bytes = (uint32_t)stride * (uint32_t)sizeof(SRC);
     const int32_t* __restrict__ ip = idx + beg;
     const float* __restrict__ vp = val + beg;
-    int ix[U], raw[U];
+    int raw[U];
     float mu[U];
     auto fetch = [&](int at, int (&i)[U], float (&x)[U]) {
+        const int t = at + sub * U;
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            const int t = at + u * L + sub;
             i[u] = -1;
             x[u] = 0.f;
-            if (t < len) {
-                i[u] = ip[t];
-                x[u] = vp[t];
-            } else if (ADDR == FM_ADDR_PTR && len > 0) {
-                i[u] = ip[len - 1];
-            }
+        }
+        if (t < len) {
+            fm_load_entries<U>(ip + t, i);
+            fm_load_entries<U>(vp + t, x);
+        }
+#pragma unroll
+        for (int u = 1; u < U; ++u) {
+            i[u] = t + u < len ? i[u] : -1;
+            x[u] = t + u < len ? x[u] : 0.f;
         }
     };
-    // Short rounds: the first indices are on their way while the longest run is found, six steps across the wavefront.
-    // Not for the columns: mini-batch click epoch 4.23 -> 3.96 ms, but full click epoch 7.37 -> 7.59 ms.
-    constexpr bool EARLY = C < 16;
-    if constexpr (EARLY) fetch(0, raw, mu);
-    int left = fm_wave_max(len);
+    fetch(0, raw, mu);
+    int left = fm_wave_max<L>(len);
     if (left <= 0) return;
-    if constexpr (!EARLY) fetch(0, raw, mu);
     for (int at = 0;; at += C, left -= C) {
         int in[U];
         float mn[U];
         const bool more = left > C;
         if (more) fetch(at + C, in, mn);
+        int ix[U];
+        typename std::decay_t<Own>::T pre[U];
 #pragma unroll
         for (int u = 0; u < U; ++u) {
+            pre[u] = own.template load<ADDR>(raw[u]);
             if constexpr (ADDR == FM_ADDR_PTR) {
-                ix[u] = raw[u] < 0 ? 0 : raw[u];  // only where the run is empty: its group sits the round out
-                if (at + u * L + sub < len) mu[u] = own(raw[u], mu[u]);
+                // a slot without an entry repeats an entry of its own run: of this lane's, or of the run's first lane,
+                // which holds one as long as the run is not over
+                const int first = fm_bcast_i<L, 0>(raw[0]);
+                ix[u] = raw[u] >= 0 ? raw[u] : first >= 0 ? first : 0;
             } else {
-                ix[u] = (int)FM_BUF_NONE;
-                if (raw[u] >= 0) {
-                    mu[u] = own(raw[u], mu[u]);
-                    ix[u] = (int)((uint32_t)raw[u] * row_bytes);
-                }
+                ix[u] = raw[u] >= 0 ? (int)((uint32_t)raw[u] * row_bytes) : (int)FM_BUF_NONE;
             }
         }
+        auto multipliers = [&] {
+#pragma unroll
+            for (int u = 0; u < U; ++u) mu[u] = own.use(pre[u], mu[u]);
+        };
         if (at < len) {
             bool done = false;
             if constexpr (SMAX == 8) {
                 if (left > 4) {
                     done = true;
-                    fm_slots<VEC, L, KIND, ADDR, 8, 0>(ix, mu, rs, src, stride, kb, rl, scalar_lane, acc, gw, s2);
-                    if (left > 8)
-                        fm_slots<VEC, L, KIND, ADDR, 8, 8>(ix, mu, rs, src, stride, kb, rl, scalar_lane, acc, gw, s2);
+                    float g[8][VEC];
+                    fm_slot_loads<VEC, L, ADDR, 8, 0>(ix, rs, src, stride, kb, g);
+                    multipliers();
+                    fm_slot_sums<VEC, L, KIND, 8, 0>(mu, g, acc, gw, s2);
+                    if (left > 8) {
+                        fm_slot_loads<VEC, L, ADDR, 8, 8>(ix, rs, src, stride, kb, g);
+                        fm_slot_sums<VEC, L, KIND, 8, 8>(mu, g, acc, gw, s2);
+                    }
                 }
             }
             if (!done) {
-                fm_slots<VEC, L, KIND, ADDR, 4, 0>(ix, mu, rs, src, stride, kb, rl, scalar_lane, acc, gw, s2);
+                float g[4][VEC];
+                fm_slot_loads<VEC, L, ADDR, 4, 0>(ix, rs, src, stride, kb, g);
+                multipliers();
+                fm_slot_sums<VEC, L, KIND, 4, 0>(mu, g, acc, gw, s2);
                 if constexpr (SMAX == 4 && C == 8) {
-                    if (left > 4)
-                        fm_slots<VEC, L, KIND, ADDR, 4, 4>(ix, mu, rs, src, stride, kb, rl, scalar_lane, acc, gw, s2);
+                    if (left > 4) {
+                        fm_slot_loads<VEC, L, ADDR, 4, 4>(ix, rs, src, stride, kb, g);
+                        fm_slot_sums<VEC, L, KIND, 4, 4>(mu, g, acc, gw, s2);
+                    }
                 }
             }
         }

@@ -17,6 +17,7 @@ constexpr int FM_BLOCK = 256;             // threads per workgroup of the pass k
 constexpr int FM_WAVES = FM_BLOCK / FM_WAVE;
 constexpr int FM_MAXP = 1 << 20;       // row blocks / batches
 constexpr int FM_MAXP_CELLS = 4096;     // the P x P table of entries per cell is only kept up to this P
+constexpr int64_t FM_ENTRY_PAD = 16;      // entries by which the arrays of entries (index, value) are longer than they need be
 constexpr int FM_XCDS = 8;                // L2 domains; workgroup b runs on XCD b % 8
 
 // Tunables of the column-side work decomposition, per handle (fm_set_tuning, fm_set_tile_tuning;
@@ -99,8 +100,8 @@ struct LongIndex {
     // non-empty columns with at most `seg` entries, in column order (per stratum: h_short_off)
     int64_t nshort = 0;
     int32_t* short_col = nullptr;
-    int64_t* short_beg = nullptr;   // per-stratum and per-batch indices only: first entry and number of
-    int32_t* short_len = nullptr;   // entries of every listed column (the full matrix has its colptr)
+    int64_t* short_beg = nullptr;   // first entry and number of entries of every listed column
+    int32_t* short_len = nullptr;
     std::vector<int64_t> h_short_off;
     // processing order of the full matrix: FM_XCDS lists of item ids, list x walked by the
     // workgroups that run on XCD x, heavy columns panel by panel; of strata and batches: by first row inside each
@@ -297,13 +298,18 @@ struct RowArgs {
     int32_t whole_rows; // packed aggregate rows: r, a, q move as one float4 (forward: and the padding is written with them)
     float* row_part;    // nullable: [2*gridDim] loss and sum r per block
     double* eval_part;  // nullable: [3*gridDim] sums of losses, squared errors and correct signs per block
-    int32_t big;          // refresh: dV is larger than FM_BUF_BYTES
+    int32_t big;          // what is gathered (V, its half copy or dV, dwn) is larger than FM_BUF_BYTES
     int32_t dense_D;      // forward: > 0 when `val` is a dense row-major N x dense_D matrix (col is then not read)
     const int32_t* rows;  // nullable: the launch covers rows[0..N) instead of rows 0..N-1, and
                           // rowptr[k], rowptr[k+1] bound the entries of rows[k]
     int32_t loss;
     float s;
 };
+// RowArgs::big of a row kernel that gathers K floats per column, and up to two more beside them
+inline int32_t fm_rows_big(const fm_matrix* m, int32_t K)
+{
+    return m->D * std::max<int64_t>(K, 2) * (int64_t)sizeof(float) > FM_BUF_BYTES || m->opt.wide_addresses ? 1 : 0;
+}
 int fm_launch_rows(fm_matrix* m, const RowArgs& A, bool refresh, hipStream_t st);
 int64_t fm_rows_grid(int64_t N, int32_t K);
 // once per device, with that device current: resolves the address of the static scratch array of
@@ -348,7 +354,7 @@ inline int fm_epi_nsums(int64_t n)
 struct ColArgs {
     int64_t D;
     int32_t K;
-    const int64_t* ptr;  // [D+1] global offsets of the full matrix; nullptr for a stratum or batch (short_beg/len, items)
+    const int64_t* ptr;  // [D+1] global offsets of the full matrix (which columns are empty); nullptr for a stratum or batch
     const int32_t* row;
     const float* val;
     const float* r;
@@ -366,7 +372,7 @@ struct ColArgs {
     float* dV;       // delta outputs (nullable)
     float2* dwn;
     const int32_t* short_col;  // list of the short non-empty columns of this launch
-    const int64_t* short_beg;  // with ptr == nullptr: first entry and number of entries of every listed column
+    const int64_t* short_beg;  // first entry and number of entries of every listed column
     const int32_t* short_len;
     int64_t nshort;
     // nullable, with ptr == nullptr and steps taken at once: every column that takes its step from data sets

@@ -75,6 +75,7 @@ extern "C" int fm_forward_noalloc(fm_matrix* m, const fm_params* p, const float*
     A.w0 = w0;
     A.w = w;
     A.V = V;
+    A.big = fm_rows_big(m, p->K);
     A.y = y;
     A.yhat = yhat;
     A.a = a;

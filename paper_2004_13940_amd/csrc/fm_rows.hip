@@ -3,17 +3,72 @@
 //
 // Layout: a wavefront is split into groups of L lanes; one group owns one row, lane
 // `sub` of the group owns VEC consecutive latent dimensions [sub*VEC, sub*VEC+VEC).
-// A group reads its row's (column, value) pairs L*CH at a time (one entry per lane
-// and slot, coalesced), broadcasts each pair inside the group and gathers the V row
-// of that column as one contiguous 4*K-byte request.
+// A group reads its row's (column, value) pairs (coalesced, each lane the ones it holds), broadcasts each pair inside the
+// group and gathers the V row of that column as one contiguous 4*K-byte request.
 #include "fm_device.h"
 #include "fm_internal.h"
 
 namespace {
 
-// FORWARD_HALF: V rows from the half-precision copy; REFRESH_BIG: dV is larger than FM_BUF_BYTES
-enum { MODE_FORWARD = 0, MODE_REFRESH = 1, MODE_FORWARD_HALF = 2, MODE_REFRESH_BIG = 3 };
+// FORWARD_HALF: V rows from the half-precision copy; *_BIG: what is gathered is larger than FM_BUF_BYTES (groups of fewer
+// than FM_WIDE_GROUP lanes; wider ones use 64-bit addresses throughout)
+enum {
+    MODE_FORWARD = 0,
+    MODE_REFRESH = 1,
+    MODE_FORWARD_HALF = 2,
+    MODE_REFRESH_BIG = 3,
+    MODE_FORWARD_BIG = 4,
+    MODE_FORWARD_HALF_BIG = 5
+};
 constexpr bool is_refresh(int mode) { return mode == MODE_REFRESH || mode == MODE_REFRESH_BIG; }
+constexpr bool is_half(int mode) { return mode == MODE_FORWARD_HALF || mode == MODE_FORWARD_HALF_BIG; }
+constexpr int addr_of(int mode)
+{
+    return mode == MODE_FORWARD || mode == MODE_FORWARD_HALF || mode == MODE_REFRESH ? FM_ADDR_BUF : FM_ADDR_PTR;
+}
+
+// Per-entry work of a score: w_j x_ij.
+struct OwnScore {
+    struct T {
+        float w[1];
+    };
+    FmOwnArray<1> w;
+    float a;
+    template <int ADDR>
+    __device__ __forceinline__ T load(int c) const
+    {
+        T t;
+        w.template get<ADDR>(c, t.w);
+        return t;
+    }
+    __device__ __forceinline__ float use(T t, float x)
+    {
+        a += t.w[0] * x;
+        return x;
+    }
+};
+
+// Per-entry work of a refresh: the changes of w_j and of |v_j|^2.
+struct OwnRefresh {
+    struct T {
+        float d[2];
+    };
+    FmOwnArray<2> dwn;
+    float a, q;
+    template <int ADDR>
+    __device__ __forceinline__ T load(int c) const
+    {
+        T t;
+        dwn.template get<ADDR>(c, t.d);
+        return t;
+    }
+    __device__ __forceinline__ float use(T t, float x)
+    {
+        a += t.d[0] * x;
+        q += t.d[1] * (x * x);
+        return x;
+    }
+};
 
 template <int VEC, int L, int MODE>
 __global__ __launch_bounds__(FM_BLOCK) void k_rows(const RowArgs A)
@@ -25,80 +80,86 @@ __global__ __launch_bounds__(FM_BLOCK) void k_rows(const RowArgs A)
     const int grp = lane / L;
     const int64_t slot = (int64_t)blockIdx.x * (FM_WAVES * R) + wave * R + grp;
     const bool valid = slot < A.N;
-    int64_t row = slot;
-    int64_t beg = 0, end = 0;
-    if (valid) {
-        int64_t at = slot;
-        if constexpr (is_refresh(MODE)) {
-            if (A.rows != nullptr)
-                row = A.rows[slot];  // pointers are indexed by list position
-            else
-                at = row;
-        }
-        beg = A.rowptr[at];
-        end = A.rowptr[at + 1];
+    // Every lane loads, of the last row where its own is past the end: without branches the loads of a stage are all on
+    // their way before the first is waited for.
+    const int64_t at = valid ? slot : A.N - 1;
+    const int64_t beg = A.rowptr[at], end = A.rowptr[at + 1];
+    int64_t row = at;
+    if constexpr (is_refresh(MODE)) {  // listed rows: pointers are indexed by list position
+        const int32_t* __restrict__ list = A.rows != nullptr ? A.rows + at : reinterpret_cast<const int32_t*>(A.rowptr);
+        const int32_t listed = *list;
+        if (A.rows != nullptr) row = listed;
     }
+    const int len = valid ? (int)(end - beg) : 0;
     const int K = A.K;
     const int kbase = sub * VEC;
     const bool kact = kbase < K;  // K is a multiple of VEC, so the whole slice is in range
+    const int kb = kact ? kbase : 0;
+    const uint64_t grow = (uint64_t)(uint32_t)row * (uint32_t)A.gs;  // row < 2^31, strides < 2^31
+    const uint64_t srow = (uint64_t)(uint32_t)row * (uint32_t)A.ss;
 
     float acc[VEC];
 #pragma unroll
     for (int u = 0; u < VEC; ++u) acc[u] = 0.f;
     float a_acc = 0.f, q_acc = 0.f;
-    const int kb = kact ? kbase : 0;
     [[maybe_unused]] bool touched = false;
     [[maybe_unused]] float g_old[VEC] = {};
     [[maybe_unused]] float a_old = 0.f, q_old = 0.f;
-    if constexpr (MODE == MODE_FORWARD) {
-        const float* __restrict__ w = A.w;
-        fm_gather_accumulate<VEC, L, true>(A.col, A.val, beg, end, A.V, K, sub, kb, acc, q_acc,
-                                           [&](int c, float x) {
-                                               a_acc += w[c] * x;
-                                               return x;
-                                           });
-    } else if constexpr (MODE == MODE_FORWARD_HALF) {
-        const float* __restrict__ w = A.w;
-        fm_gather_accumulate<VEC, L, true>(A.col, A.val, beg, end, A.Vh, K, sub, kb, acc, q_acc,
-                                           [&](int c, float x) {
-                                               a_acc += w[c] * x;
-                                               return x;
-                                           });
+    const float y_i = *(A.y != nullptr ? A.y + row : A.w0);  // not used without labels
+    if constexpr (!is_refresh(MODE)) {
+        if constexpr (L < FM_WIDE_GROUP) {
+            OwnScore own{FmOwnArray<1>(A.w, 1), 0.f};
+            float unused = 0.f;
+            if constexpr (is_half(MODE))
+                fm_walk<VEC, L, FM_WALK_SCORE, addr_of(MODE)>(A.col, A.val, beg, len, A.Vh, K, sub, kb, acc, unused, q_acc, own);
+            else
+                fm_walk<VEC, L, FM_WALK_SCORE, addr_of(MODE)>(A.col, A.val, beg, len, A.V, K, sub, kb, acc, unused, q_acc, own);
+            a_acc = own.a;
+        } else {
+            const float* __restrict__ w = A.w;
+            auto own = [&](int c, float x) {
+                a_acc += w[c] * x;
+                return x;
+            };
+            if constexpr (is_half(MODE))
+                fm_gather_accumulate<VEC, L, true>(A.col, A.val, beg, beg + len, A.Vh, K, sub, kb, acc, q_acc, own);
+            else
+                fm_gather_accumulate<VEC, L, true>(A.col, A.val, beg, beg + len, A.V, K, sub, kb, acc, q_acc, own);
+        }
     } else {
         // rows that have no entry in this stratum keep their aggregates untouched
-        touched = valid && beg < end;  // uniform inside a group
-        if (touched) {  // issued before the gathers so that it overlaps them
-            if (kact) fm_load_vec<VEC>(A.G + row * A.gs + kbase, g_old);
-            if (sub == 0) {
-                if (VEC == 4 && A.whole_rows) {  // [r | a | q | pad] of a packed row
-                    float z[4];
-                    fm_load_vec<4>(A.G + row * A.gs + K, z);
-                    a_old = z[1];
-                    q_old = z[2];
-                } else {
-                    a_old = A.a[row * A.ss];
-                    q_old = A.q[row * A.ss];
-                }
-            }
+        touched = len > 0;  // uniform inside a group
+        fm_load_vec<VEC>(A.G + grow + kb, g_old);
+        if (VEC == 4 && A.whole_rows) {  // [r | a | q | pad] of a packed row
+            float z[4];
+            fm_load_vec<4>(A.G + grow + K, z);
+            a_old = z[1];
+            q_old = z[2];
+        } else {
+            a_old = A.a[srow];
+            q_old = A.q[srow];
         }
-        const float2* __restrict__ dwn = A.dwn;
-        float unused = 0.f;
         // A row has few entries inside one stratum (1 to 4 where it has any): rounds as short as the group allows, four
         // gathers at a time, so that few registers are in use and many rows in flight; for groups of up to eight lanes a
         // slot without an entry is no request (BUF addressing).  Missing entries used to repeat the last one: three of
         // four requests of a row with one entry (stratified epoch of the click-style workload, 1e7 rows, 64 strata:
         // 39.0 -> 38.5 ms).
-        auto own = [&](int c, float x) {
-            const float2 d = dwn[c];
-            a_acc += d.x * x;
-            q_acc += d.y * (x * x);
-            return x;
-        };
-        if constexpr (L >= FM_WIDE_GROUP)
-            fm_walk_wide<VEC, L>(A.col, A.val, beg, end, A.V, K, sub, kb, acc, own);
-        else
-            fm_walk<VEC, L, FM_WALK_SUM, MODE == MODE_REFRESH ? FM_ADDR_BUF : FM_ADDR_PTR, L < 4 ? 4 : L, 4>(
-                A.col, A.val, beg, end, A.V, K, sub, kb, 0, acc, unused, unused, own);
+        if constexpr (L >= FM_WIDE_GROUP) {
+            const float2* __restrict__ dwn = A.dwn;
+            fm_walk_wide<VEC, L>(A.col, A.val, beg, beg + len, A.V, K, sub, kb, acc, [&](int c, float x) {
+                const float2 d = dwn[c];
+                a_acc += d.x * x;
+                q_acc += d.y * (x * x);
+                return x;
+            });
+        } else {
+            OwnRefresh own{FmOwnArray<2>(reinterpret_cast<const float*>(A.dwn), 2), 0.f, 0.f};
+            float unused = 0.f;
+            fm_walk<VEC, L, FM_WALK_SUM, addr_of(MODE), L < 4 ? 4 : L, 4>(A.col, A.val, beg, len, A.V, K, sub, kb, acc, unused,
+                                                                          unused, own);
+            a_acc = own.a;
+            q_acc = own.q;
+        }
     }
     if (!kact) {  // idle lanes of a group wider than K/VEC worked on a valid but foreign slice
 #pragma unroll
@@ -107,7 +168,8 @@ __global__ __launch_bounds__(FM_BLOCK) void k_rows(const RowArgs A)
     }
 
     float l_i = 0.f, r_i = 0.f;
-    [[maybe_unused]] float yh_i = 0.f, y_i = 0.f;
+    [[maybe_unused]] float yh_i = 0.f;
+    const bool want = A.row_part != nullptr || A.eval_part != nullptr;
     if constexpr (!is_refresh(MODE)) {
         float pair = 0.f;
 #pragma unroll
@@ -121,11 +183,10 @@ __global__ __launch_bounds__(FM_BLOCK) void k_rows(const RowArgs A)
                 if (A.yhat != nullptr) A.yhat[row] = yh;
                 if (A.y != nullptr) {
                     yh_i = yh;
-                    y_i = A.y[row];
-                    loss_and_multiplier(A.loss, A.s, yh, y_i, l_i, r_i);
+                    loss_and_multiplier(A.loss, A.s, yh, y_i, want, l_i, r_i);
                 }
             }
-            if (A.G != nullptr && kact) fm_store_vec<VEC>(A.G + row * A.gs + kbase, acc);
+            if (A.G != nullptr && kact) fm_store_vec<VEC>(A.G + grow + kbase, acc);
             if (A.whole_rows) {
                 // packed aggregate rows: [r | a | q] and the padding behind G go out as float4 too, so
                 // that every 128-byte line of the row is written whole
@@ -138,13 +199,13 @@ __global__ __launch_bounds__(FM_BLOCK) void k_rows(const RowArgs A)
                             z[1] = a_i;
                             z[2] = q_i;
                         }
-                        fm_store_vec<4>(A.G + row * A.gs + K + 4 * t, z);
+                        fm_store_vec<4>(A.G + grow + K + 4 * t, z);
                     }
                 }
             } else if (sub == 0) {
-                if (A.a != nullptr) A.a[row * A.ss] = a_i;
-                if (A.q != nullptr) A.q[row * A.ss] = q_i;
-                if (A.y != nullptr && A.r != nullptr) A.r[row * A.ss] = r_i;
+                if (A.a != nullptr) A.a[srow] = a_i;
+                if (A.q != nullptr) A.q[srow] = q_i;
+                if (A.y != nullptr && A.r != nullptr) A.r[srow] = r_i;
             }
         }
     } else {
@@ -165,23 +226,23 @@ __global__ __launch_bounds__(FM_BLOCK) void k_rows(const RowArgs A)
             q_i = q_old + dq;
             const float yh = A.w0[0] + a_i + 0.5f * (pair - q_i);
             if (A.yhat != nullptr) A.yhat[row] = yh;
-            loss_and_multiplier(A.loss, A.s, yh, A.y[row], l_i, r_i);
+            loss_and_multiplier(A.loss, A.s, yh, y_i, want, l_i, r_i);
         }
         // All stores of a row together, so that its line is written back once.  The kernel is bound by its requests in
         // flight, so r, a, q of a packed row go out (and come in) as one float4 and not one by one: a stratum of the
         // click-style workload (1e7 rows, 64 strata) 311 -> 252 us, of the text-like one (5e4 rows, 32 strata) 8.9 -> 7.2.
         // The rest of the padding stays as the forward pass wrote it: the line was read and is in the L2 (with it 254 and
         // 9.1 us, with non-temporal stores 270 us).
-        if (touched && kact) fm_store_vec<VEC>(A.G + row * A.gs + kbase, g);
+        if (touched && kact) fm_store_vec<VEC>(A.G + grow + kbase, g);
         if (VEC == 4 && A.whole_rows) {
             if (touched && sub == 0) {
                 const float z[4] = {r_i, a_i, q_i, 0.f};
-                fm_store_vec<4>(A.G + row * A.gs + K, z);
+                fm_store_vec<4>(A.G + grow + K, z);
             }
         } else if (touched && sub == 0) {
-            A.r[row * A.ss] = r_i;
-            A.a[row * A.ss] = a_i;
-            A.q[row * A.ss] = q_i;
+            A.r[srow] = r_i;
+            A.a[srow] = a_i;
+            A.q[srow] = q_i;
         }
     }
 
@@ -229,18 +290,28 @@ int launch_rows_t(fm_matrix* m, const RowArgs& A, bool refresh, hipStream_t st)
     if (grid <= 0) return FM_OK;
     if (grid > 0x7fffffffLL) return fm_fail(m, FM_ERANGE, "row grid too large");
     ProfScope ps(m, st, refresh ? FMK_ROWS_REFRESH : FMK_ROWS_FORWARD);
-    constexpr int BIG = L < FM_WIDE_GROUP ? MODE_REFRESH_BIG : MODE_REFRESH;  // wide groups use 64-bit addresses throughout
-    if (refresh && A.big) {
-        hipLaunchKernelGGL((k_rows<VEC, L, BIG>), dim3((unsigned)grid), dim3(FM_BLOCK), 0, st, A);
-    } else if (refresh) {
-        hipLaunchKernelGGL((k_rows<VEC, L, MODE_REFRESH>), dim3((unsigned)grid), dim3(FM_BLOCK), 0, st, A);
-    } else if (A.Vh != nullptr) {
-        if constexpr (VEC == 4)
-            hipLaunchKernelGGL((k_rows<VEC, L, MODE_FORWARD_HALF>), dim3((unsigned)grid), dim3(FM_BLOCK), 0, st, A);
+    constexpr bool W = L >= FM_WIDE_GROUP;  // wide groups use 64-bit addresses throughout: one variant
+    auto launch = [&](auto mode) {
+        hipLaunchKernelGGL((k_rows<VEC, L, decltype(mode)::value>), dim3((unsigned)grid), dim3(FM_BLOCK), 0, st, A);
+    };
+    if (refresh) {
+        if (A.big)
+            launch(std::integral_constant<int, W ? MODE_REFRESH : MODE_REFRESH_BIG>());
         else
+            launch(std::integral_constant<int, MODE_REFRESH>());
+    } else if (A.Vh != nullptr) {
+        if constexpr (VEC == 4) {
+            if (A.big)
+                launch(std::integral_constant<int, W ? MODE_FORWARD_HALF : MODE_FORWARD_HALF_BIG>());
+            else
+                launch(std::integral_constant<int, MODE_FORWARD_HALF>());
+        } else {
             return fm_fail(m, FM_EINVAL, "half_gather needs K to be a multiple of 4");
+        }
+    } else if (A.big) {
+        launch(std::integral_constant<int, W ? MODE_FORWARD : MODE_FORWARD_BIG>());
     } else {
-        hipLaunchKernelGGL((k_rows<VEC, L, MODE_FORWARD>), dim3((unsigned)grid), dim3(FM_BLOCK), 0, st, A);
+        launch(std::integral_constant<int, MODE_FORWARD>());
     }
     FM_HIP(m, hipGetLastError());
     return FM_OK;
