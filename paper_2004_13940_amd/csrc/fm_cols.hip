@@ -272,7 +272,7 @@ __device__ __forceinline__ void store_partial(const ColArgs& A, int64_t it, int 
 // workload as much as its columns did.  Items come first: they are the longest runs.
 // With an order array, workgroup b takes its items from list b % FM_XCDS (the XCD it runs on).
 template <int VEC, int L, bool UPDATE, int PACKED>
-__global__ __launch_bounds__(FM_BLOCK) void k_cols(const ColArgs A)
+__global__ __launch_bounds__(FM_BLOCK, L >= FM_WIDE_GROUP ? 8 : 1) void k_cols(const ColArgs A)
 {
     constexpr int R = FM_WAVE / L;
     const int lane = threadIdx.x & (FM_WAVE - 1);

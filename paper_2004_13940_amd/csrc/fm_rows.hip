@@ -71,7 +71,7 @@ struct OwnRefresh {
 };
 
 template <int VEC, int L, int MODE>
-__global__ __launch_bounds__(FM_BLOCK) void k_rows(const RowArgs A)
+__global__ __launch_bounds__(FM_BLOCK, L >= FM_WIDE_GROUP && is_refresh(MODE) ? 8 : 1) void k_rows(const RowArgs A)
 {
     constexpr int R = FM_WAVE / L;  // rows per wavefront
     const int lane = threadIdx.x & (FM_WAVE - 1);
@@ -130,7 +130,7 @@ __global__ __launch_bounds__(FM_BLOCK) void k_rows(const RowArgs A)
         // rows that have no entry in this stratum keep their aggregates untouched
         touched = len > 0;  // uniform inside a group
         fm_load_vec<VEC>(A.G + grow + kb, g_old);
-        if (VEC == 4 && A.whole_rows) {  // [r | a | q | pad] of a packed row
+        if (L < FM_WIDE_GROUP && VEC == 4 && A.whole_rows) {  // [r | a | q | pad] of a packed row
             float z[4];
             fm_load_vec<4>(A.G + grow + K, z);
             a_old = z[1];
@@ -234,7 +234,7 @@ __global__ __launch_bounds__(FM_BLOCK) void k_rows(const RowArgs A)
         // The rest of the padding stays as the forward pass wrote it: the line was read and is in the L2 (with it 254 and
         // 9.1 us, with non-temporal stores 270 us).
         if (touched && kact) fm_store_vec<VEC>(A.G + grow + kbase, g);
-        if (VEC == 4 && A.whole_rows) {
+        if (L < FM_WIDE_GROUP && VEC == 4 && A.whole_rows) {
             if (touched && sub == 0) {
                 const float z[4] = {r_i, a_i, q_i, 0.f};
                 fm_store_vec<4>(A.G + grow + K, z);
