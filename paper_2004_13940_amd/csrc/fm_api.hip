@@ -554,11 +554,13 @@ static int ensure_ws(fm_matrix* m, int32_t K)
     const size_t D = (size_t)m->D;
     // fm_evaluate leaves three doubles per row block there: more than the aggregates of a single row with K <= 2 take
     FM_TRY(fm_dev_alloc(m, (void**)&m->aux, (size_t)std::max<int64_t>(fm_aux_floats(m, K), 6) * sizeof(float)));
+    // the dense kernels may be switched on and off: room for both paths
+    const int64_t chunks = fm_dense_fits(m, K) ? fm_dense_chunks(m->N, m->D, K) : 0;
     const int64_t items = std::max<int64_t>(std::max<int64_t>(m->lfull.nitems, m->lstrat.nitems),
-                                            std::max<int64_t>(m->lbatch.nitems, m->ldense.nitems));
+                                            std::max<int64_t>(m->lbatch.nitems, m->D * chunks));
     FM_TRY(fm_dev_alloc(m, (void**)&m->part,
                         (size_t)std::max<int64_t>(items, 1) * (size_t)fm_part_stride(K) * sizeof(float)));
-    FM_TRY(fm_dev_alloc(m, (void**)&m->row_part, (size_t)std::max<int64_t>(fm_rows_grid(m->N, K), 1) * 2 * sizeof(float)));
+    FM_TRY(fm_dev_alloc(m, (void**)&m->row_part, (size_t)std::max<int64_t>(std::max<int64_t>(fm_rows_grid(m->N, K), chunks), 1) * 2 * sizeof(float)));
     if (m->P > 0) {
         FM_TRY(fm_dev_alloc(m, (void**)&m->dV, D * K * sizeof(float)));
         FM_TRY(fm_dev_alloc(m, (void**)&m->dwn, D * sizeof(float2)));
@@ -640,11 +642,10 @@ static int half_copy(fm_matrix* m, const fm_params* p, const float* V, const _Fl
     return FM_OK;
 }
 
-// (loss, multiplier) pairs a forward pass over N rows leaves: one per row block of the sparse kernel, one per 32 rows
-// of the dense one
+// (loss, multiplier) pairs a forward pass over N rows leaves: one per workgroup
 static int64_t forward_pairs(const fm_matrix* m, const fm_params* p)
 {
-    return !p->half_gather && fm_dense_shape_ok(m, p->K) ? (m->N + 31) / 32 : fm_rows_grid(m->N, p->K);
+    return !p->half_gather && fm_dense_shape_ok(m, p->K) ? fm_dense_chunks(m->N, m->D, p->K) : fm_rows_grid(m->N, p->K);
 }
 
 // The sums over n pairs (or, single, n multipliers `stride` floats apart) as an epilogue.
@@ -671,11 +672,10 @@ static int read_objective(fm_matrix* m, const fm_params* p, double* objective, h
 }
 
 // mode 0: caller arrays (dense); 1: handle's aggregate rows, G and r; 2: handle's rows, G r a q
-static int run_forward(fm_matrix* m, const fm_params* p, const float* y, const float* w0, const float* w,
-                       const float* V, float* yhat, float* a, float* G, float* q, float* r, int mode, bool want_sums,
-                       hipStream_t st)
+static int forward_args(fm_matrix* m, const fm_params* p, const float* y, const float* w0, const float* w,
+                        const float* V, float* yhat, float* a, float* G, float* q, float* r, int mode, bool want_sums,
+                        RowArgs& A, hipStream_t st)
 {
-    RowArgs A;
     memset(&A, 0, sizeof(A));
     A.N = m->N;
     A.K = p->K;
@@ -705,6 +705,15 @@ static int run_forward(fm_matrix* m, const fm_params* p, const float* y, const f
     FM_TRY(half_copy(m, p, V, &A.Vh, st));
     const bool dense = A.Vh == nullptr && fm_dense_shape_ok(m, p->K);
     if (dense) A.dense_D = (int32_t)m->D;
+    return FM_OK;
+}
+
+static int run_forward(fm_matrix* m, const fm_params* p, const float* y, const float* w0, const float* w,
+                       const float* V, float* yhat, float* a, float* G, float* q, float* r, int mode, bool want_sums,
+                       hipStream_t st)
+{
+    RowArgs A;
+    FM_TRY(forward_args(m, p, y, w0, w, V, yhat, a, G, q, r, mode, want_sums, A, st));
     return fm_launch_rows(m, A, false, st);  // the pairs stay in m->row_part
 }
 
@@ -792,18 +801,35 @@ extern "C" int fm_evaluate(fm_matrix* m, const fm_params* p, const float* y, con
 
 // --------------------------------------------------------------- gradient ----
 
-// Work decomposition of a column pass over the whole matrix: the items of the CSC copy, or, for a matrix that
-// stores every column in every row, chunks of rows of the dense matrix.
-static void full_long(fm_matrix* m, const fm_params* p, ColArgs& A)
+// The column pass behind a dense one over nchunks workgroups: only the finish, of all columns.
+static void dense_long(const fm_matrix* m, int64_t nchunks, ColArgs& A)
 {
-    if (fm_dense_shape_ok(m, p->K) && m->ldense.long_col != nullptr) {
-        fill_long(m, A, m->ldense, 0, false);
-        A.X = m->val;
-        A.chunk_rows = m->dense_chunk_rows;
-        A.nchunks = m->dense_chunks;
-    } else {
-        fill_long(m, A, m->lfull, 0, false);
-    }
+    A.nchunks = nchunks;
+    A.nlong = m->D;
+    A.nvlong = nchunks > m->tune.vlong ? m->D : 0;  // a workgroup per column, or a wavefront
+    A.vlong_items = m->tune.vlong;
+}
+
+// The data sums of all columns of a dense matrix from r and G of A, and A.epi's sums beside them.
+static int dense_sums(fm_matrix* m, ColArgs& A, hipStream_t st)
+{
+    DenseArgs X;
+    memset(&X, 0, sizeof(X));
+    X.N = m->N;
+    X.D = m->D;
+    X.K = A.K;
+    X.nchunks = fm_dense_chunks(m->N, m->D, A.K);
+    X.X = m->val;
+    X.G = const_cast<float*>(A.G);
+    X.r = const_cast<float*>(A.r);
+    X.gs = A.gs;
+    X.ss = A.rs;
+    X.part = A.part;
+    X.ps = A.ps;
+    X.epi = A.epi;
+    FM_TRY(fm_launch_dense(m, X, FM_DENSE_GRADIENT, st));
+    dense_long(m, X.nchunks, A);
+    return FM_OK;
 }
 
 static void base_col_args(fm_matrix* m, const fm_params* p, ColArgs& A)
@@ -867,11 +893,27 @@ extern "C" int fm_gradient(fm_matrix* m, const fm_params* p, const float* r, con
     A.V = const_cast<float*>(V);
     A.grad_w = grad_w;
     A.grad_V = grad_V;
-    full_long(m, p, A);
+    if (fm_dense_shape_ok(m, p->K) && m->N > 0)
+        FM_TRY(dense_sums(m, A, st));
+    else
+        fill_long(m, A, m->lfull, 0, false);
     return fm_launch_cols(m, A, false, st);
 }
 
 // ------------------------------------------------------------ full epoch ----
+
+// Forward and data sums of a dense pass over the rows of R in one kernel; A then has only the finish left.
+static int dense_step(fm_matrix* m, const RowArgs& R, bool regs, ColArgs& A, hipStream_t st)
+{
+    DenseArgs X;
+    fm_dense_rows(R, &X);
+    X.part = A.part;
+    X.ps = A.ps;
+    X.regs = regs ? fm_reg_scratch(m) : nullptr;
+    FM_TRY(fm_launch_dense(m, X, FM_DENSE_FORWARD | FM_DENSE_GRADIENT, st));
+    dense_long(m, X.nchunks, A);
+    return FM_OK;
+}
 
 extern "C" int fm_sgd_epoch(fm_matrix* m, const fm_params* p, const float* y, float* w0, float* w, float* V,
                             double* objective, void* hip_stream)
@@ -889,8 +931,11 @@ extern "C" int fm_sgd_epoch(fm_matrix* m, const fm_params* p, const float* y, fl
         return FM_OK;
     }
     // steps 1-3: G, r, loss and sum r
-    FM_TRY(run_forward(m, p, y, w0, w, V, nullptr, nullptr, nullptr, nullptr, nullptr, 1, true, st));
+    RowArgs R;
+    FM_TRY(forward_args(m, p, y, w0, w, V, nullptr, nullptr, nullptr, nullptr, nullptr, 1, true, R, st));
     m->aux_full = false;
+    const bool dense = R.dense_D > 0;  // then the data sums of step 4 come with them
+    if (!dense) FM_TRY(fm_launch_rows(m, R, false, st));
     // steps 4-5 fused: gradient of every column and the step on w, V
     ColArgs A;
     base_col_args(m, p, A);
@@ -905,16 +950,25 @@ extern "C" int fm_sgd_epoch(fm_matrix* m, const fm_params* p, const float* y, fl
     A.packed = fm_cols_packed_mode(m, p->K);
     A.w = w;
     A.V = V;
-    full_long(m, p, A);
+    const bool half = R.Vh != nullptr && fm_dense_shape_ok(m, p->K);  // half-precision scores of a dense matrix
+    if (!dense && !half) fill_long(m, A, m->lfull, 0, false);
     if (p->update_w0 || objective != nullptr) {
         set_epilogue(m, A.epi, m->row_part, forward_pairs(m, p), 0, false);
+        if (dense) A.epi.nsums = 0;  // the pairs of this very launch: the finish adds them
         if (p->update_w0) A.epi.w0 = w0;
         A.epi.eta = p->eta;
         if (objective != nullptr) {  // regulariser at the parameters the epoch starts from
-            FM_TRY(fm_reg_partials(m, w, m->D, V, m->D * (int64_t)p->K, &A.epi.regs, &A.epi.nregs, st));
+            if (dense) {
+                A.epi.regs = fm_reg_scratch(m);
+                A.epi.nregs = 1;
+            } else {
+                FM_TRY(fm_reg_partials(m, w, m->D, V, m->D * (int64_t)p->K, &A.epi.regs, &A.epi.nregs, st));
+            }
             A.epi.host = m->h_scal;
         }
     }
+    if (dense) FM_TRY(dense_step(m, R, objective != nullptr, A, st));
+    if (half) FM_TRY(dense_sums(m, A, st));
     FM_TRY(fm_launch_cols(m, A, true, st));
     return objective != nullptr ? read_objective(m, p, objective, st) : FM_OK;
 }
@@ -1195,8 +1249,9 @@ extern "C" int fm_minibatch_epoch(fm_matrix* m, const fm_params* p, const float*
     };
     for (int32_t b = 0; b < m->B; ++b) {
         const int64_t r0 = m->h_bb[b], nb = m->h_bb[b + 1] - r0;
+        RowArgs R;
+        bool dense = false;
         if (nb > 0) {  // steps 1-3 on the rows of the batch, at the parameters as they stand
-            RowArgs R;
             memset(&R, 0, sizeof(R));
             R.N = nb;
             R.K = p->K;
@@ -1217,7 +1272,13 @@ extern "C" int fm_minibatch_epoch(fm_matrix* m, const fm_params* p, const float*
             R.loss = p->loss;
             R.s = p->loss_scale;
             FM_TRY(half_copy(m, p, V, &R.Vh, st));  // the factors as they stand
-            FM_TRY(fm_launch_rows(m, R, false, st));
+            dense = R.Vh == nullptr && fm_dense_shape_ok(m, p->K);
+            if (dense) {
+                R.dense_D = (int32_t)m->D;
+                R.val = m->val + r0 * m->D;
+            } else {
+                FM_TRY(fm_launch_rows(m, R, false, st));
+            }
         }
         // steps 4-5 over the batch's rows: gradient and step of every column that has entries there
         ColArgs A;
@@ -1231,12 +1292,14 @@ extern "C" int fm_minibatch_epoch(fm_matrix* m, const fm_params* p, const float*
         A.gs = x.gs;
         A.rs = x.ss;
         A.packed = fm_cols_packed_mode(m, p->K);
-        fill_long(m, A, m->lbatch, b, true);
+        if (!dense) fill_long(m, A, m->lbatch, b, true);
         if (p->update_w0 && nb > 0) {
-            set_epilogue(m, A.epi, m->row_part, fm_rows_grid(nb, p->K), 0, false);
+            set_epilogue(m, A.epi, m->row_part, dense ? fm_dense_chunks(nb, m->D, p->K) : fm_rows_grid(nb, p->K), 0, false);
+            if (dense) A.epi.nsums = 0;
             A.epi.w0 = w0;
             A.epi.eta = p->eta;
         }
+        if (dense) FM_TRY(dense_step(m, R, false, A, st));
         FM_TRY(fm_launch_cols(m, A, true, st));
     }
     if (lazy) {

@@ -633,11 +633,14 @@ __global__ __launch_bounds__(FM_BLOCK) void k_cols_finish(const ColArgs A)
     }
     int64_t lc, j;
     ColState<VEC> c;  // asked for ahead of the partial sums
+    const bool dense = A.nchunks > 0;  // every column has the same number of items
     if (b < A.nvlong) {
-        lc = A.vlong[b];
-        j = A.long_col[lc];
+        lc = dense ? b : A.vlong[b];
+        const int64_t first = dense ? lc * A.nchunks : A.long_first[lc];
+        const int64_t last = dense ? first + A.nchunks : A.long_first[lc + 1];
+        j = dense ? lc : A.long_col[lc];
         c = load_column<VEC, UPDATE>(A, j, kbase, kact);
-        add_partials<VEC>(A, A.long_first[lc] + threadIdx.x / L, A.long_first[lc + 1], NG, kbase, kact, acc, gw, s2);
+        add_partials<VEC>(A, first + threadIdx.x / L, last, NG, kbase, kact, acc, gw, s2);
         add_groups<VEC, L>(acc, gw, s2);
         double* mine = sh + wave * S;
         if (lane < L) {
@@ -661,9 +664,10 @@ __global__ __launch_bounds__(FM_BLOCK) void k_cols_finish(const ColArgs A)
         const int64_t rel = (b - A.nvlong) * FM_WAVES + wave;
         if (rel >= A.nlong) return;  // whole wavefront leaves together
         lc = A.long_base + rel;
-        const int64_t first = A.long_first[lc], last = A.long_first[lc + 1];
+        const int64_t first = dense ? lc * A.nchunks : A.long_first[lc];
+        const int64_t last = dense ? first + A.nchunks : A.long_first[lc + 1];
         if (A.nvlong > 0 && last - first > A.vlong_items) return;
-        j = A.long_col[lc];
+        j = dense ? lc : A.long_col[lc];
         c = load_column<VEC, UPDATE>(A, j, kbase, kact);
         add_partials<VEC>(A, first + lane / L, last, R, kbase, kact, acc, gw, s2);
         add_groups<VEC, L>(acc, gw, s2);
@@ -798,11 +802,7 @@ int launch_cols_t(fm_matrix* m, const ColArgs& A, bool update, hipStream_t st)
         (A.lambda_w != 0.f || A.lambda_v != 0.f || !update || A.dV != nullptr) && A.lazy_last == nullptr;
     ColArgs Am = A;
     if (!need_empty || A.ptr != nullptr) Am.mark = nullptr;  // marks are only set when a kernel will clear them
-    const bool dense = A.X != nullptr;  // one kernel leaves the partial sums of every column
-    if (dense) {
-        ProfScope ps(m, st, FMK_COLS_LONG);
-        FM_TRY(fm_launch_cols_dense(m, A, st));
-    } else {
+    if (A.nchunks == 0) {  // else a dense pass has left the partial sums of every column
         // LDS-staged items go to a side stream, so that the LDS-bound kernel overlaps the memory-bound one (not while
         // per-kernel timing is on: each kernel is then timed alone on the launch stream)
         hipStream_t s_tile = st;

@@ -17,318 +17,446 @@ namespace {
 
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 
-constexpr int DT = 32;  // rows (forward) or columns (gradient) per tile
-constexpr int FM_DENSE_TILES = 8;      // 32-row tiles per wavefront of the forward kernel
-constexpr int FM_DENSE_CHUNKS = 4096;  // row chunks (one wavefront each) of the column kernel
+constexpr int DT = 32;  // rows, columns and latent dimensions per tile
+constexpr int FM_DENSE_MAX = 2 * DT;    // largest D and K of these kernels
+constexpr int FM_DENSE_TILES = 8;   // 32-row tiles to a sum in fp32 before it is added to those of the tiles before
+constexpr int FM_DENSE_CUS = 256;   // compute units
+// Workgroups that a compute unit holds: by registers, and by LDS where D and K take two tiles.
+constexpr int dense_per_cu(int db, int kb) { return db + kb > 3 ? 2 : db + kb > 2 ? 3 : 4; }
 
-__device__ __forceinline__ int c_row(int v, int lane) { return 8 * (v / 4) + 4 * (lane / 32) + (v % 4); }
+__device__ __forceinline__ int c_row(int v, int half) { return 8 * (v / 4) + 4 * half + (v % 4); }
 
-// Forward pass over 32 rows per wavefront.  DB = D / 32, KB = K / 32.
-// LDS: w (D floats), squared row norms of V (D floats), then one tile of 32 x S floats per wavefront,
-// S = max(D, K) + 1 (odd: the column-wise reads of the tile spread over the banks).
-template <int DB, int KB>
-__global__ __launch_bounds__(FM_BLOCK) void k_rows_dense(const RowArgs A)
+// What a lane of the wavefront wrote to LDS is there for its other lanes: the LDS takes a wavefront's accesses in order,
+// the compiler has to keep them so.
+__device__ __forceinline__ void wave_sync()
 {
-    constexpr int D = DB * DT, K = KB * DT;
-    constexpr int S = (D > K ? D : K) + 1;
-    extern __shared__ float lds[];
-    float* __restrict__ wl = lds;
-    float* __restrict__ nvl = lds + D;
-    const int lane = threadIdx.x & (FM_WAVE - 1);
-    const int wave = threadIdx.x / FM_WAVE;
-    float* __restrict__ tile = lds + 2 * D + wave * (DT * S);
-    for (int j = threadIdx.x; j < D; j += FM_BLOCK) {
-        wl[j] = A.w[j];
-        float n2 = 0.f;
-        for (int k = 0; k < K; ++k) {
-            const float v = A.V[(int64_t)j * K + k];
-            n2 += v * v;
-        }
-        nvl[j] = n2;
-    }
-    __syncthreads();
-    const int half = lane / 32, lo = lane % 32;
-    // B operands: V[2t + half][kb * 32 + lo] for every step t
-    float vb[KB][D / 2];
-#pragma unroll
-    for (int kb = 0; kb < KB; ++kb)
-#pragma unroll
-        for (int t = 0; t < D / 2; ++t) vb[kb][t] = A.V[(int64_t)(2 * t + half) * K + kb * DT + lo];
-
-    // A wavefront takes FM_DENSE_TILES consecutive 32-row tiles, so that its share of V is loaded once for all of
-    // them.  A tile's rows are contiguous in memory: coalesced float4 loads (rows past the end are zero), issued one
-    // tile ahead so that they are in flight while the tile before is worked on.
-    constexpr int NC = DT * (D / 4) / FM_WAVE;  // float4 per lane and tile
-    const int64_t tile0 = ((int64_t)blockIdx.x * FM_WAVES + wave) * FM_DENSE_TILES;
-    float4 xr[NC];
-    auto load_tile = [&](int64_t t) {
-        const int64_t r0 = t * DT;
-        const int64_t left = A.N - r0;
-        const int n4 = left <= 0 ? 0 : (int)((left < DT ? left : DT) * (D / 4));
-        const float4* __restrict__ src = reinterpret_cast<const float4*>(A.val + (left <= 0 ? 0 : r0 * D));
-#pragma unroll
-        for (int i = 0; i < NC; ++i) {
-            const int c = lane + i * FM_WAVE;
-            xr[i] = c < n4 ? src[c] : make_float4(0.f, 0.f, 0.f, 0.f);
-        }
-    };
-    load_tile(tile0);
-#pragma unroll 1
-    for (int tt = 0; tt < FM_DENSE_TILES; ++tt) {
-    const int64_t tid = tile0 + tt;
-    const int64_t row0 = tid * DT;
-    if (row0 >= A.N) return;  // whole wavefronts leave; no barrier follows
-    const int nrows = (int)((A.N - row0) < DT ? (A.N - row0) : DT);
-#pragma unroll
-    for (int i = 0; i < NC; ++i) {
-        const int c = lane + i * FM_WAVE;
-        const int r = c / (D / 4), k = (c % (D / 4)) * 4;
-        float* d = tile + r * S + k;
-        d[0] = xr[i].x;
-        d[1] = xr[i].y;
-        d[2] = xr[i].z;
-        d[3] = xr[i].w;
-    }
-    if (tt + 1 < FM_DENSE_TILES) load_tile(tid + 1);
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
-    f32x16 acc[KB];
-#pragma unroll
-    for (int kb = 0; kb < KB; ++kb)
-#pragma unroll
-        for (int v = 0; v < 16; ++v) acc[kb][v] = 0.f;
-    float a_part = 0.f, q_part = 0.f;  // this lane: row lo, columns of parity `half`
-#pragma unroll
-    for (int t = 0; t < D / 2; ++t) {
-        const int k = 2 * t + half;
-        const float x = tile[lo * S + k];
-        a_part += x * wl[k];
-        q_part += (x * x) * nvl[k];
-#pragma unroll
-        for (int kb = 0; kb < KB; ++kb) acc[kb] = __builtin_amdgcn_mfma_f32_32x32x2f32(x, vb[kb][t], acc[kb], 0, 0, 0);
-    }
-    __builtin_amdgcn_wave_barrier();
-    // G tile into LDS (the X tile is no longer needed)
-#pragma unroll
-    for (int kb = 0; kb < KB; ++kb)
-#pragma unroll
-        for (int v = 0; v < 16; ++v) tile[c_row(v, lane) * S + kb * DT + lo] = acc[kb][v];
-    __builtin_amdgcn_wave_barrier();
-    float pair = 0.f;
-#pragma unroll
-    for (int k = 0; k < K / 2; ++k) {
-        const float g = tile[lo * S + half * (K / 2) + k];
-        pair += g * g;
-    }
-    const float a_i = a_part + __shfl_xor(a_part, 32, FM_WAVE);
-    const float q_i = q_part + __shfl_xor(q_part, 32, FM_WAVE);
-    pair += __shfl_xor(pair, 32, FM_WAVE);
-    float l_i = 0.f, r_i = 0.f, yh = 0.f, y_i = 0.f;
-    if (half == 0 && lo < nrows) {
-        const int64_t row = row0 + lo;
-        yh = A.w0[0] + a_i + 0.5f * (pair - q_i);
-        if (A.yhat != nullptr) A.yhat[row] = yh;
-        if (A.y != nullptr) {
-            y_i = A.y[row];
-            loss_and_multiplier(A.loss, A.s, yh, y_i, A.row_part != nullptr || A.eval_part != nullptr, l_i, r_i);
-        }
-        if (A.a != nullptr) A.a[row * A.ss] = a_i;
-        if (A.q != nullptr) A.q[row * A.ss] = q_i;
-        if (A.y != nullptr && A.r != nullptr) A.r[row * A.ss] = r_i;
-    }
-    if (A.G != nullptr) {
-        for (int c = lane; c < nrows * (K / 4); c += FM_WAVE) {
-            const int r = c / (K / 4), k = (c % (K / 4)) * 4;
-            const float* s = tile + r * S + k;
-            *reinterpret_cast<float4*>(A.G + (row0 + r) * A.gs + k) = make_float4(s[0], s[1], s[2], s[3]);
-        }
-    }
-    if (A.row_part != nullptr) {  // one pair per 32-row tile, lanes added in a fixed order
-        const float ls = fm_wave_sum(l_i);
-        const float rs = fm_wave_sum(r_i);
-        if (lane == 0) {
-            A.row_part[2 * tid] = ls;
-            A.row_part[2 * tid + 1] = rs;
-        }
-    }
-    if (A.eval_part != nullptr) fm_eval_wave(half == 0 && lo < nrows, yh, y_i, l_i, lane, A.eval_part + 3 * tid);
-    __builtin_amdgcn_wave_barrier();  // the next tile overwrites the LDS tile
-    }  // tiles of this wavefront
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// Partial sums of every column over one chunk of rows per wavefront: for column j and latent k
-//   acc = sum_i x_ij r_i G_ik,  gw = sum_i x_ij r_i,  s2 = sum_i x_ij^2 r_i      (eqs. updates_w, updates_v),
-// two rows per matrix-core step (row parity = the contraction index).  Stored as the row
-// [acc | gw | s2] of item j * nchunks + c, which the finish kernels add in fp64 in item order.  The first epi.nsums
-// workgroups, if epi.on, add up the examples instead, as in k_cols; as launches of their own between this kernel and the
-// finish they took 13 us of the 216 us of a full-gradient epoch of 1e6 x 64, K=32 (two launches on the critical path).
-template <int DB, int KB>
-__global__ __launch_bounds__(FM_BLOCK) void k_cols_dense(const ColArgs A)
+// s[v] of lane l: a term of row c_row(v, l / 32).  Returns the sum over the 32 lanes of a half for row
+// c_row(l % 32 / 2, l / 32): every exchange halves the registers a lane answers for.
+__device__ __forceinline__ float row_sums(float (&s)[16], int lo)
 {
-    constexpr int D = DB * DT, K = KB * DT;
-    const int sums = A.epi.on ? A.epi.nsums : 0;
-    if ((int)blockIdx.x < sums) {
-        __shared__ double sh[FM_WAVES];
-        fm_epi_partial<FM_BLOCK>(A.epi, (int)blockIdx.x, sh);
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+        const bool up = lo & 16;
+        const float keep = up ? s[i + 8] : s[i], send = up ? s[i] : s[i + 8];
+        s[i] = keep + fm_xor_lane<16>(send);
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const bool up = lo & 8;
+        const float keep = up ? s[i + 4] : s[i], send = up ? s[i] : s[i + 4];
+        s[i] = keep + fm_xor_lane<8>(send);
+    }
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        const bool up = lo & 4;
+        const float keep = up ? s[i + 2] : s[i], send = up ? s[i] : s[i + 2];
+        s[i] = keep + fm_xor_lane<4>(send);
+    }
+    const bool up = lo & 2;
+    const float keep = up ? s[1] : s[0], send = up ? s[0] : s[1];
+    const float t = keep + fm_xor_lane<2>(send);
+    return t + fm_xor_lane<1>(t);
+}
+
+// One pass over the rows of X.  DB, KB: tiles that D and K take (what is missing to a whole tile is zero).
+//   FM_DENSE_FORWARD   aggregates, prediction, loss and multiplier of every row
+//   FM_DENSE_GRADIENT  per workgroup and column the partial sums acc = sum_i x_ij r_i G_ik, gw = sum_i x_ij r_i,
+//                      s2 = sum_i x_ij^2 r_i (eqs. updates_w, updates_v), as the row [acc | gw | s2 | pad] of item
+//                      j * nchunks + workgroup, which the finish kernel adds in fp64 in item order
+//   both               an epoch: X is read once, and the tile of G goes from one product into the other in registers
+// A wavefront takes up to FM_DENSE_TILES tiles of 32 consecutive rows, a workgroup four times as many.  A tile of X is
+// staged in LDS with an odd row stride, read by columns for the first product (A operand: 32 rows, two columns a step) and
+// by rows for the second (A operand: 32 columns, two rows a step).  The rows of a step of the second product are paired
+// as the result registers of the first hold them (rows c_row(v, 0) and c_row(v, 1)), so that register v, times r, is its
+// B operand as it stands.  Bound: 1e6 rows, D = 64, K = 32 are 392 MB of X, G, y and r (71 us at the rate of a copy) and
+// 60 us of matrix instructions, with vector instructions for a third of the issue slots beside them; it takes 112 us, the
+// epoch 120 where a forward and a column kernel that each read X took 204.  D = 45, K = 8: 123 us, 500 through the sparse
+// kernels.  X by float4 although they meet banks of the LDS four to one on the way in: 137 us, float by float 149.  The
+// operands from V are read from LDS: in registers they cost the third wavefront of a SIMD.
+// LDS of a wavefront: its tile of X, then r, a, q of the tile's rows and as many zeros.
+template <int DB>
+struct DenseLds {
+    static constexpr int S = DB * DT + 1;  // odd row stride: columns of the tile spread over the banks
+    static constexpr int R = DT * S, A = R + DT, Q = A + DT, Z = Q + DT, FLOATS = Z + DT;
+};
+
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t fm_rsrc(const float* p, int64_t bytes)
+{
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(p), 0, (int)bytes, 0x20000);
+}
+
+template <int DB, int KB, int WHAT>
+__global__ __launch_bounds__(FM_BLOCK, dense_per_cu(DB, KB)) void k_dense(const DenseArgs A)
+{
+    constexpr bool FORWARD = WHAT & FM_DENSE_FORWARD, GRADIENT = WHAT & FM_DENSE_GRADIENT;
+    constexpr int DP = DB * DT, KP = KB * DT;
+    using Lds = DenseLds<DB>;
+    constexpr int S = Lds::S;
+    extern __shared__ float lds[];
+    __shared__ double sh[FM_WAVES * 4];
+    const int64_t b = blockIdx.x;
+    if (b >= A.nchunks) {  // the workgroups behind the chunks: sums that depend on nothing here
+        if (A.epi.on)
+            fm_epi_partial<FM_BLOCK>(A.epi, (int)(b - A.nchunks), sh);
+        else
+            fm_reg_pair<FM_BLOCK>(A.w, A.D, A.V, A.D * (int64_t)A.K, A.regs, sh);
         return;
     }
+    const int D = (int)A.D, K = A.K, gs = (int)A.gs;
     const int lane = threadIdx.x & (FM_WAVE - 1);
-    const int wave = threadIdx.x / FM_WAVE;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / FM_WAVE);  // uniform, and so is all that follows from it
     const int half = lane / 32, lo = lane % 32;
-    const int64_t c = (int64_t)(blockIdx.x - sums) * FM_WAVES + wave;
-    if (c >= A.nchunks) return;
-    const int64_t beg = c * A.chunk_rows;
-    const int64_t end = (beg + A.chunk_rows) < A.N ? (beg + A.chunk_rows) : A.N;
-    f32x16 acc[DB][KB];
+    const int64_t tiles = (A.N + DT - 1) / DT, parts = A.nchunks * FM_WAVES, part = b * FM_WAVES + wave;
+    const int64_t t0 = part * tiles / parts, t1 = (part + 1) * tiles / parts;
+    // A tile's rows are contiguous in memory.  Whole float4 up to its last value: the entries are padded for the rest of the
+    // last one.  Loaded a tile ahead.
+    constexpr int NC = DT * DP / 4 / FM_WAVE;
+    float x[NC][4];
+    float row_in = 0.f;                     // label, or multiplier, of row lo of the tile
+    [[maybe_unused]] float g_in[KB][16];    // gradient alone: its tile of G
+    const float* __restrict__ row_src = FORWARD ? A.y : A.r;
+    const int64_t row_stride = FORWARD ? 1 : A.ss;
+    auto load_tile = [&](int64_t t, int ln) {
+        const int64_t left = (A.N - t * DT) * D;
+        const __amdgpu_buffer_rsrc_t xs = t < t1 ? fm_rsrc(A.X + t * DT * D, ((left < DT * D ? left : DT * D) + 3) / 4 * 16) : fm_rsrc(A.X, 0);
 #pragma unroll
-    for (int jb = 0; jb < DB; ++jb)
+        for (int i = 0; i < NC; ++i) fm_buf_load<4, false>(xs, (uint32_t)(ln + i * FM_WAVE) * 16u, x[i]);
+        const int64_t row = t * DT + ln % DT;
+        if (row_src != nullptr) row_in = row < A.N ? row_src[row * row_stride] : 0.f;
+        if constexpr (!FORWARD) {
+            const int64_t rest = (A.N - t * DT) * A.gs;
+            const __amdgpu_buffer_rsrc_t gr =
+                t < t1 ? fm_rsrc(A.G + t * DT * A.gs, (rest < DT * A.gs ? rest : DT * A.gs) * 4) : fm_rsrc(A.G, 0);
 #pragma unroll
-        for (int kb = 0; kb < KB; ++kb)
+            for (int kb = 0; kb < KB; ++kb) {
+                const int k = kb * DT + ln % DT;
+                const uint32_t at = k < A.K ? (uint32_t)(ln / DT * 4 * (int)A.gs + k) * 4u : FM_BUF_NONE;
 #pragma unroll
-            for (int v = 0; v < 16; ++v) acc[jb][kb][v] = 0.f;
-    float gw[DB], s2[DB];
+                for (int v = 0; v < 16; ++v)
+                    g_in[kb][v] = __int_as_float(__builtin_amdgcn_raw_buffer_load_b32(gr, (int)at, c_row(v, 0) * (int)A.gs * 4, 0));
+            }
+        }
+    };
+    load_tile(t0, lane);
+    float2* wn = reinterpret_cast<float2*>(lds);  // [DP] (w_j, |v_j|^2)
+    float* vl = lds + 2 * DP;                     // [DP x KP] V, padded with zeros
+    float* area = lds + (FORWARD ? 2 * DP + DP * KP : 0);
+    float* tile = area + wave * Lds::FLOATS;
+    if constexpr (FORWARD) {
+        for (int e = threadIdx.x; e < DP * KP; e += FM_BLOCK) {
+            const int j = e / KP, k = e % KP;
+            vl[e] = j < D && k < K ? A.V[j * K + k] : 0.f;
+        }
+        __syncthreads();
+        static_assert(FM_BLOCK / DP >= 4, "four threads to a column");
+        const int j = threadIdx.x / 4, p = threadIdx.x % 4;
+        float n2 = 0.f;
+        if (j < DP)
+            for (int k = p; k < KP; k += 4) n2 += vl[j * KP + k] * vl[j * KP + k];
+        n2 = fm_group_sum<4>(n2);
+        if (p == 0 && j < DP) wn[j] = make_float2(j < D ? A.w[j] : 0.f, n2);
+        __syncthreads();
+    }
+    for (int j = D + half; j < DP; j += 2) tile[lo * S + j] = 0.f;  // the columns past D stay zero
+    if (half == 0) tile[Lds::Z + lo] = 0.f;
+    // where this lane finds what it stores behind G in a packed row [G | r | a | q | pad]
+    [[maybe_unused]] const float* behind = tile + (lo == K ? Lds::R : lo == K + 1 ? Lds::A : lo == K + 2 ? Lds::Q : Lds::Z);
+    [[maybe_unused]] f32x16 acc[DB][KB], all[DB][KB];  // of up to FM_DENSE_TILES tiles, of the tiles before them
+    [[maybe_unused]] float gw[DB], s2[DB], all_gw[DB], all_s2[DB];
+    auto add_up = [&](bool clear) {
 #pragma unroll
-    for (int jb = 0; jb < DB; ++jb) gw[jb] = s2[jb] = 0.f;
-    constexpr int U = 4;  // row pairs whose loads are issued together
-    for (int64_t r0 = beg; r0 < end; r0 += 2 * U) {
-        float x[U][DB], g[U][KB], rr[U];
+        for (int jb = 0; jb < DB; ++jb) {
+            all_gw[jb] = clear ? 0.f : all_gw[jb] + gw[jb];
+            all_s2[jb] = clear ? 0.f : all_s2[jb] + s2[jb];
+            gw[jb] = s2[jb] = 0.f;
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int64_t row = r0 + 2 * u + half;
-            const bool ok = row < end;
-            const int64_t rc = ok ? row : beg;  // a valid row; its contribution is zeroed below
-            rr[u] = ok ? A.r[rc * A.rs] : 0.f;
+            for (int kb = 0; kb < KB; ++kb)
 #pragma unroll
-            for (int jb = 0; jb < DB; ++jb) x[u][jb] = ok ? A.X[rc * D + jb * DT + lo] : 0.f;
+                for (int v = 0; v < 16; ++v) {
+                    all[jb][kb][v] = clear ? 0.f : all[jb][kb][v] + acc[jb][kb][v];
+                    acc[jb][kb][v] = 0.f;
+                }
+        }
+    };
+    if constexpr (GRADIENT) add_up(true);
+    [[maybe_unused]] double sums[4] = {0.0, 0.0, 0.0, 0.0};  // loss, r, squared error, correct signs
+    const float w0 = FORWARD ? A.w0[0] : 0.f;
+    const bool want = A.row_part != nullptr || A.eval_part != nullptr;
+    const uint32_t magic = ((1u << 20) + (uint32_t)D - 1) / (uint32_t)D;  // e / D = e magic >> 20 for e < 2^12, D <= 64
+#pragma unroll 1
+    for (int64_t tid = t0; tid < t1; ++tid) {
+        if (GRADIENT && tid > t0 && (tid - t0) % FM_DENSE_TILES == 0) add_up(false);
+        const int64_t row0 = tid * DT;
+        const int nrows = (int)((A.N - row0) < DT ? (A.N - row0) : DT);
+        // The lane's number as a value of this turn of the loop: what is derived from it (addresses in LDS, w and |v|^2 read
+        // from there) is formed anew and not kept in a hundred registers for the next turn.
+        int ln = lane;
+        asm volatile("" : "+v"(ln));
+        const int half_t = ln / 32;
+        wave_sync();  // the tile before has been read
+        if (nrows < DT) {
 #pragma unroll
-            for (int kb = 0; kb < KB; ++kb) g[u][kb] = ok ? A.G[rc * A.gs + kb * DT + lo] : 0.f;
+            for (int i = 0; i < NC; ++i)
+#pragma unroll
+                for (int z = 0; z < 4; ++z)
+                    if ((ln + i * FM_WAVE) * 4 + z >= nrows * D) x[i][z] = 0.f;
         }
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
+        for (int i = 0; i < NC; ++i) {
+            const uint32_t e = (uint32_t)(ln + i * FM_WAVE) * 4;
+            if (D == DP) {
+                float* d = tile + e / DP * S + e % DP;
 #pragma unroll
-            for (int kb = 0; kb < KB; ++kb) g[u][kb] *= rr[u];
+                for (int z = 0; z < 4; ++z) d[z] = x[i][z];
+            } else {
+#pragma unroll
+                for (int z = 0; z < 4; ++z) {
+                    const uint32_t row = ((e + z) * magic) >> 20;
+                    if (e < (uint32_t)(DT * D)) tile[e + z + row * (uint32_t)(S - D)] = x[i][z];
+                }
+            }
+            __builtin_amdgcn_sched_barrier(0);  // few addresses at a time: registers
+        }
+        const float r_in = row_in;
+        [[maybe_unused]] float g_now[KB][16];
+        if constexpr (!FORWARD) {
+#pragma unroll
+            for (int kb = 0; kb < KB; ++kb)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) g_now[kb][v] = g_in[kb][v];
+        }
+        load_tile(tid + 1, ln);
+        f32x16 g[KB];
+        if constexpr (FORWARD) {
+            const __amdgpu_buffer_rsrc_t rows =
+                fm_rsrc(A.G != nullptr ? A.G + row0 * gs : A.X, A.G != nullptr ? (int64_t)nrows * gs * 4 : 0);
+            const int64_t mine = row0 + (lo < nrows ? lo : 0);
+            const float y_i = r_in;
+            wave_sync();
+#pragma unroll
+            for (int kb = 0; kb < KB; ++kb)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) g[kb][v] = 0.f;
+            float a_i = 0.f, q_i = 0.f;  // this lane: row lo, columns of parity `half`
+#pragma unroll
+            for (int t = 0; t < DP / 2; ++t) {
+                const float xt = tile[lo * S + 2 * t + half];
+                const float2 c = wn[2 * t + half_t];
+                const float* v = vl + (2 * t + half_t) * KP + lo;  // B operand: V[2t + half][kb * 32 + lo]
+                a_i += xt * c.x;
+                q_i += (xt * xt) * c.y;
+#pragma unroll
+                for (int kb = 0; kb < KB; ++kb) g[kb] = __builtin_amdgcn_mfma_f32_32x32x2f32(xt, v[kb * DT], g[kb], 0, 0, 0);
+                if (t % 8 == 7) {  // what was read so far is used up here, or it would be kept for the end of the loop
+                    asm volatile("" : "+v"(a_i), "+v"(q_i));
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+            }
+            float s[16];
+#pragma unroll
+            for (int v = 0; v < 16; ++v) {
+                s[v] = 0.f;
+#pragma unroll
+                for (int kb = 0; kb < KB; ++kb) s[v] += g[kb][v] * g[kb][v];
+            }
+            const float pair = row_sums(s, lo);
+            if ((lo & 1) == 0) tile[Lds::A + c_row(lo / 2, half)] = pair;
+            a_i += fm_xor_lane<32>(a_i);
+            q_i += fm_xor_lane<32>(q_i);
+            wave_sync();
+            const float yh = w0 + a_i + 0.5f * (tile[Lds::A + lo] - q_i);
+            wave_sync();
+            float l_i = 0.f, r_i = 0.f;
+            if (A.y != nullptr) loss_and_multiplier(A.loss, A.s, yh, y_i, want, l_i, r_i);
+            if (lo >= nrows) r_i = 0.f;
+            if (half == 0) {
+                tile[Lds::R + lo] = r_i;
+                tile[Lds::A + lo] = a_i;
+                tile[Lds::Q + lo] = q_i;
+                if (lo < nrows) {
+                    sums[0] += (double)l_i;
+                    sums[1] += (double)r_i;
+                    if (!GRADIENT && A.eval_part != nullptr) {
+                        const double d = (double)yh - (double)y_i;
+                        sums[2] += d * d;
+                        if ((yh >= 0.f ? 1.f : -1.f) == y_i) sums[3] += 1.0;
+                    }
+                    if (A.yhat != nullptr) A.yhat[mine] = yh;
+                    if (!A.whole_rows) {
+                        if (A.a != nullptr) A.a[mine * A.ss] = a_i;
+                        if (A.q != nullptr) A.q[mine * A.ss] = q_i;
+                        if (A.y != nullptr && A.r != nullptr) A.r[mine * A.ss] = r_i;
+                    }
+                }
+            }
+            wave_sync();
+            // rows past the end are out of the descriptor's range: not stored
+#pragma unroll
+            for (int kb = 0; kb < KB; ++kb) {
+                const int k = kb * DT + lo;
+                const uint32_t at = k < (A.whole_rows ? gs : K) ? (uint32_t)(4 * half * gs + k) * 4u : FM_BUF_NONE;
+                if (A.whole_rows) {  // packed aggregate rows go out whole
+#pragma unroll
+                    for (int v = 0; v < 16; ++v) {
+                        const float z = behind[c_row(v, half)];
+                        __builtin_amdgcn_raw_buffer_store_b32(__float_as_int(k < K ? g[kb][v] : z), rows, (int)at,
+                                                              c_row(v, 0) * gs * 4, 0);
+                    }
+                } else {
+#pragma unroll
+                    for (int v = 0; v < 16; ++v)
+                        __builtin_amdgcn_raw_buffer_store_b32(__float_as_int(g[kb][v]), rows, (int)at, c_row(v, 0) * gs * 4, 0);
+                }
+            }
+        } else {
+            if (half == 0) tile[Lds::R + lo] = r_in;
+#pragma unroll
+            for (int kb = 0; kb < KB; ++kb)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) g[kb][v] = g_now[kb][v];
+            wave_sync();
+        }
+        if constexpr (GRADIENT) {
+#pragma unroll
+            for (int v = 0; v < 16; ++v) {
+                const float r = tile[Lds::R + c_row(v, half)];
+                float gr[KB];
+#pragma unroll
+                for (int kb = 0; kb < KB; ++kb) gr[kb] = g[kb][v] * r;
+#pragma unroll
+                for (int jb = 0; jb < DB; ++jb) {
+                    const float xt = tile[c_row(v, half) * S + jb * DT + lo];
+                    const float xr = xt * r;
+                    gw[jb] += xr;
+                    s2[jb] += xt * xr;
+#pragma unroll
+                    for (int kb = 0; kb < KB; ++kb)
+                        acc[jb][kb] = __builtin_amdgcn_mfma_f32_32x32x2f32(xt, gr[kb], acc[jb][kb], 0, 0, 0);
+                }
+                if (v % 4 == 3) {
+#pragma unroll
+                    for (int jb = 0; jb < DB; ++jb) asm volatile("" : "+v"(gw[jb]), "+v"(s2[jb]));
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+            }
+        }
+    }  // tiles of this wavefront
+    if constexpr (GRADIENT) {
+        add_up(false);
+        // the wavefronts one after the other into one block of LDS, then whole rows of the partial sums
+        constexpr int SP = KP + 2;
+        float* sum = area;
+        static_assert(DP * SP <= FM_WAVES * Lds::FLOATS, "the sums fit where the tiles were");
+#pragma unroll 1
+        for (int w = 0; w < FM_WAVES; ++w) {
+            __syncthreads();
+            if (w != wave) continue;
 #pragma unroll
             for (int jb = 0; jb < DB; ++jb) {
-                const float xr = x[u][jb] * rr[u];
-                gw[jb] += xr;
-                s2[jb] += x[u][jb] * xr;
 #pragma unroll
-                for (int kb = 0; kb < KB; ++kb)
-                    acc[jb][kb] = __builtin_amdgcn_mfma_f32_32x32x2f32(x[u][jb], g[u][kb], acc[jb][kb], 0, 0, 0);
+                for (int v = 0; v < 16; ++v)
+#pragma unroll
+                    for (int kb = 0; kb < KB; ++kb) {
+                        float* p = sum + (jb * DT + c_row(v, half)) * SP + kb * DT + lo;
+                        *p = w == 0 ? all[jb][kb][v] : *p + all[jb][kb][v];
+                    }
+                const float gt = all_gw[jb] + fm_xor_lane<32>(all_gw[jb]);
+                const float st = all_s2[jb] + fm_xor_lane<32>(all_s2[jb]);
+                if (half == 0) {
+                    float* p = sum + (jb * DT + lo) * SP + KP;
+                    p[0] = w == 0 ? gt : p[0] + gt;
+                    p[1] = w == 0 ? st : p[1] + st;
+                }
+            }
+        }
+        __syncthreads();
+        const int ps4 = (int)A.ps / 4;
+        for (int e = threadIdx.x; e < D * ps4; e += FM_BLOCK) {
+            const int j = e / ps4, o = (e - j * ps4) * 4;
+            float z[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const int k = o + i;
+                z[i] = k < K ? sum[j * SP + k] : k < K + 2 ? sum[j * SP + KP + k - K] : 0.f;
+            }
+            fm_store_vec<4>(A.part + ((int64_t)j * A.nchunks + b) * A.ps + o, z);
+        }
+    }
+    if constexpr (FORWARD) {
+        if (want) {
+            constexpr int NS = GRADIENT ? 2 : 4;
+#pragma unroll
+            for (int c = 0; c < NS; ++c) {
+                sums[c] = fm_wave_sum(sums[c]);
+                if (lane == 0) sh[wave * 4 + c] = sums[c];
+            }
+            __syncthreads();
+            if (threadIdx.x < NS) {
+                const int c = threadIdx.x;
+                double t = 0.0;
+#pragma unroll
+                for (int w = 0; w < FM_WAVES; ++w) t += sh[w * 4 + c];
+                if (A.row_part != nullptr && c < 2) A.row_part[2 * b + c] = (float)t;
+                if (!GRADIENT && A.eval_part != nullptr && c != 1) A.eval_part[3 * b + (c == 0 ? 0 : c - 1)] = t;
             }
         }
     }
-#pragma unroll
-    for (int jb = 0; jb < DB; ++jb) {
-#pragma unroll
-        for (int v = 0; v < 16; ++v) {
-            const int64_t j = jb * DT + c_row(v, lane);
-            float* __restrict__ row = A.part + (j * A.nchunks + c) * A.ps;
-#pragma unroll
-            for (int kb = 0; kb < KB; ++kb) row[kb * DT + lo] = acc[jb][kb][v];
-        }
-        const float gt = gw[jb] + __shfl_xor(gw[jb], 32, FM_WAVE);
-        const float st = s2[jb] + __shfl_xor(s2[jb], 32, FM_WAVE);
-        if (half == 0) {
-            float* __restrict__ row = A.part + ((int64_t)(jb * DT + lo) * A.nchunks + c) * A.ps;
-            row[K] = gt;
-            row[K + 1] = st;
-        }
-    }
 }
 
-template <int DB, int KB>
-int launch_rows_dense_t(fm_matrix* m, const RowArgs& A, hipStream_t st)
+template <int DB, int KB, int WHAT>
+int launch_dense_t(fm_matrix* m, const DenseArgs& A, hipStream_t st)
 {
-    constexpr int D = DB * DT, K = KB * DT;
-    constexpr int S = (D > K ? D : K) + 1;
-    const size_t lds = (size_t)(2 * D + FM_WAVES * DT * S) * sizeof(float);
-    const int64_t tiles = (A.N + DT - 1) / DT;
-    const int64_t per = (int64_t)FM_WAVES * FM_DENSE_TILES;
-    const int64_t grid = (tiles + per - 1) / per;
-    if (grid > 0x7fffffffLL) return fm_fail(m, FM_ERANGE, "row grid too large");
-    ProfScope ps(m, st, FMK_ROWS_FORWARD);
-    hipLaunchKernelGGL((k_rows_dense<DB, KB>), dim3((unsigned)grid), dim3(FM_BLOCK), lds, st, A);
-    FM_HIP(m, hipGetLastError());
-    return FM_OK;
-}
-
-template <int DB, int KB>
-int launch_cols_dense_t(fm_matrix* m, const ColArgs& A, hipStream_t st)
-{
-    const int64_t grid = (A.nchunks + FM_WAVES - 1) / FM_WAVES + (A.epi.on ? A.epi.nsums : 0);
+    constexpr size_t LDS = ((WHAT & FM_DENSE_FORWARD ? (2 + KB * DT) * DB * DT : 0) + FM_WAVES * DenseLds<DB>::FLOATS) * sizeof(float);
+    static_assert(LDS <= 64 * 1024, "no opt-in to more LDS needed");
+    const int64_t grid = A.nchunks + (A.epi.on ? A.epi.nsums : A.regs != nullptr ? 1 : 0);
     if (grid > 0x7fffffffLL) return fm_fail(m, FM_ERANGE, "chunk grid too large");
-    hipLaunchKernelGGL((k_cols_dense<DB, KB>), dim3((unsigned)grid), dim3(FM_BLOCK), 0, st, A);
+    ProfScope ps(m, st, WHAT & FM_DENSE_GRADIENT ? FMK_COLS_LONG : FMK_ROWS_FORWARD);
+    hipLaunchKernelGGL((k_dense<DB, KB, WHAT>), dim3((unsigned)grid), dim3(FM_BLOCK), LDS, st, A);
     FM_HIP(m, hipGetLastError());
     return FM_OK;
 }
 
-__global__ void k_dense_index(int64_t D, int64_t nchunks, int32_t* __restrict__ long_col, int64_t* __restrict__ long_first,
-                              int32_t* __restrict__ vlong)
+template <int WHAT>
+int launch_dense(fm_matrix* m, const DenseArgs& A, hipStream_t st)
 {
-    const int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (j <= D) long_first[j] = j * nchunks;
-    if (j < D) {
-        long_col[j] = (int32_t)j;
-        vlong[j] = (int32_t)j;
-    }
+    const bool d2 = A.D > DT, k2 = A.K > DT;
+    if (d2 && k2) return launch_dense_t<2, 2, WHAT>(m, A, st);
+    if (d2) return launch_dense_t<2, 1, WHAT>(m, A, st);
+    if (k2) return launch_dense_t<1, 2, WHAT>(m, A, st);
+    return launch_dense_t<1, 1, WHAT>(m, A, st);
 }
 
 }  // namespace
 
-// D and K in {32, 64}: the tiles are 32 wide and the accumulators of both kernels stay in registers
-bool fm_dense_shape_ok(const fm_matrix* m, int32_t K)
+// Up to two tiles each way: the accumulators stay in registers.
+bool fm_dense_fits(const fm_matrix* m, int32_t K) { return m->is_dense && m->D <= FM_DENSE_MAX && K <= FM_DENSE_MAX; }
+bool fm_dense_shape_ok(const fm_matrix* m, int32_t K) { return m->opt.dense_rows && fm_dense_fits(m, K); }
+
+// Workgroups of a pass over N rows: one tile to a wavefront while the chip is not full, then as many as it holds at once,
+// in as few rounds as leave no wavefront more than 16 tiles (1e6 x 64, K=32: 977 workgroups of 8 tiles a wavefront took 129
+// us, the last 209 of them alone).
+int64_t fm_dense_chunks(int64_t N, int64_t D, int32_t K)
 {
-    return m->is_dense && m->opt.dense_rows && (m->D == 32 || m->D == 64) && (K == 32 || K == 64);
+    const int64_t tiles = (N + DT - 1) / DT;
+    const int64_t slots = FM_DENSE_CUS * dense_per_cu(D > DT ? 2 : 1, K > DT ? 2 : 1);
+    if (tiles <= FM_WAVES * slots) return (tiles + FM_WAVES - 1) / FM_WAVES;
+    const int64_t most = FM_WAVES * slots * 2 * FM_DENSE_TILES;
+    return slots * ((tiles + most - 1) / most);
 }
 
-// One chunk of rows per wavefront, FM_DENSE_CHUNKS of them (16 wavefronts per compute unit; with fewer the
-// kernel hides less latency than the shorter finish saves); the index says
-// that the partial sums of column j are the items j * nchunks .. (j+1) * nchunks - 1.
-int fm_dense_build_index(fm_matrix* m, hipStream_t st)
+int fm_launch_dense(fm_matrix* m, const DenseArgs& A, int what, hipStream_t st)
 {
-    LongIndex* li = &m->ldense;
-    if (li->long_col != nullptr || !m->is_dense) return FM_OK;
-    const int64_t N = m->N, D = m->D;
-    int64_t rows = (N + FM_DENSE_CHUNKS - 1) / FM_DENSE_CHUNKS;
-    rows = std::max<int64_t>(64, (rows + 7) / 8 * 8);
-    m->dense_chunk_rows = rows;
-    m->dense_chunks = (N + rows - 1) / rows;
-    FM_TRY(fm_dev_alloc(m, (void**)&li->long_col, (size_t)D * sizeof(int32_t)));
-    FM_TRY(fm_dev_alloc(m, (void**)&li->long_first, (size_t)(D + 1) * sizeof(int64_t)));
-    FM_TRY(fm_dev_alloc(m, (void**)&li->vlong, (size_t)D * sizeof(int32_t)));
-    hipLaunchKernelGGL(k_dense_index, dim3((unsigned)((D + 256) / 256)), dim3(256), 0, st, D, m->dense_chunks, li->long_col,
-                       li->long_first, li->vlong);
-    FM_HIP(m, hipGetLastError());
-    FM_HIP(m, hipStreamSynchronize(st));
-    li->nlong = D;
-    li->nitems = D * m->dense_chunks;
-    li->nvlong = m->dense_chunks > m->tune.vlong ? D : 0;  // a workgroup per column in the finish step
-    li->h_long_off.assign({0, li->nlong});
-    li->h_item_off.assign({0, li->nitems});
-    li->h_short_off.assign({0, 0});
-    return FM_OK;
-}
-
-int fm_launch_rows_dense(fm_matrix* m, const RowArgs& A, hipStream_t st)
-{
-    const int db = A.dense_D / DT, kb = A.K / DT;
-    if (A.dense_D != db * DT || A.K != kb * DT) return fm_fail(m, FM_EINVAL, "dense kernels need D and K in {32, 64}");
-    if (db == 1 && kb == 1) return launch_rows_dense_t<1, 1>(m, A, st);
-    if (db == 1 && kb == 2) return launch_rows_dense_t<1, 2>(m, A, st);
-    if (db == 2 && kb == 1) return launch_rows_dense_t<2, 1>(m, A, st);
-    if (db == 2 && kb == 2) return launch_rows_dense_t<2, 2>(m, A, st);
-    return fm_fail(m, FM_EINVAL, "dense kernels need D and K in {32, 64}");
-}
-
-int fm_launch_cols_dense(fm_matrix* m, const ColArgs& A, hipStream_t st)
-{
-    const int db = (int)(A.D / DT), kb = A.K / DT;
-    if (A.D != db * DT || A.K != kb * DT || A.X == nullptr || A.nchunks <= 0 || A.chunk_rows <= 0 ||
-        A.chunk_rows % 2 != 0)
-        return fm_fail(m, FM_EINVAL, "bad arguments of the dense column pass");
-    if (db == 1 && kb == 1) return launch_cols_dense_t<1, 1>(m, A, st);
-    if (db == 1 && kb == 2) return launch_cols_dense_t<1, 2>(m, A, st);
-    if (db == 2 && kb == 1) return launch_cols_dense_t<2, 1>(m, A, st);
-    if (db == 2 && kb == 2) return launch_cols_dense_t<2, 2>(m, A, st);
-    return fm_fail(m, FM_EINVAL, "dense kernels need D and K in {32, 64}");
+    if (A.D < 1 || A.D > FM_DENSE_MAX || A.K < 1 || A.K > FM_DENSE_MAX || A.N < 1 || A.nchunks < 1 || A.X == nullptr)
+        return fm_fail(m, FM_EINVAL, "bad arguments of the dense pass");
+    switch (what) {
+        case FM_DENSE_FORWARD: return launch_dense<FM_DENSE_FORWARD>(m, A, st);
+        case FM_DENSE_GRADIENT: return launch_dense<FM_DENSE_GRADIENT>(m, A, st);
+        case FM_DENSE_FORWARD | FM_DENSE_GRADIENT: return launch_dense<FM_DENSE_FORWARD | FM_DENSE_GRADIENT>(m, A, st);
+    }
+    return fm_fail(m, FM_EINVAL, "unknown dense pass %d", what);
 }

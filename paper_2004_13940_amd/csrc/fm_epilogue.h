@@ -51,6 +51,22 @@ __device__ __forceinline__ void fm_epi_partial(const FmEpilogue& E, int b, doubl
     }
 }
 
+// |w|^2 and |V|^2 by one workgroup, into out[0..1].
+template <int T>
+__device__ __forceinline__ void fm_reg_pair(const float* __restrict__ w, int64_t nw, const float* __restrict__ V, int64_t nV,
+                                            double* out, double* sh)
+{
+    double a = 0.0, b = 0.0;
+    for (int64_t i = threadIdx.x; i < nw; i += T) a += (double)w[i] * (double)w[i];
+    for (int64_t i = threadIdx.x; i < nV; i += T) b += (double)V[i] * (double)V[i];
+    a = fm_block_sum<T>(a, sh);
+    b = fm_block_sum<T>(b, sh);
+    if (threadIdx.x == 0) {
+        out[0] = a;
+        out[1] = b;
+    }
+}
+
 template <int T>
 __device__ __forceinline__ void fm_epi_final(const FmEpilogue& E, double* sh)
 {

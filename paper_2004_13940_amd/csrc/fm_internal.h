@@ -187,11 +187,8 @@ struct fm_matrix {
     _Float16* Vh = nullptr; // [D*K] half-precision copy of V for passes with half_gather (allocated on first use)
     int32_t VhK = 0;        // the K it was sized for
     // Every row stores all D columns in order (col[e] == e % D): `val` is then a dense row-major N x D
-    // matrix and whole-matrix passes can run as dense contractions.  ldense: the partial sums of column j
-    // over chunk c of the rows live at item j * dense_chunks + c.
+    // matrix and passes over all of it or over a batch of rows can run as dense contractions.
     bool is_dense = false;
-    LongIndex ldense;
-    int64_t dense_chunk_rows = 0, dense_chunks = 0;
     float* dV = nullptr;    // [D*K] last step's change of V
     float2* dwn = nullptr;  // [D] (change of w_j, change of |v_j|^2)
     float* part = nullptr;      // [max items * part_stride(K)] partial sums of the items, see fm_part_stride
@@ -311,6 +308,8 @@ inline int32_t fm_rows_big(const fm_matrix* m, int32_t K)
     return m->D * std::max<int64_t>(K, 2) * (int64_t)sizeof(float) > FM_BUF_BYTES || m->opt.wide_addresses ? 1 : 0;
 }
 int fm_launch_rows(fm_matrix* m, const RowArgs& A, bool refresh, hipStream_t st);
+struct DenseArgs;
+void fm_dense_rows(const RowArgs& A, DenseArgs* E);  // the forward pass A as a dense one
 int64_t fm_rows_grid(int64_t N, int32_t K);
 // once per device, with that device current: resolves the address of the static scratch array of
 // fm_forward_noalloc (fm_noalloc.hip); called when a handle is created
@@ -318,11 +317,11 @@ int fm_noalloc_init_device(fm_matrix* m);
 int fm_pack_aux(fm_matrix* m, const float* r, const float* G, hipStream_t st);  // packed layout only
 int fm_to_half(fm_matrix* m, const float* x, _Float16* out, int64_t n, hipStream_t st);  // round to nearest even
 // dense matrices (fm_dense.hip)
-bool fm_dense_shape_ok(const fm_matrix* m, int32_t K);       // the dense kernels exist for this D and K
-int fm_dense_build_index(fm_matrix* m, hipStream_t st);      // ldense, dense_chunk_rows, dense_chunks
-int fm_launch_rows_dense(fm_matrix* m, const RowArgs& A, hipStream_t st);
-struct ColArgs;
-int fm_launch_cols_dense(fm_matrix* m, const ColArgs& A, hipStream_t st);  // partial sums only; the finish kernels follow
+bool fm_dense_fits(const fm_matrix* m, int32_t K);           // the dense kernels exist for this matrix and K
+bool fm_dense_shape_ok(const fm_matrix* m, int32_t K);       // ... and are not switched off
+int64_t fm_dense_chunks(int64_t N, int64_t D, int32_t K);    // workgroups of a pass over N rows; never fewer for more rows
+enum { FM_DENSE_FORWARD = 1, FM_DENSE_GRADIENT = 2 };
+int fm_launch_dense(fm_matrix* m, const DenseArgs& A, int what, hipStream_t st);  // gradient: partial sums; the finish follows
 int fm_unpack_aux(fm_matrix* m, float* a, float* G, float* q, float* r, hipStream_t st);
 
 // What is left of an epoch when the columns have stepped: the sums over the examples, the bias step and the figures of
@@ -360,10 +359,9 @@ struct ColArgs {
     const float* r;
     const float* G;
     int64_t gs, rs;  // row strides of G and r in floats
-    // dense matrices (every row stores all D columns): X = the CSR values as a row-major N x D matrix; wavefront c
-    // sums rows [c * chunk_rows, (c+1) * chunk_rows) and stores column j's partial sums at item j * nchunks + c
-    const float* X;
-    int64_t chunk_rows, nchunks;
+    // > 0: a dense pass has left the partial sums of all columns, those of column j at the items
+    // j * nchunks .. (j + 1) * nchunks - 1; only the finish is left
+    int64_t nchunks;
     int32_t packed;  // FM_PLANAR, or FM_PACKED_LANE: G rows are packed aggregate rows [G | r | a | q | pad]
     float* w;        // updated in place when update
     float* V;
@@ -423,11 +421,32 @@ int fm_launch_cols(fm_matrix* m, const ColArgs& A, bool update, hipStream_t st);
 // takes the postponed regulariser steps of every column up to stratum A.s (exclusive)
 int fm_launch_cols_flush(fm_matrix* m, const ColArgs& A, hipStream_t st);
 
+// A pass over rows of a dense matrix (fm_dense.hip).
+struct DenseArgs {
+    int64_t N, D;
+    int32_t K;
+    int64_t nchunks;
+    const float* X;  // row-major N x D
+    const float *w0, *w, *V, *y;  // forward; y nullable
+    float *yhat, *a, *G, *q, *r;  // forward: nullable outputs; gradient alone: G and r are read
+    int64_t gs, ss;               // floats between rows of G, of r, a, q
+    int32_t whole_rows;           // forward: packed aggregate rows [G | r | a | q | pad] go out whole
+    int32_t loss;
+    float s;
+    float* row_part;    // forward, nullable: [2 * nchunks] loss and sum of r per workgroup
+    double* eval_part;  // forward alone, nullable: [3 * nchunks] sums of losses, squared errors and correct signs
+    float* part;        // gradient: partial sums, rows of ps floats at item j * nchunks + workgroup
+    int64_t ps;
+    FmEpilogue epi;     // gradient alone: on = the sums over the examples ride along
+    double* regs;       // nullable, without epi: one more workgroup leaves |w|^2 and |V|^2 there
+};
+
 constexpr int FM_REG_PAIRS = 512;      // partial pairs of fm_reg_partials
 constexpr int FM_REDUCE_TMP = 2048;  // doubles of stage-1 scratch a reduction may use
 // tmp: FM_REDUCE_TMP doubles of device scratch, or nullptr for the handle's own
 int fm_reduce_pairs(fm_matrix* m, const float* part, int64_t nblocks, double* out2, hipStream_t st,
                     double* tmp = nullptr);
+double* fm_reg_scratch(fm_matrix* m);  // 2 * FM_REG_PAIRS doubles in the handle's scratch
 // |w|^2 and |V|^2 as nregs partial pairs of doubles in the handle's scratch
 int fm_reg_partials(fm_matrix* m, const float* w, int64_t nw, const float* V, int64_t nV, const double** regs, int32_t* nregs,
                     hipStream_t st);

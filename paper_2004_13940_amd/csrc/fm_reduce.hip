@@ -167,12 +167,17 @@ int fm_reduce_pairs(fm_matrix* m, const float* part, int64_t nblocks, double* ou
     return FM_OK;
 }
 
-int fm_reg_partials(fm_matrix* m, const float* w, int64_t nw, const float* V, int64_t nV, const double** regs, int32_t* nregs,
-                    hipStream_t st)
+double* fm_reg_scratch(fm_matrix* m)
 {
     // behind the partial pairs of the epilogue (2 * 512 doubles) in the handle's scratch
     static_assert(FM_REDUCE_TMP >= 2 * 512 + 2 * FM_REG_PAIRS, "scratch of the reductions");
-    double* out = m->scal + 8 + 2 * 512;
+    return m->scal + 8 + 2 * 512;
+}
+
+int fm_reg_partials(fm_matrix* m, const float* w, int64_t nw, const float* V, int64_t nV, const double** regs, int32_t* nregs,
+                    hipStream_t st)
+{
+    double* out = fm_reg_scratch(m);
     int64_t nb = (std::max(nw, nV) + 16 * RED_THREADS - 1) / (16 * RED_THREADS);
     nb = std::min<int64_t>(std::max<int64_t>(nb, 1), FM_REG_PAIRS);
     ProfScope ps(m, st, FMK_REDUCE);

@@ -5,6 +5,8 @@
 // `sub` of the group owns VEC consecutive latent dimensions [sub*VEC, sub*VEC+VEC).
 // A group reads its row's (column, value) pairs (coalesced, each lane the ones it holds), broadcasts each pair inside the
 // group and gathers the V row of that column as one contiguous 4*K-byte request.
+#include <string.h>
+
 #include "fm_device.h"
 #include "fm_internal.h"
 
@@ -447,9 +449,39 @@ int64_t fm_rows_grid(int64_t N, int32_t K)
     return (N + per - 1) / per;
 }
 
+void fm_dense_rows(const RowArgs& A, DenseArgs* E)
+{
+    memset(E, 0, sizeof(*E));
+    E->N = A.N;
+    E->D = A.dense_D;
+    E->K = A.K;
+    E->nchunks = fm_dense_chunks(A.N, A.dense_D, A.K);
+    E->X = A.val;
+    E->w0 = A.w0;
+    E->w = A.w;
+    E->V = A.V;
+    E->y = A.y;
+    E->yhat = A.yhat;
+    E->a = A.a;
+    E->G = A.G;
+    E->q = A.q;
+    E->r = A.r;
+    E->gs = A.gs;
+    E->ss = A.ss;
+    E->whole_rows = A.whole_rows;
+    E->loss = A.loss;
+    E->s = A.s;
+    E->row_part = A.row_part;
+    E->eval_part = A.eval_part;
+}
+
 int fm_launch_rows(fm_matrix* m, const RowArgs& A, bool refresh, hipStream_t st)
 {
-    if (!refresh && A.dense_D > 0 && A.Vh == nullptr) return fm_launch_rows_dense(m, A, st);
+    if (!refresh && A.dense_D > 0 && A.Vh == nullptr) {
+        DenseArgs E;
+        fm_dense_rows(A, &E);
+        return A.N > 0 ? fm_launch_dense(m, E, FM_DENSE_FORWARD, st) : FM_OK;
+    }
     int vec, lanes;
     if (!fm_shape_for_K(A.K, &vec, &lanes)) return fm_fail(m, FM_EINVAL, "unsupported K=%d", A.K);
     switch (vec) {

@@ -343,3 +343,62 @@ def test_gathers_at_offsets_of_two_to_four_gigabytes(N, K):
     assert_close(gV.cpu().numpy().reshape(D, K), wgV, "grad_V")
     m.close()
     B.fm_trim()
+
+
+@pytest.mark.parametrize("N,D,K", [(1, 1, 1), (31, 5, 4), (32, 32, 32), (33, 33, 33), (127, 31, 28), (129, 64, 3),
+                                   (4097, 63, 17), (1000, 8, 64), (98_400, 33, 12), (99_000, 17, 40), (40_003, 64, 64)])
+def test_dense_kernels_at_the_edges_of_their_tiles(N, D, K):
+    """Tables whose rows, columns and latent dimensions end just before, at and after a tile of 32, one tile to a wavefront
+    and more than eight (where its sums are set aside); packed and planar aggregates.  Forward, metrics, gradient, an epoch
+    and a mini-batch epoch against the oracle; without the dense kernels the same entry points meet it too."""
+    import torch
+    from paper_2004_13940_amd import binding as B
+    rng = np.random.default_rng(7900 + N + 100 * D + K)
+    rowptr, col = np.arange(N + 1, dtype=np.int64) * D, np.tile(np.arange(D, dtype=np.int32), N)
+    val = rng.standard_normal(N * D).astype(np.float32)
+    y = np.where(rng.random(N) < 0.5, 1.0, -1.0).astype(np.float32)
+    w0, w = np.float32(0.1), (rng.standard_normal(D) * 0.1).astype(np.float32)
+    V = (rng.standard_normal((D, K)) * 0.3 / np.sqrt(D * K)).astype(np.float32)
+    X = O.make_matrix(N, D, rowptr, col, val)
+    kw = dict(loss=O.LOSS_LOGISTIC, s=1.0 / N, lambda_w=0.01, lambda_v=0.02, eta=0.5)
+    a, G, q, yhat = O.forward(X, float(w0), w, V)
+    l, r = O.loss_multiplier(O.LOSS_LOGISTIC, 1.0 / N, yhat, y)
+    want = dict(yhat=yhat, a=a, G=G, q=q, r=r)
+    batches = min(N, 3)
+    for dense in (1, 0):
+        print("dense tiles", N, D, K, dense, flush=True)
+        m = B.Matrix(N, D, rowptr, col, val)
+        m.fm_set_option(B.FM_OPT_DENSE_ROWS, dense)
+        p = B.make_params(K, O.LOSS_LOGISTIC, 0.01, 0.02, 0.5, 1.0 / N)
+        d_w0, d_w, d_V = dev_params(w0, w, V)
+        d_y = to_dev(y)
+        out = {k: torch.full((N * (K if k == "G" else 1),), float("nan"), device="cuda") for k in want}
+        loss_sum = m.fm_forward(p, d_y, d_w0, d_w, d_V, want_loss=True, **out)
+        for k in want:
+            assert_close(out[k].cpu().numpy().reshape(np.shape(want[k])), want[k], k)
+        assert abs(loss_sum - l.sum()) <= 1e-5 * l.sum()
+        met = m.fm_evaluate(p, d_y, d_w0, d_w, d_V)
+        assert abs(met["rmse"] - np.sqrt(np.mean((yhat - y) ** 2))) <= 1e-5 * met["rmse"]
+        m.fm_build_csc()
+        gw = torch.full((D,), float("nan"), device="cuda")
+        gV = torch.full((D * K,), float("nan"), device="cuda")
+        g0 = torch.full((1,), float("nan"), device="cuda")
+        m.fm_gradient(p, out["r"], out["G"], d_w, d_V, g0, gw, gV)
+        wg0, wgw, wgV = O.gradient(X, r, G, w, V, 0.01, 0.02)
+        assert abs(g0.item() - wg0) <= 1e-5 * np.abs(r).sum()
+        assert_close(gw.cpu().numpy(), wgw, "grad_w")
+        assert_close(gV.cpu().numpy().reshape(D, K), wgV, "grad_V")
+        obj = m.fm_sgd_epoch(p, d_y, d_w0, d_w, d_V, want_objective=True)
+        o0, ow, oV, oobj = O.full_epoch(X, y, float(w0), w, V, update_w0=True, **kw)
+        assert abs(obj[0] - oobj[0]) <= 1e-5 * oobj[0] and abs(obj[1] - oobj[1]) <= 1e-5 * oobj[1]
+        aux = {k: torch.full_like(out[k], float("nan")) for k in ("G", "r")}
+        m.fm_get_aux(K, **aux)
+        for k in aux:
+            assert_close(aux[k].cpu().numpy().reshape(np.shape(want[k])), want[k], k + " held after the epoch")
+        m.fm_partition_batches(batches)
+        m.fm_minibatch_epoch(p, d_y, d_w0, d_w, d_V)
+        o0, ow, oV, _ = O.minibatch_epoch(X, y, o0, ow, oV, B=batches, update_w0=True, reg_share=True, **kw)
+        assert_close(d_w.cpu().numpy(), ow, "w")
+        assert_close(d_V.cpu().numpy().reshape(D, K), oV, "V")
+        assert abs(d_w0.item() - o0) <= 1e-4 * max(abs(o0), 1e-2)
+        m.close()
