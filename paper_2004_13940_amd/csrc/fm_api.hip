@@ -600,6 +600,13 @@ static void fill_long(const fm_matrix* m, ColArgs& A, const LongIndex& li, int32
     A.vlong = li.vlong != nullptr ? li.vlong + v0 : nullptr;
     A.nvlong = v1 - v0;
     A.vlong_items = m->tune.vlong;
+    if (strat && li.whole) {
+        A.whole = 1;
+        A.long_beg = li.long_beg;
+        A.long_len = li.long_len;
+        A.nbig = li.h_big_off.empty() ? 0 : li.h_big_off[s + 1] - li.h_big_off[s];
+        A.big_cols = A.nbig > 0 ? li.big + li.h_big_off[s] : nullptr;
+    }
     const int64_t s0 = strat ? li.h_short_off[s] : 0, s1 = strat ? li.h_short_off[s + 1] : li.nshort;
     A.short_col = li.short_col != nullptr ? li.short_col + s0 : nullptr;
     A.short_beg = li.short_beg != nullptr ? li.short_beg + s0 : nullptr;

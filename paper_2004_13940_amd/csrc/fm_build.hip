@@ -466,13 +466,18 @@ __global__ __launch_bounds__(LI_T) void k_long_fill(const int64_t* __restrict__ 
 __global__ __launch_bounds__(256) void k_items(const int64_t* __restrict__ ptr, const int32_t* __restrict__ long_col,
                                                const int64_t* __restrict__ long_vcol, const int64_t* __restrict__ long_first,
                                                int64_t nlong, int seg, int32_t* __restrict__ item_col,
-                                               int64_t* __restrict__ item_beg, int32_t* __restrict__ item_len)
+                                               int64_t* __restrict__ item_beg, int32_t* __restrict__ item_len,
+                                               int64_t* __restrict__ long_beg, int32_t* __restrict__ long_len)
 {
     const int64_t lc = (int64_t)blockIdx.x * 4 + threadIdx.x / 64;
     if (lc >= nlong) return;
     const int64_t c = long_vcol[lc], b = ptr[c], len = ptr[c + 1] - b;
     const int64_t first = long_first[lc], n = long_first[lc + 1] - first;
     const int32_t j = long_col[lc];
+    if (long_beg != nullptr && threadIdx.x % 64 == 0) {
+        long_beg[lc] = b;
+        long_len[lc] = (int32_t)len;
+    }
     for (int64_t k = threadIdx.x % 64; k < n; k += 64) {
         const int64_t left = len - k * seg;
         item_col[first + k] = j;
@@ -853,6 +858,23 @@ static int build_vlong_list(fm_matrix* m, const std::vector<int64_t>& h_first, L
     return FM_OK;
 }
 
+// The long columns that a workgroup sums whole, stratum by stratum.
+static int build_big_list(fm_matrix* m, LongIndex* out)
+{
+    std::vector<int32_t> h_len((size_t)out->nlong), h_big;
+    FM_HIP(m, hipMemcpy(h_len.data(), out->long_len, h_len.size() * sizeof(int32_t), hipMemcpyDeviceToHost));
+    out->h_big_off.assign(out->h_long_off.size(), 0);
+    for (size_t s = 0; s + 1 < out->h_long_off.size(); ++s) {
+        for (int64_t lc = out->h_long_off[s]; lc < out->h_long_off[s + 1]; ++lc)
+            if (h_len[(size_t)lc] > FM_WHOLE_WAVE) h_big.push_back((int32_t)lc);
+        out->h_big_off[s + 1] = (int64_t)h_big.size();
+    }
+    if (h_big.empty()) return FM_OK;
+    FM_TRY(fm_dev_alloc(m, (void**)&out->big, h_big.size() * sizeof(int32_t)));
+    FM_HIP(m, hipMemcpy(out->big, h_big.data(), h_big.size() * sizeof(int32_t), hipMemcpyHostToDevice));
+    return FM_OK;
+}
+
 // Processing order of the items of a stratum or batch: by first row, so that the items of different columns that gather
 // the same rows are worked on at the same time by one workgroup.  In column order they lay a column of items apart, and
 // whether they met in the L2 of one XCD hung on that number of items: a table of 64 columns, K=32, 16 strata took 2.32 ms
@@ -904,6 +926,8 @@ int fm_build_long_index(fm_matrix* m, const int64_t* ptr, const int32_t* ids, co
     out->nlong = out->nitems = 0;
     out->h_long_off.assign(nstrata + 1, 0);
     out->h_item_off.assign(nstrata + 1, 0);
+    // Not for one block (or batch), whose steps have the bits of the full-gradient epoch's; who sets an item length gets items.
+    out->whole = nstrata > 1 && m->tune.seg <= 0 && (m->N + nstrata - 1) / nstrata <= FM_WHOLE_ROWS;
     if (ncols_total <= 0) return FM_OK;
     const int64_t ntiles = (ncols_total + LI_TILE - 1) / LI_TILE;
     int64_t *tl = nullptr, *ti = nullptr;
@@ -931,13 +955,17 @@ int fm_build_long_index(fm_matrix* m, const int64_t* ptr, const int32_t* ids, co
         FM_TRY(fm_dev_alloc(m, (void**)&out->item_beg, (size_t)nitems * sizeof(int64_t)));
         FM_TRY(fm_dev_alloc(m, (void**)&out->item_len, (size_t)nitems * sizeof(int32_t)));
         FM_TRY(fm_dev_alloc(m, (void**)&vcol, (size_t)nlong * sizeof(int64_t)));
+        if (out->whole) {
+            FM_TRY(fm_dev_alloc(m, (void**)&out->long_beg, (size_t)nlong * sizeof(int64_t)));
+            FM_TRY(fm_dev_alloc(m, (void**)&out->long_len, (size_t)nlong * sizeof(int32_t)));
+        }
         hipLaunchKernelGGL(k_long_fill, dim3((unsigned)ntiles), dim3(LI_T), 0, st, ptr, ncols_total, ids, seg,
                            (const int64_t*)tl, (const int64_t*)ti, out->long_col, vcol, out->long_first);
         FM_HIP(m, hipGetLastError());
         FM_HIP(m, hipMemcpyAsync(out->long_first + nlong, &nitems, sizeof(int64_t), hipMemcpyHostToDevice, st));
         hipLaunchKernelGGL(k_items, dim3(blocks_for(nlong, 4)), dim3(256), 0, st, ptr, (const int32_t*)out->long_col,
                            (const int64_t*)vcol, (const int64_t*)out->long_first, nlong, seg, out->item_col, out->item_beg,
-                           out->item_len);
+                           out->item_len, out->long_beg, out->long_len);
         FM_HIP(m, hipGetLastError());
         std::vector<int64_t> h_vcol((size_t)nlong), h_first((size_t)nlong + 1);
         FM_HIP(m, hipMemcpyAsync(h_vcol.data(), vcol, (size_t)nlong * sizeof(int64_t), hipMemcpyDeviceToHost, st));
@@ -953,6 +981,7 @@ int fm_build_long_index(fm_matrix* m, const int64_t* ptr, const int32_t* ids, co
         }
         fm_dev_free(m, vcol);
         FM_TRY(build_vlong_list(m, h_first, out));
+        if (out->whole) FM_TRY(build_big_list(m, out));
         FM_TRY(order_by_row(m, row, nstrata, out, st));
     }
     fm_dev_free(m, tl);
@@ -965,7 +994,7 @@ static void free_long_index(fm_matrix* m, LongIndex* li)
 {
     for (void* p : {(void*)li->long_col, (void*)li->long_first, (void*)li->item_col, (void*)li->item_beg,
                     (void*)li->item_len, (void*)li->short_col, (void*)li->short_beg, (void*)li->short_len, (void*)li->order, (void*)li->ord_beg,
-                    (void*)li->ord_len, (void*)li->tile_ptr, (void*)li->vlong})
+                    (void*)li->ord_len, (void*)li->tile_ptr, (void*)li->vlong, (void*)li->long_beg, (void*)li->long_len, (void*)li->big})
         if (p != nullptr) fm_dev_free(m, p);
     *li = LongIndex();
 }

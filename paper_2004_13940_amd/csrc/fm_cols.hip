@@ -679,6 +679,100 @@ __global__ __launch_bounds__(FM_BLOCK) void k_cols_finish(const ColArgs A)
     finish_column<VEC, L, UPDATE>(A, j, sub, kbase, kact, accf, (float)gw, (float)s2, c);
 }
 
+// A stratum or batch of few rows (FM_WHOLE_ROWS), groups of up to eight lanes: every column is summed where it is finished,
+// no partial sums and no second launch.  Workgroups: one per column of more than FM_WHOLE_WAVE entries (its groups take
+// consecutive slices, added in fp64 as k_cols_finish does), then one wavefront per other long column, one group per short
+// column, the sums over the examples, and, where nobody has to add those up first, the bias step.  Bound: latency, list ->
+// entries -> gathers -> step; what goes is a launch and the round trip of the partial sums (stratum of the text-like
+// workload, 5e4 rows, 32 strata: columns and finish 14.0 us, now 9.2).
+template <int VEC, int L, int PACKED>
+__global__ __launch_bounds__(FM_BLOCK) void k_cols_whole(const ColArgs A)
+{
+    constexpr int R = FM_WAVE / L;
+    constexpr int NG = FM_BLOCK / L;
+    constexpr int S = L * VEC + 2;
+    constexpr int ROUND = 16;  // entries of a round of the walk
+    __shared__ double sh[FM_WAVES * S];
+    const int lane = threadIdx.x & (FM_WAVE - 1);
+    const int wave = threadIdx.x / FM_WAVE;
+    const int sub = lane & (L - 1);
+    const int kbase = sub * VEC;
+    const bool kact = kbase < A.K;
+    const int64_t b = blockIdx.x;
+    const int64_t waves_end = A.nbig + A.blk_lin;
+    if (b >= waves_end + A.blk_short) {
+        if (A.epi.nsums > 0)
+            fm_epi_partial<FM_BLOCK>(A.epi, (int)(b - waves_end - A.blk_short), sh);
+        else
+            fm_epi_final<FM_BLOCK>(A.epi, sh);
+        return;
+    }
+    const bool big = b < A.nbig, whole = b < waves_end;  // uniform
+    int64_t j, beg;
+    int len;
+    bool valid = true;
+    if (whole) {
+        const int64_t rel = big ? 0 : (b - A.nbig) * FM_WAVES + wave;
+        valid = big || rel < A.nlong;
+        const int64_t lc = big ? A.big_cols[b] : A.long_base + (valid ? rel : 0);
+        j = A.long_col[lc];
+        beg = A.long_beg[lc];
+        const int n = A.long_len[lc];
+        valid = valid && (big || n <= FM_WHOLE_WAVE);
+        const int groups = big ? NG : R, group = big ? (int)threadIdx.x / L : lane / L;
+        const int slice = ((n + groups - 1) / groups + ROUND - 1) / ROUND * ROUND;
+        const int at = group * slice;
+        len = !valid || at >= n ? 0 : n - at < slice ? n - at : slice;
+        beg += at;
+    } else {
+        const int64_t pos = (b - waves_end) * (FM_WAVES * R) + wave * R + lane / L;
+        valid = pos < A.nshort;
+        const int64_t p = valid ? pos : A.nshort - 1;
+        j = A.short_col[p];
+        beg = A.short_beg[p];
+        len = valid ? A.short_len[p] : 0;
+    }
+    const ColState<VEC> c = load_column<VEC, true>(A, j, kbase, kact);
+    float acc[VEC];
+#pragma unroll
+    for (int z = 0; z < VEC; ++z) acc[z] = 0.f;
+    float gw = 0.f, s2 = 0.f;
+    accumulate_entries<VEC, L, PACKED>(A, false, beg, len, sub, kbase, kact, acc, gw, s2);
+    if (whole) {
+        double accd[VEC];
+#pragma unroll
+        for (int z = 0; z < VEC; ++z) accd[z] = (double)acc[z];
+        double gwd = (double)gw, s2d = (double)s2;
+        add_groups<VEC, L>(accd, gwd, s2d);
+        if (big) {
+            double* mine = sh + wave * S;
+            if (lane < L) {
+#pragma unroll
+                for (int z = 0; z < VEC; ++z) mine[kbase + z] = accd[z];
+                if (sub == 0) {
+                    mine[L * VEC] = gwd;
+                    mine[L * VEC + 1] = s2d;
+                }
+            }
+            __syncthreads();
+            valid = wave == 0;
+#pragma unroll
+            for (int w = 1; w < FM_WAVES; ++w) {  // wavefront 0 is the one that adds
+#pragma unroll
+                for (int z = 0; z < VEC; ++z) accd[z] += sh[w * S + kbase + z];
+                gwd += sh[w * S + L * VEC];
+                s2d += sh[w * S + L * VEC + 1];
+            }
+        }
+        valid = valid && lane < L;
+#pragma unroll
+        for (int z = 0; z < VEC; ++z) acc[z] = (float)accd[z];
+        gw = (float)gwd;
+        s2 = (float)s2d;
+    }
+    if (valid) finish_column<VEC, L, true>(A, j, sub, kbase, kact, acc, gw, s2, c);
+}
+
 // LDS-staged kernel for the tile items; false if the tile does not fit in LDS for this K
 // (the caller then runs the items through k_cols).
 template <int L>
@@ -802,6 +896,31 @@ int launch_cols_t(fm_matrix* m, const ColArgs& A, bool update, hipStream_t st)
         (A.lambda_w != 0.f || A.lambda_v != 0.f || !update || A.dV != nullptr) && A.lazy_last == nullptr;
     ColArgs Am = A;
     if (!need_empty || A.ptr != nullptr) Am.mark = nullptr;  // marks are only set when a kernel will clear them
+    if constexpr (L < FM_WIDE_GROUP) {
+        if (A.whole && A.nchunks == 0 && update) {
+            Am.blk_lin = (A.nlong + FM_WAVES - 1) / FM_WAVES;
+            Am.blk_short = (A.nshort + per - 1) / per;
+            const int64_t sums = A.epi.on ? std::max<int64_t>(A.epi.nsums, 1) : 0;
+            const int64_t grid = A.nbig + Am.blk_lin + Am.blk_short + sums;
+            if (grid > 0x7fffffffLL) return fm_fail(m, FM_ERANGE, "column grid too large");
+            if (grid > 0) {
+                ProfScope ps(m, st, FMK_COLS);
+                hipLaunchKernelGGL((k_cols_whole<VEC, L, PACKED>), dim3((unsigned)grid), dim3(FM_BLOCK), 0, st, Am);
+                FM_HIP(m, hipGetLastError());
+            }
+            if (A.epi.on && A.epi.nsums > 0) {  // added up by now
+                Am.nlong = Am.nvlong = 0;
+                ProfScope ps(m, st, FMK_COLS_FINISH);
+                hipLaunchKernelGGL((k_cols_finish<VEC, L, true>), dim3(1), dim3(FM_BLOCK), 0, st, Am);
+                FM_HIP(m, hipGetLastError());
+            }
+            if (need_empty && A.ptr == nullptr && A.D > 0) {
+                ProfScope ps(m, st, FMK_COLS);
+                FM_TRY((launch_empty<VEC>(m, Am, true, st)));
+            }
+            return FM_OK;
+        }
+    }
     if (A.nchunks == 0) {  // else a dense pass has left the partial sums of every column
         // LDS-staged items go to a side stream, so that the LDS-bound kernel overlaps the memory-bound one (not while
         // per-kernel timing is on: each kernel is then timed alone on the launch stream)

@@ -86,6 +86,11 @@ struct FmCheck {
 constexpr int FM_CHECK_BLOCKS = 512;
 constexpr size_t FM_PINNED_DOUBLES = 8 + FM_CHECK_BLOCKS * sizeof(FmCheck) / sizeof(double);
 
+// Columns of a stratum or batch hold at most as many entries as a row block (or batch) has rows.  Up to FM_WHOLE_ROWS a
+// column is summed at once, by a wavefront, or by a workgroup from FM_WHOLE_WAVE entries on.
+constexpr int64_t FM_WHOLE_ROWS = 2048;
+constexpr int32_t FM_WHOLE_WAVE = 256;
+
 // Work items for columns longer than `seg` entries (of one matrix, or of all strata
 // concatenated).  Offsets in item_beg are global offsets into the entry arrays.  Items of
 // a column are numbered consecutively (long_first); partial sums live at the item id.
@@ -117,6 +122,12 @@ struct LongIndex {
     int32_t* vlong = nullptr;       // [nvlong] indices into long_col of columns with > vlong items
     int64_t nvlong = 0;
     std::vector<int64_t> h_vlong_off;  // per stratum: where its part of vlong starts (the full matrix: all of it)
+    // strata and batches of at most FM_WHOLE_ROWS rows: the long columns as they are, for k_cols_whole
+    bool whole = false;
+    int64_t* long_beg = nullptr;    // [nlong] first entry
+    int32_t* long_len = nullptr;    // [nlong] number of entries
+    int32_t* big = nullptr;         // indices into long_col of columns with more than FM_WHOLE_WAVE entries
+    std::vector<int64_t> h_big_off;  // per stratum
 };
 
 struct ProfRec {
@@ -411,6 +422,12 @@ struct ColArgs {
     int32_t nt;                    // gathers of rows that are not used again soon carry the non-temporal hint
     int32_t big;                   // the gathered array is larger than FM_BUF_BYTES
     FmEpilogue epi;
+    // strata and batches of few rows: long columns summed whole (k_cols_whole)
+    int32_t whole;
+    const int64_t* long_beg;
+    const int32_t* long_len;
+    const int32_t* big_cols;       // the nbig of them that a workgroup sums
+    int64_t nbig;
     const int32_t* vlong;          // nullable: long columns finished by a whole workgroup
     int64_t nvlong;
     int32_t vlong_items;           // threshold that defines vlong

@@ -402,3 +402,46 @@ def test_dense_kernels_at_the_edges_of_their_tiles(N, D, K):
         assert_close(d_V.cpu().numpy().reshape(D, K), oV, "V")
         assert abs(d_w0.item() - o0) <= 1e-4 * max(abs(o0), 1e-2)
         m.close()
+
+
+@pytest.mark.parametrize("N", [4096, 4098])  # blocks of 2,048 rows, the most whose columns are summed whole, and of one more
+@pytest.mark.parametrize("K", [1, 2, 4, 6, 8, 16, 24, 28, 32, 64])  # every lane count, packed and planar rows
+def test_long_columns_of_strata_and_batches_summed_whole(N, K):
+    """Columns whose parts in the two row blocks have lengths around the item, the wavefront's and the workgroup's: strata,
+    and batches with the bias step in the same launch."""
+    from types import SimpleNamespace
+    from paper_2004_13940_amd import binding as B
+    rng = np.random.default_rng(8100 + N + K)
+    lengths = [0, 1, 31, 32, 33, 64, 127, 128, 129, 255, 256, 257, 300, 511, 1024, 1025, 2047, 2048]
+    half, D = N // 2, 2 * len(lengths)
+    mask = np.zeros((N, D), bool)
+    for t, n in enumerate(lengths):
+        mask[rng.choice(half, n, replace=False), 2 * t] = True
+        mask[half + rng.choice(N - half, lengths[-1 - t], replace=False), 2 * t] = True
+        mask[half + rng.choice(N - half, n, replace=False), 2 * t + 1] = True
+    rowptr = np.concatenate([[0], np.cumsum(mask.sum(1))]).astype(np.int64)
+    col = np.nonzero(mask)[1].astype(np.int32)
+    wl = SimpleNamespace(N=N, D=D, K=K, rowptr=rowptr, col=col, val=rng.standard_normal(len(col)).astype(np.float32),
+                         y=np.where(rng.random(N) < 0.5, 1.0, -1.0).astype(np.float32), w0=np.float32(0.1),
+                         w=(rng.standard_normal(D) * 0.2).astype(np.float32),
+                         V=(rng.standard_normal((D, K)) * 0.2 / np.sqrt(K)).astype(np.float32), loss=O.LOSS_LOGISTIC,
+                         lambda_w=0.01, lambda_v=0.02, eta=0.5, loss_scale=1.0 / N, update_w0=1)
+    print("columns summed whole", N, K, flush=True)
+    X = O.make_matrix(N, D, rowptr, col, wl.val)
+    p = B.make_params(K, wl.loss, wl.lambda_w, wl.lambda_v, wl.eta, wl.loss_scale, 1)
+    host = (float(wl.w0), wl.w.astype(np.float64), wl.V.astype(np.float64))
+    m = B.Matrix(N, D, rowptr, col, wl.val)
+    m.fm_build_csc()
+    m.fm_partition(2)
+    run_stratified_epochs(B, wl, m, p, X, (*dev_params(wl.w0, wl.w, wl.V), to_dev(wl.y)), host, 1, check_strata=True)
+    m.fm_partition_batches(2)
+    d_w0, d_w, d_V = dev_params(wl.w0, wl.w, wl.V)
+    # a batch is scored before its columns take the regulariser steps they postponed: eta lambda below what is compared
+    p = B.make_params(K, wl.loss, 1e-5, 2e-5, wl.eta, wl.loss_scale, 1)
+    m.fm_minibatch_epoch(p, to_dev(wl.y), d_w0, d_w, d_V)
+    o0, ow, oV, _ = O.minibatch_epoch(X, wl.y, *host, B=2, update_w0=True, reg_share=True, loss=wl.loss, s=1.0 / N,
+                                      lambda_w=1e-5, lambda_v=2e-5, eta=0.5)
+    assert_close(d_w.cpu().numpy(), ow, "w")
+    assert_close(d_V.cpu().numpy().reshape(D, K), oV, "V")
+    assert abs(d_w0.item() - o0) <= 1e-4 * max(abs(o0), 1e-2)
+    m.close()
