@@ -560,7 +560,7 @@ static int ensure_ws(fm_matrix* m, int32_t K)
                                             std::max<int64_t>(m->lbatch.nitems, m->D * chunks));
     FM_TRY(fm_dev_alloc(m, (void**)&m->part,
                         (size_t)std::max<int64_t>(items, 1) * (size_t)fm_part_stride(K) * sizeof(float)));
-    FM_TRY(fm_dev_alloc(m, (void**)&m->row_part, (size_t)std::max<int64_t>(std::max<int64_t>(fm_rows_grid(m->N, K), chunks), 1) * 2 * sizeof(float)));
+    FM_TRY(fm_dev_alloc(m, (void**)&m->row_part, (size_t)std::max<int64_t>(std::max<int64_t>(fm_rows_max_grid(m, m->N, K), chunks), 1) * 2 * sizeof(float)));
     if (m->P > 0) {
         FM_TRY(fm_dev_alloc(m, (void**)&m->dV, D * K * sizeof(float)));
         FM_TRY(fm_dev_alloc(m, (void**)&m->dwn, D * sizeof(float2)));
@@ -652,7 +652,7 @@ static int half_copy(fm_matrix* m, const fm_params* p, const float* V, const _Fl
 // (loss, multiplier) pairs a forward pass over N rows leaves: one per workgroup
 static int64_t forward_pairs(const fm_matrix* m, const fm_params* p)
 {
-    return !p->half_gather && fm_dense_shape_ok(m, p->K) ? fm_dense_chunks(m->N, m->D, p->K) : fm_rows_grid(m->N, p->K);
+    return !p->half_gather && fm_dense_shape_ok(m, p->K) ? fm_dense_chunks(m->N, m->D, p->K) : fm_rows_grid(m, m->N, p->K);
 }
 
 // The sums over n pairs (or, single, n multipliers `stride` floats apart) as an epilogue.
@@ -1301,7 +1301,7 @@ extern "C" int fm_minibatch_epoch(fm_matrix* m, const fm_params* p, const float*
         A.packed = fm_cols_packed_mode(m, p->K);
         if (!dense) fill_long(m, A, m->lbatch, b, true);
         if (p->update_w0 && nb > 0) {
-            set_epilogue(m, A.epi, m->row_part, dense ? fm_dense_chunks(nb, m->D, p->K) : fm_rows_grid(nb, p->K), 0, false);
+            set_epilogue(m, A.epi, m->row_part, dense ? fm_dense_chunks(nb, m->D, p->K) : fm_rows_grid(m, nb, p->K), 0, false);
             if (dense) A.epi.nsums = 0;
             A.epi.w0 = w0;
             A.epi.eta = p->eta;

@@ -108,7 +108,6 @@ __device__ __forceinline__ T fm_wave_sum(T v)
 template <int L>
 __device__ __forceinline__ int fm_wave_max(int v)
 {
-    static_assert(L <= 16, "groups inside a row of 16 lanes");
     auto take = [&](int t) { v = t > v ? t : v; };
     if constexpr (L <= 1) take(fm_xor_lane<1>(v));
     if constexpr (L <= 2) take(fm_xor_lane<2>(v));
@@ -527,10 +526,11 @@ __device__ __forceinline__ void fm_slot_sums(const float (&mu)[U], const float (
 // 4.53 -> 4.20 ms).
 // The refresh of a stratum, whose runs are mostly shorter than a round, takes rounds of four or eight in fours.
 // kb: offset of the lane's slice in a row, valid for every lane.
-template <int VEC, int L, int KIND, int ADDR, int C = 16, int SMAX = 8, class Own, class SRC>
+// SP > 1: SP groups share a run, group `part` of them takes every SP-th stretch of C entries.
+template <int VEC, int L, int KIND, int ADDR, int C = 16, int SMAX = 8, int SP = 1, class Own, class SRC>
 __device__ __forceinline__ void fm_walk(const int32_t* __restrict__ idx, const float* __restrict__ val, int64_t beg,
                                         int len, const SRC* __restrict__ src, int64_t stride, int sub, int kb,
-                                        float (&acc)[VEC], float& gw, float& s2, Own&& own)
+                                        float (&acc)[VEC], float& gw, float& s2, Own&& own, int part = 0)
 {
     constexpr int U = C / L;
     static_assert(L < FM_WIDE_GROUP && C % L == 0 && ((SMAX == 8 && C == 16) || (SMAX == 4 && (C == 4 || C == 8))),
@@ -542,7 +542,7 @@ __device__ __forceinline__ void fm_walk(const int32_t* __restrict__ idx, const f
     int raw[U];
     float mu[U];
     auto fetch = [&](int at, int (&i)[U], float (&x)[U]) {
-        const int t = at + sub * U;
+        const int t = at + part * C + sub * U;
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             i[u] = -1;
@@ -559,13 +559,13 @@ __device__ __forceinline__ void fm_walk(const int32_t* __restrict__ idx, const f
         }
     };
     fetch(0, raw, mu);
-    int left = fm_wave_max<L>(len);
+    int left = fm_wave_max<L * SP>(len);
     if (left <= 0) return;
-    for (int at = 0;; at += C, left -= C) {
+    for (int at = 0;; at += C * SP, left -= C * SP) {
         int in[U];
         float mn[U];
-        const bool more = left > C;
-        if (more) fetch(at + C, in, mn);
+        const bool more = left > C * SP;
+        if (more) fetch(at + C * SP, in, mn);
         int ix[U];
         typename std::decay_t<Own>::T pre[U];
 #pragma unroll
@@ -584,7 +584,7 @@ __device__ __forceinline__ void fm_walk(const int32_t* __restrict__ idx, const f
 #pragma unroll
             for (int u = 0; u < U; ++u) mu[u] = own.use(pre[u], mu[u]);
         };
-        if (at < len) {
+        if (at + part * C < len) {
             bool done = false;
             if constexpr (SMAX == 8) {
                 if (left > 4) {

@@ -321,7 +321,10 @@ inline int32_t fm_rows_big(const fm_matrix* m, int32_t K)
 int fm_launch_rows(fm_matrix* m, const RowArgs& A, bool refresh, hipStream_t st);
 struct DenseArgs;
 void fm_dense_rows(const RowArgs& A, DenseArgs* E);  // the forward pass A as a dense one
-int64_t fm_rows_grid(int64_t N, int32_t K);
+constexpr int64_t FM_SPLIT_LANES = 1 << 21;  // see fm_rows_split
+int fm_rows_split(const fm_matrix* m, int64_t N, int32_t K, int lanes);
+int64_t fm_rows_grid(const fm_matrix* m, int64_t N, int32_t K);      // workgroups of a forward pass over N rows
+int64_t fm_rows_max_grid(const fm_matrix* m, int64_t N, int32_t K);  // ... and the most of one over a block of them
 // once per device, with that device current: resolves the address of the static scratch array of
 // fm_forward_noalloc (fm_noalloc.hip); called when a handle is created
 int fm_noalloc_init_device(fm_matrix* m);

@@ -54,7 +54,7 @@ extern "C" int fm_forward_noalloc(fm_matrix* m, const fm_params* p, const float*
     FM_HIP(m, hipGetDevice(&dev));
     if (dev < 0 || dev >= MAX_DEVICES || g_scratch_ptr[dev] == nullptr)
         return fm_fail(m, FM_ESTATE, "no static scratch on the current device (the handle was created on another one)");
-    const int64_t blocks = fm_rows_grid(m->N, p->K);
+    const int64_t blocks = fm_rows_grid(m, m->N, p->K);
     if (sums != nullptr && blocks > NOALLOC_MAX_BLOCKS)
         return fm_fail(m, FM_ERANGE, "N=%lld at K=%d needs %lld workgroups; the static scratch holds the sums of %lld",
                        (long long)m->N, p->K, (long long)blocks, (long long)NOALLOC_MAX_BLOCKS);

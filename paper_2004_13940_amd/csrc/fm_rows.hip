@@ -72,14 +72,28 @@ struct OwnRefresh {
     }
 };
 
-template <int VEC, int L, int MODE>
+// Sum over the groups of L lanes that share a row of LS lanes, on every lane.
+template <int VEC, int L, int LS>
+__device__ __forceinline__ void add_parts(float (&acc)[VEC])
+{
+    if constexpr (L < LS) {
+#pragma unroll
+        for (int z = 0; z < VEC; ++z) acc[z] += fm_xor_lane<L>(acc[z]);
+        add_parts<VEC, 2 * L, LS>(acc);
+    }
+}
+
+// SP > 1 (forward, up to eight lanes): SP groups of L lanes share a row and add up what each has of it.
+template <int VEC, int L, int MODE, int SP = 1>
 __global__ __launch_bounds__(FM_BLOCK, L >= FM_WIDE_GROUP && is_refresh(MODE) ? 8 : 1) void k_rows(const RowArgs A)
 {
-    constexpr int R = FM_WAVE / L;  // rows per wavefront
+    constexpr int LS = L * SP;       // lanes per row
+    constexpr int R = FM_WAVE / LS;  // rows per wavefront
     const int lane = threadIdx.x & (FM_WAVE - 1);
     const int wave = threadIdx.x / FM_WAVE;
     const int sub = lane & (L - 1);
-    const int grp = lane / L;
+    const int grp = lane / LS;
+    const int part = lane / L % SP;
     const int64_t slot = (int64_t)blockIdx.x * (FM_WAVES * R) + wave * R + grp;
     const bool valid = slot < A.N;
     // Every lane loads, of the last row where its own is past the end: without branches the loads of a stage are all on
@@ -113,10 +127,13 @@ __global__ __launch_bounds__(FM_BLOCK, L >= FM_WIDE_GROUP && is_refresh(MODE) ? 
             OwnScore own{FmOwnArray<1>(A.w, 1), 0.f};
             float unused = 0.f;
             if constexpr (is_half(MODE))
-                fm_walk<VEC, L, FM_WALK_SCORE, addr_of(MODE)>(A.col, A.val, beg, len, A.Vh, K, sub, kb, acc, unused, q_acc, own);
+                fm_walk<VEC, L, FM_WALK_SCORE, addr_of(MODE), 16, 8, SP>(A.col, A.val, beg, len, A.Vh, K, sub, kb, acc, unused,
+                                                                         q_acc, own, part);
             else
-                fm_walk<VEC, L, FM_WALK_SCORE, addr_of(MODE)>(A.col, A.val, beg, len, A.V, K, sub, kb, acc, unused, q_acc, own);
+                fm_walk<VEC, L, FM_WALK_SCORE, addr_of(MODE), 16, 8, SP>(A.col, A.val, beg, len, A.V, K, sub, kb, acc, unused,
+                                                                         q_acc, own, part);
             a_acc = own.a;
+            add_parts<VEC, L, LS>(acc);
         } else {
             const float* __restrict__ w = A.w;
             auto own = [&](int c, float x) {
@@ -176,11 +193,11 @@ __global__ __launch_bounds__(FM_BLOCK, L >= FM_WIDE_GROUP && is_refresh(MODE) ? 
         float pair = 0.f;
 #pragma unroll
         for (int z = 0; z < VEC; ++z) pair += acc[z] * acc[z];
-        const float a_i = fm_group_sum<L>(a_acc);
-        const float q_i = fm_group_sum<L>(q_acc);
+        const float a_i = fm_group_sum<LS>(a_acc);
+        const float q_i = fm_group_sum<LS>(q_acc);
         pair = fm_group_sum<L>(pair);
         const float yh = A.w0[0] + a_i + 0.5f * (pair - q_i);
-        if (valid) {
+        if (valid && part == 0) {
             if (sub == 0) {
                 if (A.yhat != nullptr) A.yhat[row] = yh;
                 if (A.y != nullptr) {
@@ -272,7 +289,7 @@ __global__ __launch_bounds__(FM_BLOCK, L >= FM_WIDE_GROUP && is_refresh(MODE) ? 
     if constexpr (!is_refresh(MODE)) {
         if (A.eval_part != nullptr) {  // sums of losses, squared errors and correct signs of the block's rows
             __shared__ double she[3 * FM_WAVES];
-            fm_eval_wave(valid && sub == 0, yh_i, y_i, l_i, lane, she + 3 * wave);
+            fm_eval_wave(valid && sub == 0 && part == 0, yh_i, y_i, l_i, lane, she + 3 * wave);
             __syncthreads();
             if (threadIdx.x < 3) {
                 double t = 0.0;
@@ -287,14 +304,26 @@ __global__ __launch_bounds__(FM_BLOCK, L >= FM_WIDE_GROUP && is_refresh(MODE) ? 
 template <int VEC, int L>
 int launch_rows_t(fm_matrix* m, const RowArgs& A, bool refresh, hipStream_t st)
 {
-    constexpr int R = FM_WAVE / L;
-    const int64_t grid = (A.N + FM_WAVES * R - 1) / (FM_WAVES * R);
+    const int split = refresh ? 1 : fm_rows_split(m, A.N, A.K, L);
+    const int64_t per = FM_WAVES * (FM_WAVE / (L * split));
+    const int64_t grid = (A.N + per - 1) / per;
     if (grid <= 0) return FM_OK;
     if (grid > 0x7fffffffLL) return fm_fail(m, FM_ERANGE, "row grid too large");
     ProfScope ps(m, st, refresh ? FMK_ROWS_REFRESH : FMK_ROWS_FORWARD);
     constexpr bool W = L >= FM_WIDE_GROUP;  // wide groups use 64-bit addresses throughout: one variant
     auto launch = [&](auto mode) {
-        hipLaunchKernelGGL((k_rows<VEC, L, decltype(mode)::value>), dim3((unsigned)grid), dim3(FM_BLOCK), 0, st, A);
+        constexpr int M = decltype(mode)::value;
+        if constexpr (!W && (M == MODE_FORWARD || M == MODE_FORWARD_HALF)) {
+            if (split == 2) {
+                hipLaunchKernelGGL((k_rows<VEC, L, M, 2>), dim3((unsigned)grid), dim3(FM_BLOCK), 0, st, A);
+                return;
+            }
+            if (split == 4) {
+                hipLaunchKernelGGL((k_rows<VEC, L, M, 4>), dim3((unsigned)grid), dim3(FM_BLOCK), 0, st, A);
+                return;
+            }
+        }
+        hipLaunchKernelGGL((k_rows<VEC, L, M>), dim3((unsigned)grid), dim3(FM_BLOCK), 0, st, A);
     };
     if (refresh) {
         if (A.big)
@@ -441,12 +470,32 @@ bool fm_shape_for_K(int32_t K, int* vec, int* lanes)
     return true;
 }
 
-int64_t fm_rows_grid(int64_t N, int32_t K)
+// Lane groups that share a row of a forward pass over N rows.  A row is a chain of rounds of 16 entries, which more groups
+// shorten; that pays while the launch stays small (up to 2^21 lanes, four times what the chip holds at once)
+// and as long as it halves the rounds: evaluation of text-like rows of 60 entries, 2e5 rows, K=16 117 us
+// alone, 107 in two groups; 1e5 rows, K=8 64.4 and 55.7; click-style rows of 39 entries (3 rounds or 2), 6e4 rows, K=16 34.7
+// and 37.5.
+int fm_rows_split(const fm_matrix* m, int64_t N, int32_t K, int lanes)
+{
+    if (lanes >= FM_WIDE_GROUP || m->N <= 0 || fm_rows_big(m, K) != 0) return 1;
+    const int64_t row = m->nnz / m->N;  // entries of a row on average
+    int sp = 1;
+    auto rounds = [&](int s) { return (row + 16 * s - 1) / (16 * s); };
+    while (sp < 4 && N * lanes * 2 * sp <= FM_SPLIT_LANES && 2 * rounds(2 * sp) <= rounds(sp)) sp *= 2;
+    return sp;
+}
+
+int64_t fm_rows_grid(const fm_matrix* m, int64_t N, int32_t K)
 {
     int vec, lanes;
     if (!fm_shape_for_K(K, &vec, &lanes)) return 0;
-    const int64_t per = (int64_t)FM_WAVES * (FM_WAVE / lanes);
+    const int64_t per = (int64_t)FM_WAVES * (FM_WAVE / (lanes * fm_rows_split(m, N, K, lanes)));
     return (N + per - 1) / per;
+}
+
+int64_t fm_rows_max_grid(const fm_matrix* m, int64_t N, int32_t K)
+{
+    return std::max<int64_t>(fm_rows_grid(m, N, K), FM_SPLIT_LANES / FM_BLOCK + 1);
 }
 
 void fm_dense_rows(const RowArgs& A, DenseArgs* E)

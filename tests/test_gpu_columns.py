@@ -445,3 +445,49 @@ def test_long_columns_of_strata_and_batches_summed_whole(N, K):
     assert_close(d_V.cpu().numpy().reshape(D, K), oV, "V")
     assert abs(d_w0.item() - o0) <= 1e-4 * max(abs(o0), 1e-2)
     m.close()
+
+
+@pytest.mark.parametrize("row", [16, 17, 33, 50, 64, 65, 130])  # around the rounds of one, two and four groups
+@pytest.mark.parametrize("K,half", [(1, 0), (2, 0), (4, 1), (6, 0), (8, 0), (16, 0), (16, 1), (24, 0)])  # every lane count
+def test_forward_of_rows_shared_by_lane_groups(row, K, half):
+    """Few rows of about `row` entries, shared by one, two or four lane groups; empty, short and twice as long rows among
+    them.  Scores, aggregates, the sums of the loss and the gradient step that follow from them."""
+    import torch
+    from paper_2004_13940_amd import binding as B
+    rng = np.random.default_rng(8200 + 10 * row + K)
+    N, D = 203, 2 * row + 5
+    lens = np.clip(rng.integers(row - 2, row + 3, N), 0, D)
+    lens[::11], lens[5::17], lens[7::23] = 0, 1, 2 * row
+    mask = np.zeros((N, D), bool)
+    for i in range(N):
+        mask[i, rng.choice(D, lens[i], replace=False)] = True
+    rowptr = np.concatenate([[0], np.cumsum(lens)]).astype(np.int64)
+    col = np.nonzero(mask)[1].astype(np.int32)
+    val = rng.standard_normal(len(col)).astype(np.float32)
+    y = np.where(rng.random(N) < 0.5, 1.0, -1.0).astype(np.float32)
+    w0, w = np.float32(0.1), (rng.standard_normal(D) * 0.2).astype(np.float32)
+    V = (rng.standard_normal((D, K)) * 0.1).astype(np.float32)
+    print("rows shared by lane groups", row, K, half, flush=True)
+    X = O.make_matrix(N, D, rowptr, col, val)
+    m = B.Matrix(N, D, rowptr, col, val)
+    p = B.make_params(K, O.LOSS_LOGISTIC, 0.01, 0.02, 0.5, 1.0 / N, half_gather=half)
+    Vr = V.astype(np.float16).astype(np.float32) if half else V
+    a, G, q, yhat = O.forward(X, float(w0), w, Vr)
+    l, r = O.loss_multiplier(O.LOSS_LOGISTIC, 1.0 / N, yhat, y)
+    want = dict(yhat=yhat, a=a, G=G, q=q, r=r)
+    d_w0, d_w, d_V = dev_params(w0, w, V)
+    d_y = to_dev(y)
+    out = {k: torch.full((N * (K if k == "G" else 1),), float("nan"), device="cuda") for k in want}
+    loss_sum = m.fm_forward(p, d_y, d_w0, d_w, d_V, want_loss=True, **out)
+    for k in want:
+        assert_close(out[k].cpu().numpy().reshape(np.shape(want[k])), want[k], k)
+    assert abs(loss_sum - l.sum()) <= 1e-5 * l.sum()
+    met = m.fm_evaluate(p, d_y, d_w0, d_w, d_V)
+    assert abs(met["rmse"] - np.sqrt(np.mean((yhat - y) ** 2))) <= 1e-5 * met["rmse"]
+    m.fm_build_csc()
+    m.fm_sgd_epoch(p, d_y, d_w0, d_w, d_V)
+    g0, gw, gV = O.gradient(X, r, G, w, V, 0.01, 0.02)
+    assert_close(d_w.cpu().numpy(), w - 0.5 * gw, "w")
+    assert_close(d_V.cpu().numpy().reshape(D, K), V - 0.5 * gV, "V")
+    assert abs(d_w0.item() - (0.1 - 0.5 * g0)) <= 1e-5
+    m.close()
