@@ -731,7 +731,14 @@ static int objective_pass(fm_matrix* m, const fm_params* p, const float* y, cons
     FM_TRY(run_forward(m, p, y, w0, w, V, nullptr, nullptr, nullptr, nullptr, nullptr, mode, true, st));
     FmEpilogue E;
     set_epilogue(m, E, m->row_part, forward_pairs(m, p), 0, false);
-    FM_TRY(fm_reg_partials(m, w, m->D, V, m->D * (int64_t)p->K, &E.regs, &E.nregs, st));
+    if (m->D * ((int64_t)p->K + 1) <= FM_EPI_REG) {
+        E.reg_w = w;
+        E.reg_V = V;
+        E.reg_nw = m->D;
+        E.reg_nV = m->D * (int64_t)p->K;
+    } else {
+        FM_TRY(fm_reg_partials(m, w, m->D, V, m->D * (int64_t)p->K, &E.regs, &E.nregs, st));
+    }
     E.host = m->h_scal;
     FM_TRY(fm_run_epilogue(m, E, st));
     return read_objective(m, p, objective, st);
@@ -1091,14 +1098,35 @@ extern "C" int fm_stratified_step(fm_matrix* m, const fm_params* p, int32_t s, c
 }
 
 // The bias step from the multipliers as they stand in the aggregate rows.
-static int stratified_bias_step(fm_matrix* m, const fm_params* p, float* w0, hipStream_t st)
+static void set_bias_step(fm_matrix* m, const fm_params* p, float* w0, FmEpilogue& E)
 {
     const FmAux x = fm_aux_layout(m, p->K);
-    FmEpilogue E;
     set_epilogue(m, E, x.r, m->N, x.ss, true);
     E.w0 = w0;
     E.eta = p->eta;
+}
+
+static int stratified_bias_step(fm_matrix* m, const fm_params* p, float* w0, hipStream_t st)
+{
+    FmEpilogue E;
+    set_bias_step(m, p, w0, E);
     return fm_run_epilogue(m, E, st);
+}
+
+// lazy_last is zero when an epoch starts: it is made so with the structures, and the flush of an epoch leaves it so.  Only
+// what follows an epoch that could not be enqueued to its end clears it.  `sound`, for lazy_clear once the epoch is enqueued:
+// a clearing that is only captured has not happened yet.
+static int clear_lazy(fm_matrix* m, hipStream_t st, bool* sound)
+{
+    *sound = true;
+    if (!m->lazy_clear) {
+        hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+        FM_HIP(m, hipStreamIsCapturing(st, &capture));
+        *sound = capture == hipStreamCaptureStatusNone;
+        FM_TRY(fm_fill_i32(m, m->lazy_last, m->D, 0, st));
+    }
+    m->lazy_clear = false;
+    return FM_OK;
 }
 
 extern "C" int fm_stratified_end(fm_matrix* m, const fm_params* p, float* w0, void* hip_stream)
@@ -1119,14 +1147,14 @@ static int enqueue_stratified_epoch(fm_matrix* m, const fm_params* p, const floa
                                     bool lazy, hipStream_t st)
 {
     FM_TRY(run_forward(m, p, y, w0, w, V, nullptr, nullptr, nullptr, nullptr, nullptr, 2, false, st));
-    if (lazy) FM_TRY(fm_fill_i32(m, m->lazy_last, m->D, 0, st));
     for (int32_t s = 0; s < m->P; ++s) FM_TRY(stratified_step(m, p, s, y, w0, w, V, lazy, st));
-    if (lazy) {
+    if (lazy) {  // the sums of the bias step beside it
         ColArgs F;
         strat_col_args(m, p, m->P, w, V, true, F);
+        if (p->update_w0) set_bias_step(m, p, w0, F.epi);
         FM_TRY(fm_launch_cols_flush(m, F, st));
-    }
-    if (p->update_w0) {
+        if (F.epi.nsums > 0) FM_TRY(fm_run_epilogue_final(m, F.epi, st));
+    } else if (p->update_w0) {
         FM_TRY(stratified_bias_step(m, p, w0, st));
     }
     return FM_OK;
@@ -1211,6 +1239,8 @@ extern "C" int fm_stratified_epoch(fm_matrix* m, const fm_params* p, const float
     // 32 strata or more the replay pays even when the strata are large: 2 % on the click-style and the hashed workload)
     const bool small = m->P >= 32 || (m->nnz / m->P < (int64_t(1) << 20) && m->P >= 16);
     bool done = false;
+    bool sound = true;
+    if (lazy) FM_TRY(clear_lazy(m, st, &sound));
     if (!m->prof && (gmode == 2 || (gmode == 1 && small)) && graph_ready(m)) {
         const int rc = replay_stratified_epoch(m, p, y, w0, w, V, lazy, st);
         if (rc == FM_OK)
@@ -1219,6 +1249,7 @@ extern "C" int fm_stratified_epoch(fm_matrix* m, const fm_params* p, const float
             return rc;
     }
     if (!done) FM_TRY(enqueue_stratified_epoch(m, p, y, w0, w, V, lazy, st));
+    if (lazy) m->lazy_clear = sound;
     m->aux_full = true;
     m->aux_held = true;
     return objective != nullptr ? objective_pass(m, p, y, w0, w, V, 2, objective, st) : FM_OK;
@@ -1243,7 +1274,8 @@ extern "C" int fm_minibatch_epoch(fm_matrix* m, const fm_params* p, const float*
     // a column without entries in a batch only takes the regulariser's step there: postponed
     // until the column next has entries, or the epoch ends
     const bool lazy = m->opt.lazy_reg;
-    if (lazy) FM_TRY(fm_fill_i32(m, m->lazy_last, m->D, 0, st));
+    bool sound = true;
+    if (lazy) FM_TRY(clear_lazy(m, st, &sound));
     auto col_args = [&](int32_t b, ColArgs& A) {
         base_col_args(m, p, A);
         A.w = w;
@@ -1313,6 +1345,7 @@ extern "C" int fm_minibatch_epoch(fm_matrix* m, const fm_params* p, const float*
         ColArgs F;
         col_args(m->B, F);
         FM_TRY(fm_launch_cols_flush(m, F, st));
+        m->lazy_clear = sound;
     }
     return objective != nullptr ? objective_pass(m, p, y, w0, w, V, 1, objective, st) : FM_OK;
 }

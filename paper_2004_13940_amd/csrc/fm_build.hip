@@ -1323,7 +1323,7 @@ static int partition_impl(fm_matrix* m, int32_t P, const int32_t* place, hipStre
     FM_HIP(m, hipMemcpy(m->d_rho, h_rho.data(), (size_t)P * sizeof(float), hipMemcpyHostToDevice));
     FM_TRY(fm_dev_alloc(m, (void**)&m->d_rb, (size_t)(P + 1) * sizeof(int64_t)));
     FM_HIP(m, hipMemcpy(m->d_rb, m->h_rb.data(), (size_t)(P + 1) * sizeof(int64_t), hipMemcpyHostToDevice));
-    FM_TRY(fm_ensure_lazy(m));
+    FM_TRY(fm_ensure_lazy(m, st));
     if (place != nullptr) {
         FM_TRY(fm_dev_alloc(m, (void**)&m->d_place, (size_t)m->D * sizeof(int32_t)));
         FM_HIP(m, hipMemcpy(m->d_place, place, (size_t)m->D * sizeof(int32_t), hipMemcpyHostToDevice));
@@ -1375,10 +1375,13 @@ static int partition_impl(fm_matrix* m, int32_t P, const int32_t* place, hipStre
     return FM_OK;
 }
 
-int fm_ensure_lazy(fm_matrix* m)
+int fm_ensure_lazy(fm_matrix* m, hipStream_t st)
 {
     if (m->lazy_last != nullptr) return FM_OK;
-    return fm_dev_alloc(m, (void**)&m->lazy_last, (size_t)std::max<int64_t>(m->D, 1) * sizeof(int32_t));
+    FM_TRY(fm_dev_alloc(m, (void**)&m->lazy_last, (size_t)std::max<int64_t>(m->D, 1) * sizeof(int32_t)));
+    FM_TRY(fm_fill_i32(m, m->lazy_last, m->D, 0, st));  // the callers wait for the stream
+    m->lazy_clear = true;
+    return FM_OK;
 }
 
 extern "C" int fm_partition_batches(fm_matrix* m, int32_t B, void* hip_stream)
@@ -1398,7 +1401,7 @@ extern "C" int fm_partition_batches(fm_matrix* m, int32_t B, void* hip_stream)
     FM_HIP(m, hipMemcpy(m->d_brho, h_rho.data(), (size_t)B * sizeof(float), hipMemcpyHostToDevice));
     FM_TRY(fm_dev_alloc(m, (void**)&m->d_bb, (size_t)(B + 1) * sizeof(int64_t)));
     FM_HIP(m, hipMemcpy(m->d_bb, m->h_bb.data(), (size_t)(B + 1) * sizeof(int64_t), hipMemcpyHostToDevice));
-    FM_TRY(fm_ensure_lazy(m));
+    FM_TRY(fm_ensure_lazy(m, st));
     if (m->col_mark == nullptr) {
         FM_TRY(fm_dev_alloc(m, (void**)&m->col_mark, (size_t)m->D * sizeof(int32_t)));
         FM_HIP(m, hipMemsetAsync(m->col_mark, 0, (size_t)m->D * sizeof(int32_t), st));

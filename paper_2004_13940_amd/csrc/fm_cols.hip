@@ -429,7 +429,8 @@ __global__ __launch_bounds__(FM_BLOCK) void k_cols_empty(const ColArgs A)
 }
 
 // The postponed regulariser steps of every column, strata lazy_last[j] .. A.s-1; one group of LE
-// lanes per column, consecutive columns in consecutive groups.
+// lanes per column, consecutive columns in consecutive groups.  Leaves lazy_last at zero for the next epoch.  The
+// workgroups behind the columns: the epilogue's.
 template <int VEC, int LE>
 __global__ __launch_bounds__(FM_BLOCK) void k_cols_flush(const ColArgs A)
 {
@@ -438,9 +439,19 @@ __global__ __launch_bounds__(FM_BLOCK) void k_cols_flush(const ColArgs A)
     const int wave = threadIdx.x / FM_WAVE;
     const int sub = lane & (LE - 1);
     const int grp = lane / LE;
+    const int64_t cols = (A.D + FM_WAVES * R - 1) / (FM_WAVES * R);
+    if (blockIdx.x >= cols) {
+        __shared__ double sh[FM_WAVES];
+        if (A.epi.nsums > 0)
+            fm_epi_partial<FM_BLOCK>(A.epi, (int)(blockIdx.x - cols), sh);
+        else
+            fm_epi_final<FM_BLOCK>(A.epi, sh);
+        return;
+    }
     const int64_t j = (int64_t)blockIdx.x * (FM_WAVES * R) + wave * R + grp;
     if (j >= A.D) return;  // whole groups leave together
     const int32_t t0 = A.lazy_last[j];
+    if (sub == 0) A.lazy_last[j] = 0;
     if (t0 >= A.s) return;
     const int32_t qb = column_class(A, j);
     float fv, fw;
@@ -852,7 +863,7 @@ template <int VEC, int LE>
 int launch_flush_l(fm_matrix* m, const ColArgs& A, hipStream_t st)
 {
     const int64_t per = (int64_t)FM_WAVES * (FM_WAVE / LE);
-    const int64_t grid = (A.D + per - 1) / per;
+    const int64_t grid = (A.D + per - 1) / per + (A.epi.on ? std::max<int64_t>(A.epi.nsums, 1) : 0);
     if (grid > 0x7fffffffLL) return fm_fail(m, FM_ERANGE, "column grid too large");
     ProfScope ps(m, st, FMK_COLS);
     hipLaunchKernelGGL((k_cols_flush<VEC, LE>), dim3((unsigned)grid), dim3(FM_BLOCK), 0, st, A);

@@ -84,9 +84,13 @@ __device__ __forceinline__ void fm_epi_final(const FmEpilogue& E, double* sh)
             q0 += E.regs[2 * i];
             q1 += E.regs[2 * i + 1];
         }
+    if (E.reg_w != nullptr) {
+        for (int64_t i = threadIdx.x; i < E.reg_nw; i += T) q0 += (double)E.reg_w[i] * (double)E.reg_w[i];
+        for (int64_t i = threadIdx.x; i < E.reg_nV; i += T) q1 += (double)E.reg_V[i] * (double)E.reg_V[i];
+    }
     const double loss = fm_block_sum<T>(s0, sh);
     const double rsum = fm_block_sum<T>(s1, sh);
-    if (E.regs != nullptr) {
+    if (E.regs != nullptr || E.reg_w != nullptr) {
         q0 = fm_block_sum<T>(q0, sh);
         q1 = fm_block_sum<T>(q1, sh);
     }

@@ -164,6 +164,7 @@ struct fm_matrix {
     int64_t* d_rb = nullptr;       // [P+1] row block bounds
     int64_t* d_bb = nullptr;       // [B+1] batch bounds
     int32_t* lazy_last = nullptr;  // [D] see ColArgs::lazy_last
+    bool lazy_clear = false;       // it is zero when the next epoch starts: the flush of the last one left it so
     // Per-stratum matrices: the entries of X ordered by (stratum, row, column) in s_col/s_val and by
     // (stratum, column, row) in s_row/s_cval.  No pointer array over all P*N rows or P*D columns: only
     // the rows (columns) that have an entry in a stratum are listed, with the offset of their entries.
@@ -285,7 +286,7 @@ int fm_build_long_index(fm_matrix* m, const int64_t* ptr, const int32_t* ids, co
 int fm_build_full_index(fm_matrix* m, int32_t K, hipStream_t st);
 void fm_tile_shape(const fm_matrix* m, int32_t K, int* tile_rows, int* tile_min, int* tile_seg);
 int fm_item_length(int64_t entries);  // of a launch over so many entries
-int fm_ensure_lazy(fm_matrix* m);  // allocates lazy_last on first use
+int fm_ensure_lazy(fm_matrix* m, hipStream_t st);  // allocates and clears lazy_last on first use
 
 // ---- pass kernels (fm_rows.hip / fm_cols.hip / fm_reduce.hip) ----
 struct RowArgs {
@@ -349,6 +350,8 @@ struct FmEpilogue {
     int32_t nsums;
     const double* regs;    // nullable: [2 * nregs] partial pairs (|w|^2, |V|^2)
     int32_t nregs;
+    const float *reg_w, *reg_V;  // nullable: the parameters themselves instead, while nothing else of the launch steps them
+    int64_t reg_nw, reg_nV;
     float* w0;             // nullable: takes the bias step
     float eta;
     float* grad_w0;        // nullable
@@ -356,6 +359,7 @@ struct FmEpilogue {
     double* host;          // nullable, pinned: loss, sum of the multipliers, |w|^2, |V|^2
 };
 constexpr int FM_EPI_DIRECT = 2048;  // values the epilogue sums itself; above, workgroups of the kernel before do
+constexpr int64_t FM_EPI_REG = 1 << 15;  // parameters whose squares the epilogue adds up itself
 constexpr int FM_EPI_CHUNK = 4096;   // ... one for so many values
 inline int fm_epi_nsums(int64_t n)
 {
@@ -472,6 +476,7 @@ int fm_reg_partials(fm_matrix* m, const float* w, int64_t nw, const float* V, in
                     hipStream_t st);
 int fm_reduce_eval(fm_matrix* m, const double* part, int64_t n, double* out3, double* tmp, hipStream_t st);
 int fm_run_epilogue(fm_matrix* m, const FmEpilogue& E, hipStream_t st);  // as kernels of its own
+int fm_run_epilogue_final(fm_matrix* m, const FmEpilogue& E, hipStream_t st);  // ... where another launch left the partial sums
 int fm_fill_i32(fm_matrix* m, int32_t* x, int64_t n, int32_t v, hipStream_t st);
 
 // lanes per row/column group and floats per lane for a given K; false if K unsupported

@@ -195,6 +195,11 @@ int fm_run_epilogue(fm_matrix* m, const FmEpilogue& E, hipStream_t st)
         hipLaunchKernelGGL(k_epi_sums, dim3((unsigned)E.nsums), dim3(FM_BLOCK), 0, st, E);
         FM_HIP(m, hipGetLastError());
     }
+    return fm_run_epilogue_final(m, E, st);
+}
+
+int fm_run_epilogue_final(fm_matrix* m, const FmEpilogue& E, hipStream_t st)
+{
     hipLaunchKernelGGL(k_epi_final, dim3(1), dim3(RED_THREADS), 0, st, E);
     FM_HIP(m, hipGetLastError());
     return FM_OK;

@@ -491,3 +491,56 @@ def test_forward_of_rows_shared_by_lane_groups(row, K, half):
     assert_close(d_V.cpu().numpy().reshape(D, K), V - 0.5 * gV, "V")
     assert abs(d_w0.item() - (0.1 - 0.5 * g0)) <= 1e-5
     m.close()
+
+
+def test_postponed_steps_start_from_zero_in_every_epoch():
+    """Epochs with postponed steps follow one another on one handle: strata, batches, strata captured by the caller and
+    replayed between eager epochs, and with the steps taken at once in between.  Each meets the same epoch on a new handle."""
+    import torch
+    from paper_2004_13940_amd import binding as B
+    rng = np.random.default_rng(8300)
+    N, D, K, P = 90, 70, 8, 6
+    mask = rng.random((N, D)) < 0.06
+    rowptr = np.concatenate([[0], np.cumsum(mask.sum(1))]).astype(np.int64)
+    col = np.nonzero(mask)[1].astype(np.int32)
+    val = rng.standard_normal(len(col)).astype(np.float32)
+    y = to_dev(np.where(rng.random(N) < 0.5, 1.0, -1.0).astype(np.float32))
+    w, V = (rng.standard_normal(D) * 0.2).astype(np.float32), (rng.standard_normal((D, K)) * 0.2).astype(np.float32)
+    p = B.make_params(K, O.LOSS_LOGISTIC, 0.05, 0.1, 0.5, 1.0 / N, 1)
+
+    def handle():
+        m = B.Matrix(N, D, rowptr, col, val)
+        m.fm_build_csc()
+        m.fm_partition(P)
+        m.fm_partition_batches(P)
+        return m
+
+    m = handle()
+    m.fm_set_option(B.FM_OPT_GRAPH, 0)
+    dev = dev_params(np.float32(0.1), w, V)
+    new = dev_params(np.float32(0.1), w, V)
+    first = [t.clone() for t in dev]
+    m.fm_stratified_epoch(p, y, *dev)  # the workspace is there before the capture
+    for a, b in zip(dev, first):
+        a.copy_(b)
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        m.fm_stratified_epoch(p, y, *dev)
+    for step in ("strata", "batches", "replay", "strata", "at once", "replay", "batches", "replay", "strata"):
+        h = handle()
+        h.fm_set_option(B.FM_OPT_GRAPH, 0)
+        for q, s, args in ((m, step, dev), (h, "strata" if step == "replay" else step, new)):
+            if s == "replay":
+                g.replay()
+            elif s == "batches":
+                q.fm_minibatch_epoch(p, y, *args)
+            else:
+                q.fm_set_option(B.FM_OPT_LAZY_REG, 0 if s == "at once" else 1)
+                q.fm_stratified_epoch(p, y, *args)
+                q.fm_set_option(B.FM_OPT_LAZY_REG, 1)
+        torch.cuda.synchronize()
+        h.close()
+        for a, b, what in zip(dev, new, ("w0", "w", "V")):
+            assert torch.equal(a, b), f"{what} after {step}"
+    m.close()
