@@ -270,7 +270,8 @@ __device__ __forceinline__ void store_partial(const ColArgs& A, int64_t it, int 
 // entries; one group per column, which finishes it), or one of the epilogue's that add up the examples.  The kinds touch
 // disjoint data; as launches of their own they needed a fork and a join of streams, which cost a stratum of the text-like
 // workload as much as its columns did.  Items come first: they are the longest runs.
-// With an order array, workgroup b takes its items from list b % FM_XCDS (the XCD it runs on).
+// With an order array, workgroup b takes its items from list b % FM_XCDS (the XCD it runs on).  Items of a batch are in row
+// order; with xcd_runs every XCD takes one eighth of that order in a run, and so of the batch's rows.
 template <int VEC, int L, bool UPDATE, int PACKED>
 __global__ __launch_bounds__(FM_BLOCK, L >= FM_WIDE_GROUP ? 8 : 1) void k_cols(const ColArgs A)
 {
@@ -299,7 +300,9 @@ __global__ __launch_bounds__(FM_BLOCK, L >= FM_WIDE_GROUP ? 8 : 1) void k_cols(c
     ColState<VEC> c = {};
     if (items) {
         if (b >= A.blk_lists) {
-            const int64_t rel = (b - A.blk_lists) * (FM_WAVES * R) + slot;
+            int64_t lb = b - A.blk_lists;
+            if (A.xcd_runs) lb = lb % FM_XCDS * (A.blk_lin / FM_XCDS) + lb / FM_XCDS;
+            const int64_t rel = lb * (FM_WAVES * R) + slot;
             once = false;
             if (rel < A.lin_count) {
                 const int64_t pos = A.lin_base + rel;
@@ -960,6 +963,7 @@ int launch_cols_t(fm_matrix* m, const ColArgs& A, bool update, hipStream_t st)
                     Am.lin_base = A.list_off[FM_XCDS];
                     Am.lin_count = ntile_items;
                     Am.blk_lin = (ntile_items + per - 1) / per;
+                    if (A.xcd_runs) Am.blk_lin = (Am.blk_lin + FM_XCDS - 1) / FM_XCDS * FM_XCDS;
                 }
             } else {
                 Am.blk_lists = (A.nitems + per - 1) / per;

@@ -425,6 +425,7 @@ struct ColArgs {
     int64_t tile_rows, ntiles;     // dense-ish columns: items sorted by row tile, after the lists
     const int64_t* tile_ptr;
     int64_t lin_base, lin_count;   // positions of `order` that are taken in sequence (tile items that are not staged; all of a stratum or batch)
+    int32_t xcd_runs;              // the lin items in FM_XCDS runs, one per XCD, and not dealt out one workgroup after the other
     int64_t blk_lists, blk_lin, blk_short;  // workgroups of k_cols per role, in this order; then epi.nsums for the sums
     int32_t nt;                    // gathers of rows that are not used again soon carry the non-temporal hint
     int32_t big;                   // the gathered array is larger than FM_BUF_BYTES
