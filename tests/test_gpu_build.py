@@ -87,3 +87,33 @@ def test_trim_gives_the_blocks_of_closed_handles_back():
     assert torch.cuda.mem_get_info()[0] >= free - (8 << 20)  # the runtime keeps chunks of its own
     assert kept.fm_evaluate(p, y[:500].clone(), w0, w, V) == before
     kept.close()
+
+
+@pytest.mark.parametrize("N", [493_447, 493_448, 600_001])  # 16 columns: just below and from 64 MB on, where the upload is staged
+def test_large_matrices_arrive_whole(N):
+    """Two threads open one each at the same time; a second round takes the blocks that the first left."""
+    import threading
+    from paper_2004_13940_amd import binding as B
+    D = 16
+    rowptr, col = np.arange(N + 1, dtype=np.int64) * D, np.tile(np.arange(D, dtype=np.int32), N)
+    vals = [np.random.default_rng(k).random((N, D), dtype=np.float32) for k in range(2)]
+    print("large upload", N, flush=True)
+    wrong = []
+
+    def check(k):
+        m = B.Matrix(N, D, rowptr, col, vals[k].ravel())
+        m.fm_build_csc()
+        colptr, row, val = m.fm_get_csc()
+        m.close()
+        if not (np.array_equal(colptr, np.arange(D + 1) * N) and np.array_equal(row.reshape(D, N), np.broadcast_to(np.arange(N), (D, N)))
+                and np.array_equal(val.reshape(D, N), vals[k].T)):
+            wrong.append(k)
+
+    for _ in range(2):
+        threads = [threading.Thread(target=check, args=(k,)) for k in range(2)]
+        for t in threads:
+            t.start()
+        for t in threads:
+            t.join()
+    assert wrong == []
+    B.fm_trim()
