@@ -251,20 +251,45 @@ __device__ __forceinline__ int64_t owner_of(const int64_t* __restrict__ ptr, int
     return lo;
 }
 
-// The owners of OWN_E consecutive entries from e on: one search, then a few steps from one to the next (a long run of
-// empty owners is searched again).  f(entry, owner) for those below n.
+// Eight consecutive values of an array of n from e, a multiple of eight, on: 16 bytes at a time where all are there.
 constexpr int OWN_E = 8;
-template <class F>
-__device__ __forceinline__ void for_owners(const int64_t* __restrict__ ptr, int64_t nown, int64_t e, int64_t n, F&& f)
+template <class T>
+__device__ __forceinline__ void load_eight(const T* __restrict__ p, int64_t e, int64_t n, uint32_t (&v)[OWN_E])
 {
-    if (e >= n) return;
+    static_assert(sizeof(T) == 4, "words");
+    if (e + OWN_E <= n) {
+        const uint4 a = *reinterpret_cast<const uint4*>(p + e), b = *reinterpret_cast<const uint4*>(p + e + 4);
+        v[0] = a.x; v[1] = a.y; v[2] = a.z; v[3] = a.w; v[4] = b.x; v[5] = b.y; v[6] = b.z; v[7] = b.w;
+    } else {
+#pragma unroll
+        for (int i = 0; i < OWN_E; ++i) v[i] = e + i < n ? (uint32_t)p[e + i] : 0u;
+    }
+}
+__device__ __forceinline__ void store_eight(uint32_t* __restrict__ p, int64_t e, int64_t n, const uint32_t (&v)[OWN_E])
+{
+    if (e + OWN_E <= n) {
+        *reinterpret_cast<uint4*>(p + e) = make_uint4(v[0], v[1], v[2], v[3]);
+        *reinterpret_cast<uint4*>(p + e + 4) = make_uint4(v[4], v[5], v[6], v[7]);
+    } else {
+#pragma unroll
+        for (int i = 0; i < OWN_E; ++i)
+            if (e + i < n) p[e + i] = v[i];
+    }
+}
+
+// The owners of the entries e .. e + OWN_E - 1 below n, e < n: one search, then a few steps from one to the next (a long run
+// of empty owners is searched again).
+__device__ __forceinline__ void owners_of(const int64_t* __restrict__ ptr, int64_t nown, int64_t e, int64_t n,
+                                          uint32_t (&own)[OWN_E])
+{
     int64_t k = owner_of(ptr, nown, e), next = ptr[k + 1];
-    for (int i = 0; i < OWN_E && e + i < n; ++i) {
-        for (int step = 0; next <= e + i; ++step) {
+#pragma unroll
+    for (int i = 0; i < OWN_E; ++i) {
+        for (int step = 0; e + i < n && next <= e + i; ++step) {
             k = step < 4 ? k + 1 : owner_of(ptr, nown, e + i);
             next = ptr[k + 1];
         }
-        f(e + i, k);
+        own[i] = (uint32_t)k;
     }
 }
 
@@ -272,7 +297,10 @@ __global__ __launch_bounds__(256) void k_owners(const int64_t* __restrict__ ptr,
                                                 uint32_t* __restrict__ out)
 {
     const int64_t e = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) * OWN_E;
-    for_owners(ptr, nown, e, n, [&](int64_t i, int64_t k) { out[i] = (uint32_t)k; });
+    if (e >= n) return;
+    uint32_t own[OWN_E];
+    owners_of(ptr, nown, e, n, own);
+    store_eight(out, e, n, own);
 }
 
 // ptr[j] = number of sorted keys smaller than j, j = 0..ncols
@@ -298,26 +326,29 @@ __global__ __launch_bounds__(256) void k_stratum_keys(const int64_t* __restrict_
                                                       uint32_t* __restrict__ keys, uint32_t* __restrict__ maj)
 {
     const int64_t e = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) * OWN_E;
-    for_owners(major, nmajor, e, n, [&](int64_t t, int64_t mj) {
-        const int64_t mn = minor[t];
-        const int64_t i = by_rows == 1 ? mj : mn;
-        const int64_t j = by_rows == 1 ? mn : mj;
+    if (e >= n) return;
+    uint32_t own[OWN_E], mn[OWN_E], key[OWN_E];
+    load_eight(minor, e, n, mn);
+    owners_of(major, nmajor, e, n, own);
+#pragma unroll
+    for (int u = 0; u < OWN_E; ++u) {
+        const int64_t i = by_rows == 1 ? own[u] : mn[u];
+        const int64_t j = by_rows == 1 ? mn[u] : own[u];
         const int32_t p = fm_block_of(i, N, P);
-        int32_t s;
-        if (by_rows == 2) {  // row batches: the key is the row block alone
-            s = p;
-        } else {
+        int32_t s = p;  // row batches: the key is the row block alone
+        if (by_rows != 2) {
             s = (place != nullptr ? place[j] : fm_block_of(j, D, P)) - p;
             if (s < 0) s += P;
         }
-        keys[t] = (uint32_t)s;
-        maj[t] = (uint32_t)mj;
-    });
+        key[u] = (uint32_t)s;
+    }
+    store_eight(keys, e, n, key);
+    store_eight(maj, e, n, own);
 }
 
 // The (stratum, major) pairs of the entries in stratum order are runs: entry i opens one where it differs from the entry
 // before.  Pass 0 counts a tile's runs, pass 1 lists them (tile_cnt then scanned): major index and first entry.
-constexpr int HD_E = 8;
+constexpr int HD_E = OWN_E;
 constexpr int HD_TILE = 256 * HD_E;
 __global__ __launch_bounds__(256) void k_heads(const uint32_t* __restrict__ keys, const uint32_t* __restrict__ maj, int64_t n,
                                                int pass, int64_t* __restrict__ tile_cnt, int32_t* __restrict__ nz_major,
@@ -325,17 +356,16 @@ __global__ __launch_bounds__(256) void k_heads(const uint32_t* __restrict__ keys
 {
     __shared__ int64_t sh[2][SCAN_T];
     const int64_t base = (int64_t)blockIdx.x * HD_TILE + (int64_t)threadIdx.x * HD_E;
-    uint32_t mj[HD_E];
+    uint32_t mj[HD_E], ky[HD_E];
     unsigned heads = 0;
     if (base < n) {
         uint32_t pk = base > 0 ? keys[base - 1] : 0u, pm = base > 0 ? maj[base - 1] : 0u;
+        load_eight(keys, base, n, ky);
+        load_eight(maj, base, n, mj);
 #pragma unroll
         for (int u = 0; u < HD_E; ++u) {
-            const int64_t i = base + u < n ? base + u : n - 1;
-            const uint32_t k = keys[i];
-            mj[u] = maj[i];
-            if (base + u < n && (i == 0 || k != pk || mj[u] != pm)) heads |= 1u << u;
-            pk = k;
+            if (base + u < n && (base + u == 0 || ky[u] != pk || mj[u] != pm)) heads |= 1u << u;
+            pk = ky[u];
             pm = mj[u];
         }
     }
