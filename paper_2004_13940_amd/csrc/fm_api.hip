@@ -924,9 +924,13 @@ extern "C" int fm_evaluate(fm_matrix* m, const fm_params* p, const float* y, con
     FM_TRY(ensure_ws(m, p->K));
     metrics[0] = metrics[1] = metrics[2] = 0.0;
     if (m->N == 0) return FM_OK;
-    // the sums per row block go to the start of the aggregate storage, which holds nothing afterwards
+    // The sums per row block go to the start of the aggregate storage, which holds nothing afterwards; those of few blocks
+    // straight to pinned memory, where they are added up without another launch (49,990 x 22, K=4: 24.9 -> 23.4 us).
     m->aux_held = false;
     m->aux_full = false;
+    const int64_t blocks = forward_pairs(m, p);
+    const bool direct = blocks <= FM_CHECK_BLOCKS;
+    static_assert(sizeof(FmCheck) == 3 * sizeof(double), "the block results of the CSR check leave room for as many triples");
     RowArgs A;
     memset(&A, 0, sizeof(A));
     A.N = m->N;
@@ -941,15 +945,20 @@ extern "C" int fm_evaluate(fm_matrix* m, const fm_params* p, const float* y, con
     A.y = y;
     A.gs = p->K;
     A.ss = 1;
-    A.eval_part = reinterpret_cast<double*>(m->aux);
+    A.eval_part = direct ? m->h_scal + 8 : reinterpret_cast<double*>(m->aux);
     A.loss = p->loss;
     A.s = 1.f;
     FM_TRY(half_copy(m, p, V, &A.Vh, st));
     const bool dense = A.Vh == nullptr && fm_dense_shape_ok(m, p->K);
     if (dense) A.dense_D = (int32_t)m->D;
     FM_TRY(fm_launch_rows(m, A, false, st));
-    FM_TRY(fm_reduce_eval(m, A.eval_part, forward_pairs(m, p), m->h_scal, m->scal + 8, st));
+    if (!direct) FM_TRY(fm_reduce_eval(m, A.eval_part, blocks, m->h_scal, m->scal + 8, st));
     FM_HIP(m, hipStreamSynchronize(st));
+    if (direct) {
+        for (int c = 0; c < 3; ++c) m->h_scal[c] = 0.0;
+        for (int64_t b = 0; b < blocks; ++b)
+            for (int c = 0; c < 3; ++c) m->h_scal[c] += A.eval_part[3 * b + c];
+    }
     const double n = (double)m->N;
     metrics[0] = m->h_scal[0] / n;
     metrics[1] = sqrt(m->h_scal[1] / n);
