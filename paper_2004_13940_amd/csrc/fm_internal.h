@@ -309,6 +309,7 @@ struct RowArgs {
     double* eval_part;  // nullable: [3*gridDim] sums of losses, squared errors and correct signs per block
     int32_t big;          // what is gathered (V, its half copy or dV, dwn) is larger than FM_BUF_BYTES
     int32_t dense_D;      // forward: > 0 when `val` is a dense row-major N x dense_D matrix (col is then not read)
+    int32_t xcd_runs;     // refresh: the rows in FM_XCDS runs, one per XCD, and not dealt out one workgroup after the other
     const int32_t* rows;  // nullable: the launch covers rows[0..N) instead of rows 0..N-1, and
                           // rowptr[k], rowptr[k+1] bound the entries of rows[k]
     int32_t loss;

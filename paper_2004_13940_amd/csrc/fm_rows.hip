@@ -94,7 +94,11 @@ __global__ __launch_bounds__(FM_BLOCK, L >= FM_WIDE_GROUP && is_refresh(MODE) ? 
     const int sub = lane & (L - 1);
     const int grp = lane / LS;
     const int part = lane / L % SP;
-    const int64_t slot = (int64_t)blockIdx.x * (FM_WAVES * R) + wave * R + grp;
+    int64_t blk = blockIdx.x;
+    if constexpr (is_refresh(MODE)) {
+        if (A.xcd_runs) blk = blk % FM_XCDS * (gridDim.x / FM_XCDS) + blk / FM_XCDS;
+    }
+    const int64_t slot = blk * (FM_WAVES * R) + wave * R + grp;
     const bool valid = slot < A.N;
     // Every lane loads, of the last row where its own is past the end: without branches the loads of a stage are all on
     // their way before the first is waited for.
@@ -306,8 +310,9 @@ int launch_rows_t(fm_matrix* m, const RowArgs& A, bool refresh, hipStream_t st)
 {
     const int split = refresh ? 1 : fm_rows_split(m, A.N, A.K, L);
     const int64_t per = FM_WAVES * (FM_WAVE / (L * split));
-    const int64_t grid = (A.N + per - 1) / per;
+    int64_t grid = (A.N + per - 1) / per;
     if (grid <= 0) return FM_OK;
+    if (refresh && A.xcd_runs) grid = (grid + FM_XCDS - 1) / FM_XCDS * FM_XCDS;
     if (grid > 0x7fffffffLL) return fm_fail(m, FM_ERANGE, "row grid too large");
     ProfScope ps(m, st, refresh ? FMK_ROWS_REFRESH : FMK_ROWS_FORWARD);
     constexpr bool W = L >= FM_WIDE_GROUP;  // wide groups use 64-bit addresses throughout: one variant
