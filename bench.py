@@ -295,7 +295,7 @@ def traffic_from(fetch_csv, write_csv, name):
             k = re.sub(r"^void ", "", k)
             acc.setdefault(k, []).append(float(row["Counter_Value"]))
         # per pass over the matrix: a pass launches k_cols twice when its short columns run on a side stream
-        passes = max([len(v) for k, v in acc.items() if re.search(r"^k_rows<.*, 0>", k)], default=0)
+        passes = max([len(v) for k, v in acc.items() if re.search(r"^k_rows<\d+, \d+, 0, \d+>", k)], default=0)
         return {k: sum(v) / (passes if passes and not k.startswith("k_probe") else len(v)) for k, v in acc.items()}
     fetch, write = per_kernel(fetch_csv, "FETCH_SIZE"), per_kernel(write_csv, "WRITE_SIZE")
     copy = [k for k in fetch if "k_probe_copy" in k]
@@ -303,7 +303,7 @@ def traffic_from(fetch_csv, write_csv, name):
         sys.exit("no k_probe_copy dispatch in the counter file: run bench.py with --copy-calibration")
     f_scale = (COPY_BYTES / 1024.0) / fetch[copy[0]]
     w_scale = (COPY_BYTES / 1024.0) / write[copy[0]]
-    groups = {"rows_forward": r"^k_rows<.*, 0>", "cols": r"^k_cols(_empty)?<", "cols_tile": r"^k_cols_tile<",
+    groups = {"rows_forward": r"^k_rows<\d+, \d+, 0, \d+>", "cols": r"^k_cols(_empty)?<", "cols_tile": r"^k_cols_tile<",
               "cols_finish": r"^k_cols_finish<", "reduce": r"^k_(reduce|reg|epi)_"}
     out = {"_kind": TRAFFIC_KIND, "_csrc_sha256": csrc_sha256(), "_fetch_scale": f_scale, "_write_scale": w_scale,
            "_copy_reads_KiB": fetch[copy[0]], "_copy_writes_KiB": write[copy[0]]}
