@@ -1271,17 +1271,16 @@ static int stratified_bias_step(fm_matrix* m, const fm_params* p, float* w0, hip
 }
 
 // lazy_last is zero when an epoch starts: it is made so with the structures, and the flush of an epoch leaves it so.  Only
-// what follows an epoch that could not be enqueued to its end clears it.  `sound`, for lazy_clear once the epoch is enqueued:
-// a clearing that is only captured has not happened yet.
+// what follows an epoch that could not be enqueued to its end clears it, and an epoch that a caller captures: its graph may
+// be replayed after such a one.  `sound`, for lazy_clear once the epoch is enqueued: a captured epoch has not run yet.
 static int clear_lazy(fm_matrix* m, hipStream_t st, bool* sound)
 {
-    *sound = true;
-    if (!m->lazy_clear) {
-        hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
-        FM_HIP(m, hipStreamIsCapturing(st, &capture));
-        *sound = capture == hipStreamCaptureStatusNone;
-        FM_TRY(fm_fill_i32(m, m->lazy_last, m->D, 0, st));
-    }
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    const bool known = hipStreamIsCapturing(st, &capture) == hipSuccess;
+    if (!known) (void)hipGetLastError();
+    const bool captured = !known || capture != hipStreamCaptureStatusNone;
+    *sound = !captured || m->lazy_clear;
+    if (captured || !m->lazy_clear) FM_TRY(fm_fill_i32(m, m->lazy_last, m->D, 0, st));
     m->lazy_clear = false;
     return FM_OK;
 }
