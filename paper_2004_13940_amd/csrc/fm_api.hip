@@ -796,7 +796,7 @@ static int half_copy(fm_matrix* m, const fm_params* p, const float* V, const _Fl
 // (loss, multiplier) pairs a forward pass over N rows leaves: one per workgroup
 static int64_t forward_pairs(const fm_matrix* m, const fm_params* p)
 {
-    return !p->half_gather && fm_dense_shape_ok(m, p->K) ? fm_dense_chunks(m->N, m->D, p->K) : fm_rows_grid(m, m->N, p->K);
+    return fm_dense_shape_ok(m, p->K) ? fm_dense_chunks(m->N, m->D, p->K) : fm_rows_grid(m, m->N, p->K);
 }
 
 // The sums over n pairs (or, single, n multipliers `stride` floats apart) as an epilogue.
@@ -853,9 +853,12 @@ static int forward_args(fm_matrix* m, const fm_params* p, const float* y, const 
     A.row_part = (want_sums && y != nullptr) ? m->row_part : nullptr;
     A.loss = p->loss;
     A.s = p->loss_scale;
-    FM_TRY(half_copy(m, p, V, &A.Vh, st));
-    const bool dense = A.Vh == nullptr && fm_dense_shape_ok(m, p->K);
-    if (dense) A.dense_D = (int32_t)m->D;
+    if (fm_dense_shape_ok(m, p->K)) {
+        A.dense_D = (int32_t)m->D;
+        A.dense_half = p->half_gather;
+    } else {
+        FM_TRY(half_copy(m, p, V, &A.Vh, st));
+    }
     return FM_OK;
 }
 
@@ -948,9 +951,12 @@ extern "C" int fm_evaluate(fm_matrix* m, const fm_params* p, const float* y, con
     A.eval_part = direct ? m->h_scal + 8 : reinterpret_cast<double*>(m->aux);
     A.loss = p->loss;
     A.s = 1.f;
-    FM_TRY(half_copy(m, p, V, &A.Vh, st));
-    const bool dense = A.Vh == nullptr && fm_dense_shape_ok(m, p->K);
-    if (dense) A.dense_D = (int32_t)m->D;
+    if (fm_dense_shape_ok(m, p->K)) {
+        A.dense_D = (int32_t)m->D;
+        A.dense_half = p->half_gather;
+    } else {
+        FM_TRY(half_copy(m, p, V, &A.Vh, st));
+    }
     FM_TRY(fm_launch_rows(m, A, false, st));
     if (!direct) FM_TRY(fm_reduce_eval(m, A.eval_part, blocks, m->h_scal, m->scal + 8, st));
     FM_HIP(m, hipStreamSynchronize(st));
@@ -1117,8 +1123,7 @@ extern "C" int fm_sgd_epoch(fm_matrix* m, const fm_params* p, const float* y, fl
     A.packed = fm_cols_packed_mode(m, p->K);
     A.w = w;
     A.V = V;
-    const bool half = R.Vh != nullptr && fm_dense_shape_ok(m, p->K);  // half-precision scores of a dense matrix
-    if (!dense && !half) fill_long(m, A, m->lfull, 0, false);
+    if (!dense) fill_long(m, A, m->lfull, 0, false);
     if (p->update_w0 || objective != nullptr) {
         set_epilogue(m, A.epi, m->row_part, forward_pairs(m, p), 0, false);
         if (dense) A.epi.nsums = 0;  // the pairs of this very launch: the finish adds them
@@ -1135,7 +1140,6 @@ extern "C" int fm_sgd_epoch(fm_matrix* m, const fm_params* p, const float* y, fl
         }
     }
     if (dense) FM_TRY(dense_step(m, R, objective != nullptr, A, st));
-    if (half) FM_TRY(dense_sums(m, A, st));
     FM_TRY(fm_launch_cols(m, A, true, st));
     return objective != nullptr ? read_objective(m, p, objective, st) : FM_OK;
 }
@@ -1466,12 +1470,13 @@ extern "C" int fm_minibatch_epoch(fm_matrix* m, const fm_params* p, const float*
             R.row_part = p->update_w0 ? m->row_part : nullptr;
             R.loss = p->loss;
             R.s = p->loss_scale;
-            FM_TRY(half_copy(m, p, V, &R.Vh, st));  // the factors as they stand
-            dense = R.Vh == nullptr && fm_dense_shape_ok(m, p->K);
+            dense = fm_dense_shape_ok(m, p->K);
             if (dense) {
                 R.dense_D = (int32_t)m->D;
+                R.dense_half = p->half_gather;
                 R.val = m->val + r0 * m->D;
             } else {
+                FM_TRY(half_copy(m, p, V, &R.Vh, st));  // the factors as they stand
                 FM_TRY(fm_launch_rows(m, R, false, st));
             }
         }

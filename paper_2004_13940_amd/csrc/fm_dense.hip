@@ -150,7 +150,9 @@ __global__ __launch_bounds__(FM_BLOCK, dense_per_cu(DB, KB)) void k_dense(const 
     if constexpr (FORWARD) {
         for (int e = threadIdx.x; e < DP * KP; e += FM_BLOCK) {
             const int j = e / KP, k = e % KP;
-            vl[e] = j < D && k < K ? A.V[j * K + k] : 0.f;
+            // half_gather: rounded here, no copy of V (evaluation of 1e6 x 64, K = 32: 387 us by the sparse kernel, 83 by this)
+            const float v = j < D && k < K ? A.V[j * K + k] : 0.f;
+            vl[e] = A.half ? (float)(_Float16)v : v;
         }
         __syncthreads();
         static_assert(FM_BLOCK / DP >= 4, "four threads to a column");

@@ -309,6 +309,7 @@ struct RowArgs {
     double* eval_part;  // nullable: [3*gridDim] sums of losses, squared errors and correct signs per block
     int32_t big;          // what is gathered (V, its half copy or dV, dwn) is larger than FM_BUF_BYTES
     int32_t dense_D;      // forward: > 0 when `val` is a dense row-major N x dense_D matrix (col is then not read)
+    int32_t dense_half;   // ... whose scores take V rounded to half precision (the kernel rounds it: no copy)
     int32_t xcd_runs;     // refresh: the rows in FM_XCDS runs, one per XCD, and not dealt out one workgroup after the other
     const int32_t* rows;  // nullable: the launch covers rows[0..N) instead of rows 0..N-1, and
                           // rowptr[k], rowptr[k+1] bound the entries of rows[k]
@@ -454,6 +455,7 @@ struct DenseArgs {
     int64_t nchunks;
     const float* X;  // row-major N x D
     const float *w0, *w, *V, *y;  // forward; y nullable
+    int32_t half;                 // forward: V rounded to half precision
     float *yhat, *a, *G, *q, *r;  // forward: nullable outputs; gradient alone: G and r are read
     int64_t gs, ss;               // floats between rows of G, of r, a, q
     int32_t whole_rows;           // forward: packed aggregate rows [G | r | a | q | pad] go out whole

@@ -520,6 +520,7 @@ void fm_dense_rows(const RowArgs& A, DenseArgs* E)
     E->w0 = A.w0;
     E->w = A.w;
     E->V = A.V;
+    E->half = A.dense_half;
     E->y = A.y;
     E->yhat = A.yhat;
     E->a = A.a;
@@ -537,7 +538,7 @@ void fm_dense_rows(const RowArgs& A, DenseArgs* E)
 
 int fm_launch_rows(fm_matrix* m, const RowArgs& A, bool refresh, hipStream_t st)
 {
-    if (!refresh && A.dense_D > 0 && A.Vh == nullptr) {
+    if (!refresh && A.dense_D > 0) {
         DenseArgs E;
         fm_dense_rows(A, &E);
         return A.N > 0 ? fm_launch_dense(m, E, FM_DENSE_FORWARD, st) : FM_OK;

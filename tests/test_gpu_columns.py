@@ -404,6 +404,38 @@ def test_dense_kernels_at_the_edges_of_their_tiles(N, D, K):
         m.close()
 
 
+@pytest.mark.parametrize("N,D,K", [(33, 5, 4), (4097, 33, 36), (40_003, 64, 32)])
+def test_half_gather_of_dense_tables(N, D, K):
+    """The dense kernel rounds the factors of the scores itself; the step is taken on the fp32 factors.  Metrics, scores and an
+    epoch against the oracle: its forward on the rounded factors, its gradient on the factors as they are."""
+    import torch
+    from paper_2004_13940_amd import binding as B
+    rng = np.random.default_rng(8050 + N)
+    rowptr, col = np.arange(N + 1, dtype=np.int64) * D, np.tile(np.arange(D, dtype=np.int32), N)
+    val = rng.standard_normal(N * D).astype(np.float32)
+    y = np.where(rng.random(N) < 0.5, 1.0, -1.0).astype(np.float32)
+    w0, w = np.float32(0.1), (rng.standard_normal(D) * 0.1).astype(np.float32)
+    V = (rng.standard_normal((D, K)) * 0.3 / np.sqrt(D * K)).astype(np.float32)
+    X = O.make_matrix(N, D, rowptr, col, val)
+    a, G, q, yhat = O.forward(X, float(w0), w, V.astype(np.float16).astype(np.float32))
+    _, r = O.loss_multiplier(O.LOSS_LOGISTIC, 1.0 / N, yhat, y)
+    _, gw, gV = O.gradient(X, r, G, w, V, 0.01, 0.02)
+    m = B.Matrix(N, D, rowptr, col, val)
+    p = B.make_params(K, O.LOSS_LOGISTIC, 0.01, 0.02, 0.5, 1.0 / N, half_gather=1)
+    d_w0, d_w, d_V = dev_params(w0, w, V)
+    d_y = to_dev(y)
+    out = torch.full((N,), float("nan"), device="cuda")
+    m.fm_forward(p, d_y, d_w0, d_w, d_V, yhat=out)
+    assert_close(out.cpu().numpy(), yhat, "yhat")
+    met = m.fm_evaluate(p, d_y, d_w0, d_w, d_V)
+    assert abs(met["rmse"] - np.sqrt(np.mean((yhat - y) ** 2))) <= 1e-5 * met["rmse"]
+    m.fm_build_csc()
+    m.fm_sgd_epoch(p, d_y, d_w0, d_w, d_V)
+    assert_close(d_w.cpu().numpy(), w - 0.5 * gw, "w")
+    assert_close(d_V.cpu().numpy().reshape(D, K), V - 0.5 * gV, "V")
+    m.close()
+
+
 @pytest.mark.parametrize("N", [4096, 4098])  # blocks of 2,048 rows, the most whose columns are summed whole, and of one more
 @pytest.mark.parametrize("K", [1, 2, 4, 6, 8, 16, 24, 28, 32, 64])  # every lane count, packed and planar rows
 def test_long_columns_of_strata_and_batches_summed_whole(N, K):
