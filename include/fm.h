@@ -298,7 +298,7 @@ int fm_set_tile_tuning(fm_matrix* m, int32_t tile_rows, int32_t min_per_tile, in
 
 /* Device memory in blocks of more than 1 MB that fm_destroy and the build calls give up is kept for the next handle on
  * the same device, at most 4 GiB per process; it goes back to the driver when an allocation of this library fails.
- * fm_build_csr of 64 MB and more copies through 32 MB of pinned host memory with three threads of its own, which end
+ * fm_build_csr of 64 MB and more copies through 32 MB of pinned host memory with four threads of its own, which end
  * before it returns; two such blocks per process are kept.
  * fm_trim gives all of it back at once, for programs whose other allocators need it.  It frees device memory, so it
  * must not be called while a stream is being captured; open handles are not touched. */

@@ -6,12 +6,11 @@
 #include <string.h>
 
 #include <algorithm>
-#include <atomic>
 #include <mutex>
-#include <thread>
 #include <utility>
 
 #include "fm_internal.h"
+#include "fm_upload.h"
 
 static thread_local std::string g_build_error;
 
@@ -144,145 +143,16 @@ void fm_dev_free(fm_matrix* m, void* p)
         (void)hipFree(p);
 }
 
-// Upload of large arrays from pageable host memory through a ring of pinned blocks: a few threads copy into the blocks while
-// the blocks before are on their way.  The runtime's own path for such memory moved 4e8 bytes at 30 GB/s, pinned memory
-// moves them at 57, and four threads copy at 65.  Opening 1.25e6 click-style rows, 16 strata and one epoch: 24.7 -> 19 ms.
-// A ring belongs to one upload at a time; up to RING_POOL of them are kept for the next, and fm_trim gives them back.
-namespace {
-constexpr size_t RING_BLOCK = size_t(4) << 20;
-constexpr int RING_THREADS = 4;
-constexpr int RING_SLOTS = 2 * RING_THREADS;
-constexpr size_t RING_POOL = 2;
-// From so many bytes on: 6.4e7 bytes take 2.2 ms on the runtime's path; below, starting the threads and filling the ring for
-// the first blocks is no longer small beside what is gained.
-constexpr size_t RING_MIN = size_t(64) << 20;
-
-struct UploadRing {
-    int device = 0;
-    char* block = nullptr;  // RING_SLOTS blocks of RING_BLOCK bytes
-    hipEvent_t done[RING_SLOTS] = {};
-    bool busy[RING_SLOTS] = {};
-};
-std::vector<UploadRing*> g_rings;
-
-void ring_destroy(UploadRing* r)
-{
-    if (r == nullptr) return;
-    for (hipEvent_t e : r->done)
-        if (e != nullptr) (void)hipEventDestroy(e);
-    if (r->block != nullptr) (void)hipHostFree(r->block);
-    delete r;
-}
-
-UploadRing* ring_take(int device)
-{
-    {
-        std::lock_guard<std::mutex> g(g_pool_lock);
-        for (size_t i = g_rings.size(); i-- > 0;)
-            if (g_rings[i]->device == device) {
-                UploadRing* r = g_rings[i];
-                g_rings.erase(g_rings.begin() + (ptrdiff_t)i);
-                return r;
-            }
-    }
-    UploadRing* r = new (std::nothrow) UploadRing();
-    if (r == nullptr) return nullptr;
-    r->device = device;
-    bool ok = hipHostMalloc((void**)&r->block, RING_SLOTS * RING_BLOCK) == hipSuccess;
-    for (hipEvent_t& e : r->done) ok = ok && hipEventCreateWithFlags(&e, hipEventDisableTiming) == hipSuccess;
-    if (ok) return r;
-    (void)hipGetLastError();
-    ring_destroy(r);
-    return nullptr;
-}
-
-// Its last copies have arrived.
-void ring_give(UploadRing* r)
-{
-    if (r == nullptr) return;
-    for (bool& b : r->busy) b = false;
-    {
-        std::lock_guard<std::mutex> g(g_pool_lock);
-        if (g_rings.size() < RING_POOL) {
-            try {
-                g_rings.push_back(r);
-                return;
-            } catch (...) {
-            }
-        }
-    }
-    ring_destroy(r);
-}
-
-struct UploadPart {
-    void* dev;
-    const void* host;
-    size_t bytes;
-};
-
-// Enqueues all copies on st; the host arrays have been read when it returns.  False: something failed, nothing is known
-// about the destination.
-bool ring_upload(UploadRing* r, const UploadPart* parts, int nparts, hipStream_t st)
-{
-    struct Chunk {
-        char* dev;
-        const char* host;
-        size_t bytes;
-    };
-    std::vector<Chunk> chunks;
-    std::atomic<size_t> next{0};
-    std::atomic<bool> ok{true};
-    auto work = [&](int t) {
-        if (hipSetDevice(r->device) != hipSuccess) ok = false;
-        for (int k = 0; ok; ++k) {
-            const size_t i = next.fetch_add(1);
-            if (i >= chunks.size()) break;
-            const int slot = 2 * t + k % 2;
-            char* block = r->block + (size_t)slot * RING_BLOCK;
-            bool good = !r->busy[slot] || hipEventSynchronize(r->done[slot]) == hipSuccess;
-            if (good) {
-                memcpy(block, chunks[i].host, chunks[i].bytes);
-                r->busy[slot] = true;
-                good = hipMemcpyAsync(chunks[i].dev, block, chunks[i].bytes, hipMemcpyHostToDevice, st) == hipSuccess &&
-                       hipEventRecord(r->done[slot], st) == hipSuccess;
-            }
-            if (!good) {
-                (void)hipGetLastError();
-                ok = false;
-            }
-        }
-    };
-    try {
-        for (int p = 0; p < nparts; ++p)
-            for (size_t o = 0; o < parts[p].bytes; o += RING_BLOCK)
-                chunks.push_back({(char*)parts[p].dev + o, (const char*)parts[p].host + o, std::min(RING_BLOCK, parts[p].bytes - o)});
-    } catch (...) {
-        return false;
-    }
-    std::vector<std::thread> threads;
-    try {
-        threads.reserve(RING_THREADS - 1);
-        for (int t = 1; t < RING_THREADS; ++t) threads.emplace_back(work, t);
-    } catch (...) {  // no thread to be had: those that run do the work
-    }
-    work(0);
-    for (std::thread& t : threads) t.join();
-    return ok;
-}
-}  // namespace
-
 extern "C" int fm_trim(void)
 {
     pool_drain();
     std::vector<std::pair<int, void*>> pinned;
-    std::vector<UploadRing*> rings;
     {
         std::lock_guard<std::mutex> g(g_pool_lock);
         pinned.swap(g_pinned);
-        rings.swap(g_rings);
     }
     for (const auto& b : pinned) (void)hipHostFree(b.second);
-    for (UploadRing* r : rings) ring_destroy(r);
+    fm_ring_trim();
     return FM_OK;
 }
 
@@ -446,14 +316,14 @@ extern "C" int fm_build_csr(int64_t N, int64_t D, int64_t nnz, const int64_t* ro
     if (rc == FM_OK) rc = fm_dev_alloc(m, (void**)&m->rowptr, pointers);
     if (rc == FM_OK) rc = fm_dev_alloc(m, (void**)&m->col, entries + pad);
     if (rc == FM_OK) rc = fm_dev_alloc(m, (void**)&m->val, entries + pad);
-    const UploadPart parts[3] = {{m->rowptr, rowptr, pointers}, {m->col, col, entries}, {m->val, val, entries}};
-    UploadRing* ring = rc == FM_OK && pointers + 2 * entries >= RING_MIN ? ring_take(m->device) : nullptr;
-    if (rc == FM_OK && !(ring != nullptr && ring_upload(ring, parts, 3, st))) {
-        auto copy = [&](const UploadPart& p) -> int {
+    const FmUploadPart parts[3] = {{m->rowptr, rowptr, pointers}, {m->col, col, entries}, {m->val, val, entries}};
+    FmUploadRing* ring = rc == FM_OK && pointers + 2 * entries >= FM_RING_MIN ? fm_ring_take(m->device) : nullptr;
+    if (rc == FM_OK && !(ring != nullptr && fm_ring_upload(ring, parts, 3, st))) {
+        auto copy = [&](const FmUploadPart& p) -> int {
             if (p.bytes > 0) FM_HIP(m, hipMemcpyAsync(p.dev, p.host, p.bytes, hipMemcpyHostToDevice, st));
             return FM_OK;
         };
-        for (const UploadPart& p : parts)
+        for (const FmUploadPart& p : parts)
             if (rc == FM_OK) rc = copy(p);
     }
     if (rc == FM_OK) rc = fm_dev_alloc(m, (void**)&m->scal, (8 + FM_REDUCE_TMP) * sizeof(double));
@@ -462,7 +332,7 @@ extern "C" int fm_build_csr(int64_t N, int64_t D, int64_t nnz, const int64_t* ro
     if (rc == FM_OK) rc = fm_check_csr(m, st, &valid);  // waits for the uploads
     if (ring != nullptr) {
         if (rc != FM_OK) (void)hipStreamSynchronize(st);
-        ring_give(ring);
+        fm_ring_give(ring);
     }
     if (!valid) {  // also where a step failed: what is wrong with the matrix itself is reported first
         const int bad = first_csr_error(N, D, nnz, rowptr, col);
