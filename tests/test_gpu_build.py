@@ -89,31 +89,31 @@ def test_trim_gives_the_blocks_of_closed_handles_back():
     kept.close()
 
 
+@pytest.mark.parametrize("per_thread", [0, 1])
 @pytest.mark.parametrize("N", [493_447, 493_448, 600_001])  # 16 columns: just below and from 64 MB on, where the upload is staged
-def test_large_matrices_arrive_whole(N):
-    """Two threads open one each at the same time; a second round takes the blocks that the first left."""
-    import threading
+def test_large_matrices_arrive_whole(N, per_thread):
+    """Two threads open one each at the same time, on the default stream or on hipStreamPerThread (handle 2); a second round
+    takes the blocks that the first left.  What a thread raises is raised here."""
+    from concurrent.futures import ThreadPoolExecutor
+    from types import SimpleNamespace
     from paper_2004_13940_amd import binding as B
     D = 16
     rowptr, col = np.arange(N + 1, dtype=np.int64) * D, np.tile(np.arange(D, dtype=np.int32), N)
     vals = [np.random.default_rng(k).random((N, D), dtype=np.float32) for k in range(2)]
-    print("large upload", N, flush=True)
-    wrong = []
+    stream = SimpleNamespace(cuda_stream=2) if per_thread else None
+    print("large upload", N, per_thread, flush=True)
 
     def check(k):
-        m = B.Matrix(N, D, rowptr, col, vals[k].ravel())
-        m.fm_build_csc()
+        m = B.Matrix(N, D, rowptr, col, vals[k].ravel(), stream=stream)
+        m.fm_build_csc(stream=stream)
         colptr, row, val = m.fm_get_csc()
         m.close()
-        if not (np.array_equal(colptr, np.arange(D + 1) * N) and np.array_equal(row.reshape(D, N), np.broadcast_to(np.arange(N), (D, N)))
-                and np.array_equal(val.reshape(D, N), vals[k].T)):
-            wrong.append(k)
+        assert np.array_equal(colptr, np.arange(D + 1) * N)
+        assert np.array_equal(row.reshape(D, N), np.broadcast_to(np.arange(N), (D, N)))
+        assert np.array_equal(val.reshape(D, N), vals[k].T)
+        return k
 
-    for _ in range(2):
-        threads = [threading.Thread(target=check, args=(k,)) for k in range(2)]
-        for t in threads:
-            t.start()
-        for t in threads:
-            t.join()
-    assert wrong == []
+    with ThreadPoolExecutor(2) as threads:
+        for _ in range(2):
+            assert list(threads.map(check, range(2))) == [0, 1]
     B.fm_trim()
