@@ -90,6 +90,18 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t fm_rsrc(const float* p, int64_
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(p), 0, (int)bytes, 0x20000);
 }
 
+// Byte offsets from the start of a tile of G (gs floats to a row) of value k of the rows that a lane's result registers hold.
+// All of it is in the offset that is compared with the range of the descriptor, so that a row past the end is out of range by
+// its own number (the scalar offset of a buffer access is not part of what the compiler promises to check).
+struct RowOffsets {
+    uint32_t base, row;  // a lane that takes no part: FM_BUF_NONE throughout, a sum past it could wrap
+    __device__ __forceinline__ RowOffsets(bool takes_part, int half, int k, int gs)
+        : base(takes_part ? (uint32_t)(4 * half * gs + k) * 4u : FM_BUF_NONE), row(takes_part ? (uint32_t)gs * 4u : 0u)
+    {
+    }
+    __device__ __forceinline__ int operator()(int v) const { return (int)(base + __umul24((uint32_t)c_row(v, 0), row)); }
+};
+
 template <int DB, int KB, int WHAT>
 __global__ __launch_bounds__(FM_BLOCK, dense_per_cu(DB, KB)) void k_dense(const DenseArgs A)
 {
@@ -135,10 +147,10 @@ __global__ __launch_bounds__(FM_BLOCK, dense_per_cu(DB, KB)) void k_dense(const 
 #pragma unroll
             for (int kb = 0; kb < KB; ++kb) {
                 const int k = kb * DT + ln % DT;
-                const uint32_t at = k < A.K ? (uint32_t)(ln / DT * 4 * (int)A.gs + k) * 4u : FM_BUF_NONE;
+                const RowOffsets at(k < A.K, ln / DT, k, (int)A.gs);
 #pragma unroll
                 for (int v = 0; v < 16; ++v)
-                    g_in[kb][v] = __int_as_float(__builtin_amdgcn_raw_buffer_load_b32(gr, (int)at, c_row(v, 0) * (int)A.gs * 4, 0));
+                    g_in[kb][v] = __int_as_float(__builtin_amdgcn_raw_buffer_load_b32(gr, at(v), 0, 0));
             }
         }
     };
@@ -186,9 +198,9 @@ __global__ __launch_bounds__(FM_BLOCK, dense_per_cu(DB, KB)) void k_dense(const 
         }
     };
     if constexpr (GRADIENT) add_up(true);
-    [[maybe_unused]] double sums[4] = {0.0, 0.0, 0.0, 0.0};  // loss, r, squared error, correct signs
+    [[maybe_unused]] double sum_lr = 0.0, sum_es = 0.0;  // lower half: loss, squared error; upper: r, correct signs
     const float w0 = FORWARD ? A.w0[0] : 0.f;
-    const bool want = A.row_part != nullptr || A.eval_part != nullptr;
+    const bool want = A.row_part != nullptr || (!GRADIENT && A.eval_part != nullptr);
     const uint32_t magic = ((1u << 20) + (uint32_t)D - 1) / (uint32_t)D;  // e / D = e magic >> 20 for e < 2^12, D <= 64
 #pragma unroll 1
     for (int64_t tid = t0; tid < t1; ++tid) {
@@ -275,23 +287,21 @@ __global__ __launch_bounds__(FM_BLOCK, dense_per_cu(DB, KB)) void k_dense(const 
             wave_sync();
             float l_i = 0.f, r_i = 0.f;
             if (A.y != nullptr) loss_and_multiplier(A.loss, A.s, yh, y_i, want, l_i, r_i);
-            if (lo >= nrows) r_i = 0.f;
+            if (lo >= nrows) l_i = r_i = 0.f;
+            sum_lr += (double)(half == 0 ? l_i : r_i);
+            if (!GRADIENT && A.eval_part != nullptr && lo < nrows) {
+                const double d = (double)yh - (double)y_i;
+                sum_es += half == 0 ? d * d : (yh >= 0.f ? 1.f : -1.f) == y_i ? 1.0 : 0.0;
+            }
             if (half == 0) {
                 tile[Lds::R + lo] = r_i;
                 tile[Lds::A + lo] = a_i;
                 tile[Lds::Q + lo] = q_i;
                 if (lo < nrows) {
-                    sums[0] += (double)l_i;
-                    sums[1] += (double)r_i;
-                    if (!GRADIENT && A.eval_part != nullptr) {
-                        const double d = (double)yh - (double)y_i;
-                        sums[2] += d * d;
-                        if ((yh >= 0.f ? 1.f : -1.f) == y_i) sums[3] += 1.0;
-                    }
-                    if (A.yhat != nullptr) A.yhat[mine] = yh;
+                    if (!GRADIENT && A.yhat != nullptr) A.yhat[mine] = yh;
                     if (!A.whole_rows) {
-                        if (A.a != nullptr) A.a[mine * A.ss] = a_i;
-                        if (A.q != nullptr) A.q[mine * A.ss] = q_i;
+                        if (!GRADIENT && A.a != nullptr) A.a[mine * A.ss] = a_i;
+                        if (!GRADIENT && A.q != nullptr) A.q[mine * A.ss] = q_i;
                         if (A.y != nullptr && A.r != nullptr) A.r[mine * A.ss] = r_i;
                     }
                 }
@@ -300,19 +310,18 @@ __global__ __launch_bounds__(FM_BLOCK, dense_per_cu(DB, KB)) void k_dense(const 
             // rows past the end are out of the descriptor's range: not stored
 #pragma unroll
             for (int kb = 0; kb < KB; ++kb) {
-                const int k = kb * DT + lo;
-                const uint32_t at = k < (A.whole_rows ? gs : K) ? (uint32_t)(4 * half * gs + k) * 4u : FM_BUF_NONE;
+                const int k = kb * DT + ln % DT;
+                const RowOffsets at(k < (A.whole_rows ? gs : K), half_t, k, gs);
                 if (A.whole_rows) {  // packed aggregate rows go out whole
 #pragma unroll
                     for (int v = 0; v < 16; ++v) {
                         const float z = behind[c_row(v, half)];
-                        __builtin_amdgcn_raw_buffer_store_b32(__float_as_int(k < K ? g[kb][v] : z), rows, (int)at,
-                                                              c_row(v, 0) * gs * 4, 0);
+                        __builtin_amdgcn_raw_buffer_store_b32(__float_as_int(k < K ? g[kb][v] : z), rows, at(v), 0, 0);
                     }
                 } else {
 #pragma unroll
                     for (int v = 0; v < 16; ++v)
-                        __builtin_amdgcn_raw_buffer_store_b32(__float_as_int(g[kb][v]), rows, (int)at, c_row(v, 0) * gs * 4, 0);
+                        __builtin_amdgcn_raw_buffer_store_b32(__float_as_int(g[kb][v]), rows, at(v), 0, 0);
                 }
             }
         } else {
@@ -348,6 +357,9 @@ __global__ __launch_bounds__(FM_BLOCK, dense_per_cu(DB, KB)) void k_dense(const 
             }
         }
     }  // tiles of this wavefront
+    int thread = threadIdx.x;  // formed anew, not kept over the loop: registers
+    asm volatile("" : "+v"(thread));
+    const int half_e = thread % FM_WAVE / 32, lo_e = thread % 32;
     if constexpr (GRADIENT) {
         add_up(false);
         // the wavefronts one after the other into one block of LDS, then whole rows of the partial sums
@@ -364,13 +376,13 @@ __global__ __launch_bounds__(FM_BLOCK, dense_per_cu(DB, KB)) void k_dense(const 
                 for (int v = 0; v < 16; ++v)
 #pragma unroll
                     for (int kb = 0; kb < KB; ++kb) {
-                        float* p = sum + (jb * DT + c_row(v, half)) * SP + kb * DT + lo;
+                        float* p = sum + (jb * DT + c_row(v, half_e)) * SP + kb * DT + lo_e;
                         *p = w == 0 ? all[jb][kb][v] : *p + all[jb][kb][v];
                     }
                 const float gt = all_gw[jb] + fm_xor_lane<32>(all_gw[jb]);
                 const float st = all_s2[jb] + fm_xor_lane<32>(all_s2[jb]);
-                if (half == 0) {
-                    float* p = sum + (jb * DT + lo) * SP + KP;
+                if (half_e == 0) {
+                    float* p = sum + (jb * DT + lo_e) * SP + KP;
                     p[0] = w == 0 ? gt : p[0] + gt;
                     p[1] = w == 0 ? st : p[1] + st;
                 }
@@ -391,14 +403,14 @@ __global__ __launch_bounds__(FM_BLOCK, dense_per_cu(DB, KB)) void k_dense(const 
     }
     if constexpr (FORWARD) {
         if (want) {
-            constexpr int NS = GRADIENT ? 2 : 4;
-#pragma unroll
-            for (int c = 0; c < NS; ++c) {
-                sums[c] = fm_wave_sum(sums[c]);
-                if (lane == 0) sh[wave * 4 + c] = sums[c];
+            sum_lr = fm_group_sum<32>(sum_lr);
+            if constexpr (!GRADIENT) sum_es = fm_group_sum<32>(sum_es);
+            if (lo_e == 0) {
+                sh[wave * 4 + half_e] = sum_lr;
+                if constexpr (!GRADIENT) sh[wave * 4 + 2 + half_e] = sum_es;
             }
             __syncthreads();
-            if (threadIdx.x < NS) {
+            if (threadIdx.x < (GRADIENT ? 2 : 4)) {
                 const int c = threadIdx.x;
                 double t = 0.0;
 #pragma unroll
@@ -455,6 +467,8 @@ int fm_launch_dense(fm_matrix* m, const DenseArgs& A, int what, hipStream_t st)
 {
     if (A.D < 1 || A.D > FM_DENSE_MAX || A.K < 1 || A.K > FM_DENSE_MAX || A.N < 1 || A.nchunks < 1 || A.X == nullptr)
         return fm_fail(m, FM_EINVAL, "bad arguments of the dense pass");
+    const bool outputs = A.yhat != nullptr || A.eval_part != nullptr || (!A.whole_rows && (A.a != nullptr || A.q != nullptr));
+    if (what == (FM_DENSE_FORWARD | FM_DENSE_GRADIENT) && outputs) return fm_fail(m, FM_EINVAL, "an epoch leaves G and r only");
     switch (what) {
         case FM_DENSE_FORWARD: return launch_dense<FM_DENSE_FORWARD>(m, A, st);
         case FM_DENSE_GRADIENT: return launch_dense<FM_DENSE_GRADIENT>(m, A, st);

@@ -404,6 +404,42 @@ def test_dense_kernels_at_the_edges_of_their_tiles(N, D, K):
         m.close()
 
 
+@pytest.mark.parametrize("N,D,K", [(1, 1, 1), (1, 64, 64), (4, 33, 20), (5, 32, 32), (31, 8, 8), (33, 64, 33), (129, 7, 64)])
+def test_dense_kernels_leave_what_lies_behind_the_last_row(N, D, K):
+    """The last tile of a table has rows that do not exist: nothing is written behind the caller's G, r, a, q and scores, and
+    the NaN that lie behind G and r do not reach the gradient."""
+    import torch
+    from paper_2004_13940_amd import binding as B
+    rng = np.random.default_rng(7950 + N + D + K)
+    rowptr, col = np.arange(N + 1, dtype=np.int64) * D, np.tile(np.arange(D, dtype=np.int32), N)
+    val = rng.standard_normal(N * D).astype(np.float32)
+    y = rng.standard_normal(N).astype(np.float32)
+    w0, w = np.float32(0.1), (rng.standard_normal(D) * 0.1).astype(np.float32)
+    V = (rng.standard_normal((D, K)) * 0.1).astype(np.float32)
+    print("behind the last row", N, D, K, flush=True)
+    X = O.make_matrix(N, D, rowptr, col, val)
+    a, G, q, yhat = O.forward(X, float(w0), w, V)
+    _, r = O.loss_multiplier(O.LOSS_SQUARED, 1.0, yhat, y)
+    want = dict(yhat=yhat, a=a, G=G, q=q, r=r)
+    m = B.Matrix(N, D, rowptr, col, val)
+    p = B.make_params(K, O.LOSS_SQUARED, 0.01, 0.02, 0.5, 1.0)
+    d_w0, d_w, d_V = dev_params(w0, w, V)
+    d_y = to_dev(y)
+    out = {k: torch.full(((N + 64) * (K if k == "G" else 1),), float("nan"), device="cuda") for k in want}
+    m.fm_forward(p, d_y, d_w0, d_w, d_V, **{k: t[:len(t) - 64 * (K if k == "G" else 1)] for k, t in out.items()})
+    for k, t in out.items():
+        n = want[k].size
+        assert_close(t[:n].cpu().numpy().reshape(want[k].shape), want[k], k)
+        assert torch.isnan(t[n:]).all(), k
+    m.fm_build_csc()
+    gw, gV, g0 = torch.zeros(D, device="cuda"), torch.zeros(D * K, device="cuda"), torch.zeros(1, device="cuda")
+    m.fm_gradient(p, out["r"][:N], out["G"][:N * K], d_w, d_V, g0, gw, gV)
+    _, wgw, wgV = O.gradient(X, r, G, w, V, 0.01, 0.02)
+    assert_close(gw.cpu().numpy(), wgw, "grad_w")
+    assert_close(gV.cpu().numpy().reshape(D, K), wgV, "grad_V")
+    m.close()
+
+
 @pytest.mark.parametrize("N,D,K", [(33, 5, 4), (4097, 33, 36), (40_003, 64, 32)])
 def test_half_gather_of_dense_tables(N, D, K):
     """The dense kernel rounds the factors of the scores itself; the step is taken on the fp32 factors.  Metrics, scores and an
