@@ -570,8 +570,9 @@ static int ensure_ws(fm_matrix* m, int32_t K)
     FM_TRY(fm_dev_alloc(m, (void**)&m->aux, (size_t)std::max<int64_t>(fm_aux_floats(m, K), 6) * sizeof(float)));
     // the dense kernels may be switched on and off: room for both paths
     const int64_t chunks = fm_dense_fits(m, K) ? fm_dense_chunks(m->N, m->D, K) : 0;
+    const int64_t dense_items = chunks * 2;  // a batch of few rows has two to a column and workgroup
     const int64_t items = std::max<int64_t>(std::max<int64_t>(m->lfull.nitems, m->lstrat.nitems),
-                                            std::max<int64_t>(m->lbatch.nitems, m->D * chunks));
+                                            std::max<int64_t>(m->lbatch.nitems, m->D * dense_items));
     FM_TRY(fm_dev_alloc(m, (void**)&m->part,
                         (size_t)std::max<int64_t>(items, 1) * (size_t)fm_part_stride(K) * sizeof(float)));
     FM_TRY(fm_dev_alloc(m, (void**)&m->row_part, (size_t)std::max<int64_t>(std::max<int64_t>(fm_rows_max_grid(m, m->N, K), chunks), 1) * 2 * sizeof(float)));
@@ -844,12 +845,12 @@ extern "C" int fm_evaluate(fm_matrix* m, const fm_params* p, const float* y, con
 
 // --------------------------------------------------------------- gradient ----
 
-// The column pass behind a dense one over nchunks workgroups: only the finish, of all columns.
-static void dense_long(const fm_matrix* m, int64_t nchunks, ColArgs& A)
+// The column pass behind the dense one X: only the finish, of all columns.
+static void dense_long(const fm_matrix* m, const DenseArgs& X, ColArgs& A)
 {
-    A.nchunks = nchunks;
+    A.ndense = X.nchunks * X.nparts;
     A.nlong = m->D;
-    A.nvlong = nchunks > m->tune.vlong ? m->D : 0;  // a workgroup per column, or a wavefront
+    A.nvlong = A.ndense > m->tune.vlong ? m->D : 0;  // a workgroup per column, or a wavefront
     A.vlong_items = m->tune.vlong;
 }
 
@@ -869,9 +870,10 @@ static int dense_sums(fm_matrix* m, ColArgs& A, hipStream_t st)
     X.ss = A.rs;
     X.part = A.part;
     X.ps = A.ps;
+    X.nparts = fm_dense_parts(X.N, X.D, X.K);
     X.epi = A.epi;
     FM_TRY(fm_launch_dense(m, X, FM_DENSE_GRADIENT, st));
-    dense_long(m, X.nchunks, A);
+    dense_long(m, X, A);
     return FM_OK;
 }
 
@@ -952,9 +954,10 @@ static int dense_step(fm_matrix* m, const RowArgs& R, bool regs, ColArgs& A, hip
     fm_dense_rows(R, &X);
     X.part = A.part;
     X.ps = A.ps;
+    X.nparts = fm_dense_parts(X.N, X.D, X.K);
     X.regs = regs ? fm_reg_scratch(m) : nullptr;
     FM_TRY(fm_launch_dense(m, X, FM_DENSE_FORWARD | FM_DENSE_GRADIENT, st));
-    dense_long(m, X.nchunks, A);
+    dense_long(m, X, A);
     return FM_OK;
 }
 

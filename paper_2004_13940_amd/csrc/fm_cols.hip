@@ -647,11 +647,11 @@ __global__ __launch_bounds__(FM_BLOCK) void k_cols_finish(const ColArgs A)
     }
     int64_t lc, j;
     ColState<VEC> c;  // asked for ahead of the partial sums
-    const bool dense = A.nchunks > 0;  // every column has the same number of items
+    const bool dense = A.ndense > 0;  // every column has the same number of items
     if (b < A.nvlong) {
         lc = dense ? b : A.vlong[b];
-        const int64_t first = dense ? lc * A.nchunks : A.long_first[lc];
-        const int64_t last = dense ? first + A.nchunks : A.long_first[lc + 1];
+        const int64_t first = dense ? lc * A.ndense : A.long_first[lc];
+        const int64_t last = dense ? first + A.ndense : A.long_first[lc + 1];
         j = dense ? lc : A.long_col[lc];
         c = load_column<VEC, UPDATE>(A, j, kbase, kact);
         add_partials<VEC>(A, first + threadIdx.x / L, last, NG, kbase, kact, acc, gw, s2);
@@ -678,8 +678,8 @@ __global__ __launch_bounds__(FM_BLOCK) void k_cols_finish(const ColArgs A)
         const int64_t rel = (b - A.nvlong) * FM_WAVES + wave;
         if (rel >= A.nlong) return;  // whole wavefront leaves together
         lc = A.long_base + rel;
-        const int64_t first = dense ? lc * A.nchunks : A.long_first[lc];
-        const int64_t last = dense ? first + A.nchunks : A.long_first[lc + 1];
+        const int64_t first = dense ? lc * A.ndense : A.long_first[lc];
+        const int64_t last = dense ? first + A.ndense : A.long_first[lc + 1];
         if (A.nvlong > 0 && last - first > A.vlong_items) return;
         j = dense ? lc : A.long_col[lc];
         c = load_column<VEC, UPDATE>(A, j, kbase, kact);
@@ -911,7 +911,7 @@ int launch_cols_t(fm_matrix* m, const ColArgs& A, bool update, hipStream_t st)
     ColArgs Am = A;
     if (!need_empty || A.ptr != nullptr) Am.mark = nullptr;  // marks are only set when a kernel will clear them
     if constexpr (L < FM_WIDE_GROUP) {
-        if (A.whole && A.nchunks == 0 && update) {
+        if (A.whole && A.ndense == 0 && update) {
             Am.blk_lin = (A.nlong + FM_WAVES - 1) / FM_WAVES;
             Am.blk_short = (A.nshort + per - 1) / per;
             const int64_t sums = A.epi.on ? std::max<int64_t>(A.epi.nsums, 1) : 0;
@@ -935,7 +935,7 @@ int launch_cols_t(fm_matrix* m, const ColArgs& A, bool update, hipStream_t st)
             return FM_OK;
         }
     }
-    if (A.nchunks == 0) {  // else a dense pass has left the partial sums of every column
+    if (A.ndense == 0) {  // else a dense pass has left the partial sums of every column
         // LDS-staged items go to a side stream, so that the LDS-bound kernel overlaps the memory-bound one (not while
         // per-kernel timing is on: each kernel is then timed alone on the launch stream)
         hipStream_t s_tile = st;

@@ -9,6 +9,8 @@
 // Operand layout of the 32x32x2 tile C[32 x 32] += A[32 x 2] B[2 x 32] over the 64 lanes of a wavefront:
 //   A: lane l holds A[l % 32][l / 32];   B: lane l holds B[l / 32][l % 32];
 //   C: register v of lane l holds C[8 * (v / 4) + 4 * (l / 32) + v % 4][l % 32].
+#include <float.h>
+
 #include "fm_device.h"
 #include "fm_epilogue.h"
 #include "fm_internal.h"
@@ -19,11 +21,10 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
 
 constexpr int DT = 32;  // rows, columns and latent dimensions per tile
 constexpr int FM_DENSE_MAX = 2 * DT;    // largest D and K of these kernels
-constexpr int FM_DENSE_TILES = 8;   // 32-row tiles to a sum in fp32 before it is added to those of the tiles before
+constexpr int FM_DENSE_TILES = 8;   // 32-row tiles to a sum in fp32 at most; a wavefront has two such sums
 constexpr int FM_DENSE_CUS = 256;   // compute units
 // Workgroups that a compute unit holds: by registers, and by LDS where D and K take two tiles.
 constexpr int dense_per_cu(int db, int kb) { return db + kb > 3 ? 2 : db + kb > 2 ? 3 : 4; }
-
 __device__ __forceinline__ int c_row(int v, int half) { return 8 * (v / 4) + 4 * half + (v % 4); }
 
 // What a lane of the wavefront wrote to LDS is there for its other lanes: the LDS takes a wavefront's accesses in order,
@@ -66,11 +67,13 @@ __device__ __forceinline__ float row_sums(float (&s)[16], int lo)
 // One pass over the rows of X.  DB, KB: tiles that D and K take (what is missing to a whole tile is zero).
 //   FM_DENSE_FORWARD   aggregates, prediction, loss and multiplier of every row
 //   FM_DENSE_GRADIENT  per workgroup and column the partial sums acc = sum_i x_ij r_i G_ik, gw = sum_i x_ij r_i,
-//                      s2 = sum_i x_ij^2 r_i (eqs. updates_w, updates_v), as the row [acc | gw | s2 | pad] of item
-//                      j * nchunks + workgroup, which the finish kernel adds in fp64 in item order
+//                      s2 = sum_i x_ij^2 r_i (eqs. updates_w, updates_v), as the rows [acc | gw | s2 | pad] of the
+//                      items that the workgroup has for the column, which the finish kernel adds
+//                      in fp64 in item order
 //   both               an epoch: X is read once, and the tile of G goes from one product into the other in registers
-// A wavefront takes up to FM_DENSE_TILES tiles of 32 consecutive rows, a workgroup four times as many.  A tile of X is
-// staged in LDS with an odd row stride, read by columns for the first product (A operand: 32 rows, two columns a step) and
+// A wavefront takes up to 2 * FM_DENSE_TILES tiles of 32 consecutive rows, a workgroup four times as many.  Sums in fp32 end
+// with half of a wavefront's tiles, 256 rows at most; from there on, across wavefronts and workgroups, they are fp64.  A tile
+// of X is staged in LDS with an odd row stride, read by columns for the first product (A operand: 32 rows, two columns a step) and
 // by rows for the second (A operand: 32 columns, two rows a step).  The rows of a step of the second product are paired
 // as the result registers of the first hold them (rows c_row(v, 0) and c_row(v, 1)), so that register v, times r, is its
 // B operand as it stands.  Bound: 1e6 rows, D = 64, K = 32 are 392 MB of X, G, y and r (71 us at the rate of a copy) and
@@ -180,31 +183,34 @@ __global__ __launch_bounds__(FM_BLOCK, dense_per_cu(DB, KB)) void k_dense(const 
     if (half == 0) tile[Lds::Z + lo] = 0.f;
     // where this lane finds what it stores behind G in a packed row [G | r | a | q | pad]
     [[maybe_unused]] const float* behind = tile + (lo == K ? Lds::R : lo == K + 1 ? Lds::A : lo == K + 2 ? Lds::Q : Lds::Z);
-    [[maybe_unused]] f32x16 acc[DB][KB], all[DB][KB];  // of up to FM_DENSE_TILES tiles, of the tiles before them
-    [[maybe_unused]] float gw[DB], s2[DB], all_gw[DB], all_s2[DB];
-    auto add_up = [&](bool clear) {
+    // Sums of the tiles from t_half on, and of those before: neither stands for more than FM_DENSE_TILES tiles, and they are
+    // not added in fp32 (`first` is zero when it takes the sum).
+    const int t_half = t0 + (t1 - t0 + 1) / 2;
+    [[maybe_unused]] f32x16 acc[DB][KB], first[DB][KB];
+    [[maybe_unused]] float gw[DB], s2[DB], first_gw[DB], first_s2[DB];
+    auto next_sum = [&](bool clear) {
 #pragma unroll
         for (int jb = 0; jb < DB; ++jb) {
-            all_gw[jb] = clear ? 0.f : all_gw[jb] + gw[jb];
-            all_s2[jb] = clear ? 0.f : all_s2[jb] + s2[jb];
+            first_gw[jb] = clear ? 0.f : first_gw[jb] + gw[jb];
+            first_s2[jb] = clear ? 0.f : first_s2[jb] + s2[jb];
             gw[jb] = s2[jb] = 0.f;
 #pragma unroll
             for (int kb = 0; kb < KB; ++kb)
 #pragma unroll
                 for (int v = 0; v < 16; ++v) {
-                    all[jb][kb][v] = clear ? 0.f : all[jb][kb][v] + acc[jb][kb][v];
+                    first[jb][kb][v] = clear ? 0.f : first[jb][kb][v] + acc[jb][kb][v];
                     acc[jb][kb][v] = 0.f;
                 }
         }
     };
-    if constexpr (GRADIENT) add_up(true);
+    if constexpr (GRADIENT) next_sum(true);
     [[maybe_unused]] double sum_lr = 0.0, sum_es = 0.0;  // lower half: loss, squared error; upper: r, correct signs
     const float w0 = FORWARD ? A.w0[0] : 0.f;
     const bool want = A.row_part != nullptr || (!GRADIENT && A.eval_part != nullptr);
     const uint32_t magic = ((1u << 20) + (uint32_t)D - 1) / (uint32_t)D;  // e / D = e magic >> 20 for e < 2^12, D <= 64
 #pragma unroll 1
     for (int64_t tid = t0; tid < t1; ++tid) {
-        if (GRADIENT && tid > t0 && (tid - t0) % FM_DENSE_TILES == 0) add_up(false);
+        if (GRADIENT && tid == t_half) next_sum(false);
         const int64_t row0 = tid * DT;
         const int nrows = (int)((A.N - row0) < DT ? (A.N - row0) : DT);
         // The lane's number as a value of this turn of the loop: what is derived from it (addresses in LDS, w and |v|^2 read
@@ -361,30 +367,37 @@ __global__ __launch_bounds__(FM_BLOCK, dense_per_cu(DB, KB)) void k_dense(const 
     asm volatile("" : "+v"(thread));
     const int half_e = thread % FM_WAVE / 32, lo_e = thread % 32;
     if constexpr (GRADIENT) {
-        add_up(false);
-        // the wavefronts one after the other into one block of LDS, then whole rows of the partial sums
+        // The wavefronts are added in fp64 in one block of LDS, each at another quarter of the rows c_row(v, .) at a time (one after
+        // the other, the pass over 262,000 x 64, K=64 took 6 us longer); the order of the terms is fixed.  From there they go out
+        // as whole rows of the partial sums, see fm_dense_parts.
         constexpr int SP = KP + 2;
-        float* sum = area;
-        static_assert(DP * SP <= FM_WAVES * Lds::FLOATS, "the sums fit where the tiles were");
+        double* sum = reinterpret_cast<double*>(area);
+        static_assert(DP * SP * sizeof(double) <= FM_WAVES * Lds::FLOATS * sizeof(float), "the sums fit where the tiles were");
+        static_assert((2 * DP + DP * KP) % 2 == 0, "aligned doubles");
+        static_assert(FM_WAVES == 4, "a quarter to a wavefront");
 #pragma unroll 1
-        for (int w = 0; w < FM_WAVES; ++w) {
+        for (int step = 0; step < FM_WAVES; ++step) {
             __syncthreads();
-            if (w != wave) continue;
+            auto add = [&](double* p, double x) { *p = step == 0 ? x : *p + x; };
+            const int mine = (wave + step) % FM_WAVES;
 #pragma unroll
-            for (int jb = 0; jb < DB; ++jb) {
+            for (int part = 0; part < FM_WAVES; ++part) {
+                if (part != mine) continue;
 #pragma unroll
-                for (int v = 0; v < 16; ++v)
+                for (int jb = 0; jb < DB; ++jb) {
 #pragma unroll
-                    for (int kb = 0; kb < KB; ++kb) {
-                        float* p = sum + (jb * DT + c_row(v, half_e)) * SP + kb * DT + lo_e;
-                        *p = w == 0 ? all[jb][kb][v] : *p + all[jb][kb][v];
+                    for (int v = 4 * part; v < 4 * part + 4; ++v)
+#pragma unroll
+                        for (int kb = 0; kb < KB; ++kb)
+                            add(sum + (jb * DT + c_row(v, half_e)) * SP + kb * DT + lo_e,
+                                (double)first[jb][kb][v] + (double)acc[jb][kb][v]);
+                    if (part != jb) continue;
+                    const double gd = (double)first_gw[jb] + (double)gw[jb], sd = (double)first_s2[jb] + (double)s2[jb];
+                    const double gt = gd + fm_xor_lane<32>(gd), st = sd + fm_xor_lane<32>(sd);
+                    if (half_e == 0) {
+                        add(sum + (jb * DT + lo_e) * SP + KP, gt);
+                        add(sum + (jb * DT + lo_e) * SP + KP + 1, st);
                     }
-                const float gt = all_gw[jb] + fm_xor_lane<32>(all_gw[jb]);
-                const float st = all_s2[jb] + fm_xor_lane<32>(all_s2[jb]);
-                if (half_e == 0) {
-                    float* p = sum + (jb * DT + lo_e) * SP + KP;
-                    p[0] = w == 0 ? gt : p[0] + gt;
-                    p[1] = w == 0 ? st : p[1] + st;
                 }
             }
         }
@@ -392,13 +405,18 @@ __global__ __launch_bounds__(FM_BLOCK, dense_per_cu(DB, KB)) void k_dense(const 
         const int ps4 = (int)A.ps / 4;
         for (int e = threadIdx.x; e < D * ps4; e += FM_BLOCK) {
             const int j = e / ps4, o = (e - j * ps4) * 4;
-            float z[4];
+            float z[4], left[4];
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
                 const int k = o + i;
-                z[i] = k < K ? sum[j * SP + k] : k < K + 2 ? sum[j * SP + KP + k - K] : 0.f;
+                const double t = k < K ? sum[j * SP + k] : k < K + 2 ? sum[j * SP + KP + k - K] : 0.0;
+                z[i] = (float)t;
+                // nothing is left of a sum that is no finite float: infinity minus itself would make it NaN
+                left[i] = fabsf(z[i]) <= FLT_MAX ? (float)(t - (double)z[i]) : 0.f;
             }
-            fm_store_vec<4>(A.part + ((int64_t)j * A.nchunks + b) * A.ps + o, z);
+            float* out = A.part + ((int64_t)j * A.nchunks + b) * A.nparts * A.ps + o;
+            fm_store_vec<4>(out, z);
+            if (A.nparts == 2) fm_store_vec<4>(out + A.ps, left);
         }
     }
     if constexpr (FORWARD) {
@@ -461,6 +479,17 @@ int64_t fm_dense_chunks(int64_t N, int64_t D, int32_t K)
     if (tiles <= FM_WAVES * slots) return (tiles + FM_WAVES - 1) / FM_WAVES;
     const int64_t most = FM_WAVES * slots * 2 * FM_DENSE_TILES;
     return slots * ((tiles + most - 1) / most);
+}
+
+// Items that a workgroup leaves for a column: the sum rounded to fp32 and, second, what rounding left.  Rounding once more
+// shows where the sums in fp32 are short (one tile to a wavefront) or a workgroup stands for few of them (D and K of two
+// tiles each): 262,144 x 64, K=64, sums of terms of one sign, error relative to the sum of their magnitudes 1.7e-9 with the
+// second item, as with an fp32 sum to every 64 rows that are all added in fp64.  Elsewhere one item is no worse than that
+// and costs half the memory (gradient of 1e6 x 32, K=32 52.1 us, with two items 56.6).
+int fm_dense_parts(int64_t N, int64_t D, int32_t K)
+{
+    const int64_t slots = FM_DENSE_CUS * dense_per_cu(D > DT ? 2 : 1, K > DT ? 2 : 1);
+    return (D > DT && K > DT) || (N + DT - 1) / DT <= FM_WAVES * slots ? 2 : 1;
 }
 
 int fm_launch_dense(fm_matrix* m, const DenseArgs& A, int what, hipStream_t st)

@@ -337,6 +337,7 @@ int fm_to_half(fm_matrix* m, const float* x, _Float16* out, int64_t n, hipStream
 bool fm_dense_fits(const fm_matrix* m, int32_t K);           // the dense kernels exist for this matrix and K
 bool fm_dense_shape_ok(const fm_matrix* m, int32_t K);       // ... and are not switched off
 int64_t fm_dense_chunks(int64_t N, int64_t D, int32_t K);    // workgroups of a pass over N rows; never fewer for more rows
+int fm_dense_parts(int64_t N, int64_t D, int32_t K);         // items that one of them leaves for a column
 enum { FM_DENSE_FORWARD = 1, FM_DENSE_GRADIENT = 2 };
 int fm_launch_dense(fm_matrix* m, const DenseArgs& A, int what, hipStream_t st);  // gradient: partial sums; the finish follows
 int fm_unpack_aux(fm_matrix* m, float* a, float* G, float* q, float* r, hipStream_t st);
@@ -380,8 +381,8 @@ struct ColArgs {
     const float* G;
     int64_t gs, rs;  // row strides of G and r in floats
     // > 0: a dense pass has left the partial sums of all columns, those of column j at the items
-    // j * nchunks .. (j + 1) * nchunks - 1; only the finish is left
-    int64_t nchunks;
+    // j * ndense .. (j + 1) * ndense - 1; only the finish is left
+    int64_t ndense;
     int32_t packed;  // FM_PLANAR, or FM_PACKED_LANE: G rows are packed aggregate rows [G | r | a | q | pad]
     float* w;        // updated in place when update
     float* V;
@@ -463,8 +464,9 @@ struct DenseArgs {
     float s;
     float* row_part;    // forward, nullable: [2 * nchunks] loss and sum of r per workgroup
     double* eval_part;  // forward alone, nullable: [3 * nchunks] sums of losses, squared errors and correct signs
-    float* part;        // gradient: partial sums, rows of ps floats at item j * nchunks + workgroup
+    float* part;        // gradient: partial sums, rows of ps floats, nparts items to a column and workgroup
     int64_t ps;
+    int32_t nparts;
     FmEpilogue epi;     // gradient alone: on = the sums over the examples ride along
     double* regs;       // nullable, without epi: one more workgroup leaves |w|^2 and |V|^2 there
 };

@@ -440,6 +440,31 @@ def test_dense_kernels_leave_what_lies_behind_the_last_row(N, D, K):
     m.close()
 
 
+@pytest.mark.parametrize("N,D,K", [(5_000, 64, 64), (40_000, 20, 8), (200_000, 32, 32), (230_000, 64, 32), (262_144, 64, 64),
+                                   (300_000, 20, 8), (400_000, 64, 64), (500_000, 32, 64)])
+def test_dense_gradient_adds_few_rows_in_fp32(N, D, K):
+    """Sums over terms of one sign in the first half of the rows, of the other in the second: the total is small and its own
+    rounding does not hide the error of the partial sums.  An fp32 sum of n terms makes n roundings of at most 2^-24 of the sum
+    so far (rms 2^-24 / sqrt 3 of it), together sqrt(n / 3) of that; N / n such sums added exactly are off by
+    2^-24 n / (3 sqrt N) of the sum of the magnitudes.  The bound is that of n = max(64, N / 4096) rows."""
+    import torch
+    from paper_2004_13940_amd import binding as B
+    rng = np.random.default_rng(7970)
+    X, G, r = (rng.random(s, dtype=np.float32) + np.float32(0.5) for s in ((N, D), (N, K), N))
+    r[N // 2:] *= -1
+    print("rows to an fp32 sum", N, D, K, flush=True)
+    m = B.Matrix(N, D, np.arange(N + 1, dtype=np.int64) * D, np.tile(np.arange(D, dtype=np.int32), N), X.ravel())
+    m.fm_build_csc()
+    p = B.make_params(K, O.LOSS_SQUARED, 0.0, 0.0, 0.5, 1.0)
+    gw, gV, g0 = torch.zeros(D, device="cuda"), torch.zeros(D * K, device="cuda"), torch.zeros(1, device="cuda")
+    m.fm_gradient(p, to_dev(r), to_dev(G.ravel()), torch.zeros(D, device="cuda"), torch.zeros(D * K, device="cuda"), g0, gw, gV)
+    m.close()
+    X, rG, r = X.astype(np.float64).T, G.astype(np.float64) * r[:, None], r.astype(np.float64)
+    bound = 2.0 ** -24 * max(64, N / 4096) / (3 * np.sqrt(N))
+    for got, want, size in ((gw.cpu().numpy(), X @ r, X @ np.abs(r)), (gV.cpu().numpy().reshape(D, K), X @ rG, X @ np.abs(rG))):
+        assert np.sqrt(np.mean(((got - want) / size) ** 2)) <= bound
+
+
 @pytest.mark.parametrize("N,D,K", [(33, 5, 4), (4097, 33, 36), (40_003, 64, 32)])
 def test_half_gather_of_dense_tables(N, D, K):
     """The dense kernel rounds the factors of the scores itself; the step is taken on the fp32 factors.  Metrics, scores and an
