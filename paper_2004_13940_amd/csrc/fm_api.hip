@@ -1107,10 +1107,14 @@ static int stratified_step(fm_matrix* m, const fm_params* p, int32_t s, const fl
     R.dwn = m->dwn;
     R.y = y;
     aux_outputs(m, p->K, R, true);
-    // Aggregates that fit the L2s of the chip (4 MB each): an XCD keeps to one run of rows (text-like strata, 5e4 rows,
-    // 32 strata: 603 -> 576 us).  Larger ones do not stay there, and runs of unequal work leave XCDs idle (click-style
-    // strata 32.3 -> 34.8 ms, hashed 3.55 -> 4.58).
-    R.xcd_runs = m->N * R.gs * (int64_t)sizeof(float) <= int64_t(FM_XCDS) << 22 ? 1 : 0;
+    // An XCD keeps to one run of rows where the aggregates fit half of the chip's L2s (4 MB each) and row blocks are small: up
+    // to FM_WHOLE_ROWS rows.  The block that meets a popular column block has most of a stratum's entries, and its XCD most of
+    // the work when it fills the XCD's run.  Epochs with runs / without, us: text-like 5e4 rows, K=16, 32 strata 577 / 599;
+    // click-style K=16, 64 strata, 6e4 rows 953 / 1001, 1.2e5 1225 / 1298; hashed K=32, 64 strata, 2e4 rows 1510 / 1607,
+    // 5e4 1790 / 1868.  Outside: hashed K=32, 16 strata, 5e4 rows 846 / 816, 2e5 2650 / 1975; K=64, 64 strata, 1.2e5 rows
+    // (31 MB) 3635 / 3420; click-style 2.5e5 rows, 16 strata 1002 / 926.
+    const int64_t aggregates = m->N * R.gs * (int64_t)sizeof(float);
+    R.xcd_runs = aggregates <= int64_t(FM_XCDS) << 21 && m->N <= FM_WHOLE_ROWS * m->P ? 1 : 0;
     R.loss = p->loss;
     R.s = p->loss_scale;
     return fm_launch_rows(m, R, true, st);
