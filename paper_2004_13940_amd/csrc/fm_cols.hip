@@ -272,9 +272,13 @@ __device__ __forceinline__ void store_partial(const ColArgs& A, int64_t it, int 
 // workload as much as its columns did.  Items come first: they are the longest runs.
 // With an order array, workgroup b takes its items from list b % FM_XCDS (the XCD it runs on).  Items of a batch are in row
 // order; with xcd_runs every XCD takes one eighth of that order in a run, and so of the batch's rows.
-template <int VEC, int L, bool UPDATE, int PACKED>
+// FEW: four wavefronts to a SIMD and not the five that its registers leave room for, by naming a register that nothing uses
+// (LDS, the other means, is what k_cols_tile beside it lives on).  The items in panel order then have fewer panels' rows in
+// flight and find more of them in the L2: see few_wavefronts.
+template <int VEC, int L, bool UPDATE, int PACKED, bool FEW = false>
 __global__ __launch_bounds__(FM_BLOCK, L >= FM_WIDE_GROUP ? 8 : 1) void k_cols(const ColArgs A)
 {
+    if constexpr (FEW) asm volatile("" ::: "v103");
     constexpr int R = FM_WAVE / L;
     const int lane = threadIdx.x & (FM_WAVE - 1);
     const int wave = threadIdx.x / FM_WAVE;
@@ -479,6 +483,9 @@ __global__ __launch_bounds__(FM_BLOCK) void k_cols_tile(const ColArgs A)
 {
     constexpr int VEC = 4;
     constexpr int NG = FM_BLOCK / L;
+    // Beside k_cols, which waits for memory most of the time: its wavefronts go first where both could issue (click-style
+    // gradient, 1e7 rows 4585 -> 4538 us, 6e6 rows, K=12 2524 -> 2490; text-like, 1e6 rows 796 -> 795).
+    __builtin_amdgcn_s_setprio(3);
     extern __shared__ float tile[];  // G part: tile_rows x K floats, then r: tile_rows floats
     const int K = A.K;
     const int S = K;
@@ -897,6 +904,15 @@ int launch_flush(fm_matrix* m, const ColArgs& A, hipStream_t st)
 // (click-style epoch, 1e7 rows: 7.31 -> 7.98 ms).
 constexpr int64_t FM_EMPTY_BESIDE = int64_t(1) << 27;
 
+// Columns of a matrix whose aggregate rows do not fit the memory-side cache (256 MB): what the L2 does not hold comes from
+// HBM.  Click-style gradient, K=16, five wavefronts / four, us: 1e7 rows 4538 / 4495, 5e6 rows 2316 / 2267, 2.5e6 rows (320
+// MB) 1246 / 1244; epoch 7139 / 7131, 3607 / 3570, 1895 / 1890.  Below it the fifth hides latency: text-like, 1e6 rows (128
+// MB) 795 / 844.
+inline bool few_wavefronts(const ColArgs& A)
+{
+    return A.ptr != nullptr && A.N * A.gs * (int64_t)sizeof(float) > int64_t(256) << 20;
+}
+
 template <int VEC, int L, int PACKED>
 int launch_cols_t(fm_matrix* m, const ColArgs& A, bool update, hipStream_t st)
 {
@@ -983,10 +999,21 @@ int launch_cols_t(fm_matrix* m, const ColArgs& A, bool update, hipStream_t st)
             if (grid > 0x7fffffffLL) return fm_fail(m, FM_ERANGE, "column grid too large");
             if (grid <= 0) return FM_OK;
             ProfScope ps(m, q, FMK_COLS);
-            if (update)
-                hipLaunchKernelGGL((k_cols<VEC, L, true, PACKED>), dim3((unsigned)grid), dim3(FM_BLOCK), 0, q, B);
-            else
-                hipLaunchKernelGGL((k_cols<VEC, L, false, PACKED>), dim3((unsigned)grid), dim3(FM_BLOCK), 0, q, B);
+            auto go = [&](auto few) {
+                constexpr bool F = decltype(few)::value;
+                if (update)
+                    hipLaunchKernelGGL((k_cols<VEC, L, true, PACKED, F>), dim3((unsigned)grid), dim3(FM_BLOCK), 0, q, B);
+                else
+                    hipLaunchKernelGGL((k_cols<VEC, L, false, PACKED, F>), dim3((unsigned)grid), dim3(FM_BLOCK), 0, q, B);
+            };
+            if constexpr (VEC == 4 && L == 8) {
+                if (few_wavefronts(B))
+                    go(std::true_type());
+                else
+                    go(std::false_type());
+            } else {
+                go(std::false_type());
+            }
             FM_HIP(m, hipGetLastError());
             return FM_OK;
         };

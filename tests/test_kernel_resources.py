@@ -58,3 +58,11 @@ def test_wide_groups_leave_room_for_eight_wavefronts(kernels):
             if re.search(r"k_colsILi[124]ELi(16|32|64)E|k_rowsILi[124]ELi(16|32|64)ELi1E", n)}
     assert len(wide) == 27, sorted(wide)
     assert {n: v for n, v in wide.items() if v > 64} == {}
+
+
+def test_columns_of_large_aggregates_keep_to_four_wavefronts(kernels):
+    """Column kernels for aggregates beyond the memory-side cache: more than a fifth and at most a quarter of the 512
+    registers per lane of a SIMD, so that four wavefronts fit and not five."""
+    few = {n: k[".vgpr_count"] for n, k in kernels.items() if re.search(r"k_colsILi4ELi8ELb[01]ELi[01]ELb1EE", n)}
+    assert len(few) == 4, sorted(few)
+    assert {n: v for n, v in few.items() if not 512 // 5 < (v + 7) // 8 * 8 <= 512 // 4} == {}
