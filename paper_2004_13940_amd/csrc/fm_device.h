@@ -433,22 +433,6 @@ struct FmOwnArray {
     }
 };
 
-// One gathered row slice, from fp32 or half-precision rows.
-template <int VEC, bool NT>
-__device__ __forceinline__ void fm_buf_row(__amdgpu_buffer_rsrc_t rs, uint32_t off, float (&v)[VEC], const float*)
-{
-    fm_buf_load<VEC, NT>(rs, off, v);
-}
-template <int VEC, bool NT>
-__device__ __forceinline__ void fm_buf_row(__amdgpu_buffer_rsrc_t rs, uint32_t off, float (&v)[VEC], const _Float16*)
-{
-    static_assert(VEC == 4, "half rows come four at a time");
-    typedef int i2 __attribute__((ext_vector_type(2)));
-    const i2 t = __builtin_amdgcn_raw_buffer_load_b64(rs, (int)off, 0, NT ? 2 : 0);
-    const fm_h4 h = __builtin_bit_cast(fm_h4, t);
-    v[0] = (float)h.x; v[1] = (float)h.y; v[2] = (float)h.z; v[3] = (float)h.w;
-}
-
 // N consecutive entries at once; the arrays of entries are padded by FM_ENTRY_PAD, so that a load that begins inside a run
 // stays inside its array.  Entries lie at any multiple of four bytes.
 template <int N, typename T>
@@ -472,19 +456,43 @@ __device__ __forceinline__ void fm_load_entries(const T* __restrict__ p, T (&v)[
 }
 
 // S slots of a round from slot S0 on (a lane holds U consecutive ones): the gathers ...
-template <int VEC, int L, int ADDR, int S, int S0, int U, class SRC>
+template <int VEC, int L, int ADDR, int S, int S0, bool FIRST, int U, class SRC>
 __device__ __forceinline__ void fm_slot_loads(const int (&ix)[U], __amdgpu_buffer_rsrc_t rs, const SRC* __restrict__ src,
                                               int64_t stride, int kb, float (&g)[S][VEC])
 {
-    fm_static_for<0, S>([&](auto sc) {
-        constexpr int s = decltype(sc)::value;
-        constexpr int u = (S0 + s) % U, T = (S0 + s) / U;
-        const int it = fm_bcast_i<L, T>(ix[u]);
-        if constexpr (ADDR == FM_ADDR_PTR)
-            fm_load_vec<VEC>(src + (int64_t)it * stride + kb, g[s]);
-        else
-            fm_buf_row<VEC, ADDR == FM_ADDR_BUF_NT>(rs, (uint32_t)it + (uint32_t)(kb * (int)sizeof(SRC)), g[s], src);
-    });
+    auto load_all = [&](auto&& load) {
+        fm_static_for<0, S>([&](auto sc) {
+            constexpr int s = decltype(sc)::value;
+            constexpr int u = (S0 + s) % U, T = (S0 + s) / U;
+            load(s, fm_bcast_i<L, T>(ix[u]));
+        });
+    };
+    if constexpr (sizeof(SRC) == 2) {
+        // FIRST: all requests before the first conversion.  Left to itself the compiler converts what two loads of eight lanes
+        // have brought before it asks for more.
+        static_assert(VEC == 4, "half rows come four at a time");
+        typedef int i2 __attribute__((ext_vector_type(2)));
+        i2 raw[S];
+        load_all([&](int s, int it) {
+            if constexpr (ADDR == FM_ADDR_PTR)
+                raw[s] = *reinterpret_cast<const i2*>(src + (int64_t)it * stride + kb);
+            else
+                raw[s] = __builtin_amdgcn_raw_buffer_load_b64(rs, it + kb * (int)sizeof(SRC), 0, ADDR == FM_ADDR_BUF_NT ? 2 : 0);
+        });
+        if constexpr (FIRST) __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int s = 0; s < S; ++s) {
+            const fm_h4 h = __builtin_bit_cast(fm_h4, raw[s]);
+            g[s][0] = (float)h.x; g[s][1] = (float)h.y; g[s][2] = (float)h.z; g[s][3] = (float)h.w;
+        }
+    } else {
+        load_all([&](int s, int it) {
+            if constexpr (ADDR == FM_ADDR_PTR)
+                fm_load_vec<VEC>(src + (int64_t)it * stride + kb, g[s]);
+            else
+                fm_buf_load<VEC, ADDR == FM_ADDR_BUF_NT>(rs, (uint32_t)it + (uint32_t)(kb * (int)sizeof(SRC)), g[s]);
+        });
+    }
 }
 
 // ... and the sums in entry order.
@@ -526,8 +534,9 @@ __device__ __forceinline__ void fm_slot_sums(const float (&mu)[U], const float (
 // 4.53 -> 4.20 ms).
 // The refresh of a stratum, whose runs are mostly shorter than a round, takes rounds of four or eight in fours.
 // kb: offset of the lane's slice in a row, valid for every lane.
+// FIRST: see fm_slot_loads.
 // SP > 1: SP groups share a run, group `part` of them takes every SP-th stretch of C entries.
-template <int VEC, int L, int KIND, int ADDR, int C = 16, int SMAX = 8, int SP = 1, class Own, class SRC>
+template <int VEC, int L, int KIND, int ADDR, int C = 16, int SMAX = 8, int SP = 1, bool FIRST = false, class Own, class SRC>
 __device__ __forceinline__ void fm_walk(const int32_t* __restrict__ idx, const float* __restrict__ val, int64_t beg,
                                         int len, const SRC* __restrict__ src, int64_t stride, int sub, int kb,
                                         float (&acc)[VEC], float& gw, float& s2, Own&& own, int part = 0)
@@ -590,23 +599,23 @@ __device__ __forceinline__ void fm_walk(const int32_t* __restrict__ idx, const f
                 if (left > 4) {
                     done = true;
                     float g[8][VEC];
-                    fm_slot_loads<VEC, L, ADDR, 8, 0>(ix, rs, src, stride, kb, g);
+                    fm_slot_loads<VEC, L, ADDR, 8, 0, FIRST>(ix, rs, src, stride, kb, g);
                     multipliers();
                     fm_slot_sums<VEC, L, KIND, 8, 0>(mu, g, acc, gw, s2);
                     if (left > 8) {
-                        fm_slot_loads<VEC, L, ADDR, 8, 8>(ix, rs, src, stride, kb, g);
+                        fm_slot_loads<VEC, L, ADDR, 8, 8, FIRST>(ix, rs, src, stride, kb, g);
                         fm_slot_sums<VEC, L, KIND, 8, 8>(mu, g, acc, gw, s2);
                     }
                 }
             }
             if (!done) {
                 float g[4][VEC];
-                fm_slot_loads<VEC, L, ADDR, 4, 0>(ix, rs, src, stride, kb, g);
+                fm_slot_loads<VEC, L, ADDR, 4, 0, FIRST>(ix, rs, src, stride, kb, g);
                 multipliers();
                 fm_slot_sums<VEC, L, KIND, 4, 0>(mu, g, acc, gw, s2);
                 if constexpr (SMAX == 4 && C == 8) {
                     if (left > 4) {
-                        fm_slot_loads<VEC, L, ADDR, 4, 4>(ix, rs, src, stride, kb, g);
+                        fm_slot_loads<VEC, L, ADDR, 4, 4, FIRST>(ix, rs, src, stride, kb, g);
                         fm_slot_sums<VEC, L, KIND, 4, 4>(mu, g, acc, gw, s2);
                     }
                 }

@@ -12,7 +12,7 @@
 
 namespace {
 
-// FORWARD_HALF: V rows from the half-precision copy; *_BIG: what is gathered is larger than FM_BUF_BYTES (groups of fewer
+// FORWARD_HALF: V rows from the half-precision copy, _SMALL: in a small launch; *_BIG: what is gathered is larger than FM_BUF_BYTES (groups of fewer
 // than FM_WIDE_GROUP lanes; wider ones use 64-bit addresses throughout)
 enum {
     MODE_FORWARD = 0,
@@ -20,13 +20,19 @@ enum {
     MODE_FORWARD_HALF = 2,
     MODE_REFRESH_BIG = 3,
     MODE_FORWARD_BIG = 4,
-    MODE_FORWARD_HALF_BIG = 5
+    MODE_FORWARD_HALF_BIG = 5,
+    MODE_FORWARD_HALF_SMALL = 6
 };
 constexpr bool is_refresh(int mode) { return mode == MODE_REFRESH || mode == MODE_REFRESH_BIG; }
-constexpr bool is_half(int mode) { return mode == MODE_FORWARD_HALF || mode == MODE_FORWARD_HALF_BIG; }
+constexpr bool is_half(int mode)
+{
+    return mode == MODE_FORWARD_HALF || mode == MODE_FORWARD_HALF_BIG || mode == MODE_FORWARD_HALF_SMALL;
+}
 constexpr int addr_of(int mode)
 {
-    return mode == MODE_FORWARD || mode == MODE_FORWARD_HALF || mode == MODE_REFRESH ? FM_ADDR_BUF : FM_ADDR_PTR;
+    return mode == MODE_FORWARD || mode == MODE_FORWARD_HALF || mode == MODE_FORWARD_HALF_SMALL || mode == MODE_REFRESH
+               ? FM_ADDR_BUF
+               : FM_ADDR_PTR;
 }
 
 // Per-entry work of a score: w_j x_ij.
@@ -131,8 +137,8 @@ __global__ __launch_bounds__(FM_BLOCK, L >= FM_WIDE_GROUP && is_refresh(MODE) ? 
             OwnScore own{FmOwnArray<1>(A.w, 1), 0.f};
             float unused = 0.f;
             if constexpr (is_half(MODE))
-                fm_walk<VEC, L, FM_WALK_SCORE, addr_of(MODE), 16, 8, SP>(A.col, A.val, beg, len, A.Vh, K, sub, kb, acc, unused,
-                                                                         q_acc, own, part);
+                fm_walk<VEC, L, FM_WALK_SCORE, addr_of(MODE), 16, 8, SP, MODE == MODE_FORWARD_HALF_SMALL>(
+                    A.col, A.val, beg, len, A.Vh, K, sub, kb, acc, unused, q_acc, own, part);
             else
                 fm_walk<VEC, L, FM_WALK_SCORE, addr_of(MODE), 16, 8, SP>(A.col, A.val, beg, len, A.V, K, sub, kb, acc, unused,
                                                                          q_acc, own, part);
@@ -318,7 +324,7 @@ int launch_rows_t(fm_matrix* m, const RowArgs& A, bool refresh, hipStream_t st)
     constexpr bool W = L >= FM_WIDE_GROUP;  // wide groups use 64-bit addresses throughout: one variant
     auto launch = [&](auto mode) {
         constexpr int M = decltype(mode)::value;
-        if constexpr (!W && (M == MODE_FORWARD || M == MODE_FORWARD_HALF)) {
+        if constexpr (!W && (M == MODE_FORWARD || M == MODE_FORWARD_HALF || M == MODE_FORWARD_HALF_SMALL)) {
             if (split == 2) {
                 hipLaunchKernelGGL((k_rows<VEC, L, M, 2>), dim3((unsigned)grid), dim3(FM_BLOCK), 0, st, A);
                 return;
@@ -343,8 +349,14 @@ int launch_rows_t(fm_matrix* m, const RowArgs& A, bool refresh, hipStream_t st)
             launch(std::integral_constant<int, MODE_REFRESH>());
     } else if (A.Vh != nullptr) {
         if constexpr (VEC == 4) {
+            // Groups of eight lanes, small launches: each batch of requests whole before it is converted (scores of 3,000 text-like
+            // rows, K=32 19.6 -> 15.5 us, 6e4 rows 50.4 -> 47.6).  Large ones are bound by the lines they ask for, and fewer
+            // requests in flight find more of them in the caches (click-style rows, K=32: 5e5 184 -> 189 us, 2e6 670 -> 701).
+            constexpr int SMALL = L == 8 ? MODE_FORWARD_HALF_SMALL : MODE_FORWARD_HALF;
             if (A.big)
                 launch(std::integral_constant<int, W ? MODE_FORWARD_HALF : MODE_FORWARD_HALF_BIG>());
+            else if (A.N * L <= FM_SPLIT_LANES)
+                launch(std::integral_constant<int, SMALL>());
             else
                 launch(std::integral_constant<int, MODE_FORWARD_HALF>());
         } else {

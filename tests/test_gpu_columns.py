@@ -586,6 +586,31 @@ def test_forward_of_rows_shared_by_lane_groups(row, K, half):
     m.close()
 
 
+@pytest.mark.parametrize("K", [20, 32])  # five and eight of the eight lanes of a group
+@pytest.mark.parametrize("N,row", [(203, 3), (203, 17), (203, 40), (262_144, 5), (262_145, 5)])  # up to 2^21 lanes and beyond
+def test_half_gather_of_eight_lane_groups(N, row, K):
+    """Scores and aggregates from half-precision V, empty and short rows among them, in small and in large launches."""
+    import torch
+    from paper_2004_13940_amd import binding as B
+    rng = np.random.default_rng(8250 + N + row + K)
+    D = 2 * row + 5
+    lens = rng.integers(0, row + 3, N)
+    rowptr = np.concatenate([[0], np.cumsum(lens)]).astype(np.int64)
+    col = np.concatenate([np.sort(rng.permutation(D)[:n]) for n in lens[:203]] + [np.arange(n) for n in lens[203:]]).astype(np.int32)
+    val = rng.standard_normal(len(col)).astype(np.float32)
+    w0, w = np.float32(0.1), (rng.standard_normal(D) * 0.2).astype(np.float32)
+    V = (rng.standard_normal((D, K)) * 0.1).astype(np.float32)
+    print("half of eight lanes", N, row, K, flush=True)
+    a, G, q, yhat = O.forward(O.make_matrix(N, D, rowptr, col, val), float(w0), w, V.astype(np.float16).astype(np.float32))
+    m = B.Matrix(N, D, rowptr, col, val)
+    p = B.make_params(K, O.LOSS_LOGISTIC, 0.0, 0.0, 0.5, 1.0 / N, half_gather=1)
+    out = {k: torch.full((N * (K if k == "G" else 1),), float("nan"), device="cuda") for k in ("yhat", "a", "G", "q")}
+    m.fm_forward(p, None, *dev_params(w0, w, V), **out)
+    for k, want in dict(yhat=yhat, a=a, G=G, q=q).items():
+        assert_close(out[k].cpu().numpy().reshape(np.shape(want)), want, k)
+    m.close()
+
+
 def test_postponed_steps_start_from_zero_in_every_epoch():
     """Epochs with postponed steps follow one another on one handle: strata, batches, strata captured by the caller and
     replayed between eager epochs, and with the steps taken at once in between.  Each meets the same epoch on a new handle."""
