@@ -258,7 +258,7 @@ def time_config(torch, B, wl, reps, oracle_rows):
         m.fm_sgd_epoch(p, y, w0, w, V)
         ms, _ = T.run(lambda: m.fm_sgd_epoch(p, y, w0, w, V), reps, before=restore)
         out["epoch_sparse_kernels"] = entry(ms, b_epoch)
-        m.fm_set_option(B.FM_OPT_DENSE_ROWS, 1)
+        m.fm_set_option(B.FM_OPT_DENSE_ROWS, 2)
     del yhat, a, q, r, G, gw, gV
     torch.cuda.empty_cache()
     B.fm_trim()  # the pool neither lends to the partition nor hides what it keeps

@@ -259,10 +259,11 @@ int fm_profile_read(fm_matrix* m, int64_t* launches /*HOST nk*/, double* total_m
  *   FM_OPT_GRAPH         fm_stratified_epoch replayed from a captured HIP graph: 0 never, 1 (default)
  *                        when there are 32 strata or more, or 16 and strata small enough for the launches
  *                        to dominate, 2 always.
- *   FM_OPT_DENSE_ROWS    1 (default): a matrix in which every row stores all D columns (D and K up to 64)
- *                        takes dense kernels on the matrix cores for fm_forward, fm_evaluate, fm_gradient,
- *                        fm_sgd_epoch and fm_minibatch_epoch (G = XV and X^T(r.G) as fp32 contractions; the
- *                        column indices are not read); 0: the sparse kernels, as for every other matrix.
+ *   FM_OPT_DENSE_ROWS    1: a matrix in which every row stores all D columns (D and K up to 64) takes dense
+ *                        kernels on the matrix cores for fm_forward, fm_evaluate, fm_gradient, fm_sgd_epoch and
+ *                        fm_minibatch_epoch (G = XV and X^T(r.G) as fp32 contractions; the column indices are
+ *                        not read); 2 (default): unless the call has so few rows that the sparse kernels are
+ *                        the faster ones; 0: the sparse kernels, as for every other matrix.
  *   FM_OPT_WIDE_ADDRESSES  1: the rows that the column kernels and the refresh gather are addressed with 64
  *                        bits, as they are when they take more than 4 GB; 0 (default): only then. */
 typedef enum {

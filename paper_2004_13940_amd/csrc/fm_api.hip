@@ -664,10 +664,10 @@ static int half_copy(fm_matrix* m, const fm_params* p, const float* V, const _Fl
     return FM_OK;
 }
 
-// (loss, multiplier) pairs a forward pass over N rows leaves: one per workgroup
-static int64_t forward_pairs(const fm_matrix* m, const fm_params* p)
+// (loss, multiplier) pairs that a forward pass over all rows leaves (what: see forward_args): one per workgroup
+static int64_t forward_pairs(const fm_matrix* m, const fm_params* p, int what = FM_DENSE_FORWARD)
 {
-    return fm_dense_shape_ok(m, p->K) ? fm_dense_chunks(m->N, m->D, p->K) : fm_rows_grid(m, m->N, p->K);
+    return fm_dense_takes(m, p->K, m->N, what) ? fm_dense_chunks(m->N, m->D, p->K) : fm_rows_grid(m, m->N, p->K);
 }
 
 // The sums over n pairs (or, single, n multipliers `stride` floats apart) as an epilogue.
@@ -696,7 +696,7 @@ static int read_objective(fm_matrix* m, const fm_params* p, double* objective, h
 // mode 0: caller arrays (dense); 1: handle's aggregate rows, G and r; 2: handle's rows, G r a q
 static int forward_args(fm_matrix* m, const fm_params* p, const float* y, const float* w0, const float* w,
                         const float* V, float* yhat, float* a, float* G, float* q, float* r, int mode, bool want_sums,
-                        RowArgs& A, hipStream_t st)
+                        int what, RowArgs& A, hipStream_t st)
 {
     memset(&A, 0, sizeof(A));
     A.N = m->N;
@@ -724,7 +724,7 @@ static int forward_args(fm_matrix* m, const fm_params* p, const float* y, const 
     A.row_part = (want_sums && y != nullptr) ? m->row_part : nullptr;
     A.loss = p->loss;
     A.s = p->loss_scale;
-    if (fm_dense_shape_ok(m, p->K)) {
+    if (fm_dense_takes(m, p->K, m->N, what)) {
         A.dense_D = (int32_t)m->D;
         A.dense_half = p->half_gather;
     } else {
@@ -738,7 +738,7 @@ static int run_forward(fm_matrix* m, const fm_params* p, const float* y, const f
                        hipStream_t st)
 {
     RowArgs A;
-    FM_TRY(forward_args(m, p, y, w0, w, V, yhat, a, G, q, r, mode, want_sums, A, st));
+    FM_TRY(forward_args(m, p, y, w0, w, V, yhat, a, G, q, r, mode, want_sums, FM_DENSE_FORWARD, A, st));
     return fm_launch_rows(m, A, false, st);  // the pairs stay in m->row_part
 }
 
@@ -822,7 +822,7 @@ extern "C" int fm_evaluate(fm_matrix* m, const fm_params* p, const float* y, con
     A.eval_part = direct ? m->h_scal + 8 : reinterpret_cast<double*>(m->aux);
     A.loss = p->loss;
     A.s = 1.f;
-    if (fm_dense_shape_ok(m, p->K)) {
+    if (fm_dense_takes(m, p->K, m->N, FM_DENSE_FORWARD)) {
         A.dense_D = (int32_t)m->D;
         A.dense_half = p->half_gather;
     } else {
@@ -938,7 +938,7 @@ extern "C" int fm_gradient(fm_matrix* m, const fm_params* p, const float* r, con
     A.V = const_cast<float*>(V);
     A.grad_w = grad_w;
     A.grad_V = grad_V;
-    if (fm_dense_shape_ok(m, p->K) && m->N > 0)
+    if (fm_dense_takes(m, p->K, m->N, FM_DENSE_GRADIENT))
         FM_TRY(dense_sums(m, A, st));
     else
         fill_long(m, A, m->lfull, 0, false);
@@ -978,7 +978,8 @@ extern "C" int fm_sgd_epoch(fm_matrix* m, const fm_params* p, const float* y, fl
     }
     // steps 1-3: G, r, loss and sum r
     RowArgs R;
-    FM_TRY(forward_args(m, p, y, w0, w, V, nullptr, nullptr, nullptr, nullptr, nullptr, 1, true, R, st));
+    FM_TRY(forward_args(m, p, y, w0, w, V, nullptr, nullptr, nullptr, nullptr, nullptr, 1, true,
+                        FM_DENSE_FORWARD | FM_DENSE_GRADIENT, R, st));
     m->aux_full = false;
     const bool dense = R.dense_D > 0;  // then the data sums of step 4 come with them
     if (!dense) FM_TRY(fm_launch_rows(m, R, false, st));
@@ -998,7 +999,7 @@ extern "C" int fm_sgd_epoch(fm_matrix* m, const fm_params* p, const float* y, fl
     A.V = V;
     if (!dense) fill_long(m, A, m->lfull, 0, false);
     if (p->update_w0 || objective != nullptr) {
-        set_epilogue(m, A.epi, m->row_part, forward_pairs(m, p), 0, false);
+        set_epilogue(m, A.epi, m->row_part, forward_pairs(m, p, FM_DENSE_FORWARD | FM_DENSE_GRADIENT), 0, false);
         if (dense) A.epi.nsums = 0;  // the pairs of this very launch: the finish adds them
         if (p->update_w0) A.epi.w0 = w0;
         A.epi.eta = p->eta;
@@ -1323,6 +1324,8 @@ extern "C" int fm_minibatch_epoch(fm_matrix* m, const fm_params* p, const float*
         if (!p->reg_full_per_cell) set_shares(A, m->d_brho, m->d_bb, m->N, m->B);
         if (lazy) A.lazy_last = m->lazy_last;
     };
+    int vec = 0, lanes = 0;
+    (void)fm_shape_for_K(p->K, &vec, &lanes);  // checked with the parameters
     for (int32_t b = 0; b < m->B; ++b) {
         const int64_t r0 = m->h_bb[b], nb = m->h_bb[b + 1] - r0;
         RowArgs R;
@@ -1347,7 +1350,11 @@ extern "C" int fm_minibatch_epoch(fm_matrix* m, const fm_params* p, const float*
             R.row_part = p->update_w0 ? m->row_part : nullptr;
             R.loss = p->loss;
             R.s = p->loss_scale;
-            dense = fm_dense_shape_ok(m, p->K);
+            // Batches of few rows whose columns are summed whole (groups of up to eight lanes) are the sparse kernels', us for
+            // six batches dense / sparse: 64 columns, K=32 1,000 rows each 108 / 71, 2,000 111 / 89, 4,000 (not whole) 109 / 114;
+            // 22 columns, K=8 80 / 59, 82 / 66, 87 / 101.
+            dense = fm_dense_takes(m, p->K, nb, FM_DENSE_FORWARD | FM_DENSE_GRADIENT) &&
+                    !(m->lbatch.whole && lanes <= 8 && m->opt.dense_rows != 1);
             if (dense) {
                 R.dense_D = (int32_t)m->D;
                 R.dense_half = p->half_gather;
@@ -1426,7 +1433,7 @@ extern "C" int fm_set_option(fm_matrix* m, int32_t option, int32_t value)
             m->opt.lazy_reg = value != 0;
             return FM_OK;
         case FM_OPT_DENSE_ROWS:
-            m->opt.dense_rows = value != 0;
+            m->opt.dense_rows = value == 0 || value == 2 ? value : 1;
             return FM_OK;
         case FM_OPT_WIDE_ADDRESSES:
             m->opt.wide_addresses = value != 0;

@@ -467,7 +467,26 @@ int launch_dense(fm_matrix* m, const DenseArgs& A, hipStream_t st)
 
 // Up to two tiles each way: the accumulators stay in registers.
 bool fm_dense_fits(const fm_matrix* m, int32_t K) { return m->is_dense && m->D <= FM_DENSE_MAX && K <= FM_DENSE_MAX; }
-bool fm_dense_shape_ok(const fm_matrix* m, int32_t K) { return m->opt.dense_rows && fm_dense_fits(m, K); }
+
+// A launch of few rows spends its time in one chain, from V or G through LDS and the products to the sums, the longer the more
+// tiles D and K take.  The sparse kernels spread such a launch over more wavefronts.  Dense / sparse, us:
+//   gradient  60 columns, K=64  1,000 rows 16.7 / 11.0  4,000 17.1 / 14.8  8,000 21.3 / 16.9  16,000 21.2 / 23.5
+//             64 columns, K=32               12.4 / 10.9        12.3 / 12.2        15.3 / 13.2         15.5 / 18.2
+//             22 columns, K=8                14.0 / 14.6        12.1 / 13.7        14.0 / 12.4         12.7 / 14.4
+//   evaluate  60 columns, K=64               24.6 / 22.1        24.6 / 22.5        24.8 / 23.7         25.0 / 28.2
+//             20 columns, K=64               21.4 / 19.0        21.6 / 19.4        21.7 / 20.3         21.9 / 23.2
+//             64 columns, K=32               21.3 / 18.3        21.3 / 19.7        21.6 / 23.3         21.7 / 26.8
+//   epoch     60 columns, K=64               25.3 / 22.7  2,000 25.0 / 25.5  4,000 25.9 / 27.3         30.4 / 38.4
+//             64 columns, K=32               17.6 / 17.4        18.0 / 17.3        18.0 / 18.7         21.2 / 29.4
+bool fm_dense_takes(const fm_matrix* m, int32_t K, int64_t rows, int what)
+{
+    if (m->opt.dense_rows == 0 || rows < 1 || !fm_dense_fits(m, K)) return false;
+    if (m->opt.dense_rows == 1) return true;
+    const bool both = m->D > DT && K > DT, either = m->D > DT || K > DT;
+    if (what == FM_DENSE_GRADIENT) return !either || rows > 8192;
+    if (what == FM_DENSE_FORWARD) return !either || rows > (K > DT ? 8192 : 4096);
+    return !both || rows > 2048;
+}
 
 // Workgroups of a pass over N rows: one tile to a wavefront while the chip is not full, then as many as it holds at once,
 // in as few rounds as leave no wavefront more than 16 tiles (1e6 x 64, K=32: 977 workgroups of 8 tiles a wavefront took 129

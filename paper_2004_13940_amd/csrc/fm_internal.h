@@ -41,7 +41,8 @@ struct FmOptions {
     bool side_streams = true;  // column kernels that touch disjoint columns overlap on internal side streams
     bool lazy_reg = true;      // regulariser-only steps of a stratified or mini-batch epoch are postponed
     int graph = 1;             // stratified epoch from a captured graph: 0 never, 1 when launch-bound, 2 always
-    bool dense_rows = true;    // matrices that store every column in every row take the dense (MFMA) kernels
+    int dense_rows = 2;        // matrices that store every column in every row take the dense (MFMA) kernels: 0 never, 1 always,
+                               // 2 where fm_dense_takes says that they are the faster ones
     bool wide_addresses = false;  // gathers take 64-bit addresses at any size
 };
 
@@ -335,10 +336,10 @@ int fm_pack_aux(fm_matrix* m, const float* r, const float* G, hipStream_t st);  
 int fm_to_half(fm_matrix* m, const float* x, _Float16* out, int64_t n, hipStream_t st);  // round to nearest even
 // dense matrices (fm_dense.hip)
 bool fm_dense_fits(const fm_matrix* m, int32_t K);           // the dense kernels exist for this matrix and K
-bool fm_dense_shape_ok(const fm_matrix* m, int32_t K);       // ... and are not switched off
 int64_t fm_dense_chunks(int64_t N, int64_t D, int32_t K);    // workgroups of a pass over N rows; never fewer for more rows
 int fm_dense_parts(int64_t N, int64_t D, int32_t K);         // items that one of them leaves for a column
 enum { FM_DENSE_FORWARD = 1, FM_DENSE_GRADIENT = 2 };
+bool fm_dense_takes(const fm_matrix* m, int32_t K, int64_t rows, int what);  // ... and take such a pass over so many rows
 int fm_launch_dense(fm_matrix* m, const DenseArgs& A, int what, hipStream_t st);  // gradient: partial sums; the finish follows
 int fm_unpack_aux(fm_matrix* m, float* a, float* G, float* q, float* r, hipStream_t st);
 

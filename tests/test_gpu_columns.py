@@ -422,6 +422,7 @@ def test_dense_kernels_leave_what_lies_behind_the_last_row(N, D, K):
     _, r = O.loss_multiplier(O.LOSS_SQUARED, 1.0, yhat, y)
     want = dict(yhat=yhat, a=a, G=G, q=q, r=r)
     m = B.Matrix(N, D, rowptr, col, val)
+    m.fm_set_option(B.FM_OPT_DENSE_ROWS, 1)
     p = B.make_params(K, O.LOSS_SQUARED, 0.01, 0.02, 0.5, 1.0)
     d_w0, d_w, d_V = dev_params(w0, w, V)
     d_y = to_dev(y)
@@ -454,6 +455,7 @@ def test_dense_gradient_adds_few_rows_in_fp32(N, D, K):
     r[N // 2:] *= -1
     print("rows to an fp32 sum", N, D, K, flush=True)
     m = B.Matrix(N, D, np.arange(N + 1, dtype=np.int64) * D, np.tile(np.arange(D, dtype=np.int32), N), X.ravel())
+    m.fm_set_option(B.FM_OPT_DENSE_ROWS, 1)
     m.fm_build_csc()
     p = B.make_params(K, O.LOSS_SQUARED, 0.0, 0.0, 0.5, 1.0)
     gw, gV, g0 = torch.zeros(D, device="cuda"), torch.zeros(D * K, device="cuda"), torch.zeros(1, device="cuda")
@@ -463,6 +465,53 @@ def test_dense_gradient_adds_few_rows_in_fp32(N, D, K):
     bound = 2.0 ** -24 * max(64, N / 4096) / (3 * np.sqrt(N))
     for got, want, size in ((gw.cpu().numpy(), X @ r, X @ np.abs(r)), (gV.cpu().numpy().reshape(D, K), X @ rG, X @ np.abs(rG))):
         assert np.sqrt(np.mean(((got - want) / size) ** 2)) <= bound
+
+
+@pytest.mark.parametrize("N,D,K", [(2048, 60, 40), (2049, 60, 40), (8192, 33, 33), (8193, 33, 33), (8192, 20, 64), (8193, 40, 8), (4096, 40, 8), (4097, 40, 8)])
+def test_tables_around_the_rows_that_the_dense_kernels_take(N, D, K):
+    """Just up to and just beyond the numbers of rows from which the dense kernels take an epoch, a forward pass, a gradient
+    and batches: every call against the oracle, and against the dense kernels whatever the number of rows."""
+    import torch
+    from paper_2004_13940_amd import binding as B
+    rng = np.random.default_rng(8000 + N + D)
+    rowptr, col = np.arange(N + 1, dtype=np.int64) * D, np.tile(np.arange(D, dtype=np.int32), N)
+    val = rng.standard_normal(N * D).astype(np.float32)
+    y = np.where(rng.random(N) < 0.5, 1.0, -1.0).astype(np.float32)
+    w0, w = np.float32(0.1), (rng.standard_normal(D) * 0.1).astype(np.float32)
+    V = (rng.standard_normal((D, K)) * 0.3 / np.sqrt(D * K)).astype(np.float32)
+    print("rows of the dense kernels", N, D, K, flush=True)
+    X = O.make_matrix(N, D, rowptr, col, val)
+    a, G, q, yhat = O.forward(X, float(w0), w, V)
+    l, r = O.loss_multiplier(O.LOSS_LOGISTIC, 1.0 / N, yhat, y)
+    _, wgw, wgV = O.gradient(X, r, G, w, V, 0.01, 0.02)
+    kw = dict(loss=O.LOSS_LOGISTIC, s=1.0 / N, lambda_w=0.01, lambda_v=0.02, eta=0.5, update_w0=True)
+    o0, ow, oV, oobj = O.full_epoch(X, y, float(w0), w, V, **kw)
+    b0, bw, bV, _ = O.minibatch_epoch(X, y, o0, ow, oV, B=4, reg_share=True, **kw)
+    p = B.make_params(K, O.LOSS_LOGISTIC, 0.01, 0.02, 0.5, 1.0 / N)
+    for option in (2, 1):
+        m = B.Matrix(N, D, rowptr, col, val)
+        m.fm_set_option(B.FM_OPT_DENSE_ROWS, option)
+        d_w0, d_w, d_V = dev_params(w0, w, V)
+        d_y = to_dev(y)
+        dG, dr = torch.full((N * K,), float("nan"), device="cuda"), torch.full((N,), float("nan"), device="cuda")
+        loss_sum = m.fm_forward(p, d_y, d_w0, d_w, d_V, G=dG, r=dr, want_loss=True)
+        assert abs(loss_sum - l.sum()) <= 1e-5 * l.sum()
+        assert_close(dG.cpu().numpy().reshape(N, K), G, "G")
+        met = m.fm_evaluate(p, d_y, d_w0, d_w, d_V)
+        assert abs(met["rmse"] - np.sqrt(np.mean((yhat - y) ** 2))) <= 1e-5 * met["rmse"]
+        m.fm_build_csc()
+        gw, gV, g0 = torch.zeros(D, device="cuda"), torch.zeros(D * K, device="cuda"), torch.zeros(1, device="cuda")
+        m.fm_gradient(p, dr, dG, d_w, d_V, g0, gw, gV)
+        assert_close(gw.cpu().numpy(), wgw, "grad_w")
+        assert_close(gV.cpu().numpy().reshape(D, K), wgV, "grad_V")
+        obj = m.fm_sgd_epoch(p, d_y, d_w0, d_w, d_V, want_objective=True)
+        assert abs(obj[0] - oobj[0]) <= 1e-5 * oobj[0] and abs(obj[1] - oobj[1]) <= 1e-5 * oobj[1]
+        assert_close(d_V.cpu().numpy().reshape(D, K), oV, "V")
+        m.fm_partition_batches(4)
+        m.fm_minibatch_epoch(p, d_y, d_w0, d_w, d_V)
+        assert_close(d_w.cpu().numpy(), bw, "w after batches")
+        assert_close(d_V.cpu().numpy().reshape(D, K), bV, "V after batches")
+        m.close()
 
 
 @pytest.mark.parametrize("N,D,K", [(33, 5, 4), (4097, 33, 36), (40_003, 64, 32)])
@@ -482,6 +531,7 @@ def test_half_gather_of_dense_tables(N, D, K):
     _, r = O.loss_multiplier(O.LOSS_LOGISTIC, 1.0 / N, yhat, y)
     _, gw, gV = O.gradient(X, r, G, w, V, 0.01, 0.02)
     m = B.Matrix(N, D, rowptr, col, val)
+    m.fm_set_option(B.FM_OPT_DENSE_ROWS, 1)
     p = B.make_params(K, O.LOSS_LOGISTIC, 0.01, 0.02, 0.5, 1.0 / N, half_gather=1)
     d_w0, d_w, d_V = dev_params(w0, w, V)
     d_y = to_dev(y)
