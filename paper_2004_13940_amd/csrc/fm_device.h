@@ -210,106 +210,45 @@ __device__ __forceinline__ float fm_bcast_f(float v)
     return __int_as_float(fm_bcast_i<L, T>(__float_as_int(v)));
 }
 
-// Entry slots per lane and iteration so that a group keeps 16 row gathers in flight.
-template <int L>
-struct FmChunk {
-    static constexpr int CH = (16 / L) > 0 ? (16 / L) : 1;
-};
-
-// S entry slots (slot s = entry s%L of lane-slot s/L): broadcast each entry's index and
-// multiplier inside the group, gather the rows with at most 16 loads in flight, then
-// accumulate.
-template <int VEC, int L, bool SQ, int S, class IX, class MU, class SRC>
-__device__ __forceinline__ void fm_gather_slots(const IX& ix, const MU& mu, const SRC* __restrict__ src,
-                                                int64_t stride, int kb, float (&acc)[VEC], float& sq)
-{
-    constexpr int B = S < 16 ? S : 16;
-    fm_static_for<0, S / B>([&](auto bc) {
-        constexpr int B0 = decltype(bc)::value * B;
-        float g[B][VEC];
-        float mt[B];
-        fm_static_for<0, B>([&](auto sc) {
-            constexpr int s = B0 + decltype(sc)::value;
-            constexpr int u = s / L, T = s % L;
-            const int raw = fm_bcast_i<L, T>(ix[u]);
-            mt[s - B0] = fm_bcast_f<L, T>(mu[u]);
-            fm_load_vec<VEC>(src + (int64_t)raw * stride + kb, g[s - B0]);
-        });
-#pragma unroll
-        for (int s = 0; s < B; ++s) {
-#pragma unroll
-            for (int z = 0; z < VEC; ++z) {
-                acc[z] += mt[s] * g[s][z];
-                if constexpr (SQ) sq += (mt[s] * mt[s]) * (g[s][z] * g[s][z]);
-            }
-        }
-    });
-}
-
-// The inner loop of the row kernels.  A group of L lanes walks the entries [beg,end) of one sparse row: idx[e] names a row of `src`
-// (`stride` floats apart) and val[e] its coefficient.  Lane `sub` of the group
-//   * loads entry e+sub of every L-entry slot (coalesced) and calls
+// The score of a row by a wide group of L lanes: it walks the entries [beg,end), idx[e] names a row of `src` (`stride` floats
+// apart) and val[e] its coefficient.  Lane `sub` of the group
+//   * loads entry e+sub of every L entries (coalesced) and calls
 //       m = own(index, value)      -- per-entry work of that lane, linear in the value;
 //                                     returns the multiplier of the gathered row
-//   * receives every entry's (index, m) by broadcast and accumulates
-//       acc[z] += m * src[index*stride + kb + z]     (and, if SQ, sq += m^2 * src[..]^2).
-// Full chunks of L*CH entries run without masking; the tail runs in L-entry slots whose
-// missing entries repeat the last entry with value 0.  `kb` must be a valid offset for
-// every lane (idle lanes pass 0 and discard acc).
-template <int VEC, int L, bool SQ, int CH = FmChunk<L>::CH, class Own, class SRC = float>
+//   * receives every entry's (index, m) by broadcast, four gathers at a time, and accumulates
+//       acc[z] += m * src[index*stride + kb + z]     and     sq += m^2 * src[..]^2.
+// Few registers, so that more rows are in flight.  `kb` must be a valid offset for every lane (idle lanes pass 0 and discard
+// acc).
+template <int VEC, int L, class Own, class SRC>
 __device__ __forceinline__ void fm_gather_accumulate(const int32_t* __restrict__ idx, const float* __restrict__ val,
                                                      int64_t beg, int64_t end, const SRC* __restrict__ src,
                                                      int64_t stride, int sub, int kb, float (&acc)[VEC], float& sq,
                                                      Own&& own)
 {
-    int64_t e = beg;
-    // the lean form (CH == 1) of wide groups takes every entry through the four-at-a-time loop below:
-    // few registers, so that more rows or columns are in flight
-    constexpr bool CHUNKS = !(CH == 1 && L >= 16);
-    for (; CHUNKS && e + L * CH <= end; e += L * CH) {
-        int ix[CH];
-        float mu[CH];
-#pragma unroll
-        for (int u = 0; u < CH; ++u) {
-            const int64_t my = e + u * L + sub;
-            ix[u] = idx[my];
-            mu[u] = val[my];
-        }
-#pragma unroll
-        for (int u = 0; u < CH; ++u) mu[u] = own(ix[u], mu[u]);
-        fm_gather_slots<VEC, L, SQ, CH * L>(ix, mu, src, stride, kb, acc, sq);
-    }
-    for (; e < end; e += L) {
+    for (int64_t e = beg; e < end; e += L) {
         const int64_t want = e + sub;
         const bool has = want < end;
         const int64_t my = has ? want : end - 1;
-        int ix[1];
-        float mu[1];
-        ix[0] = idx[my];
-        mu[0] = own(ix[0], has ? val[my] : 0.f);
-        if constexpr (L <= 4) {
-            fm_gather_slots<VEC, L, SQ, L>(ix, mu, src, stride, kb, acc, sq);
-        } else {
-            // wide groups: only the entries that exist, four gathers at a time
-            const int nv = (int)((end - e) < L ? (end - e) : L);
-            for (int t0 = 0; t0 < nv; t0 += 4) {
-                float g[4][VEC];
-                float mt[4];
+        const int ix = idx[my];
+        const float mu = own(ix, has ? val[my] : 0.f);
+        const int nv = (int)((end - e) < L ? (end - e) : L);  // only the entries that exist
+        for (int t0 = 0; t0 < nv; t0 += 4) {
+            float g[4][VEC];
+            float mt[4];
 #pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    const int t = t0 + u < nv ? t0 + u : nv - 1;
-                    const int it = __shfl(ix[0], t, L);
-                    const float mm = __shfl(mu[0], t, L);
-                    mt[u] = t0 + u < nv ? mm : 0.f;
-                    fm_load_vec<VEC>(src + (int64_t)it * stride + kb, g[u]);
-                }
+            for (int u = 0; u < 4; ++u) {
+                const int t = t0 + u < nv ? t0 + u : nv - 1;
+                const int it = __shfl(ix, t, L);
+                const float mm = __shfl(mu, t, L);
+                mt[u] = t0 + u < nv ? mm : 0.f;
+                fm_load_vec<VEC>(src + (int64_t)it * stride + kb, g[u]);
+            }
 #pragma unroll
-                for (int u = 0; u < 4; ++u) {
+            for (int u = 0; u < 4; ++u) {
 #pragma unroll
-                    for (int z = 0; z < VEC; ++z) {
-                        acc[z] += mt[u] * g[u][z];
-                        if constexpr (SQ) sq += (mt[u] * mt[u]) * (g[u][z] * g[u][z]);
-                    }
+                for (int z = 0; z < VEC; ++z) {
+                    acc[z] += mt[u] * g[u][z];
+                    sq += (mt[u] * mt[u]) * (g[u][z] * g[u][z]);
                 }
             }
         }

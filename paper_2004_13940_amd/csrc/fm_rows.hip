@@ -151,9 +151,9 @@ __global__ __launch_bounds__(FM_BLOCK, L >= FM_WIDE_GROUP && is_refresh(MODE) ? 
                 return x;
             };
             if constexpr (is_half(MODE))
-                fm_gather_accumulate<VEC, L, true>(A.col, A.val, beg, beg + len, A.Vh, K, sub, kb, acc, q_acc, own);
+                fm_gather_accumulate<VEC, L>(A.col, A.val, beg, beg + len, A.Vh, K, sub, kb, acc, q_acc, own);
             else
-                fm_gather_accumulate<VEC, L, true>(A.col, A.val, beg, beg + len, A.V, K, sub, kb, acc, q_acc, own);
+                fm_gather_accumulate<VEC, L>(A.col, A.val, beg, beg + len, A.V, K, sub, kb, acc, q_acc, own);
         }
     } else {
         // rows that have no entry in this stratum keep their aggregates untouched
