@@ -336,9 +336,10 @@ int launch_rows_t(fm_matrix* m, const RowArgs& A, bool refresh, hipStream_t st)
         }
         // A forward pass of many rounds of workgroups: three of them to a compute unit (by LDS that nobody uses), so that the
         // entries of their rows stay in its L1 until they are used up (click-style scores, 2.5e6 rows, K=16: 722 -> 702 us;
-        // a small launch needs the fourth: text-like epoch of 5e4 rows 59.2 -> 60.5 us).  Groups of eight lanes hold half as
-        // many rows and want every workgroup that fits (K=32, 5.4e5 rows: 193 us with three, 175 without; half-precision V,
-        // 1e6 rows: 507 and 379).
+        // a small launch needs the fourth: text-like epoch of 5e4 rows 59.2 -> 60.5 us).  With and without for fewer lanes: K=8,
+        // 2e6 click-style rows 490 and 501 us, 9e5 text-like 332 and 346; K=2 408 and 415; K=4 441 and 441; K=1 409 and 413.
+        // Groups of eight lanes hold half as many rows and want every workgroup that fits (K=32, 5.4e5 rows: 193 us with three,
+        // 175 without; half-precision V, 1e6 rows: 507 and 379).
         const size_t lds = L < 8 && !is_refresh(M) && grid >= 4 * 3 * 256 ? 52 * 1024 : 0;
         hipLaunchKernelGGL((k_rows<VEC, L, M>), dim3((unsigned)grid), dim3(FM_BLOCK), lds, st, A);
     };
