@@ -264,8 +264,9 @@ int fm_profile_read(fm_matrix* m, int64_t* launches /*HOST nk*/, double* total_m
  *                        fm_minibatch_epoch (G = XV and X^T(r.G) as fp32 contractions; the column indices are
  *                        not read); 2 (default): unless the call has so few rows that the sparse kernels are
  *                        the faster ones; 0: the sparse kernels, as for every other matrix.
- *   FM_OPT_WIDE_ADDRESSES  1: the rows that the column kernels and the refresh gather are addressed with 64
- *                        bits, as they are when they take more than 4 GB; 0 (default): only then. */
+ *   FM_OPT_WIDE_ADDRESSES  1: the rows that the column kernels, the forward pass and the refresh gather are
+ *                        addressed with 64 bits, as they are when they take more than 4 GB; 0 (default): only
+ *                        then. */
 typedef enum {
     FM_OPT_AUX_PLANAR = 0,
     FM_OPT_SIDE_STREAMS = 1,

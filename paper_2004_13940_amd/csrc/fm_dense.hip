@@ -77,10 +77,11 @@ __device__ __forceinline__ float row_sums(float (&s)[16], int lo)
 // by rows for the second (A operand: 32 columns, two rows a step).  The rows of a step of the second product are paired
 // as the result registers of the first hold them (rows c_row(v, 0) and c_row(v, 1)), so that register v, times r, is its
 // B operand as it stands.  Bound: 1e6 rows, D = 64, K = 32 are 392 MB of X, G, y and r (71 us at the rate of a copy) and
-// 60 us of matrix instructions, with vector instructions for a third of the issue slots beside them; it takes 112 us, the
-// epoch 120 where a forward and a column kernel that each read X took 204.  D = 45, K = 8: 123 us, 500 through the sparse
-// kernels.  X by float4 although they meet banks of the LDS four to one on the way in: 137 us, float by float 149.  The
-// operands from V are read from LDS: in registers they cost the third wavefront of a SIMD.
+// 52 us of matrix instructions (47 % of the time by their counter), with vector instructions for another quarter of the issue
+// slots; the epoch takes 120 us, 6 of them the finish, where a forward and a column kernel that each read X took 204.  D = 45,
+// K = 8: 118 us, 500 through the sparse kernels.  X by float4 although they meet banks of the LDS four to one on the way in:
+// when the kernel was new, 137 us, float by float 149.  The operands from V are read from LDS: in registers they cost the
+// third wavefront of a SIMD.
 // LDS of a wavefront: its tile of X, then r, a, q of the tile's rows and as many zeros.
 template <int DB>
 struct DenseLds {
