@@ -339,8 +339,13 @@ int launch_rows_t(fm_matrix* m, const RowArgs& A, bool refresh, hipStream_t st)
         // a small launch needs the fourth: text-like epoch of 5e4 rows 59.2 -> 60.5 us).  With and without for fewer lanes: K=8,
         // 2e6 click-style rows 490 and 501 us, 9e5 text-like 332 and 346; K=2 408 and 415; K=4 441 and 441; K=1 409 and 413.
         // Groups of eight lanes hold half as many rows and want every workgroup that fits (K=32, 5.4e5 rows: 193 us with three,
-        // 175 without; half-precision V, 1e6 rows: 507 and 379).
-        const size_t lds = L < 8 && !is_refresh(M) && grid >= 4 * 3 * 256 ? 52 * 1024 : 0;
+        // 175 without; half-precision V, 1e6 rows: 507 and 379), unless V is far beyond the L1: four of the six for which there
+        // are registers then find more of it in the L2 (K=32, 8e5 rows of 50 uniform columns: 8,000 columns, 1 MB, 351 -> 313 us,
+        // 25,000 453 -> 424; 2e6 click-style rows 687 -> 675; but 1.5e6 rows of 12 of 1,200 columns 176 -> 189, 8e5 rows of 50 of
+        // 80 203 -> 215; and half-precision V, whose rows are half as long, 2e6 click-style rows 664 -> 732).
+        const bool many = grid >= 4 * 3 * 256;
+        const bool beyond_l1 = m->D * (int64_t)A.K * (int64_t)sizeof(float) > 512 * 1024;
+        const size_t lds = L < 8 && !is_refresh(M) && many ? 52 * 1024 : L == 8 && M == MODE_FORWARD && many && beyond_l1 ? 36 * 1024 : 0;
         hipLaunchKernelGGL((k_rows<VEC, L, M>), dim3((unsigned)grid), dim3(FM_BLOCK), lds, st, A);
     };
     if (refresh) {
