@@ -667,7 +667,7 @@ static int half_copy(fm_matrix* m, const fm_params* p, const float* V, const _Fl
 // (loss, multiplier) pairs that a forward pass over all rows leaves (what: see forward_args): one per workgroup
 static int64_t forward_pairs(const fm_matrix* m, const fm_params* p, int what = FM_DENSE_FORWARD)
 {
-    return fm_dense_takes(m, p->K, m->N, what) ? fm_dense_chunks(m->N, m->D, p->K) : fm_rows_grid(m, m->N, p->K);
+    return fm_dense_takes(m, p, m->N, what) ? fm_dense_chunks(m->N, m->D, p->K) : fm_rows_grid(m, m->N, p->K);
 }
 
 // The sums over n pairs (or, single, n multipliers `stride` floats apart) as an epilogue.
@@ -724,7 +724,7 @@ static int forward_args(fm_matrix* m, const fm_params* p, const float* y, const 
     A.row_part = (want_sums && y != nullptr) ? m->row_part : nullptr;
     A.loss = p->loss;
     A.s = p->loss_scale;
-    if (fm_dense_takes(m, p->K, m->N, what)) {
+    if (fm_dense_takes(m, p, m->N, what)) {
         A.dense_D = (int32_t)m->D;
         A.dense_half = p->half_gather;
     } else {
@@ -822,7 +822,7 @@ extern "C" int fm_evaluate(fm_matrix* m, const fm_params* p, const float* y, con
     A.eval_part = direct ? m->h_scal + 8 : reinterpret_cast<double*>(m->aux);
     A.loss = p->loss;
     A.s = 1.f;
-    if (fm_dense_takes(m, p->K, m->N, FM_DENSE_FORWARD)) {
+    if (fm_dense_takes(m, p, m->N, FM_DENSE_FORWARD)) {
         A.dense_D = (int32_t)m->D;
         A.dense_half = p->half_gather;
     } else {
@@ -938,7 +938,7 @@ extern "C" int fm_gradient(fm_matrix* m, const fm_params* p, const float* r, con
     A.V = const_cast<float*>(V);
     A.grad_w = grad_w;
     A.grad_V = grad_V;
-    if (fm_dense_takes(m, p->K, m->N, FM_DENSE_GRADIENT))
+    if (fm_dense_takes(m, p, m->N, FM_DENSE_GRADIENT))
         FM_TRY(dense_sums(m, A, st));
     else
         fill_long(m, A, m->lfull, 0, false);
@@ -1353,8 +1353,8 @@ extern "C" int fm_minibatch_epoch(fm_matrix* m, const fm_params* p, const float*
             // Batches of few rows whose columns are summed whole (groups of up to eight lanes) are the sparse kernels', us for
             // six batches dense / sparse: 64 columns, K=32 1,000 rows each 108 / 71, 2,000 111 / 89, 4,000 (not whole) 109 / 114;
             // 22 columns, K=8 80 / 59, 82 / 66, 87 / 101.
-            dense = fm_dense_takes(m, p->K, nb, FM_DENSE_FORWARD | FM_DENSE_GRADIENT) &&
-                    !(m->lbatch.whole && lanes <= 8 && m->opt.dense_rows != 1);
+            dense = fm_dense_takes(m, p, nb, FM_DENSE_FORWARD | FM_DENSE_GRADIENT) &&
+                    !(m->lbatch.whole && lanes <= 8 && m->opt.dense_rows != 1 && !p->half_gather);
             if (dense) {
                 R.dense_D = (int32_t)m->D;
                 R.dense_half = p->half_gather;

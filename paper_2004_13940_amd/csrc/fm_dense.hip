@@ -479,10 +479,12 @@ bool fm_dense_fits(const fm_matrix* m, int32_t K) { return m->is_dense && m->D <
 //             64 columns, K=32               21.3 / 18.3        21.3 / 19.7        21.6 / 23.3         21.7 / 26.8
 //   epoch     60 columns, K=64               25.3 / 22.7  2,000 25.0 / 25.5  4,000 25.9 / 27.3         30.4 / 38.4
 //             64 columns, K=32               17.6 / 17.4        18.0 / 17.3        18.0 / 18.7         21.2 / 29.4
-bool fm_dense_takes(const fm_matrix* m, int32_t K, int64_t rows, int what)
+// Half-precision factors are always the dense kernels': they need no copy of V, which is a launch of its own and memory.
+bool fm_dense_takes(const fm_matrix* m, const fm_params* p, int64_t rows, int what)
 {
+    const int32_t K = p->K;
     if (m->opt.dense_rows == 0 || rows < 1 || !fm_dense_fits(m, K)) return false;
-    if (m->opt.dense_rows == 1) return true;
+    if (m->opt.dense_rows == 1 || p->half_gather) return true;
     const bool both = m->D > DT && K > DT, either = m->D > DT || K > DT;
     if (what == FM_DENSE_GRADIENT) return !either || rows > 8192;
     if (what == FM_DENSE_FORWARD) return !either || rows > (K > DT ? 8192 : 4096);

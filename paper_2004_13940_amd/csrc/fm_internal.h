@@ -342,7 +342,8 @@ bool fm_dense_fits(const fm_matrix* m, int32_t K);           // the dense kernel
 int64_t fm_dense_chunks(int64_t N, int64_t D, int32_t K);    // workgroups of a pass over N rows; never fewer for more rows
 int fm_dense_parts(int64_t N, int64_t D, int32_t K);         // items that one of them leaves for a column
 enum { FM_DENSE_FORWARD = 1, FM_DENSE_GRADIENT = 2 };
-bool fm_dense_takes(const fm_matrix* m, int32_t K, int64_t rows, int what);  // ... and take such a pass over so many rows
+// ... and take such a pass over so many rows
+bool fm_dense_takes(const fm_matrix* m, const fm_params* p, int64_t rows, int what);
 int fm_launch_dense(fm_matrix* m, const DenseArgs& A, int what, hipStream_t st);  // gradient: partial sums; the finish follows
 int fm_unpack_aux(fm_matrix* m, float* a, float* G, float* q, float* r, hipStream_t st);
 

@@ -514,6 +514,34 @@ def test_tables_around_the_rows_that_the_dense_kernels_take(N, D, K):
         m.close()
 
 
+def test_captured_half_precision_pass_of_a_small_table_needs_no_copy_of_the_factors():
+    """After a pass in fp32 the workspace is there; a first pass with half_gather is then captured, which a memory allocation
+    would spoil, and replayed between eager passes."""
+    import torch
+    from paper_2004_13940_amd import binding as B
+    rng = np.random.default_rng(8060)
+    N, D, K = 700, 40, 36
+    val = rng.standard_normal(N * D).astype(np.float32)
+    m = B.Matrix(N, D, np.arange(N + 1, dtype=np.int64) * D, np.tile(np.arange(D, dtype=np.int32), N), val)
+    w0, w, V = dev_params(np.float32(0.1), (rng.standard_normal(D) * 0.1).astype(np.float32), (rng.standard_normal((D, K)) * 0.1).astype(np.float32))
+    p = B.make_params(K, O.LOSS_LOGISTIC, 0.0, 0.0, 0.5, 1.0 / N)
+    ph = B.make_params(K, O.LOSS_LOGISTIC, 0.0, 0.0, 0.5, 1.0 / N, half_gather=1)
+    out = torch.zeros(N, device="cuda")
+    m.fm_forward(p, None, w0, w, V, yhat=out)
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        m.fm_forward(ph, None, w0, w, V, yhat=out)
+    eager = torch.zeros(N, device="cuda")
+    for _ in range(3):
+        out.zero_()
+        g.replay()
+        m.fm_forward(ph, None, w0, w, V, yhat=eager)
+        torch.cuda.synchronize()
+        assert torch.equal(out, eager)
+    m.close()
+
+
 @pytest.mark.parametrize("N,D,K", [(33, 5, 4), (4097, 33, 36), (40_003, 64, 32)])
 def test_half_gather_of_dense_tables(N, D, K):
     """The dense kernel rounds the factors of the scores itself; the step is taken on the fp32 factors.  Metrics, scores and an
