@@ -245,9 +245,10 @@ int fm_profile_read(fm_matrix* m, int64_t* launches /*HOST nk*/, double* total_m
 
 /* Switches between code paths that compute the same thing, per handle; tests run every one of them
  * against the oracle.  Results do not depend on them beyond fp32 rounding, except as FM_OPT_LAZY_REG says.
- *   FM_OPT_AUX_PLANAR    1: the handle keeps the aggregates planar (G [N x K], then r, a, q) for every
- *                        K; 0 (default): as packed rows [G | r | a | q | pad] when [G | r] fits one
- *                        128-byte line (K % 4 == 0, K <= 28).  Changing it drops the aggregates held.
+ *   FM_OPT_AUX_PLANAR    1: the handle keeps the aggregates planar (G [N x K], (a, q) and r apart) for every
+ *                        K; 2: as packed rows [G | r | a | q | pad] when [G | r] fits one 128-byte line
+ *                        (K % 4 == 0, K <= 28); 0 (default): as 2, but planar where K and the rows of the
+ *                        pass make that the faster one.  Changing it drops the aggregates held.
  *   FM_OPT_SIDE_STREAMS  1 (default): column kernels that touch disjoint columns overlap on two
  *                        internal streams; 0: everything on the caller's stream.
  *   FM_OPT_LAZY_REG      1 (default): fm_stratified_epoch and fm_minibatch_epoch postpone the

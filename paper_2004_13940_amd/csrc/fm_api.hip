@@ -478,26 +478,42 @@ static int no_half(fm_matrix* m, const fm_params* p)
     return FM_OK;
 }
 
-// Packed rows are used when [G | r] of a row fits one 128-byte line (a whole number of float4,
-// K <= 28): a column-side gather is then a single request.  For larger K a row of G is one or
-// more whole lines by itself and the planar layout gathers fewer of them.  The option aux_planar
-// selects the planar layout always.
-bool fm_aux_packed(const fm_matrix* m, int32_t K) { return !m->opt.aux_planar && K % 4 == 0 && K + 1 <= 32; }
+// Packed rows exist when [G | r] of a row fits one 128-byte line (a whole number of float4, K <= 28): a column-side gather
+// is then a single request.  For larger K a row of G is one or more whole lines by itself.
+static bool packed_exists(const fm_matrix* m, int32_t K) { return m->opt.aux != 1 && K % 4 == 0 && K + 1 <= 32; }
+
+// Which layout a pass takes whose columns gather from so many rows (all of the matrix, a row block, a batch).  At K = 16 a
+// row of G is half a line and a packed row a whole one: planar moves half the bytes, and as long as the multipliers of the
+// rows (4 bytes each) stay in an XCD's L2 beside them, the second request for r is a cheap one.  Packed / planar, us, K = 16:
+// stratified epochs of click-style rows 156,250 rows to a block 32200 / 27500, 37,500 1880 / 1480, 75,000 3460 / 2670, 625,000
+// 9105 / 8890, text-like 1,562 rows 558 / 493; mini-batch epochs 75,000 rows to a batch 754 / 700, 156,250 2900 / 2510, 300,000
+// 1252 / 1284, 1.25e6 2390 / 2630; full epochs text-like 5e4 rows 60 / 55, 2e5 287 / 275, click-style 1.5e5 154 / 153, 6e5
+// 510 / 531, 1e7 7120 / 8300.  Any other K packs better: a packed row up to K = 12 is half a line itself (click-style 6e5 rows,
+// K = 8: full epoch 464 / 548, mini-batch 613 / 642, strata 1341 / 1258; K = 12 470 / 558, 654 / 718, 1430 / 1498), and from
+// K = 20 on a planar row straddles lines (K = 20 593 / 666, 856 / 924, 2132 / 2062; K = 28 632 / 749, 914 / 1015, 2128 / 2309).
+constexpr int64_t FM_PLANAR_ROWS = 200000;                    // full epochs, gradients, batches
+constexpr int64_t FM_PACK_ROWS = 40000;                      // see fm_gradient
+constexpr int64_t FM_PLANAR_ROWS_STRATA = int64_t(1) << 19;  // strata: the refresh gains by it too
+static bool take_packed(const fm_matrix* m, int32_t K, int64_t rows, int64_t planar_rows)
+{
+    return packed_exists(m, K) && (m->opt.aux == 2 || K != 16 || rows > planar_rows);
+}
 
 static int64_t packed_stride(int32_t K) { return ((int64_t)K + 3 + 15) / 16 * 16; }
 
-int fm_cols_packed_mode(const fm_matrix* m, int32_t K) { return fm_aux_packed(m, K) ? FM_PACKED_LANE : FM_PLANAR; }
+static int64_t whole_lines(int64_t floats) { return (floats + 31) / 32 * 32; }
 
-int64_t fm_aux_floats(const fm_matrix* m, int32_t K)
+int64_t fm_aux_floats(const fm_matrix* m, int32_t K, bool packed)
 {
-    return fm_aux_packed(m, K) ? m->N * packed_stride(K) : m->N * ((int64_t)K + 3);
+    if (packed) return m->N * packed_stride(K);
+    return whole_lines(m->N * (int64_t)K) + whole_lines(m->N * 2) + m->N;
 }
 
-FmAux fm_aux_layout(const fm_matrix* m, int32_t K)
+FmAux fm_aux_layout(const fm_matrix* m, int32_t K, bool packed)
 {
     FmAux x;
-    if (fm_aux_packed(m, K)) {
-        x.gs = x.ss = packed_stride(K);
+    if (packed) {
+        x.gs = x.ss = x.as = packed_stride(K);
         x.G = m->aux;
         x.r = m->aux + K;
         x.a = m->aux + K + 1;
@@ -505,10 +521,11 @@ FmAux fm_aux_layout(const fm_matrix* m, int32_t K)
     } else {
         x.gs = K;
         x.ss = 1;
+        x.as = 2;
         x.G = m->aux;
-        x.r = m->aux + m->N * (int64_t)K;
-        x.a = x.r + m->N;
-        x.q = x.a + m->N;
+        x.a = m->aux + whole_lines(m->N * (int64_t)K);
+        x.q = x.a + 1;
+        x.r = x.a + whole_lines(m->N * 2);
     }
     return x;
 }
@@ -567,7 +584,10 @@ static int ensure_ws(fm_matrix* m, int32_t K)
     }
     const size_t D = (size_t)m->D;
     // fm_evaluate leaves three doubles per row block there: more than the aggregates of a single row with K <= 2 take
-    FM_TRY(fm_dev_alloc(m, (void**)&m->aux, (size_t)std::max<int64_t>(fm_aux_floats(m, K), 6) * sizeof(float)));
+    // either layout: which one a call takes is its own matter
+    const int64_t rows = packed_exists(m, K) ? fm_aux_floats(m, K, true) : 0;
+    FM_TRY(fm_dev_alloc(m, (void**)&m->aux,
+                        (size_t)std::max<int64_t>(std::max<int64_t>(rows, fm_aux_floats(m, K, false)), 6) * sizeof(float)));
     // the dense kernels may be switched on and off: room for both paths
     const int64_t chunks = fm_dense_fits(m, K) ? fm_dense_chunks(m->N, m->D, K) : 0;
     const int64_t dense_items = chunks * 2;  // a batch of few rows has two to a column and workgroup
@@ -629,14 +649,15 @@ static void fill_long(const fm_matrix* m, ColArgs& A, const LongIndex& li, int32
     A.nshort = s1 - s0;
 }
 
-// RowArgs outputs pointing into the handle's aggregate rows [G | r | a | q | pad]
+// RowArgs outputs pointing into the handle's aggregates, which the pass leaves in the layout m->aux_packed
 static void aux_outputs(fm_matrix* m, int32_t K, RowArgs& A, bool with_aq)
 {
-    const FmAux x = fm_aux_layout(m, K);
-    A.whole_rows = (fm_aux_packed(m, K) && A.y != nullptr) ? 1 : 0;  // never leave a line partly written
+    const FmAux x = fm_aux_layout(m, K, m->aux_packed);
+    A.whole_rows = (m->aux_packed && A.y != nullptr) ? 1 : 0;  // never leave a line partly written
     A.G = x.G;
     A.gs = x.gs;
     A.ss = x.ss;
+    A.as = x.as;
     A.r = x.r;
     A.a = with_aq ? x.a : nullptr;
     A.q = with_aq ? x.q : nullptr;
@@ -716,7 +737,7 @@ static int forward_args(fm_matrix* m, const fm_params* p, const float* y, const 
         A.q = q;
         A.r = r;
         A.gs = p->K;
-        A.ss = 1;
+        A.ss = A.as = 1;
     } else {
         aux_outputs(m, p->K, A, mode == 2);
         m->aux_held = true;
@@ -818,7 +839,7 @@ extern "C" int fm_evaluate(fm_matrix* m, const fm_params* p, const float* y, con
     A.big = fm_rows_big(m, p->K);
     A.y = y;
     A.gs = p->K;
-    A.ss = 1;
+    A.ss = A.as = 1;
     A.eval_part = direct ? m->h_scal + 8 : reinterpret_cast<double*>(m->aux);
     A.loss = p->loss;
     A.s = 1.f;
@@ -877,7 +898,7 @@ static int dense_sums(fm_matrix* m, ColArgs& A, hipStream_t st)
     return FM_OK;
 }
 
-static void base_col_args(fm_matrix* m, const fm_params* p, ColArgs& A)
+static void base_col_args(fm_matrix* m, const fm_params* p, bool packed, ColArgs& A)
 {
     memset(&A, 0, sizeof(A));
     A.D = m->D;
@@ -889,7 +910,8 @@ static void base_col_args(fm_matrix* m, const fm_params* p, ColArgs& A)
     A.part = m->part;
     A.ps = fm_part_stride(p->K);
     // Aggregates that do not fit the memory-side cache: rows that are gathered once do not push others out of the L2.
-    const int64_t aux_bytes = fm_aux_floats(m, p->K) * (int64_t)sizeof(float);
+    const int64_t aux_bytes = fm_aux_floats(m, p->K, packed) * (int64_t)sizeof(float);
+    A.packed = packed ? FM_PACKED_LANE : FM_PLANAR;
     A.nt = aux_bytes > (int64_t(256) << 20) ? 1 : 0;
     A.big = aux_bytes > FM_BUF_BYTES || m->opt.wide_addresses ? 1 : 0;
 }
@@ -910,24 +932,30 @@ extern "C" int fm_gradient(fm_matrix* m, const fm_params* p, const float* r, con
     E.grad_w0 = grad_w0;
     if (m->D == 0 || (grad_w == nullptr && grad_V == nullptr))
         return grad_w0 != nullptr ? fm_run_epilogue(m, E, st) : FM_OK;
+    const bool dense = fm_dense_takes(m, p, m->N, FM_DENSE_GRADIENT);
+    // Planar, the caller's arrays are read as they are, and up to FM_PACK_ROWS rows the pass that packs them costs more than
+    // it gives at any K (packed / planar, us: uniform rows of 15, 2e4 rows, K = 8 15 / 12, K = 28 17 / 13; text-like 5e4 rows
+    // K = 8 32 / 28, K = 24 45 / 43, K = 28 45 / 48; 2e5 rows, K = 8 157 / 173, K = 24 196 / 200).  The dense kernels read
+    // either once, row by row.
+    const bool packed = !dense && (m->N > FM_PACK_ROWS || m->opt.aux == 2) && take_packed(m, p->K, m->N, FM_PLANAR_ROWS);
+    if (packed_exists(m, p->K)) m->aux_full = false;  // as packing leaves it, whichever path the call takes
     ColArgs A;
-    base_col_args(m, p, A);
+    base_col_args(m, p, packed, A);
     if (grad_w0 != nullptr) A.epi = E;
     A.ptr = m->colptr;
     A.row = m->crow;
     A.val = m->cval;
-    if (fm_aux_packed(m, p->K)) {
+    if (packed) {
         // one streaming pass puts r and G into packed aggregate rows, so that every gather of the
         // column pass is one request (and dense-ish columns can be staged through LDS)
         FM_TRY(fm_pack_aux(m, r, G, st));
         m->aux_held = true;
-        m->aux_full = false;
-        const FmAux x = fm_aux_layout(m, p->K);
+        m->aux_packed = true;
+        const FmAux x = fm_aux_layout(m, p->K, true);
         A.r = x.r;
         A.G = x.G;
         A.gs = x.gs;
         A.rs = x.ss;
-        A.packed = fm_cols_packed_mode(m, p->K);
     } else {
         A.r = r;
         A.G = G;
@@ -938,7 +966,7 @@ extern "C" int fm_gradient(fm_matrix* m, const fm_params* p, const float* r, con
     A.V = const_cast<float*>(V);
     A.grad_w = grad_w;
     A.grad_V = grad_V;
-    if (fm_dense_takes(m, p, m->N, FM_DENSE_GRADIENT))
+    if (dense)
         FM_TRY(dense_sums(m, A, st));
     else
         fill_long(m, A, m->lfull, 0, false);
@@ -977,6 +1005,7 @@ extern "C" int fm_sgd_epoch(fm_matrix* m, const fm_params* p, const float* y, fl
         return FM_OK;
     }
     // steps 1-3: G, r, loss and sum r
+    m->aux_packed = take_packed(m, p->K, m->N, FM_PLANAR_ROWS);
     RowArgs R;
     FM_TRY(forward_args(m, p, y, w0, w, V, nullptr, nullptr, nullptr, nullptr, nullptr, 1, true,
                         FM_DENSE_FORWARD | FM_DENSE_GRADIENT, R, st));
@@ -985,16 +1014,15 @@ extern "C" int fm_sgd_epoch(fm_matrix* m, const fm_params* p, const float* y, fl
     if (!dense) FM_TRY(fm_launch_rows(m, R, false, st));
     // steps 4-5 fused: gradient of every column and the step on w, V
     ColArgs A;
-    base_col_args(m, p, A);
+    base_col_args(m, p, m->aux_packed, A);
     A.ptr = m->colptr;
     A.row = m->crow;
     A.val = m->cval;
-    const FmAux x = fm_aux_layout(m, p->K);
+    const FmAux x = fm_aux_layout(m, p->K, m->aux_packed);
     A.r = x.r;
     A.G = x.G;
     A.gs = x.gs;
     A.rs = x.ss;
-    A.packed = fm_cols_packed_mode(m, p->K);
     A.w = w;
     A.V = V;
     if (!dense) fill_long(m, A, m->lfull, 0, false);
@@ -1032,6 +1060,7 @@ extern "C" int fm_stratified_begin(fm_matrix* m, const fm_params* p, const float
     FM_TRY(fm_check_vec_aligned(m, {V}));
     hipStream_t st = (hipStream_t)hip_stream;
     FM_TRY(ensure_strat_ws(m, p->K));
+    m->aux_packed = take_packed(m, p->K, m->N / m->P, FM_PLANAR_ROWS_STRATA);
     FM_TRY(run_forward(m, p, y, w0, w, V, nullptr, nullptr, nullptr, nullptr, nullptr, 2, false, st));
     m->aux_full = true;
     return FM_OK;
@@ -1050,7 +1079,7 @@ static void set_shares(ColArgs& A, const float* rho, const int64_t* bounds, int6
 // Column-side arguments of stratum s (s == P: the flush after the last stratum).
 static void strat_col_args(fm_matrix* m, const fm_params* p, int32_t s, float* w, float* V, bool lazy, ColArgs& A)
 {
-    base_col_args(m, p, A);
+    base_col_args(m, p, m->aux_packed, A);
     A.w = w;
     A.V = V;
     A.P = m->P;
@@ -1072,12 +1101,11 @@ static int stratified_step(fm_matrix* m, const fm_params* p, int32_t s, const fl
     A.mark = lazy ? nullptr : m->col_mark;
     A.row = m->s_row;
     A.val = m->s_cval;
-    const FmAux x = fm_aux_layout(m, p->K);
+    const FmAux x = fm_aux_layout(m, p->K, m->aux_packed);
     A.r = x.r;
     A.G = x.G;
     A.gs = x.gs;
     A.rs = x.ss;
-    A.packed = fm_cols_packed_mode(m, p->K);
     if (!p->stale_aux) {  // the changes are only recorded for the refresh
         A.dV = m->dV;
         A.dwn = m->dwn;
@@ -1139,7 +1167,7 @@ extern "C" int fm_stratified_step(fm_matrix* m, const fm_params* p, int32_t s, c
 // The bias step from the multipliers as they stand in the aggregate rows.
 static void set_bias_step(fm_matrix* m, const fm_params* p, float* w0, FmEpilogue& E)
 {
-    const FmAux x = fm_aux_layout(m, p->K);
+    const FmAux x = fm_aux_layout(m, p->K, m->aux_packed);
     set_epilogue(m, E, x.r, m->N, x.ss, true);
     E.w0 = w0;
     E.eta = p->eta;
@@ -1267,6 +1295,7 @@ extern "C" int fm_stratified_epoch(fm_matrix* m, const fm_params* p, const float
     FM_TRY(fm_check_vec_aligned(m, {V}));
     hipStream_t st = (hipStream_t)hip_stream;
     FM_TRY(ensure_strat_ws(m, p->K));
+    m->aux_packed = take_packed(m, p->K, m->N / m->P, FM_PLANAR_ROWS_STRATA);
     // The refresh of a stratum reads the change of a column only where the column has entries in
     // its cell, so the regulariser-only steps of the other columns can wait (not when every row
     // is refreshed from every column's change).
@@ -1308,14 +1337,15 @@ extern "C" int fm_minibatch_epoch(fm_matrix* m, const fm_params* p, const float*
     FM_TRY(ensure_ws(m, p->K));
     m->aux_full = false;
     m->aux_held = true;
-    const FmAux x = fm_aux_layout(m, p->K);
+    m->aux_packed = take_packed(m, p->K, m->N / m->B, FM_PLANAR_ROWS);
+    const FmAux x = fm_aux_layout(m, p->K, m->aux_packed);
     // a column without entries in a batch only takes the regulariser's step there: postponed
     // until the column next has entries, or the epoch ends
     const bool lazy = m->opt.lazy_reg;
     bool sound = true;
     if (lazy) FM_TRY(clear_lazy(m, st, &sound));
     auto col_args = [&](int32_t b, ColArgs& A) {
-        base_col_args(m, p, A);
+        base_col_args(m, p, m->aux_packed, A);
         A.w = w;
         A.V = V;
         A.P = m->B;
@@ -1345,8 +1375,9 @@ extern "C" int fm_minibatch_epoch(fm_matrix* m, const fm_params* p, const float*
             R.G = x.G + r0 * x.gs;
             R.gs = x.gs;
             R.ss = x.ss;
+            R.as = x.as;
             R.r = x.r + r0 * x.ss;
-            R.whole_rows = fm_aux_packed(m, p->K) ? 1 : 0;
+            R.whole_rows = m->aux_packed ? 1 : 0;
             R.row_part = p->update_w0 ? m->row_part : nullptr;
             R.loss = p->loss;
             R.s = p->loss_scale;
@@ -1375,7 +1406,6 @@ extern "C" int fm_minibatch_epoch(fm_matrix* m, const fm_params* p, const float*
         A.G = x.G;
         A.gs = x.gs;
         A.rs = x.ss;
-        A.packed = fm_cols_packed_mode(m, p->K);
         if (!dense) fill_long(m, A, m->lbatch, b, true);
         // An eighth of the batch's aggregate rows fits the L2 of an XCD (4 MB): then each XCD keeps to its own (mini-batch
         // epoch of the click-style workload, batches of 156,250 rows and 20 MB: 3092 -> 2927 us; 0.86 to 1.01 times the time
@@ -1420,10 +1450,10 @@ extern "C" int fm_set_option(fm_matrix* m, int32_t option, int32_t value)
     if (m == nullptr) return FM_EINVAL;
     switch (option) {
         case FM_OPT_AUX_PLANAR:
-            if (m->opt.aux_planar != (value != 0)) {
+            if (m->opt.aux != (value == 0 || value == 2 ? value : 1)) {
                 FM_HIP(m, hipDeviceSynchronize());
                 fm_drop_workspace(m);  // the aggregates change layout
-                m->opt.aux_planar = value != 0;
+                m->opt.aux = value == 0 || value == 2 ? value : 1;
             }
             return FM_OK;
         case FM_OPT_SIDE_STREAMS:

@@ -307,8 +307,8 @@ __global__ __launch_bounds__(FM_BLOCK, dense_per_cu(DB, KB)) void k_dense(const 
                 if (lo < nrows) {
                     if (!GRADIENT && A.yhat != nullptr) A.yhat[mine] = yh;
                     if (!A.whole_rows) {
-                        if (!GRADIENT && A.a != nullptr) A.a[mine * A.ss] = a_i;
-                        if (!GRADIENT && A.q != nullptr) A.q[mine * A.ss] = q_i;
+                        if (!GRADIENT && A.a != nullptr) A.a[mine * A.as] = a_i;
+                        if (!GRADIENT && A.q != nullptr) A.q[mine * A.as] = q_i;
                         if (A.y != nullptr && A.r != nullptr) A.r[mine * A.ss] = r_i;
                     }
                 }

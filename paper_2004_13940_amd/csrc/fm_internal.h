@@ -37,7 +37,7 @@ struct FmTune {
 
 // Per-handle switches between code paths that compute the same thing (fm_set_option).
 struct FmOptions {
-    bool aux_planar = false;   // planar aggregates for every K (default: packed rows when [G | r] fits one line)
+    int aux = 0;               // layout of the aggregates: 0 as take_packed chooses, 1 planar, 2 packed where that exists
     bool side_streams = true;  // column kernels that touch disjoint columns overlap on internal side streams
     bool lazy_reg = true;      // regulariser-only steps of a stratified or mini-batch epoch are postponed
     int graph = 1;             // stratified epoch from a captured graph: 0 never, 1 when launch-bound, 2 always
@@ -46,15 +46,13 @@ struct FmOptions {
     bool wide_addresses = false;  // gathers take 64-bit addresses at any size
 };
 
-// Where the handle keeps the aggregates.  Packed (when [G | r] fits one 128-byte line: K % 4 == 0,
+// Where the handle keeps the aggregates.  Packed (exists when [G | r] fits one 128-byte line: K % 4 == 0,
 // K <= 28): one row [G_0..G_{K-1}, r, a, q, pad] per example with a stride that is a multiple of
-// 16 floats.  Planar otherwise: G dense [N x K], then r, a, q as dense vectors.
+// 16 floats.  Planar: G dense [N x K], pairs (a, q), and r as a dense vector.
 struct FmAux {
     float *G, *r, *a, *q;
-    int64_t gs, ss;
+    int64_t gs, ss, as;  // floats between rows of G, of r, of a and q
 };
-struct fm_matrix;
-bool fm_aux_packed(const fm_matrix* m, int32_t K);
 // floats per row of partial sums [acc_0..acc_{K-1} | gw | s2 | pad]: a multiple of 32 (128 bytes)
 inline int64_t fm_part_stride(int32_t K) { return ((int64_t)K + 2 + 31) / 32 * 32; }
 // Arrays up to this size are gathered through a buffer descriptor with offsets of 32 bits (see fm_walk; wide groups use
@@ -62,9 +60,8 @@ inline int64_t fm_part_stride(int32_t K) { return ((int64_t)K + 2 + 31) / 32 * 3
 constexpr int64_t FM_BUF_BYTES = 0xFFFFF000LL;
 // How the column kernels read the aggregate rows (ColArgs::packed).
 enum { FM_PLANAR = 0, FM_PACKED_LANE = 1 };
-int fm_cols_packed_mode(const fm_matrix* m, int32_t K);
-int64_t fm_aux_floats(const fm_matrix* m, int32_t K);
-FmAux fm_aux_layout(const fm_matrix* m, int32_t K);
+int64_t fm_aux_floats(const fm_matrix* m, int32_t K, bool packed);
+FmAux fm_aux_layout(const fm_matrix* m, int32_t K, bool packed);
 
 enum fm_kernel_id {
     FMK_ROWS_FORWARD = 0,
@@ -213,6 +210,7 @@ struct fm_matrix {
     double* h_scal = nullptr;   // pinned: 8 doubles that mirror scal, then one FmCheck per workgroup of k_check_csr
     bool aux_full = false;      // a, q valid (not only G, r)
     bool aux_held = false;      // the aggregate rows hold the result of a pass (fm_get_aux may read them)
+    bool aux_packed = false;    // ... in packed rows
     // side streams so that the LDS-bound and the memory-bound column kernels overlap
     hipStream_t side1 = nullptr, side2 = nullptr;
     hipEvent_t ev_fork = nullptr, ev_join1 = nullptr, ev_join2 = nullptr;
@@ -307,7 +305,8 @@ struct RowArgs {
     const float* y;     // nullable
     float *yhat, *a, *G, *q, *r;  // forward: nullable outputs ; refresh: in/out aggregates
     int64_t gs;         // floats between consecutive rows of G
-    int64_t ss;         // floats between consecutive rows of r, a, q (1, or the aggregate row stride)
+    int64_t ss;         // floats between consecutive rows of r (1, or the aggregate row stride)
+    int64_t as;         // ... of a and q (2: they are pairs and move as one float2)
     int32_t whole_rows; // packed aggregate rows: r, a, q move as one float4 (forward: and the padding is written with them)
     float* row_part;    // nullable: [2*gridDim] loss and sum r per block
     double* eval_part;  // nullable: [3*gridDim] sums of losses, squared errors and correct signs per block
@@ -463,7 +462,7 @@ struct DenseArgs {
     const float *w0, *w, *V, *y;  // forward; y nullable
     int32_t half;                 // forward: V rounded to half precision
     float *yhat, *a, *G, *q, *r;  // forward: nullable outputs; gradient alone: G and r are read
-    int64_t gs, ss;               // floats between rows of G, of r, a, q
+    int64_t gs, ss, as;           // floats between rows of G, of r, of a and q
     int32_t whole_rows;           // forward: packed aggregate rows [G | r | a | q | pad] go out whole
     int32_t loss;
     float s;

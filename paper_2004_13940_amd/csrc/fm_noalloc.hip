@@ -83,7 +83,7 @@ extern "C" int fm_forward_noalloc(fm_matrix* m, const fm_params* p, const float*
     A.q = q;
     A.r = r;
     A.gs = p->K;
-    A.ss = 1;
+    A.ss = A.as = 1;
     // every workgroup of the launch writes its pair, and the reduction reads exactly those: nothing
     // in the scratch has to start at zero
     A.row_part = sums != nullptr ? pairs : nullptr;

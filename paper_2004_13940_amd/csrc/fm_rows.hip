@@ -123,6 +123,7 @@ __global__ __launch_bounds__(FM_BLOCK, L >= FM_WIDE_GROUP && is_refresh(MODE) ? 
     const int kb = kact ? kbase : 0;
     const uint64_t grow = (uint64_t)(uint32_t)row * (uint32_t)A.gs;  // row < 2^31, strides < 2^31
     const uint64_t srow = (uint64_t)(uint32_t)row * (uint32_t)A.ss;
+    const uint64_t arow = (uint64_t)(uint32_t)row * (uint32_t)A.as;
 
     float acc[VEC];
 #pragma unroll
@@ -164,9 +165,11 @@ __global__ __launch_bounds__(FM_BLOCK, L >= FM_WIDE_GROUP && is_refresh(MODE) ? 
             fm_load_vec<4>(A.G + grow + K, z);
             a_old = z[1];
             q_old = z[2];
-        } else {
-            a_old = A.a[srow];
-            q_old = A.q[srow];
+        } else {  // (a, q) of a planar row
+            float z[2];
+            fm_load_vec<2>(A.a + arow, z);
+            a_old = z[0];
+            q_old = z[1];
         }
         // A row has few entries inside one stratum (1 to 4 where it has any): rounds as short as the group allows, four
         // gathers at a time, so that few registers are in use and many rows in flight; for groups of up to eight lanes a
@@ -232,8 +235,8 @@ __global__ __launch_bounds__(FM_BLOCK, L >= FM_WIDE_GROUP && is_refresh(MODE) ? 
                     }
                 }
             } else if (sub == 0) {
-                if (A.a != nullptr) A.a[srow] = a_i;
-                if (A.q != nullptr) A.q[srow] = q_i;
+                if (A.a != nullptr) A.a[arow] = a_i;
+                if (A.q != nullptr) A.q[arow] = q_i;
                 if (A.y != nullptr && A.r != nullptr) A.r[srow] = r_i;
             }
         }
@@ -269,9 +272,9 @@ __global__ __launch_bounds__(FM_BLOCK, L >= FM_WIDE_GROUP && is_refresh(MODE) ? 
                 fm_store_vec<4>(A.G + grow + K, z);
             }
         } else if (touched && sub == 0) {
+            const float z[2] = {a_i, q_i};
+            fm_store_vec<2>(A.a + arow, z);
             A.r[srow] = r_i;
-            A.a[srow] = a_i;
-            A.q[srow] = q_i;
         }
     }
 
@@ -407,9 +410,9 @@ __global__ void k_unpack_aux(const FmAux x, int64_t N, int32_t K, float* a, floa
     } else if (c == K) {
         if (r != nullptr) r[i] = x.r[i * x.ss];
     } else if (c == K + 1) {
-        if (a != nullptr) a[i] = x.a[i * x.ss];
+        if (a != nullptr) a[i] = x.a[i * x.as];
     } else {
-        if (q != nullptr) q[i] = x.q[i * x.ss];
+        if (q != nullptr) q[i] = x.q[i * x.as];
     }
 }
 }  // namespace
@@ -464,7 +467,7 @@ int fm_to_half(fm_matrix* m, const float* x, _Float16* out, int64_t n, hipStream
 
 int fm_pack_aux(fm_matrix* m, const float* r, const float* G, hipStream_t st)
 {
-    const FmAux x = fm_aux_layout(m, m->wsK);
+    const FmAux x = fm_aux_layout(m, m->wsK, true);
     const int64_t total = m->N * (x.gs / 4);
     if (total <= 0) return FM_OK;
     const int64_t grid = (total + 255) / 256;
@@ -480,7 +483,7 @@ int fm_unpack_aux(fm_matrix* m, float* a, float* G, float* q, float* r, hipStrea
     if (total <= 0) return FM_OK;
     const int64_t grid = (total + 255) / 256;
     if (grid > 0x7fffffffLL) return fm_fail(m, FM_ERANGE, "aggregate copy too large");
-    hipLaunchKernelGGL(k_unpack_aux, dim3((unsigned)grid), dim3(256), 0, st, fm_aux_layout(m, m->wsK), m->N, m->wsK, a, G,
+    hipLaunchKernelGGL(k_unpack_aux, dim3((unsigned)grid), dim3(256), 0, st, fm_aux_layout(m, m->wsK, m->aux_packed), m->N, m->wsK, a, G,
                        q, r);
     FM_HIP(m, hipGetLastError());
     return FM_OK;
@@ -547,6 +550,7 @@ void fm_dense_rows(const RowArgs& A, DenseArgs* E)
     E->r = A.r;
     E->gs = A.gs;
     E->ss = A.ss;
+    E->as = A.as;
     E->whole_rows = A.whole_rows;
     E->loss = A.loss;
     E->s = A.s;

@@ -740,3 +740,61 @@ def test_postponed_steps_start_from_zero_in_every_epoch():
         for a, b, what in zip(dev, new, ("w0", "w", "V")):
             assert torch.equal(a, b), f"{what} after {step}"
     m.close()
+
+
+@pytest.mark.parametrize("K", [4, 8, 12, 16, 20, 28])
+def test_packed_rows_where_planar_ones_are_the_default(K, monkeypatch):
+    """Aggregates forced into packed rows: small gradients and, at K = 16, strata and batches take planar ones by themselves."""
+    from paper_2004_13940_amd import binding as B
+    build = B.Matrix.fm_build_csc
+
+    def packed(m, *a, **k):
+        m.fm_set_option(B.FM_OPT_AUX_PLANAR, 2)
+        build(m, *a, **k)
+
+    monkeypatch.setattr(B.Matrix, "fm_build_csc", packed)
+    test_columns_of_every_length_around_the_rounds_and_the_item(K)
+    for P in (1, 3):
+        test_refresh_of_rows_of_every_length_around_the_rounds(K, P)
+
+
+@pytest.mark.parametrize("N", [199_999, 200_003])  # full epochs planar, packed; strata and small batches planar
+def test_layouts_of_the_aggregates_follow_one_another_on_a_handle(N):
+    import torch
+    from types import SimpleNamespace
+    from paper_2004_13940_amd import binding as B
+    rng = np.random.default_rng(N)
+    D, K, row = 40, 16, 3
+    col = np.sort(np.argpartition(rng.random((N, D)), row, axis=1)[:, :row], axis=1).astype(np.int32).ravel()
+    wl = SimpleNamespace(N=N, D=D, K=K, rowptr=np.arange(N + 1, dtype=np.int64) * row, col=col,
+                         val=rng.standard_normal(N * row).astype(np.float32),
+                         y=np.where(rng.random(N) < 0.5, 1.0, -1.0).astype(np.float32), w0=np.float32(0.1),
+                         w=(rng.standard_normal(D) * 0.2).astype(np.float32),
+                         V=(rng.standard_normal((D, K)) * 0.2 / np.sqrt(K)).astype(np.float32), loss=O.LOSS_LOGISTIC,
+                         lambda_w=0.01, lambda_v=0.02, eta=0.5, loss_scale=1.0 / N, update_w0=1)
+    print("layouts one after the other", N, flush=True)
+    m, p, X, dev, host = run_full_epochs(B, wl, 1)
+    m.fm_partition(3)
+    host = run_stratified_epochs(B, wl, m, p, X, dev, host, 1, check_strata=True)
+    m.fm_partition_batches(4)
+    m.fm_minibatch_epoch(p, dev[3], *dev[:3])
+    host = O.minibatch_epoch(X, wl.y, *host, B=4, update_w0=True, reg_share=True, loss=wl.loss, s=wl.loss_scale,
+                             lambda_w=wl.lambda_w, lambda_v=wl.lambda_v, eta=wl.eta)[:3]
+    m.fm_sgd_epoch(p, dev[3], *dev[:3])
+    host = O.full_epoch(X, wl.y, *host, update_w0=True, loss=wl.loss, s=wl.loss_scale, lambda_w=wl.lambda_w,
+                        lambda_v=wl.lambda_v, eta=wl.eta)[:3]
+    m.fm_stratified_begin(p, dev[3], *dev[:3])
+    a, G, q, yhat = O.forward(X, *host)
+    out = {k: torch.full((N * (K if k == "G" else 1),), float("nan"), device="cuda") for k in "aGqr"}
+    m.fm_get_aux(K, **out)
+    r = O.loss_multiplier(wl.loss, wl.loss_scale, yhat, wl.y)[1]
+    for k, want in dict(a=a, G=G, q=q, r=r).items():
+        assert_close(out[k].cpu().numpy().reshape(np.shape(want)), want, k)
+    gw, gV = torch.full((D,), float("nan"), device="cuda"), torch.full((D * K,), float("nan"), device="cuda")
+    m.fm_gradient(p, out["r"], out["G"], dev[1], dev[2], grad_w=gw, grad_V=gV)
+    _, wgw, wgV = O.gradient(X, r, G, host[1], host[2], wl.lambda_w, wl.lambda_v)
+    assert_close(gw.cpu().numpy(), wgw, "grad_w")
+    assert_close(gV.cpu().numpy().reshape(D, K), wgV, "grad_V")
+    with pytest.raises(B.FMError):  # a gradient takes the aggregates that strata go on from
+        m.fm_stratified_step(p, 0, dev[3], *dev[:3])
+    m.close()
