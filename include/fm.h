@@ -285,7 +285,8 @@ int fm_set_option(fm_matrix* m, int32_t option /*fm_option*/, int32_t value);
  *   panel            rows per panel of the L2-blocked traversal of heavy columns (default 32768)
  *   heavy_per_panel  a column is heavy if it averages this many entries per panel (default 16)
  *   vlong            columns with more items are summed by a whole workgroup      (default 128)
- *   min_panels       matrices with fewer panels use plain segments only           (default 64)
+ *   min_panels       matrices with fewer panels use plain segments only (default: 24, and matrices of
+ *                    fewer than 64,513 rows use plain segments)
  * Results do not depend on these values beyond fp32 rounding. */
 int fm_set_tuning(fm_matrix* m, int32_t seg, int32_t panel, int32_t heavy_per_panel, int32_t vlong,
                   int32_t min_panels);
@@ -294,8 +295,7 @@ int fm_set_tuning(fm_matrix* m, int32_t seg, int32_t panel, int32_t heavy_per_pa
  *   tile_seg      entries per work item inside a tile
  * Defaults follow the shape of the matrix and the latent size of the pass: 1024 / 12 / 512 for tall
  * matrices (N >= 2^21) while two tiles of 1024 rows fit the LDS of a compute unit (K a multiple of
- * 4, K <= 16); no tiles for matrices of fewer than 2^17 rows; 256 / 4 / 256 below 2^18 rows; else
- * 512 / 8 / 256.
+ * 4, K <= 16); no tiles for matrices of fewer than 360,000 rows; else 512 / 8 / 256.
  * min_per_tile < 0 keeps the current value. */
 int fm_set_tile_tuning(fm_matrix* m, int32_t tile_rows, int32_t min_per_tile, int32_t tile_seg);
 

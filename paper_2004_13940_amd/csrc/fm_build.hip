@@ -1046,18 +1046,16 @@ void fm_tile_shape(const fm_matrix* m, int32_t K, int* tile_rows, int* tile_min,
 {
     const FmTune& T = m->tune;
     const int64_t N = m->N;
-    // one workgroup works on one tile: tall matrices take big tiles (fewer items, hence fewer partial
-    // sums), shorter ones small tiles (enough workgroups to fill the chip), and below 2^17 rows none: their aggregate
-    // rows stay in the caches anyway, and one launch over short items beats three kernels on three streams.  Epochs in us
-    // without tiles and with tiles of 128 rows, at 8,000 / 30,000 / 120,000 rows: click-like K=16 30, 43, 124 and 71, 74,
-    // 129; text-like K=16 33, 46, 213 and 76, 88, 196; table of 22 columns, K=16 18, 26, 48 and 43, 43, 61
+    // One workgroup works on one tile: tall matrices take big tiles (fewer items, hence fewer partial sums), and shorter ones
+    // none: their panels hold the rows in the L2 as well, and one launch over longer items beats three kernels on three
+    // streams.  Gradients in us, with tiles of 512 (below 2^18 rows 256) and without: text-like rows, K = 16 1.4e5 197 / 145, 2e5
+    // 180 / 158, 4e5 300 / 342, 1e6 516 / 568, K = 32 2e5 196 / 189, 4e5 354 / 398; click-style, K = 16 1.8e5 130 / 103, 2.6e5
+    // 164 / 142, 3e5 167 / 162, 4.2e5 229 / 235, 1e6 513 / 560, K = 32 3e5 196 / 194, 4.2e5 262 / 288, 7e5 472 / 518.
     int rows = 512, dense = 8, seg = 256;
     if (K > 0 && K % 4 == 0 && K <= 16 && N >= (int64_t(1) << 21)) {
         rows = 1024, dense = 12, seg = 512;
-    } else if (N < (int64_t(1) << 17)) {
-        rows = 128, dense = 0, seg = 128;
-    } else if (N < (int64_t(1) << 18)) {
-        rows = 256, dense = 4, seg = 256;
+    } else if (N < 360000) {
+        dense = 0;
     }
     *tile_rows = T.tile > 0 ? (T.tile < 64 ? 64 : T.tile) : rows;
     *tile_min = T.tile_min >= 0 ? T.tile_min : dense;
@@ -1110,12 +1108,13 @@ int fm_build_full_index(fm_matrix* m, int32_t K, hipStream_t st)
     // Panels shrink (down to 1024 rows) so that a matrix of moderate height still has
     // min_panels of them to spread over the XCD lists; the density that makes a column
     // heavy (heavy_per_panel / panel) is kept.
+    const int64_t min_panels = T.min_panels > 0 ? T.min_panels : FM_MIN_PANELS;
     int64_t panel = T.panel;
-    while (panel > 1024 && (m->N + panel - 1) / panel < T.min_panels) panel /= 2;
+    while (panel > 1024 && (m->N + panel - 1) / panel < min_panels) panel /= 2;
     const int64_t npanels = (m->N + panel - 1) / panel;
     const double heavy_density = (double)T.heavy_per_panel / (double)T.panel;
     // the panel order pays off only when there are many more panels than XCDs
-    const int64_t heavy_min = npanels >= T.min_panels
+    const int64_t heavy_min = npanels >= min_panels && (T.min_panels > 0 || m->N >= FM_PANEL_ROWS)
                                   ? std::max<int64_t>((int64_t)(heavy_density * (double)m->N) + 1, (int64_t)T.seg + 1)
                                   : INT64_MAX;
     const int64_t maxpos = (npanels + FM_XCDS - 1) / FM_XCDS;

@@ -798,3 +798,33 @@ def test_layouts_of_the_aggregates_follow_one_another_on_a_handle(N):
     with pytest.raises(B.FMError):  # a gradient takes the aggregates that strata go on from
         m.fm_stratified_step(p, 0, dev[3], *dev[:3])
     m.close()
+
+
+@pytest.mark.parametrize("N,K", [(64_512, 8), (64_513, 8), (64_513, 64), (131_073, 16), (359_999, 12), (360_000, 12), (360_000, 36)])
+def test_panels_and_tiles_where_their_rules_change(N, K):
+    """Plain segments below 64,513 rows, panels from there on, LDS tiles from 360,000; columns of every density."""
+    import torch
+    from paper_2004_13940_amd import binding as B
+    rng = np.random.default_rng(N + K)
+    density = np.array([0.6, 0.2, 0.05, 0.02, 0.01, 0.004, 0.001, 5e-4, 2e-4, 1e-4, 0.0])
+    D = len(density)
+    mask = rng.random((N, D)) < density
+    rowptr = np.concatenate([[0], np.cumsum(mask.sum(1))]).astype(np.int64)
+    col = np.nonzero(mask)[1].astype(np.int32)
+    val = rng.standard_normal(len(col)).astype(np.float32)
+    r = (rng.standard_normal(N) / N).astype(np.float32)
+    G = rng.standard_normal((N, K)).astype(np.float32)
+    w, V = (rng.standard_normal(D) * 0.1).astype(np.float32), (rng.standard_normal((D, K)) * 0.1).astype(np.float32)
+    print("panels and tiles", N, K, len(col), flush=True)
+    m = B.Matrix(N, D, rowptr, col, val)
+    m.fm_build_csc()
+    m.fm_profile_enable(True)
+    _, d_w, d_V = dev_params(np.float32(0), w, V)
+    gw, gV = torch.full((D,), float("nan"), device="cuda"), torch.full((D * K,), float("nan"), device="cuda")
+    m.fm_gradient(B.make_params(K, O.LOSS_SQUARED, 0.01, 0.02, 0.1), to_dev(r), to_dev(G.ravel()), d_w, d_V, grad_w=gw, grad_V=gV)
+    torch.cuda.synchronize()
+    assert m.fm_profile_read()["cols_tile"][0] == (1 if N >= 360_000 and K <= 32 else 0)
+    _, wgw, wgV = O.gradient(O.make_matrix(N, D, rowptr, col, val), r, G, w, V, 0.01, 0.02)
+    assert_close(gw.cpu().numpy(), wgw, "grad_w")
+    assert_close(gV.cpu().numpy().reshape(D, K), wgV, "grad_V")
+    m.close()
