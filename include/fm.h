@@ -281,7 +281,7 @@ int fm_set_option(fm_matrix* m, int32_t option /*fm_option*/, int32_t value);
 /* Work-decomposition knobs of the column side, per handle, for callers that tune or test them; they
  * must be set before fm_build_csc (FM_ESTATE afterwards).  A value <= 0 keeps the current one.
  *   seg              entries per work item of a long column        (default 32 to 256, by the entries of
- *                    the launch: of the matrix, or of a stratum or batch)
+ *                    the matrix, 32 or 48 by those of a stratum or batch)
  *   panel            rows per panel of the L2-blocked traversal of heavy columns (default 32768)
  *   heavy_per_panel  a column is heavy if it averages this many entries per panel (default 16)
  *   vlong            columns with more items are summed by a whole workgroup      (default 128)

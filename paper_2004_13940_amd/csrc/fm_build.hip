@@ -963,7 +963,7 @@ int fm_build_long_index(fm_matrix* m, const int64_t* ptr, const int32_t* ids, co
     int64_t *tl = nullptr, *ti = nullptr;
     FM_TRY(fm_dev_alloc(m, (void**)&tl, (size_t)(ntiles + 1) * sizeof(int64_t)));
     FM_TRY(fm_dev_alloc(m, (void**)&ti, (size_t)(ntiles + 1) * sizeof(int64_t)));
-    const int seg = m->tune.seg > 0 ? m->tune.seg : fm_item_length(m->nnz / nstrata);
+    const int seg = m->tune.seg > 0 ? m->tune.seg : fm_item_length(m->nnz / nstrata, nstrata > 1);
     FM_TRY(build_short_list(m, ptr, ids, ncols_total, h_bounds, nstrata, seg, out, st));
     FM_HIP(m, hipMemsetAsync(tl, 0, (size_t)(ntiles + 1) * sizeof(int64_t), st));
     FM_HIP(m, hipMemsetAsync(ti, 0, (size_t)(ntiles + 1) * sizeof(int64_t), st));
@@ -1031,11 +1031,19 @@ static void free_long_index(fm_matrix* m, LongIndex* li)
 
 // Entries per item when nobody has set it: a run is a serial chain of rounds of 16 entries, so items are as short as
 // still fills the chip (8 groups of 8 lanes per wavefront, 16 wavefronts on each of 256 compute units) once over; below
-// 32 the partial sums (one row per item) would cost as much as the entries, above 256 nothing is gained.
-int fm_item_length(int64_t entries)
+// 32 the partial sums (one row per item) would cost as much as the entries, above 256 nothing is gained, and 256 only by
+// launches that fill the chip twice over (gradients of 256 / 128: text-like 1.2e7 entries, K = 16 157 / 151 us, K = 64 307 / 299;
+// click-style 1e7, K = 16 141 / 134; 3.9e7 511 / 513; hashed 3.2e7, K = 64 1403 / 1411).
+// A stratum or batch (part of the matrix) has no panels: its items are worked on by their first rows, and the shorter they are
+// the fewer rows are in flight and the more of their lines are shared (click-style, K = 16, items of 128 or 256 / 64 / 48 /
+// 32: strata of 6.1e6 entries 27.3 / 26.9 / 26.6 / 26.6 ms, batches of 6.1e6 2568 / 2489 / 2468 / 2498 us, of 3e6, K = 8
+// - / 1236 / 1221 / 1261, strata of 1.2e7 4596 / 4365 / - / -; hashed batches of 2e6, K = 64 1573 / 1580 / 1596 / 1613).
+int fm_item_length(int64_t entries, bool part)
 {
+    constexpr int64_t FILL = 8 * 16 * 256;
+    if (part) return entries / 64 >= FILL ? 48 : 32;
     int seg = 32;
-    while (seg < 256 && entries / (2 * seg) >= 8 * 16 * 256) seg *= 2;
+    while (seg < 256 && entries / (2 * seg) >= (seg < 128 ? FILL : 2 * FILL)) seg *= 2;
     return seg;
 }
 
@@ -1067,7 +1075,7 @@ int fm_build_full_index(fm_matrix* m, int32_t K, hipStream_t st)
     LongIndex* out = &m->lfull;
     free_long_index(m, out);
     FmTune T = m->tune;
-    if (T.seg <= 0) T.seg = fm_item_length(m->nnz);
+    if (T.seg <= 0) T.seg = fm_item_length(m->nnz, false);
     fm_tile_shape(m, K, &T.tile, &T.tile_min, &T.tile_seg);
     m->lfull_shape[0] = T.tile;
     m->lfull_shape[1] = T.tile_min;

@@ -297,7 +297,7 @@ int fm_build_long_index(fm_matrix* m, const int64_t* ptr, const int32_t* ids, co
 // lfull, with the panel order of heavy columns and the LDS tiles shaped for latent size K (0: unknown)
 int fm_build_full_index(fm_matrix* m, int32_t K, hipStream_t st);
 void fm_tile_shape(const fm_matrix* m, int32_t K, int* tile_rows, int* tile_min, int* tile_seg);
-int fm_item_length(int64_t entries);  // of a launch over so many entries
+int fm_item_length(int64_t entries, bool part);  // of a launch over so many entries, all of the matrix or part of it
 int fm_ensure_lazy(fm_matrix* m, hipStream_t st);  // allocates and clears lazy_last on first use
 
 // ---- pass kernels (fm_rows.hip / fm_cols.hip / fm_reduce.hip) ----
