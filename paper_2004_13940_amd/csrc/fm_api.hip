@@ -143,6 +143,64 @@ void fm_dev_free(fm_matrix* m, void* p)
         (void)hipFree(p);
 }
 
+void fm_spend(fm_matrix* m, std::initializer_list<void*> scratch)
+{
+    for (void* p : scratch)
+        if (p != nullptr) m->spent.push_back(p);
+}
+
+// Room in the pinned block for so many bytes, or nullptr.
+static char* pinned_room(fm_matrix* m, size_t bytes)
+{
+    if (m->pin_used + bytes > (FM_PINNED_DOUBLES - 8) * sizeof(double)) return nullptr;
+    char* p = reinterpret_cast<char*>(m->h_scal + 8) + m->pin_used;
+    m->pin_used += (bytes + 7) / 8 * 8;
+    return p;
+}
+
+// Through pinned memory: the runtime's way to and from pageable memory takes 15 us and more whatever the size.
+int fm_read_later(fm_matrix* m, void* dst, const void* src, size_t bytes, hipStream_t st)
+{
+    if (bytes == 0) return FM_OK;
+    char* pin = pinned_room(m, bytes);
+    FM_HIP(m, hipMemcpyAsync(pin != nullptr ? pin : dst, src, bytes, hipMemcpyDeviceToHost, st));
+    if (pin != nullptr) m->reads.push_back({dst, (size_t)(pin - reinterpret_cast<char*>(m->h_scal + 8)), bytes});
+    return FM_OK;
+}
+
+int fm_send(fm_matrix* m, void* dst, const void* src, size_t bytes, hipStream_t st)
+{
+    if (bytes == 0) return FM_OK;
+    char* pin = pinned_room(m, bytes);
+    if (pin != nullptr) memcpy(pin, src, bytes);
+    FM_HIP(m, hipMemcpyAsync(dst, pin != nullptr ? pin : src, bytes, hipMemcpyHostToDevice, st));
+    if (pin == nullptr) FM_HIP(m, hipStreamSynchronize(st));  // src is the caller's
+    return FM_OK;
+}
+
+void fm_unsettled(fm_matrix* m)
+{
+    if (m->reads.empty() && m->spent.empty() && m->pin_used == 0) return;
+    (void)hipDeviceSynchronize();
+    m->reads.clear();
+    m->pin_used = 0;
+    for (void* p : m->spent) fm_dev_free(m, p);
+    m->spent.clear();
+}
+
+int fm_settle(fm_matrix* m, hipStream_t st)
+{
+    const hipError_t e = hipStreamSynchronize(st);
+    if (e == hipSuccess)
+        for (const FmRead& r : m->reads) memcpy(r.dst, reinterpret_cast<char*>(m->h_scal + 8) + r.at, r.bytes);
+    m->reads.clear();
+    m->pin_used = 0;
+    if (e != hipSuccess) return fm_fail(m, FM_EHIP, "building failed: %s", hipGetErrorString(e));
+    for (void* p : m->spent) fm_dev_free(m, p);
+    m->spent.clear();
+    return FM_OK;
+}
+
 extern "C" int fm_trim(void)
 {
     pool_drain();
@@ -578,7 +636,9 @@ static int ensure_ws(fm_matrix* m, int32_t K)
         fm_tile_shape(m, K, &shape[0], &shape[1], &shape[2]);
         if (memcmp(shape, m->lfull_shape, sizeof(shape)) != 0) {
             FM_HIP(m, hipDeviceSynchronize());
+            fm_unsettled(m);
             FM_TRY(fm_build_full_index(m, K, nullptr));
+            FM_TRY(fm_settle(m, nullptr));
             FM_HIP(m, hipDeviceSynchronize());
         }
     }
@@ -1250,6 +1310,13 @@ static int replay_stratified_epoch(fm_matrix* m, const fm_params* p, const float
     const bool same = m->gexec != nullptr && memcmp(&m->gkey_p, p, sizeof(fm_params)) == 0 &&
                       memcmp(m->gkey_ptr, key, sizeof(key)) == 0 && m->gkey_lazy == lazy;
     if (!same) {
+        // Capturing and instantiating take longer than the launches of one epoch (text-like, 5e4 rows, 16 strata, host time: 390 us
+        // before the first kernel): worth it from the second epoch with the same arguments on.
+        if (m->opt.graph != 2 && !(memcmp(&m->gseen_p, p, sizeof(fm_params)) == 0 && memcmp(m->gseen_ptr, key, sizeof(key)) == 0)) {
+            m->gseen_p = *p;
+            memcpy(m->gseen_ptr, key, sizeof(key));
+            return FM_ESTATE;
+        }
         fm_drop_graph(m);
         (void)fm_side_streams(m);  // created outside the capture
         if (hipStreamBeginCapture(m->gstream, hipStreamCaptureModeThreadLocal) != hipSuccess) {

@@ -777,8 +777,7 @@ int fm_scan_exclusive_i64(fm_matrix* m, int64_t* d, int64_t n, hipStream_t st)
         hipLaunchKernelGGL(k_scan_apply, dim3((unsigned)ntiles), dim3(SCAN_T), 0, st, d, n, (const int64_t*)sums);
         if (hipGetLastError() != hipSuccess) rc = fm_fail(m, FM_EHIP, "scan apply launch failed");
     }
-    if (hipStreamSynchronize(st) != hipSuccess && rc == FM_OK) rc = fm_fail(m, FM_EHIP, "scan failed");
-    fm_dev_free(m, sums);
+    fm_spend(m, {sums});
     return rc;
 }
 
@@ -807,8 +806,7 @@ static int sort_pairs(fm_matrix* m, const SortIn& in, const SortOut& out, const 
         from.key = to.key;
         for (int a = 0; a < RS_VALUES; ++a) from.v[a] = to.v[a];
     }
-    if (hipStreamSynchronize(st) != hipSuccess && rc == FM_OK) rc = fm_fail(m, FM_EHIP, "radix sort failed");
-    fm_dev_free(m, hist);
+    fm_spend(m, {hist});
     return rc;
 }
 
@@ -826,25 +824,31 @@ int fm_sort_by_key_u32(fm_matrix* m, uint32_t* keys, uint32_t* idx, uint32_t* ke
 // List of the non-empty columns with at most `seg` entries.  ptr[c], ptr[c+1] bound the entries of list
 // position c, ids[c] is its column (nullptr: c itself); per stratum when nstrata > 1: h_bounds[s] is the
 // first position of stratum s and h_short_off[s] where it starts in the short list.  Every listed column comes with its
-// first entry and its length, so that a kernel asks for all three at once.
-static int build_short_list(fm_matrix* m, const int64_t* ptr, const int32_t* ids, int64_t ncols_total,
-                            const std::vector<int64_t>& h_bounds, int32_t nstrata, int seg, LongIndex* out, hipStream_t st)
+// first entry and its length, so that a kernel asks for all three at once.  Two steps: the count, which arrives in out->nshort
+// with the next fm_settle, and the list; h_short_off arrives with the one behind it.
+static int count_short_list(fm_matrix* m, const int64_t* ptr, const int32_t* ids, int64_t ncols_total, int32_t nstrata, int seg,
+                            LongIndex* out, int64_t** tc, hipStream_t st)
 {
     out->nshort = 0;
     out->h_short_off.assign(nstrata + 1, 0);
+    *tc = nullptr;
     if (ncols_total <= 0) return FM_OK;
     const int64_t ntiles = (ncols_total + LI_TILE - 1) / LI_TILE;
-    int64_t* tc = nullptr;
-    FM_TRY(fm_dev_alloc(m, (void**)&tc, (size_t)(ntiles + 1) * sizeof(int64_t)));
-    FM_HIP(m, hipMemsetAsync(tc, 0, (size_t)(ntiles + 1) * sizeof(int64_t), st));
-    hipLaunchKernelGGL(k_short_list, dim3((unsigned)ntiles), dim3(LI_T), 0, st, ptr, ncols_total, ids, seg, 0, tc,
+    FM_TRY(fm_dev_alloc(m, (void**)tc, (size_t)(ntiles + 1) * sizeof(int64_t)));
+    FM_HIP(m, hipMemsetAsync(*tc, 0, (size_t)(ntiles + 1) * sizeof(int64_t), st));
+    hipLaunchKernelGGL(k_short_list, dim3((unsigned)ntiles), dim3(LI_T), 0, st, ptr, ncols_total, ids, seg, 0, *tc,
                        (int32_t*)nullptr, (int64_t*)nullptr, (int64_t*)nullptr, (int32_t*)nullptr);
     FM_HIP(m, hipGetLastError());
-    FM_TRY(fm_scan_exclusive_i64(m, tc, ntiles + 1, st));
-    int64_t n = 0;
-    FM_HIP(m, hipMemcpyAsync(&n, tc + ntiles, sizeof(int64_t), hipMemcpyDeviceToHost, st));
-    FM_HIP(m, hipStreamSynchronize(st));
+    FM_TRY(fm_scan_exclusive_i64(m, *tc, ntiles + 1, st));
+    return fm_read_later(m, &out->nshort, *tc + ntiles, sizeof(int64_t), st);
+}
+
+static int fill_short_list(fm_matrix* m, const int64_t* ptr, const int32_t* ids, int64_t ncols_total,
+                           const std::vector<int64_t>& h_bounds, int32_t nstrata, int seg, LongIndex* out, int64_t* tc, hipStream_t st)
+{
+    const int64_t n = out->nshort;
     if (n > 0) {
+        const int64_t ntiles = (ncols_total + LI_TILE - 1) / LI_TILE;
         int64_t *vcol = nullptr, *d_off = nullptr, *d_bounds = nullptr;
         FM_TRY(fm_dev_alloc(m, (void**)&out->short_col, (size_t)n * sizeof(int32_t)));
         FM_TRY(fm_dev_alloc(m, (void**)&out->short_beg, (size_t)n * sizeof(int64_t)));
@@ -852,27 +856,22 @@ static int build_short_list(fm_matrix* m, const int64_t* ptr, const int32_t* ids
         FM_TRY(fm_dev_alloc(m, (void**)&vcol, (size_t)n * sizeof(int64_t)));
         FM_TRY(fm_dev_alloc(m, (void**)&d_off, (size_t)(nstrata + 1) * sizeof(int64_t)));
         FM_TRY(fm_dev_alloc(m, (void**)&d_bounds, (size_t)(nstrata + 1) * sizeof(int64_t)));
-        FM_HIP(m, hipMemcpyAsync(d_bounds, h_bounds.data(), (size_t)(nstrata + 1) * sizeof(int64_t), hipMemcpyHostToDevice, st));
+        FM_TRY(fm_send(m, d_bounds, h_bounds.data(), (size_t)(nstrata + 1) * sizeof(int64_t), st));
         hipLaunchKernelGGL(k_short_list, dim3((unsigned)ntiles), dim3(LI_T), 0, st, ptr, ncols_total, ids, seg, 1, tc,
                            out->short_col, vcol, out->short_beg, out->short_len);
         FM_HIP(m, hipGetLastError());
         hipLaunchKernelGGL(k_stratum_offsets, dim3(blocks_for(nstrata + 1, 256)), dim3(256), 0, st, (const int64_t*)vcol,
                            n, (const int64_t*)d_bounds, nstrata, d_off);
         FM_HIP(m, hipGetLastError());
-        FM_HIP(m, hipMemcpyAsync(out->h_short_off.data(), d_off, (size_t)(nstrata + 1) * sizeof(int64_t),
-                                 hipMemcpyDeviceToHost, st));
-        FM_HIP(m, hipStreamSynchronize(st));
-        fm_dev_free(m, vcol);
-        fm_dev_free(m, d_off);
-        fm_dev_free(m, d_bounds);
+        FM_TRY(fm_read_later(m, out->h_short_off.data(), d_off, (size_t)(nstrata + 1) * sizeof(int64_t), st));
+        fm_spend(m, {vcol, d_off, d_bounds});
     }
-    out->nshort = n;
-    fm_dev_free(m, tc);
+    fm_spend(m, {tc});
     return FM_OK;
 }
 
 // Columns with very many items get a workgroup each in the finish step: their list, stratum by stratum.
-static int build_vlong_list(fm_matrix* m, const std::vector<int64_t>& h_first, LongIndex* out)
+static int build_vlong_list(fm_matrix* m, const std::vector<int64_t>& h_first, LongIndex* out, hipStream_t st)
 {
     std::vector<int32_t> h_vlong;
     out->h_vlong_off.assign(out->h_long_off.size(), 0);
@@ -884,15 +883,13 @@ static int build_vlong_list(fm_matrix* m, const std::vector<int64_t>& h_first, L
     out->nvlong = (int64_t)h_vlong.size();
     if (out->nvlong == 0) return FM_OK;
     FM_TRY(fm_dev_alloc(m, (void**)&out->vlong, h_vlong.size() * sizeof(int32_t)));
-    FM_HIP(m, hipMemcpy(out->vlong, h_vlong.data(), h_vlong.size() * sizeof(int32_t), hipMemcpyHostToDevice));
-    return FM_OK;
+    return fm_send(m, out->vlong, h_vlong.data(), h_vlong.size() * sizeof(int32_t), st);
 }
 
 // The long columns that a workgroup sums whole, stratum by stratum.
-static int build_big_list(fm_matrix* m, LongIndex* out)
+static int build_big_list(fm_matrix* m, const std::vector<int32_t>& h_len, LongIndex* out, hipStream_t st)
 {
-    std::vector<int32_t> h_len((size_t)out->nlong), h_big;
-    FM_HIP(m, hipMemcpy(h_len.data(), out->long_len, h_len.size() * sizeof(int32_t), hipMemcpyDeviceToHost));
+    std::vector<int32_t> h_big;
     out->h_big_off.assign(out->h_long_off.size(), 0);
     for (size_t s = 0; s + 1 < out->h_long_off.size(); ++s) {
         for (int64_t lc = out->h_long_off[s]; lc < out->h_long_off[s + 1]; ++lc)
@@ -901,8 +898,7 @@ static int build_big_list(fm_matrix* m, LongIndex* out)
     }
     if (h_big.empty()) return FM_OK;
     FM_TRY(fm_dev_alloc(m, (void**)&out->big, h_big.size() * sizeof(int32_t)));
-    FM_HIP(m, hipMemcpy(out->big, h_big.data(), h_big.size() * sizeof(int32_t), hipMemcpyHostToDevice));
-    return FM_OK;
+    return fm_send(m, out->big, h_big.data(), h_big.size() * sizeof(int32_t), st);
 }
 
 // Processing order of the items of a stratum or batch: by first row, so that the items of different columns that gather
@@ -930,7 +926,7 @@ static int order_by_row(fm_matrix* m, const int32_t* row, int32_t nstrata, LongI
     FM_TRY(fm_dev_alloc(m, (void**)&d_off, (size_t)(nstrata + 1) * sizeof(int64_t)));
     FM_TRY(fm_dev_alloc(m, (void**)&out->ord_beg, (size_t)n * sizeof(int64_t)));
     FM_TRY(fm_dev_alloc(m, (void**)&out->ord_len, (size_t)n * sizeof(int32_t)));
-    FM_HIP(m, hipMemcpyAsync(d_off, out->h_item_off.data(), (size_t)(nstrata + 1) * sizeof(int64_t), hipMemcpyHostToDevice, st));
+    FM_TRY(fm_send(m, d_off, out->h_item_off.data(), (size_t)(nstrata + 1) * sizeof(int64_t), st));
     hipLaunchKernelGGL(k_row_keys, dim3(blocks_for(n, 256)), dim3(256), 0, st, (const int64_t*)out->item_beg, n, row,
                        (const int64_t*)d_off, nstrata, row_bits_all - row_bits, row_bits, k0, i0);
     FM_HIP(m, hipGetLastError());
@@ -940,9 +936,7 @@ static int order_by_row(fm_matrix* m, const int32_t* row, int32_t nstrata, LongI
     hipLaunchKernelGGL(k_order_items, dim3(blocks_for(n, 256)), dim3(256), 0, st, (const uint32_t*)out->order, n,
                        (const int64_t*)out->item_beg, (const int32_t*)out->item_len, out->ord_beg, out->ord_len);
     FM_HIP(m, hipGetLastError());
-    FM_HIP(m, hipStreamSynchronize(st));
-    for (void* p : {(void*)k0, (void*)k1, (void*)(alt ? i0 : i1), (void*)d_off, (void*)out->item_beg, (void*)out->item_len})
-        fm_dev_free(m, p);
+    fm_spend(m, {k0, k1, alt ? i0 : i1, d_off, out->item_beg, out->item_len});
     out->item_beg = nullptr;
     out->item_len = nullptr;
     return FM_OK;
@@ -964,7 +958,8 @@ int fm_build_long_index(fm_matrix* m, const int64_t* ptr, const int32_t* ids, co
     FM_TRY(fm_dev_alloc(m, (void**)&tl, (size_t)(ntiles + 1) * sizeof(int64_t)));
     FM_TRY(fm_dev_alloc(m, (void**)&ti, (size_t)(ntiles + 1) * sizeof(int64_t)));
     const int seg = m->tune.seg > 0 ? m->tune.seg : fm_item_length(m->nnz / nstrata, nstrata > 1);
-    FM_TRY(build_short_list(m, ptr, ids, ncols_total, h_bounds, nstrata, seg, out, st));
+    int64_t* tc = nullptr;
+    FM_TRY(count_short_list(m, ptr, ids, ncols_total, nstrata, seg, out, &tc, st));
     FM_HIP(m, hipMemsetAsync(tl, 0, (size_t)(ntiles + 1) * sizeof(int64_t), st));
     FM_HIP(m, hipMemsetAsync(ti, 0, (size_t)(ntiles + 1) * sizeof(int64_t), st));
     hipLaunchKernelGGL(k_long_count, dim3((unsigned)ntiles), dim3(LI_T), 0, st, ptr, ncols_total, seg, tl, ti);
@@ -972,9 +967,10 @@ int fm_build_long_index(fm_matrix* m, const int64_t* ptr, const int32_t* ids, co
     FM_TRY(fm_scan_exclusive_i64(m, tl, ntiles + 1, st));
     FM_TRY(fm_scan_exclusive_i64(m, ti, ntiles + 1, st));
     int64_t nlong = 0, nitems = 0;
-    FM_HIP(m, hipMemcpyAsync(&nlong, tl + ntiles, sizeof(int64_t), hipMemcpyDeviceToHost, st));
-    FM_HIP(m, hipMemcpyAsync(&nitems, ti + ntiles, sizeof(int64_t), hipMemcpyDeviceToHost, st));
-    FM_HIP(m, hipStreamSynchronize(st));
+    FM_TRY(fm_read_later(m, &nlong, tl + ntiles, sizeof(int64_t), st));
+    FM_TRY(fm_read_later(m, &nitems, ti + ntiles, sizeof(int64_t), st));
+    FM_TRY(fm_settle(m, st));
+    FM_TRY(fill_short_list(m, ptr, ids, ncols_total, h_bounds, nstrata, seg, out, tc, st));
     out->nlong = nlong;
     out->nitems = nitems;
     if (nlong > 0) {
@@ -992,16 +988,17 @@ int fm_build_long_index(fm_matrix* m, const int64_t* ptr, const int32_t* ids, co
         hipLaunchKernelGGL(k_long_fill, dim3((unsigned)ntiles), dim3(LI_T), 0, st, ptr, ncols_total, ids, seg,
                            (const int64_t*)tl, (const int64_t*)ti, out->long_col, vcol, out->long_first);
         FM_HIP(m, hipGetLastError());
-        FM_HIP(m, hipMemcpyAsync(out->long_first + nlong, &nitems, sizeof(int64_t), hipMemcpyHostToDevice, st));
+        FM_TRY(fm_send(m, out->long_first + nlong, &nitems, sizeof(int64_t), st));
         hipLaunchKernelGGL(k_items, dim3(blocks_for(nlong, 4)), dim3(256), 0, st, ptr, (const int32_t*)out->long_col,
                            (const int64_t*)vcol, (const int64_t*)out->long_first, nlong, seg, out->item_col, out->item_beg,
                            out->item_len, out->long_beg, out->long_len);
         FM_HIP(m, hipGetLastError());
         std::vector<int64_t> h_vcol((size_t)nlong), h_first((size_t)nlong + 1);
-        FM_HIP(m, hipMemcpyAsync(h_vcol.data(), vcol, (size_t)nlong * sizeof(int64_t), hipMemcpyDeviceToHost, st));
-        FM_HIP(m, hipStreamSynchronize(st));
-        FM_HIP(m, hipMemcpy(h_first.data(), out->long_first, (size_t)(nlong + 1) * sizeof(int64_t),
-                            hipMemcpyDeviceToHost));
+        std::vector<int32_t> h_len(out->whole ? (size_t)nlong : 0);
+        FM_TRY(fm_read_later(m, h_vcol.data(), vcol, (size_t)nlong * sizeof(int64_t), st));
+        FM_TRY(fm_read_later(m, h_first.data(), out->long_first, (size_t)(nlong + 1) * sizeof(int64_t), st));
+        FM_TRY(fm_read_later(m, h_len.data(), out->long_len, h_len.size() * sizeof(int32_t), st));
+        FM_TRY(fm_settle(m, st));
         // per-stratum ranges of the concatenated lists
         int64_t k = 0;
         for (int32_t s = 0; s <= nstrata; ++s) {
@@ -1009,13 +1006,12 @@ int fm_build_long_index(fm_matrix* m, const int64_t* ptr, const int32_t* ids, co
             out->h_long_off[s] = k;
             out->h_item_off[s] = h_first[(size_t)k];
         }
-        fm_dev_free(m, vcol);
-        FM_TRY(build_vlong_list(m, h_first, out));
-        if (out->whole) FM_TRY(build_big_list(m, out));
+        fm_spend(m, {vcol});
+        FM_TRY(build_vlong_list(m, h_first, out, st));
+        if (out->whole) FM_TRY(build_big_list(m, h_len, out, st));
         FM_TRY(order_by_row(m, row, nstrata, out, st));
     }
-    fm_dev_free(m, tl);
-    fm_dev_free(m, ti);
+    fm_spend(m, {tl, ti});
     return FM_OK;
 }
 
@@ -1080,12 +1076,17 @@ int fm_build_full_index(fm_matrix* m, int32_t K, hipStream_t st)
     m->lfull_shape[0] = T.tile;
     m->lfull_shape[1] = T.tile_min;
     m->lfull_shape[2] = T.tile_seg;
-    FM_TRY(build_short_list(m, m->colptr, nullptr, m->D, {0, m->D}, 1, T.seg, out, st));
+    int64_t* tc = nullptr;
+    FM_TRY(count_short_list(m, m->colptr, nullptr, m->D, 1, T.seg, out, &tc, st));
     out->nlong = out->nitems = 0;
     out->h_long_off.assign(2, 0);
     out->h_item_off.assign(2, 0);
     const int64_t D = m->D;
-    if (D <= 0 || m->nnz == 0) return FM_OK;
+    if (D <= 0 || m->nnz == 0) {
+        FM_TRY(fm_settle(m, st));  // no columns with entries: none short
+        fm_spend(m, {tc});
+        return FM_OK;
+    }
     // 1. the long columns, in column order
     const int64_t ntiles = (D + LI_TILE - 1) / LI_TILE;
     int64_t *tl = nullptr, *ti = nullptr, *vcol = nullptr;
@@ -1097,13 +1098,11 @@ int fm_build_full_index(fm_matrix* m, int32_t K, hipStream_t st)
     FM_HIP(m, hipGetLastError());
     FM_TRY(fm_scan_exclusive_i64(m, tl, ntiles + 1, st));
     int64_t nlong = 0;
-    FM_HIP(m, hipMemcpyAsync(&nlong, tl + ntiles, sizeof(int64_t), hipMemcpyDeviceToHost, st));
-    FM_HIP(m, hipStreamSynchronize(st));
-    if (nlong == 0) {
-        fm_dev_free(m, tl);
-        fm_dev_free(m, ti);
-        return FM_OK;
-    }
+    FM_TRY(fm_read_later(m, &nlong, tl + ntiles, sizeof(int64_t), st));
+    FM_TRY(fm_settle(m, st));
+    fm_spend(m, {tl, ti});
+    FM_TRY(fill_short_list(m, m->colptr, nullptr, m->D, {0, m->D}, 1, T.seg, out, tc, st));
+    if (nlong == 0) return FM_OK;
     if (nlong > 0x7fffffffLL) return fm_fail(m, FM_ERANGE, "too many long columns");
     FM_TRY(fm_dev_alloc(m, (void**)&out->long_col, (size_t)nlong * sizeof(int32_t)));
     FM_TRY(fm_dev_alloc(m, (void**)&out->long_first, (size_t)(nlong + 1) * sizeof(int64_t)));
@@ -1142,9 +1141,8 @@ int fm_build_full_index(fm_matrix* m, int32_t K, hipStream_t st)
     FM_HIP(m, hipGetLastError());
     FM_TRY(fm_scan_exclusive_i64(m, out->long_first, nlong + 1, st));
     std::vector<int64_t> h_first((size_t)nlong + 1);
-    FM_HIP(m, hipMemcpyAsync(h_first.data(), out->long_first, (size_t)(nlong + 1) * sizeof(int64_t),
-                             hipMemcpyDeviceToHost, st));
-    FM_HIP(m, hipStreamSynchronize(st));
+    FM_TRY(fm_read_later(m, h_first.data(), out->long_first, (size_t)(nlong + 1) * sizeof(int64_t), st));
+    FM_TRY(fm_settle(m, st));
     const int64_t nitems = h_first[(size_t)nlong];
     if (nitems >= (1LL << 32)) return fm_fail(m, FM_ERANGE, "too many column items");
     FM_TRY(fm_dev_alloc(m, (void**)&out->item_col, (size_t)nitems * sizeof(int32_t)));
@@ -1170,8 +1168,8 @@ int fm_build_full_index(fm_matrix* m, int32_t K, hipStream_t st)
     hipLaunchKernelGGL(k_list_offsets, dim3(1), dim3(64), 0, st, (const uint32_t*)(alt ? k1 : k0), nitems, maxpos, d_off);
     FM_HIP(m, hipGetLastError());
     int64_t h_off[2 * FM_XCDS + 1];
-    FM_HIP(m, hipMemcpyAsync(h_off, d_off, sizeof(h_off), hipMemcpyDeviceToHost, st));
-    FM_HIP(m, hipStreamSynchronize(st));
+    FM_TRY(fm_read_later(m, h_off, d_off, sizeof(h_off), st));
+    FM_TRY(fm_settle(m, st));
     for (int x = 0; x <= FM_XCDS; ++x) out->list_off[x] = h_off[x];
     for (int x = 0; x < FM_XCDS; ++x) out->list_mid[x] = h_off[FM_XCDS + 1 + x];
     out->tile_rows = tile;
@@ -1182,29 +1180,21 @@ int fm_build_full_index(fm_matrix* m, int32_t K, hipStream_t st)
         hipLaunchKernelGGL(k_tile_ptr, dim3(blocks_for(nrtiles + 1, 256)), dim3(256), 0, st,
                            (const uint32_t*)(alt ? k1 : k0), nitems, key_tiles, nrtiles, out->tile_ptr);
         FM_HIP(m, hipGetLastError());
-        FM_HIP(m, hipStreamSynchronize(st));
     }
     out->order = alt ? i1 : i0;
-    fm_dev_free(m, alt ? i0 : i1);
+    fm_spend(m, {alt ? i0 : i1});
     FM_TRY(fm_dev_alloc(m, (void**)&out->ord_beg, (size_t)nitems * sizeof(int64_t)));
     FM_TRY(fm_dev_alloc(m, (void**)&out->ord_len, (size_t)nitems * sizeof(int32_t)));
     hipLaunchKernelGGL(k_order_items, dim3(blocks_for(nitems, 256)), dim3(256), 0, st, (const uint32_t*)out->order,
                        nitems, (const int64_t*)out->item_beg, (const int32_t*)out->item_len, out->ord_beg,
                        out->ord_len);
     FM_HIP(m, hipGetLastError());
-    FM_HIP(m, hipStreamSynchronize(st));
-    fm_dev_free(m, k0);
-    fm_dev_free(m, k1);
-    fm_dev_free(m, d_off);
+    fm_spend(m, {k0, k1, d_off, vcol});
     out->nlong = nlong;
     out->nitems = nitems;
     out->h_long_off[1] = nlong;
     out->h_item_off[1] = nitems;
-    FM_TRY(build_vlong_list(m, h_first, out));
-    fm_dev_free(m, vcol);
-    fm_dev_free(m, tl);
-    fm_dev_free(m, ti);
-    return FM_OK;
+    return build_vlong_list(m, h_first, out, st);
 }
 
 extern "C" int fm_build_csc(fm_matrix* m, void* hip_stream)
@@ -1212,6 +1202,7 @@ extern "C" int fm_build_csc(fm_matrix* m, void* hip_stream)
     if (m == nullptr) return FM_EINVAL;
     hipStream_t st = (hipStream_t)hip_stream;
     if (m->has_csc) return FM_OK;
+    fm_unsettled(m);
     const int64_t n = m->nnz;
     FM_TRY(fm_dev_alloc(m, (void**)&m->colptr, (size_t)(m->D + 1) * sizeof(int64_t)));
     FM_TRY(fm_dev_alloc(m, (void**)&m->crow, (size_t)(n + FM_ENTRY_PAD) * sizeof(int32_t)));
@@ -1234,11 +1225,10 @@ extern "C" int fm_build_csc(fm_matrix* m, void* hip_stream)
         hipLaunchKernelGGL(k_ptr_from_sorted, dim3(blocks_for(m->D + 1, 256)), dim3(256), 0, st, (const uint32_t*)key, n, m->D,
                            m->colptr);
         FM_HIP(m, hipGetLastError());
-        FM_HIP(m, hipStreamSynchronize(st));
-        for (uint32_t* x : {row, key, t[0], t[1], t[2]}) fm_dev_free(m, x);
+        fm_spend(m, {row, key, t[0], t[1], t[2]});
     }
     FM_TRY(fm_build_full_index(m, 0, st));
-    FM_HIP(m, hipStreamSynchronize(st));
+    FM_TRY(fm_settle(m, st));
     m->has_csc = true;
     fm_drop_workspace(m);
     return FM_OK;
@@ -1298,15 +1288,15 @@ static int build_strata_side(fm_matrix* m, bool by_rows, hipStream_t st, StrataS
     FM_HIP(m, hipGetLastError());
     FM_TRY(fm_scan_exclusive_i64(m, pos, htiles + 1, st));
     int64_t count = 0;
-    FM_HIP(m, hipMemcpyAsync(&count, pos + htiles, sizeof(int64_t), hipMemcpyDeviceToHost, st));
-    FM_HIP(m, hipStreamSynchronize(st));
+    FM_TRY(fm_read_later(m, &count, pos + htiles, sizeof(int64_t), st));
+    FM_TRY(fm_settle(m, st));
     out->count = count;
     FM_TRY(fm_dev_alloc(m, (void**)&out->nz_major, (size_t)count * sizeof(int32_t)));
     FM_TRY(fm_dev_alloc(m, (void**)&out->nz_beg, (size_t)(count + 1) * sizeof(int64_t)));
     hipLaunchKernelGGL(k_heads, dim3((unsigned)htiles), dim3(256), 0, st, (const uint32_t*)keys, (const uint32_t*)maj, n, 1, pos,
                        out->nz_major, out->nz_beg);
     FM_HIP(m, hipGetLastError());
-    FM_HIP(m, hipMemcpyAsync(out->nz_beg + count, &n, sizeof(int64_t), hipMemcpyHostToDevice, st));
+    FM_TRY(fm_send(m, out->nz_beg + count, &n, sizeof(int64_t), st));
     // where every stratum starts: in the entries (keys smaller than s), then in the list of pairs
     int64_t *d_ent = nullptr, *d_list = nullptr;
     FM_TRY(fm_dev_alloc(m, (void**)&d_ent, (size_t)(P + 1) * sizeof(int64_t)));
@@ -1316,12 +1306,9 @@ static int build_strata_side(fm_matrix* m, bool by_rows, hipStream_t st, StrataS
     hipLaunchKernelGGL(k_lower_bounds, dim3(blocks_for(P + 1, 256)), dim3(256), 0, st, (const int64_t*)out->nz_beg, count,
                        (const int64_t*)d_ent, (int64_t)(P + 1), d_list);
     FM_HIP(m, hipGetLastError());
-    FM_HIP(m, hipMemcpyAsync(out->h_ent_off.data(), d_ent, (size_t)(P + 1) * sizeof(int64_t), hipMemcpyDeviceToHost, st));
-    FM_HIP(m, hipMemcpyAsync(out->h_list_off.data(), d_list, (size_t)(P + 1) * sizeof(int64_t), hipMemcpyDeviceToHost, st));
-    FM_HIP(m, hipStreamSynchronize(st));
-    for (void* q : {(void*)k0, (void*)j0, (void*)keys, (void*)maj, (void*)t[0], (void*)t[1], (void*)t[2], (void*)t[3], (void*)pos,
-                    (void*)d_ent, (void*)d_list})
-        fm_dev_free(m, q);
+    FM_TRY(fm_read_later(m, out->h_ent_off.data(), d_ent, (size_t)(P + 1) * sizeof(int64_t), st));
+    FM_TRY(fm_read_later(m, out->h_list_off.data(), d_list, (size_t)(P + 1) * sizeof(int64_t), st));
+    fm_spend(m, {k0, j0, keys, maj, t[0], t[1], t[2], t[3], pos, d_ent, d_list});
     return FM_OK;
 }
 
@@ -1347,6 +1334,7 @@ static int partition_impl(fm_matrix* m, int32_t P, const int32_t* place, hipStre
     if (P < 1 || P > FM_MAXP) return fm_fail(m, FM_EINVAL, "P=%d outside 1..%d", P, FM_MAXP);
     if (m->P != 0) return fm_fail(m, FM_ESTATE, "matrix is already partitioned (P=%d)", m->P);
     if (m->N < 1 || m->D < 1) return fm_fail(m, FM_EINVAL, "cannot partition an empty matrix");
+    fm_unsettled(m);
     m->P = P;
     m->h_rb.resize(P + 1);
     m->h_cb.resize(P + 1);
@@ -1357,20 +1345,22 @@ static int partition_impl(fm_matrix* m, int32_t P, const int32_t* place, hipStre
     std::vector<float> h_rho((size_t)P);
     for (int32_t b = 0; b < P; ++b) h_rho[b] = (float)((double)(m->h_rb[b + 1] - m->h_rb[b]) / (double)m->N);
     FM_TRY(fm_dev_alloc(m, (void**)&m->d_rho, (size_t)P * sizeof(float)));
-    FM_HIP(m, hipMemcpy(m->d_rho, h_rho.data(), (size_t)P * sizeof(float), hipMemcpyHostToDevice));
+    FM_TRY(fm_send(m, m->d_rho, h_rho.data(), (size_t)P * sizeof(float), st));
     FM_TRY(fm_dev_alloc(m, (void**)&m->d_rb, (size_t)(P + 1) * sizeof(int64_t)));
-    FM_HIP(m, hipMemcpy(m->d_rb, m->h_rb.data(), (size_t)(P + 1) * sizeof(int64_t), hipMemcpyHostToDevice));
+    FM_TRY(fm_send(m, m->d_rb, m->h_rb.data(), (size_t)(P + 1) * sizeof(int64_t), st));
     FM_TRY(fm_ensure_lazy(m, st));
     if (place != nullptr) {
         FM_TRY(fm_dev_alloc(m, (void**)&m->d_place, (size_t)m->D * sizeof(int32_t)));
-        FM_HIP(m, hipMemcpy(m->d_place, place, (size_t)m->D * sizeof(int32_t), hipMemcpyHostToDevice));
+        FM_TRY(fm_send(m, m->d_place, place, (size_t)m->D * sizeof(int32_t), st));
     }
     FM_TRY(fm_dev_alloc(m, (void**)&m->col_mark, (size_t)m->D * sizeof(int32_t)));
     FM_HIP(m, hipMemsetAsync(m->col_mark, 0, (size_t)m->D * sizeof(int32_t), st));
 
     StrataSide rows, cols;
     FM_TRY(build_strata_side(m, true, st, &rows, P));
+    FM_TRY(fm_settle(m, st));  // its scratch serves the other side
     FM_TRY(build_strata_side(m, false, st, &cols, P));
+    FM_TRY(fm_settle(m, st));
     m->s_col = rows.ind;
     m->s_val = rows.val;
     // the rows that have an entry in stratum s: its refresh visits only these (a row's entries end
@@ -1395,19 +1385,17 @@ static int partition_impl(fm_matrix* m, int32_t P, const int32_t* place, hipStre
             int64_t *d_cell = nullptr, *d_off = nullptr;
             FM_TRY(fm_dev_alloc(m, (void**)&d_cell, (size_t)P * P * sizeof(int64_t)));
             FM_TRY(fm_dev_alloc(m, (void**)&d_off, (size_t)(P + 1) * sizeof(int64_t)));
-            FM_HIP(m, hipMemcpyAsync(d_off, m->h_touch_off.data(), (size_t)(P + 1) * sizeof(int64_t), hipMemcpyHostToDevice, st));
+            FM_TRY(fm_send(m, d_off, m->h_touch_off.data(), (size_t)(P + 1) * sizeof(int64_t), st));
             hipLaunchKernelGGL(k_cell_table, dim3(blocks_for((int64_t)P * P, 256)), dim3(256), 0, st,
                                (const int32_t*)m->s_touched, (const int64_t*)m->s_touched_beg, (const int64_t*)d_off,
                                (const int64_t*)m->d_rb, P, d_cell);
             FM_HIP(m, hipGetLastError());
-            FM_HIP(m, hipMemcpyAsync(m->h_cell_nnz.data(), d_cell, (size_t)P * P * sizeof(int64_t), hipMemcpyDeviceToHost, st));
-            FM_HIP(m, hipStreamSynchronize(st));
-            fm_dev_free(m, d_cell);
-            fm_dev_free(m, d_off);
+            FM_TRY(fm_read_later(m, m->h_cell_nnz.data(), d_cell, (size_t)P * P * sizeof(int64_t), st));
+            fm_spend(m, {d_cell, d_off});
         }
     }
     FM_TRY(fm_build_long_index(m, m->s_ncol_beg, m->s_ncol, m->s_row, m->nncol, m->h_ncol_off, P, &m->lstrat, st));
-    FM_HIP(m, hipStreamSynchronize(st));
+    FM_TRY(fm_settle(m, st));
     fm_drop_workspace(m);
     return FM_OK;
 }
@@ -1429,15 +1417,16 @@ extern "C" int fm_partition_batches(fm_matrix* m, int32_t B, void* hip_stream)
     if (B < 1 || B > FM_MAXP) return fm_fail(m, FM_EINVAL, "B=%d outside 1..%d", B, FM_MAXP);
     if (m->B != 0) return fm_fail(m, FM_ESTATE, "row batches are already built (B=%d)", m->B);
     if (m->N < 1 || m->D < 1) return fm_fail(m, FM_EINVAL, "cannot split an empty matrix");
+    fm_unsettled(m);
     m->B = B;
     m->h_bb.resize(B + 1);
     std::vector<float> h_rho((size_t)B);
     for (int32_t b = 0; b <= B; ++b) m->h_bb[b] = (int64_t)(((__int128)b * (__int128)m->N) / (__int128)B);
     for (int32_t b = 0; b < B; ++b) h_rho[b] = (float)((double)(m->h_bb[b + 1] - m->h_bb[b]) / (double)m->N);
     FM_TRY(fm_dev_alloc(m, (void**)&m->d_brho, (size_t)B * sizeof(float)));
-    FM_HIP(m, hipMemcpy(m->d_brho, h_rho.data(), (size_t)B * sizeof(float), hipMemcpyHostToDevice));
+    FM_TRY(fm_send(m, m->d_brho, h_rho.data(), (size_t)B * sizeof(float), st));
     FM_TRY(fm_dev_alloc(m, (void**)&m->d_bb, (size_t)(B + 1) * sizeof(int64_t)));
-    FM_HIP(m, hipMemcpy(m->d_bb, m->h_bb.data(), (size_t)(B + 1) * sizeof(int64_t), hipMemcpyHostToDevice));
+    FM_TRY(fm_send(m, m->d_bb, m->h_bb.data(), (size_t)(B + 1) * sizeof(int64_t), st));
     FM_TRY(fm_ensure_lazy(m, st));
     if (m->col_mark == nullptr) {
         FM_TRY(fm_dev_alloc(m, (void**)&m->col_mark, (size_t)m->D * sizeof(int32_t)));
@@ -1445,6 +1434,7 @@ extern "C" int fm_partition_batches(fm_matrix* m, int32_t B, void* hip_stream)
     }
     StrataSide cols;
     FM_TRY(build_strata_side(m, false, st, &cols, B, true));
+    FM_TRY(fm_settle(m, st));
     m->b_row = cols.ind;
     m->b_cval = cols.val;
     m->b_ncol = cols.nz_major;
@@ -1453,7 +1443,7 @@ extern "C" int fm_partition_batches(fm_matrix* m, int32_t B, void* hip_stream)
     m->h_bcol_off = cols.h_list_off;
     m->h_batch_nnz_off = cols.h_ent_off;
     FM_TRY(fm_build_long_index(m, m->b_ncol_beg, m->b_ncol, m->b_row, m->nbcol, m->h_bcol_off, B, &m->lbatch, st));
-    FM_HIP(m, hipStreamSynchronize(st));
+    FM_TRY(fm_settle(m, st));
     fm_drop_workspace(m);
     return FM_OK;
 }

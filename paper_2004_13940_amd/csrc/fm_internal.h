@@ -92,7 +92,8 @@ struct FmCheck {
     int64_t not_dense;  // row i does not start at i * D
 };
 constexpr int FM_CHECK_BLOCKS = 512;
-constexpr size_t FM_PINNED_DOUBLES = 8 + FM_CHECK_BLOCKS * sizeof(FmCheck) / sizeof(double);
+constexpr size_t FM_PINNED_DOUBLES = 8192;  // of a handle: 8 scalars, then the block results or what a build moves
+static_assert(8 + FM_CHECK_BLOCKS * sizeof(FmCheck) / sizeof(double) <= FM_PINNED_DOUBLES, "room for the CSR check");
 
 // Columns of a stratum or batch hold at most as many entries as a row block (or batch) has rows.  Up to FM_WHOLE_ROWS a
 // column is summed at once, by a wavefront, or by a workgroup from FM_WHOLE_WAVE entries on.  Epochs of 8 and 32 strata or
@@ -149,6 +150,12 @@ struct ProfRec {
 struct FmAlloc {
     void* p;
     size_t pool_bytes;  // size of a block that goes back to the pool; 0: to the runtime
+};
+
+// A value on its way to the host, see fm_read_later.
+struct FmRead {
+    void* dst;
+    size_t at, bytes;  // in the pinned block
 };
 
 struct fm_matrix {
@@ -233,6 +240,8 @@ struct fm_matrix {
     fm_params gkey_p = {};
     const void* gkey_ptr[4] = {nullptr, nullptr, nullptr, nullptr};
     bool gkey_lazy = false;
+    fm_params gseen_p = {};  // of the last epoch that was enqueued without a graph although it is worth one
+    const void* gseen_ptr[4] = {nullptr, nullptr, nullptr, nullptr};
     int graph_state = 0;  // 0 not tried, 1 stream and events ready, -1 unavailable
     // profiling
     bool prof = false;
@@ -243,6 +252,10 @@ struct fm_matrix {
     // bookkeeping
     int device = 0;  // the device the handle was created on
     std::vector<FmAlloc> allocs;
+    // what a build has enqueued and not waited for yet (fm_settle)
+    std::vector<void*> spent;
+    std::vector<FmRead> reads;
+    size_t pin_used = 0;  // bytes of the pinned block behind its scalars
     std::string err;
 };
 
@@ -258,6 +271,14 @@ inline int fm_check_vec_aligned(fm_matrix* m, std::initializer_list<const void*>
 }
 int fm_dev_alloc(fm_matrix* m, void** p, size_t bytes);
 void fm_dev_free(fm_matrix* m, void* p);
+// Builds enqueue on one stream and wait as rarely as they can: scratch is given up with fm_spend, values are read with
+// fm_read_later (dst must live until then) and written with fm_send, and fm_settle waits, delivers the values and gives the
+// scratch back.
+void fm_spend(fm_matrix* m, std::initializer_list<void*> scratch);
+int fm_read_later(fm_matrix* m, void* dst, const void* src, size_t bytes, hipStream_t st);
+int fm_send(fm_matrix* m, void* dst, const void* src, size_t bytes, hipStream_t st);
+int fm_settle(fm_matrix* m, hipStream_t st);
+void fm_unsettled(fm_matrix* m);  // forgets what a build that failed left behind
 void fm_drop_workspace(fm_matrix* m);  // forces reallocation after the structures changed
 void fm_drop_graph(fm_matrix* m);      // a captured epoch holds pointers into the workspace and the structures
 bool fm_side_streams(fm_matrix* m);    // creates them on first use; false if switched off or unavailable
