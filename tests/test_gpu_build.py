@@ -117,3 +117,43 @@ def test_large_matrices_arrive_whole(N, per_thread):
         for _ in range(2):
             assert list(threads.map(check, range(2))) == [0, 1]
     B.fm_trim()
+
+
+@pytest.mark.parametrize("P", [1, 3, 16, 300])  # one to nine bits of the stratum: one pass of the sort or two
+@pytest.mark.parametrize("nnz", [1, 511, 512, 4095, 8191, 8192, 8193, 16_391])  # wavefronts and tiles of the sort, and one more
+def test_transpose_and_strata_at_the_edges_of_the_sort(nnz, P):
+    """Two thirds of the entries in a few full columns (equal digits side by side), rows and columns without entries between."""
+    from paper_2004_13940_amd import binding as B
+    rng = np.random.default_rng(nnz * 1000 + P)
+    N, D = max(nnz // 3, 400), 1_000
+    cells = set()
+    while len(cells) < nnz:
+        i = int(rng.integers(0, N))
+        if 0.2 * N < i < 0.6 * N and nnz < N * 4 // 10:  # a long stretch of empty rows
+            continue
+        cells.add((i, int(rng.choice([0, 1, 2])) if rng.random() < 0.67 else int(rng.integers(600, D))))
+    r, c = np.array(sorted(cells), np.int64).T
+    rowptr = np.concatenate([[0], np.cumsum(np.bincount(r, minlength=N))]).astype(np.int64)
+    val = rng.standard_normal(nnz).astype(np.float32)
+    print("sort edges", nnz, P, flush=True)
+    m = B.Matrix(N, D, rowptr, c.astype(np.int32), val)
+    m.fm_build_csc()
+    order = np.argsort(c, kind="stable")
+    colptr, row, cval = m.fm_get_csc()
+    assert np.array_equal(colptr, np.concatenate([[0], np.cumsum(np.bincount(c, minlength=D))]))
+    assert np.array_equal(row, r[order]) and np.array_equal(cval, val[order])
+    m.fm_partition(P)
+    rb, cb, cell = m.fm_get_block_index()
+    p = np.searchsorted(rb, r, side="right") - 1
+    s = (np.searchsorted(cb, c, side="right") - 1 - p) % P
+    assert cell.sum() == nnz
+    for t in range(P) if P < 300 else (0, 1, 150, 255, 256, 299):
+        mine = np.nonzero(s == t)[0]
+        ptr, col, v = m.fm_get_stratum_csr(t)
+        assert np.array_equal(np.diff(ptr), np.bincount(r[mine], minlength=N))
+        assert np.array_equal(col, c[mine]) and np.array_equal(v, val[mine])
+        mine = order[s[order] == t]
+        ptr, row, v = m.fm_get_stratum_csc(t)
+        assert np.array_equal(np.diff(ptr), np.bincount(c[mine], minlength=D))
+        assert np.array_equal(row, r[mine]) and np.array_equal(v, val[mine])
+    m.close()
