@@ -257,9 +257,9 @@ int fm_profile_read(fm_matrix* m, int64_t* launches /*HOST nk*/, double* total_m
  *                        before their columns have taken the steps they postponed, so there the two
  *                        differ by the part eta lambda of the parameters that those steps are, in the
  *                        scores, not only by rounding.
- *   FM_OPT_GRAPH         fm_stratified_epoch replayed from a captured HIP graph: 0 never, 1 (default)
- *                        when there are 32 strata or more, or 16 and strata small enough for the launches
- *                        to dominate, 2 always.
+ *   FM_OPT_GRAPH         fm_stratified_epoch replayed from a captured HIP graph, which takes one call of the host
+ *                        instead of two or three a stratum: 2 always; 1 (default) where the replay is the faster
+ *                        one, which it is nowhere; 0 never.
  *   FM_OPT_DENSE_ROWS    1: a matrix in which every row stores all D columns (D and K up to 64) takes dense
  *                        kernels on the matrix cores for fm_forward, fm_evaluate, fm_gradient, fm_sgd_epoch and
  *                        fm_minibatch_epoch (G = XV and X^T(r.G) as fp32 contractions; the column indices are

@@ -1310,13 +1310,6 @@ static int replay_stratified_epoch(fm_matrix* m, const fm_params* p, const float
     const bool same = m->gexec != nullptr && memcmp(&m->gkey_p, p, sizeof(fm_params)) == 0 &&
                       memcmp(m->gkey_ptr, key, sizeof(key)) == 0 && m->gkey_lazy == lazy;
     if (!same) {
-        // Capturing and instantiating take longer than the launches of one epoch (text-like, 5e4 rows, 16 strata, host time: 390 us
-        // before the first kernel): worth it from the second epoch with the same arguments on.
-        if (m->opt.graph != 2 && !(memcmp(&m->gseen_p, p, sizeof(fm_params)) == 0 && memcmp(m->gseen_ptr, key, sizeof(key)) == 0)) {
-            m->gseen_p = *p;
-            memcpy(m->gseen_ptr, key, sizeof(key));
-            return FM_ESTATE;
-        }
         fm_drop_graph(m);
         (void)fm_side_streams(m);  // created outside the capture
         if (hipStreamBeginCapture(m->gstream, hipStreamCaptureModeThreadLocal) != hipSuccess) {
@@ -1367,15 +1360,15 @@ extern "C" int fm_stratified_epoch(fm_matrix* m, const fm_params* p, const float
     // its cell, so the regulariser-only steps of the other columns can wait (not when every row
     // is refreshed from every column's change).
     const bool lazy = (!p->refresh_all_rows || p->stale_aux) && m->lazy_last != nullptr && m->opt.lazy_reg;
-    // small strata are bound by their launches: replay them from a graph
-    const int gmode = m->opt.graph;  // 0 never, 1 for matrices whose strata are small enough for the launches to dominate, 2 always
-    // (worth it from some tens of launches on: below that the two events and the graph launch cost more; with
-    // 32 strata or more the replay pays even when the strata are large: 2 % on the click-style and the hashed workload)
-    const bool small = m->P >= 32 || (m->nnz / m->P < (int64_t(1) << 20) && m->P >= 16);
+    // Replay from a graph costs two events, the graph's launch and, first of all, its making (390 us for 16 strata of 5e4 rows),
+    // and a kernel in it starts no sooner behind the one before than a kernel on the stream, which the host enqueues three
+    // times as fast as the smallest strata run.  Epochs direct / replayed, us: text-like 5e4 rows, 32 strata 441 / 493, 3e3 rows, 32
+    // strata 303 / 372; click-style 1e7 rows, 64 strata 26280 / 26340, 5e4 rows, 64 strata 768 / 880; hashed 4e5 rows, K = 64, 64
+    // strata 7410 / 7490; uniform 2e3 rows, 4 strata 67 / 94.  It is for callers whose host thread has other things to do.
     bool done = false;
     bool sound = true;
     if (lazy) FM_TRY(clear_lazy(m, st, &sound));
-    if (!m->prof && (gmode == 2 || (gmode == 1 && small)) && graph_ready(m)) {
+    if (!m->prof && m->opt.graph == 2 && graph_ready(m)) {
         const int rc = replay_stratified_epoch(m, p, y, w0, w, V, lazy, st);
         if (rc == FM_OK)
             done = true;

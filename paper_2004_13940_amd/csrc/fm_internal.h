@@ -50,7 +50,7 @@ struct FmOptions {
     int aux = 0;               // layout of the aggregates: 0 as take_packed chooses, 1 planar, 2 packed where that exists
     bool side_streams = true;  // column kernels that touch disjoint columns overlap on internal side streams
     bool lazy_reg = true;      // regulariser-only steps of a stratified or mini-batch epoch are postponed
-    int graph = 1;             // stratified epoch from a captured graph: 0 never, 1 when launch-bound, 2 always
+    int graph = 1;             // stratified epoch from a captured graph: 2 always; 0, 1 never (nowhere the faster one)
     int dense_rows = 2;        // matrices that store every column in every row take the dense (MFMA) kernels: 0 never, 1 always,
                                // 2 where fm_dense_takes says that they are the faster ones
     bool wide_addresses = false;  // gathers take 64-bit addresses at any size
@@ -240,8 +240,6 @@ struct fm_matrix {
     fm_params gkey_p = {};
     const void* gkey_ptr[4] = {nullptr, nullptr, nullptr, nullptr};
     bool gkey_lazy = false;
-    fm_params gseen_p = {};  // of the last epoch that was enqueued without a graph although it is worth one
-    const void* gseen_ptr[4] = {nullptr, nullptr, nullptr, nullptr};
     int graph_state = 0;  // 0 not tried, 1 stream and events ready, -1 unavailable
     // profiling
     bool prof = false;

@@ -246,7 +246,7 @@ def test_full_size_minibatch_epoch_and_gradient_entry_point(full):
 
 @pytest.mark.parametrize("idx", [3, 2])
 def test_full_shape_every_epoch_of_the_config(idx):
-    """Configs 3 (text-like, 10 epochs, P=32: the stratified epochs are replayed from a graph) and 2 (every
+    """Configs 3 (text-like, 10 epochs, P=32) and 2 (every
     row stores all 64 columns: forward and gradient on the matrix cores, K=32 planar aggregates, 5 epochs,
     P=16) at their stated shapes: the stated
     number of full-gradient epochs, then as many stratified epochs from where those ended, every epoch's
