@@ -1171,6 +1171,7 @@ static int stratified_step(fm_matrix* m, const fm_params* p, int32_t s, const fl
         A.dwn = m->dwn;
     }
     fill_long(m, A, m->lstrat, s, true);
+    A.xcd_runs = A.order != nullptr ? 1 : 0;
     FM_TRY(fm_launch_cols(m, A, true, st));
     if (p->stale_aux) return FM_OK;  // Algorithm 1: the aggregates wait for the re-computation
     // phase B: incremental refresh of the aggregates and multipliers
@@ -1467,11 +1468,7 @@ extern "C" int fm_minibatch_epoch(fm_matrix* m, const fm_params* p, const float*
         A.gs = x.gs;
         A.rs = x.ss;
         if (!dense) fill_long(m, A, m->lbatch, b, true);
-        // An eighth of the batch's aggregate rows fits the L2 of an XCD (4 MB): then each XCD keeps to its own (mini-batch
-        // epoch of the click-style workload, batches of 156,250 rows and 20 MB: 3092 -> 2927 us; 0.86 to 1.01 times the time
-        // over click-style, text-like and hashed batches of 5,000 to 125,000 rows, K 8 to 64; strata, whose rows are spread
-        // over all of the matrix, lose by it: 32.4 -> 33.0 ms).
-        A.xcd_runs = A.order != nullptr && nb * x.gs * (int64_t)sizeof(float) <= int64_t(FM_XCDS) << 22 ? 1 : 0;
+        A.xcd_runs = A.order != nullptr ? 1 : 0;
         if (p->update_w0 && nb > 0) {
             set_epilogue(m, A.epi, m->row_part, dense ? fm_dense_chunks(nb, m->D, p->K) : fm_rows_grid(m, nb, p->K), 0, false);
             if (dense) A.epi.nsums = 0;

@@ -270,8 +270,9 @@ __device__ __forceinline__ void store_partial(const ColArgs& A, int64_t it, int 
 // entries; one group per column, which finishes it), or one of the epilogue's that add up the examples.  The kinds touch
 // disjoint data; as launches of their own they needed a fork and a join of streams, which cost a stratum of the text-like
 // workload as much as its columns did.  Items come first: they are the longest runs.
-// With an order array, workgroup b takes its items from list b % FM_XCDS (the XCD it runs on).  Items of a batch are in row
-// order; with xcd_runs every XCD takes one eighth of that order in a run, and so of the batch's rows.
+// With an order array, workgroup b takes its items from list b % FM_XCDS (the XCD it runs on).  Items of strata and batches are
+// in row order; with xcd_runs every XCD takes FM_RUN_BLOCKS workgroups of that order in a run, and the rows and multipliers
+// that the items of a run share are asked for by one L2.
 // FEW: four wavefronts to a SIMD and not the five that its registers leave room for, by naming a register that nothing uses
 // (LDS, the other means, is what k_cols_tile beside it lives on).  The items in panel order then have fewer panels' rows in
 // flight and find more of them in the L2: see few_wavefronts.
@@ -305,7 +306,10 @@ __global__ __launch_bounds__(FM_BLOCK, L >= FM_WIDE_GROUP ? 8 : 1) void k_cols(c
     if (items) {
         if (b >= A.blk_lists) {
             int64_t lb = b - A.blk_lists;
-            if (A.xcd_runs) lb = lb % FM_XCDS * (A.blk_lin / FM_XCDS) + lb / FM_XCDS;
+            if (A.xcd_runs) {
+                const int64_t k = lb / FM_XCDS;
+                lb = (k / FM_RUN_BLOCKS * FM_XCDS + lb % FM_XCDS) * FM_RUN_BLOCKS + k % FM_RUN_BLOCKS;
+            }
             const int64_t rel = lb * (FM_WAVES * R) + slot;
             once = false;
             if (rel < A.lin_count) {
@@ -979,7 +983,10 @@ int launch_cols_t(fm_matrix* m, const ColArgs& A, bool update, hipStream_t st)
                     Am.lin_base = A.list_off[FM_XCDS];
                     Am.lin_count = ntile_items;
                     Am.blk_lin = (ntile_items + per - 1) / per;
-                    if (A.xcd_runs) Am.blk_lin = (Am.blk_lin + FM_XCDS - 1) / FM_XCDS * FM_XCDS;
+                    if (A.xcd_runs) {
+                        constexpr int64_t all = FM_XCDS * FM_RUN_BLOCKS;
+                        Am.blk_lin = (Am.blk_lin + all - 1) / all * all;
+                    }
                 }
             } else {
                 Am.blk_lists = (A.nitems + per - 1) / per;

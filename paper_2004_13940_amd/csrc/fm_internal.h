@@ -404,6 +404,13 @@ inline int fm_epi_nsums(int64_t n)
     return (int)(nb < 512 ? nb : 512);
 }
 
+// Workgroups of k_cols that work on consecutive items of a stratum or batch on one XCD.  Epochs with 1 / 4 / 8 / 16 / 64, us:
+// strata, K = 16: click-style 1e7 rows, 64 strata 26345 / 26244 / 26214 / 26292 / 30400, 1.25e6 rows, 16 strata 2779 / 2714 /
+// 2693 / 2682 / 3020, text-like 2e5 rows 774 / 764 / 762 / 766 / -, hashed 4e5 rows, K = 32 4289 / 4290 / 4288 / 4296 / -;
+// batches: click-style 156,250 rows, K = 16 - / 2413 / 2398 / 2390 / - (an eighth of the batch to an XCD: 2479), 312,500
+// rows, K = 8 - / 984 / 969 / 965 / - (990), text-like 25,000 rows - / 364 / 367 / 366 / - (372).  Longer runs are uneven.
+constexpr int FM_RUN_BLOCKS = 8;
+
 struct ColArgs {
     int64_t D;
     int32_t K;
@@ -461,7 +468,7 @@ struct ColArgs {
     int64_t tile_rows, ntiles;     // dense-ish columns: items sorted by row tile, after the lists
     const int64_t* tile_ptr;
     int64_t lin_base, lin_count;   // positions of `order` that are taken in sequence (tile items that are not staged; all of a stratum or batch)
-    int32_t xcd_runs;              // the lin items in FM_XCDS runs, one per XCD, and not dealt out one workgroup after the other
+    int32_t xcd_runs;              // the lin items in runs of FM_RUN_BLOCKS workgroups to an XCD, not dealt out one after the other
     int64_t blk_lists, blk_lin, blk_short;  // workgroups of k_cols per role, in this order; then epi.nsums for the sums
     int32_t nt;                    // gathers of rows that are not used again soon carry the non-temporal hint
     int32_t big;                   // the gathered array is larger than FM_BUF_BYTES
