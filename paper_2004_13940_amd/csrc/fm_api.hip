@@ -543,18 +543,25 @@ static bool packed_exists(const fm_matrix* m, int32_t K) { return m->opt.aux != 
 // Which layout a pass takes whose columns gather from so many rows (all of the matrix, a row block, a batch).  At K = 16 a
 // row of G is half a line and a packed row a whole one: planar moves half the bytes, and as long as the multipliers of the
 // rows (4 bytes each) stay in an XCD's L2 beside them, the second request for r is a cheap one.  Packed / planar, us, K = 16:
-// stratified epochs of click-style rows 156,250 rows to a block 32200 / 27500, 37,500 1880 / 1480, 75,000 3460 / 2670, 625,000
-// 9105 / 8890, text-like 1,562 rows 558 / 493; mini-batch epochs 75,000 rows to a batch 754 / 700, 156,250 2900 / 2510, 300,000
-// 1252 / 1284, 1.25e6 2390 / 2630; full epochs text-like 5e4 rows 60 / 55, 2e5 287 / 275, click-style 1.5e5 154 / 153, 6e5
-// 510 / 531, 1e7 7120 / 8300.  Any other K packs better: a packed row up to K = 12 is half a line itself (click-style 6e5 rows,
-// K = 8: full epoch 464 / 548, mini-batch 613 / 642, strata 1341 / 1258; K = 12 470 / 558, 654 / 718, 1430 / 1498), and from
-// K = 20 on a planar row straddles lines (K = 20 593 / 666, 856 / 924, 2132 / 2062; K = 28 632 / 749, 914 / 1015, 2128 / 2309).
-constexpr int64_t FM_PLANAR_ROWS = 200000;                    // full epochs, gradients, batches
+// strata of click-style rows 4,700 rows to a block 601 / 519, 75,000 3540 / 2677, 156,250 32200 / 26100, 833,000 3691 / 3472,
+// 1e6 18384 / 16122, text-like 1,562 rows 558 / 493, 500,000 1439 / 1382; batches of 75,000 rows 767 / 684, 156,250 2900 /
+// 2400, 312,500 1175 / 1138, 625,000 1094 / 1099 and 2255 / 2180; full epochs text-like 5e4 rows 60 / 55, 2e5 257 / 239, hashed
+// 1e5 222 / 200, click-style 6e4 71 / 68, 1e5 99 / 112, 1.5e5 133 / 129, 1.8e5 150 / 147, 6e5 502 / 529, 1e7 7120 / 8300.  Any
+// other K packs better: a packed row up to K = 12 is half a line itself (click-style 6e5 rows, K = 8: full epoch 457 / 537,
+// batches 610 / 627, strata 1317 / 1256; K = 12 466 / 557, 652 / 700, 1413 / 1448), and from K = 20 on a planar row straddles
+// lines (K = 20 583 / 663, 870 / 914, 2119 / 2009; K = 28 623 / 753, 929 / 1009, 2113 / 2260).  Where every row stores every
+// column the rows are gathered one after the other, whole lines in any layout, and planar ones are the shorter (tables of 40
+// columns, 1e6 rows, strata K = 8 1066 / 873, K = 20 1979 / 1586, epochs 115 / 112, 118 / 112; 1e5 rows, strata K = 8 189 / 181, K =
+// 28 235 / 232, but K = 4 180 / 189).
+constexpr int64_t FM_PLANAR_ROWS = 200000;                   // full epochs, gradients
 constexpr int64_t FM_PACK_ROWS = 40000;                      // see fm_gradient
-constexpr int64_t FM_PLANAR_ROWS_STRATA = int64_t(1) << 19;  // strata: the refresh gains by it too
+constexpr int64_t FM_PLANAR_ROWS_BATCH = 400000;             // batches: their items are worked on in row order
+constexpr int64_t FM_PLANAR_ROWS_STRATA = int64_t(1) << 20;  // strata: the refresh gains by it too
 static bool take_packed(const fm_matrix* m, int32_t K, int64_t rows, int64_t planar_rows)
 {
-    return packed_exists(m, K) && (m->opt.aux == 2 || K != 16 || rows > planar_rows);
+    if (!packed_exists(m, K)) return false;
+    if (m->opt.aux == 2) return true;
+    return m->is_dense && K >= 8 ? false : K != 16 || rows > planar_rows;
 }
 
 static int64_t packed_stride(int32_t K) { return ((int64_t)K + 3 + 15) / 16 * 16; }
@@ -1398,7 +1405,7 @@ extern "C" int fm_minibatch_epoch(fm_matrix* m, const fm_params* p, const float*
     FM_TRY(ensure_ws(m, p->K));
     m->aux_full = false;
     m->aux_held = true;
-    m->aux_packed = take_packed(m, p->K, m->N / m->B, FM_PLANAR_ROWS);
+    m->aux_packed = take_packed(m, p->K, m->N / m->B, FM_PLANAR_ROWS_BATCH);
     const FmAux x = fm_aux_layout(m, p->K, m->aux_packed);
     // a column without entries in a batch only takes the regulariser's step there: postponed
     // until the column next has entries, or the epoch ends
