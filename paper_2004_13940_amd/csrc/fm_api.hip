@@ -1208,8 +1208,10 @@ static int stratified_step(fm_matrix* m, const fm_params* p, int32_t s, const fl
     // to FM_WHOLE_ROWS rows.  The block that meets a popular column block has most of a stratum's entries, and its XCD most of
     // the work when it fills the XCD's run.  Epochs with runs / without, us: text-like 5e4 rows, K=16, 32 strata 577 / 599;
     // click-style K=16, 64 strata, 6e4 rows 953 / 1001, 1.2e5 1225 / 1298; hashed K=32, 64 strata, 2e4 rows 1510 / 1607,
-    // 5e4 1790 / 1868.  Outside: hashed K=32, 16 strata, 5e4 rows 846 / 816, 2e5 2650 / 1975; K=64, 64 strata, 1.2e5 rows
-    // (31 MB) 3635 / 3420; click-style 2.5e5 rows, 16 strata 1002 / 926.
+    // 5e4 1790 / 1868; with planar rows at K=16, half the bytes: text-like 6e4 rows, 32 strata 468 / 506, 2e5, 128 strata 1918 /
+    // 2071, click-style 1.2e5, 64 strata 930 / 1044, 2.5e5, 128 strata 2045 / 2237, hashed 2e5, 128 strata 4200 / 4345.  Outside:
+    // hashed K=32, 16 strata, 5e4 rows 785 / 753, 2e5, 32 strata 3165 / 2500; K=64, 64 strata, 1.2e5 rows (31 MB) 3635 / 3420;
+    // click-style 2.5e5 rows, 16 strata 776 / 708.
     const int64_t aggregates = m->N * R.gs * (int64_t)sizeof(float);
     R.xcd_runs = aggregates <= int64_t(FM_XCDS) << 21 && m->N <= FM_WHOLE_ROWS * m->P ? 1 : 0;
     R.loss = p->loss;

@@ -232,7 +232,7 @@ struct fm_matrix {
     hipStream_t side1 = nullptr, side2 = nullptr;
     hipEvent_t ev_fork = nullptr, ev_join1 = nullptr, ev_join2 = nullptr;
     int side_state = 0;  // 0 not tried, 1 ready, -1 unavailable or disabled
-    // the stratified epoch as a captured graph (launch-bound for small matrices), replayed while the
+    // the stratified epoch as a captured graph (for callers that ask for it), replayed while the
     // caller passes the same parameters and arrays; built on an internal stream
     hipStream_t gstream = nullptr;
     hipEvent_t g_in = nullptr, g_out = nullptr;
