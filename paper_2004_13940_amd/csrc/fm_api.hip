@@ -384,7 +384,8 @@ extern "C" int fm_build_csr(int64_t N, int64_t D, int64_t nnz, const int64_t* ro
         for (const FmUploadPart& p : parts)
             if (rc == FM_OK) rc = copy(p);
     }
-    if (rc == FM_OK) rc = fm_dev_alloc(m, (void**)&m->scal, (8 + FM_REDUCE_TMP) * sizeof(double));
+    if (rc == FM_OK) rc = fm_dev_alloc(m, (void**)&m->scal, (8 + FM_REDUCE_TMP + 1) * sizeof(double));
+    if (rc == FM_OK) m->aux_rows = reinterpret_cast<int32_t*>(m->scal + 8 + FM_REDUCE_TMP);
     if (rc == FM_OK) rc = pinned_alloc(m);
     bool valid = false;
     if (rc == FM_OK) rc = fm_check_csr(m, st, &valid);  // waits for the uploads
@@ -716,11 +717,12 @@ static void fill_long(const fm_matrix* m, ColArgs& A, const LongIndex& li, int32
     A.nshort = s1 - s0;
 }
 
-// RowArgs outputs pointing into the handle's aggregates, which the pass leaves in the layout m->aux_packed
-static void aux_outputs(fm_matrix* m, int32_t K, RowArgs& A, bool with_aq)
+// RowArgs outputs pointing into the handle's aggregates, for a pass that keeps them packed or planar
+static void aux_outputs(fm_matrix* m, int32_t K, RowArgs& A, bool with_aq, bool packed)
 {
-    const FmAux x = fm_aux_layout(m, K, m->aux_packed);
-    A.whole_rows = (m->aux_packed && A.y != nullptr) ? 1 : 0;  // never leave a line partly written
+    const FmAux x = fm_aux_layout(m, K, packed);
+    A.whole_rows = packed ? 1 : 0;  // never leave a line partly written
+    A.aux_rows = m->aux_rows;
     A.G = x.G;
     A.gs = x.gs;
     A.ss = x.ss;
@@ -781,10 +783,10 @@ static int read_objective(fm_matrix* m, const fm_params* p, double* objective, h
     return FM_OK;
 }
 
-// mode 0: caller arrays (dense); 1: handle's aggregate rows, G and r; 2: handle's rows, G r a q
+// mode 0: caller arrays (dense); 1: handle's aggregates, G and r; 2: handle's, G r a q; packed: their layout
 static int forward_args(fm_matrix* m, const fm_params* p, const float* y, const float* w0, const float* w,
-                        const float* V, float* yhat, float* a, float* G, float* q, float* r, int mode, bool want_sums,
-                        int what, RowArgs& A, hipStream_t st)
+                        const float* V, float* yhat, float* a, float* G, float* q, float* r, int mode, bool packed,
+                        bool want_sums, int what, RowArgs& A, hipStream_t st)
 {
     memset(&A, 0, sizeof(A));
     A.N = m->N;
@@ -806,7 +808,7 @@ static int forward_args(fm_matrix* m, const fm_params* p, const float* y, const 
         A.gs = p->K;
         A.ss = A.as = 1;
     } else {
-        aux_outputs(m, p->K, A, mode == 2);
+        aux_outputs(m, p->K, A, mode == 2, packed);
         m->aux_held = true;
     }
     A.row_part = (want_sums && y != nullptr) ? m->row_part : nullptr;
@@ -822,19 +824,19 @@ static int forward_args(fm_matrix* m, const fm_params* p, const float* y, const 
 }
 
 static int run_forward(fm_matrix* m, const fm_params* p, const float* y, const float* w0, const float* w,
-                       const float* V, float* yhat, float* a, float* G, float* q, float* r, int mode, bool want_sums,
-                       hipStream_t st)
+                       const float* V, float* yhat, float* a, float* G, float* q, float* r, int mode, bool packed,
+                       bool want_sums, hipStream_t st)
 {
     RowArgs A;
-    FM_TRY(forward_args(m, p, y, w0, w, V, yhat, a, G, q, r, mode, want_sums, FM_DENSE_FORWARD, A, st));
+    FM_TRY(forward_args(m, p, y, w0, w, V, yhat, a, G, q, r, mode, packed, want_sums, FM_DENSE_FORWARD, A, st));
     return fm_launch_rows(m, A, false, st);  // the pairs stay in m->row_part
 }
 
 // Forward at the parameters as they stand, the sums and the objective: what the epochs with several steps report.
 static int objective_pass(fm_matrix* m, const fm_params* p, const float* y, const float* w0, const float* w, const float* V,
-                          int mode, double* objective, hipStream_t st)
+                          int mode, bool packed, double* objective, hipStream_t st)
 {
-    FM_TRY(run_forward(m, p, y, w0, w, V, nullptr, nullptr, nullptr, nullptr, nullptr, mode, true, st));
+    FM_TRY(run_forward(m, p, y, w0, w, V, nullptr, nullptr, nullptr, nullptr, nullptr, mode, packed, true, st));
     FmEpilogue E;
     set_epilogue(m, E, m->row_part, forward_pairs(m, p), 0, false);
     if (m->D * ((int64_t)p->K + 1) <= FM_EPI_REG) {
@@ -865,7 +867,7 @@ extern "C" int fm_forward(fm_matrix* m, const fm_params* p, const float* y, cons
         if (loss_sum) *loss_sum = 0.0;
         return FM_OK;
     }
-    FM_TRY(run_forward(m, p, y, w0, w, V, yhat, a, G, q, r, 0, loss_sum != nullptr, st));
+    FM_TRY(run_forward(m, p, y, w0, w, V, yhat, a, G, q, r, 0, false, loss_sum != nullptr, st));
     if (loss_sum != nullptr) {
         FM_TRY(fm_reduce_pairs(m, m->row_part, forward_pairs(m, p), m->h_scal, st));
         FM_HIP(m, hipStreamSynchronize(st));
@@ -1017,7 +1019,6 @@ extern "C" int fm_gradient(fm_matrix* m, const fm_params* p, const float* r, con
         // column pass is one request (and dense-ish columns can be staged through LDS)
         FM_TRY(fm_pack_aux(m, r, G, st));
         m->aux_held = true;
-        m->aux_packed = true;
         const FmAux x = fm_aux_layout(m, p->K, true);
         A.r = x.r;
         A.G = x.G;
@@ -1072,20 +1073,20 @@ extern "C" int fm_sgd_epoch(fm_matrix* m, const fm_params* p, const float* y, fl
         return FM_OK;
     }
     // steps 1-3: G, r, loss and sum r
-    m->aux_packed = take_packed(m, p->K, m->N, FM_PLANAR_ROWS);
+    const bool packed = take_packed(m, p->K, m->N, FM_PLANAR_ROWS);
     RowArgs R;
-    FM_TRY(forward_args(m, p, y, w0, w, V, nullptr, nullptr, nullptr, nullptr, nullptr, 1, true,
+    FM_TRY(forward_args(m, p, y, w0, w, V, nullptr, nullptr, nullptr, nullptr, nullptr, 1, packed, true,
                         FM_DENSE_FORWARD | FM_DENSE_GRADIENT, R, st));
     m->aux_full = false;
     const bool dense = R.dense_D > 0;  // then the data sums of step 4 come with them
     if (!dense) FM_TRY(fm_launch_rows(m, R, false, st));
     // steps 4-5 fused: gradient of every column and the step on w, V
     ColArgs A;
-    base_col_args(m, p, m->aux_packed, A);
+    base_col_args(m, p, packed, A);
     A.ptr = m->colptr;
     A.row = m->crow;
     A.val = m->cval;
-    const FmAux x = fm_aux_layout(m, p->K, m->aux_packed);
+    const FmAux x = fm_aux_layout(m, p->K, packed);
     A.r = x.r;
     A.G = x.G;
     A.gs = x.gs;
@@ -1115,6 +1116,10 @@ extern "C" int fm_sgd_epoch(fm_matrix* m, const fm_params* p, const float* y, fl
 
 // ------------------------------------------------------- stratified epoch ----
 
+// All of the strata's calls ask for the layout here: a step goes on from aggregates that fm_stratified_begin left, now or in a
+// graph.
+static bool strata_packed(const fm_matrix* m, int32_t K) { return take_packed(m, K, m->N / m->P, FM_PLANAR_ROWS_STRATA); }
+
 extern "C" int fm_stratified_begin(fm_matrix* m, const fm_params* p, const float* y, const float* w0,
                                    const float* w, const float* V, void* hip_stream)
 {
@@ -1127,8 +1132,7 @@ extern "C" int fm_stratified_begin(fm_matrix* m, const fm_params* p, const float
     FM_TRY(fm_check_vec_aligned(m, {V}));
     hipStream_t st = (hipStream_t)hip_stream;
     FM_TRY(ensure_strat_ws(m, p->K));
-    m->aux_packed = take_packed(m, p->K, m->N / m->P, FM_PLANAR_ROWS_STRATA);
-    FM_TRY(run_forward(m, p, y, w0, w, V, nullptr, nullptr, nullptr, nullptr, nullptr, 2, false, st));
+    FM_TRY(run_forward(m, p, y, w0, w, V, nullptr, nullptr, nullptr, nullptr, nullptr, 2, strata_packed(m, p->K), false, st));
     m->aux_full = true;
     return FM_OK;
 }
@@ -1146,7 +1150,7 @@ static void set_shares(ColArgs& A, const float* rho, const int64_t* bounds, int6
 // Column-side arguments of stratum s (s == P: the flush after the last stratum).
 static void strat_col_args(fm_matrix* m, const fm_params* p, int32_t s, float* w, float* V, bool lazy, ColArgs& A)
 {
-    base_col_args(m, p, m->aux_packed, A);
+    base_col_args(m, p, strata_packed(m, p->K), A);
     A.w = w;
     A.V = V;
     A.P = m->P;
@@ -1168,7 +1172,7 @@ static int stratified_step(fm_matrix* m, const fm_params* p, int32_t s, const fl
     A.mark = lazy ? nullptr : m->col_mark;
     A.row = m->s_row;
     A.val = m->s_cval;
-    const FmAux x = fm_aux_layout(m, p->K, m->aux_packed);
+    const FmAux x = fm_aux_layout(m, p->K, strata_packed(m, p->K));
     A.r = x.r;
     A.G = x.G;
     A.gs = x.gs;
@@ -1203,7 +1207,7 @@ static int stratified_step(fm_matrix* m, const fm_params* p, int32_t s, const fl
     R.big = fm_rows_big(m, p->K);
     R.dwn = m->dwn;
     R.y = y;
-    aux_outputs(m, p->K, R, true);
+    aux_outputs(m, p->K, R, true, strata_packed(m, p->K));
     // An XCD keeps to one run of rows where the aggregates fit half of the chip's L2s (4 MB each) and row blocks are small: up
     // to FM_WHOLE_ROWS rows.  The block that meets a popular column block has most of a stratum's entries, and its XCD most of
     // the work when it fills the XCD's run.  Epochs with runs / without, us: text-like 5e4 rows, K=16, 32 strata 577 / 599;
@@ -1237,7 +1241,7 @@ extern "C" int fm_stratified_step(fm_matrix* m, const fm_params* p, int32_t s, c
 // The bias step from the multipliers as they stand in the aggregate rows.
 static void set_bias_step(fm_matrix* m, const fm_params* p, float* w0, FmEpilogue& E)
 {
-    const FmAux x = fm_aux_layout(m, p->K, m->aux_packed);
+    const FmAux x = fm_aux_layout(m, p->K, strata_packed(m, p->K));
     set_epilogue(m, E, x.r, m->N, x.ss, true);
     E.w0 = w0;
     E.eta = p->eta;
@@ -1282,7 +1286,7 @@ extern "C" int fm_stratified_end(fm_matrix* m, const fm_params* p, float* w0, vo
 static int enqueue_stratified_epoch(fm_matrix* m, const fm_params* p, const float* y, float* w0, float* w, float* V,
                                     bool lazy, hipStream_t st)
 {
-    FM_TRY(run_forward(m, p, y, w0, w, V, nullptr, nullptr, nullptr, nullptr, nullptr, 2, false, st));
+    FM_TRY(run_forward(m, p, y, w0, w, V, nullptr, nullptr, nullptr, nullptr, nullptr, 2, strata_packed(m, p->K), false, st));
     for (int32_t s = 0; s < m->P; ++s) FM_TRY(stratified_step(m, p, s, y, w0, w, V, lazy, st));
     if (lazy) {  // the sums of the bias step beside it
         ColArgs F;
@@ -1365,7 +1369,6 @@ extern "C" int fm_stratified_epoch(fm_matrix* m, const fm_params* p, const float
     FM_TRY(fm_check_vec_aligned(m, {V}));
     hipStream_t st = (hipStream_t)hip_stream;
     FM_TRY(ensure_strat_ws(m, p->K));
-    m->aux_packed = take_packed(m, p->K, m->N / m->P, FM_PLANAR_ROWS_STRATA);
     // The refresh of a stratum reads the change of a column only where the column has entries in
     // its cell, so the regulariser-only steps of the other columns can wait (not when every row
     // is refreshed from every column's change).
@@ -1389,7 +1392,7 @@ extern "C" int fm_stratified_epoch(fm_matrix* m, const fm_params* p, const float
     if (lazy) m->lazy_clear = sound;
     m->aux_full = true;
     m->aux_held = true;
-    return objective != nullptr ? objective_pass(m, p, y, w0, w, V, 2, objective, st) : FM_OK;
+    return objective != nullptr ? objective_pass(m, p, y, w0, w, V, 2, strata_packed(m, p->K), objective, st) : FM_OK;
 }
 
 // ------------------------------------------------------- mini-batch epoch ----
@@ -1407,15 +1410,15 @@ extern "C" int fm_minibatch_epoch(fm_matrix* m, const fm_params* p, const float*
     FM_TRY(ensure_ws(m, p->K));
     m->aux_full = false;
     m->aux_held = true;
-    m->aux_packed = take_packed(m, p->K, m->N / m->B, FM_PLANAR_ROWS_BATCH);
-    const FmAux x = fm_aux_layout(m, p->K, m->aux_packed);
+    const bool packed = take_packed(m, p->K, m->N / m->B, FM_PLANAR_ROWS_BATCH);
+    const FmAux x = fm_aux_layout(m, p->K, packed);
     // a column without entries in a batch only takes the regulariser's step there: postponed
     // until the column next has entries, or the epoch ends
     const bool lazy = m->opt.lazy_reg;
     bool sound = true;
     if (lazy) FM_TRY(clear_lazy(m, st, &sound));
     auto col_args = [&](int32_t b, ColArgs& A) {
-        base_col_args(m, p, m->aux_packed, A);
+        base_col_args(m, p, packed, A);
         A.w = w;
         A.V = V;
         A.P = m->B;
@@ -1447,7 +1450,8 @@ extern "C" int fm_minibatch_epoch(fm_matrix* m, const fm_params* p, const float*
             R.ss = x.ss;
             R.as = x.as;
             R.r = x.r + r0 * x.ss;
-            R.whole_rows = m->aux_packed ? 1 : 0;
+            R.whole_rows = packed ? 1 : 0;
+            R.aux_rows = m->aux_rows;
             R.row_part = p->update_w0 ? m->row_part : nullptr;
             R.loss = p->loss;
             R.s = p->loss_scale;
@@ -1493,7 +1497,7 @@ extern "C" int fm_minibatch_epoch(fm_matrix* m, const fm_params* p, const float*
         FM_TRY(fm_launch_cols_flush(m, F, st));
         m->lazy_clear = sound;
     }
-    return objective != nullptr ? objective_pass(m, p, y, w0, w, V, 1, objective, st) : FM_OK;
+    return objective != nullptr ? objective_pass(m, p, y, w0, w, V, 1, packed, objective, st) : FM_OK;
 }
 
 extern "C" int fm_get_aux(const fm_matrix* m, float* a, float* G, float* q, float* r, void* hip_stream)
@@ -1504,7 +1508,7 @@ extern "C" int fm_get_aux(const fm_matrix* m, float* a, float* G, float* q, floa
     if ((a != nullptr || q != nullptr) && !m->aux_full)
         return fm_fail(mm, FM_ESTATE, "a and q are only held after a stratified call");
     hipStream_t st = (hipStream_t)hip_stream;
-    FM_TRY(fm_unpack_aux(mm, a, G, q, r, st));
+    FM_TRY(fm_unpack_aux(mm, packed_exists(m, m->wsK), a, G, q, r, st));
     return FM_OK;
 }
 

@@ -123,6 +123,7 @@ __global__ __launch_bounds__(FM_BLOCK, dense_per_cu(DB, KB)) void k_dense(const 
             fm_reg_pair<FM_BLOCK>(A.w, A.D, A.V, A.D * (int64_t)A.K, A.regs, sh);
         return;
     }
+    if (FORWARD && A.aux_rows != nullptr && b == 0 && threadIdx.x == 0) *A.aux_rows = A.whole_rows;
     const int D = (int)A.D, K = A.K, gs = (int)A.gs;
     const int lane = threadIdx.x & (FM_WAVE - 1);
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / FM_WAVE);  // uniform, and so is all that follows from it

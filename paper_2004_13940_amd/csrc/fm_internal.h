@@ -227,7 +227,7 @@ struct fm_matrix {
     double* h_scal = nullptr;   // pinned: 8 doubles that mirror scal, then one FmCheck per workgroup of k_check_csr
     bool aux_full = false;      // a, q valid (not only G, r)
     bool aux_held = false;      // the aggregate rows hold the result of a pass (fm_get_aux may read them)
-    bool aux_packed = false;    // ... in packed rows
+    int32_t* aux_rows = nullptr;  // device, behind scal: 1 where they are packed rows, 0 where planar; see fm_unpack_aux
     // side streams so that the LDS-bound and the memory-bound column kernels overlap
     hipStream_t side1 = nullptr, side2 = nullptr;
     hipEvent_t ev_fork = nullptr, ev_join1 = nullptr, ev_join2 = nullptr;
@@ -337,6 +337,7 @@ struct RowArgs {
     int64_t ss;         // floats between consecutive rows of r (1, or the aggregate row stride)
     int64_t as;         // ... of a and q (2: they are pairs and move as one float2)
     int32_t whole_rows; // packed aggregate rows: r, a, q move as one float4 (forward: and the padding is written with them)
+    int32_t* aux_rows;  // forward into the handle's aggregates: takes whole_rows; nullable
     float* row_part;    // nullable: [2*gridDim] loss and sum r per block
     double* eval_part;  // nullable: [3*gridDim] sums of losses, squared errors and correct signs per block
     int32_t big;          // what is gathered (V, its half copy or dV, dwn) is larger than FM_BUF_BYTES
@@ -373,7 +374,7 @@ enum { FM_DENSE_FORWARD = 1, FM_DENSE_GRADIENT = 2 };
 // ... and take such a pass over so many rows
 bool fm_dense_takes(const fm_matrix* m, const fm_params* p, int64_t rows, int what);
 int fm_launch_dense(fm_matrix* m, const DenseArgs& A, int what, hipStream_t st);  // gradient: partial sums; the finish follows
-int fm_unpack_aux(fm_matrix* m, float* a, float* G, float* q, float* r, hipStream_t st);
+int fm_unpack_aux(fm_matrix* m, bool rows_exist, float* a, float* G, float* q, float* r, hipStream_t st);
 
 // What is left of an epoch when the columns have stepped: the sums over the examples, the bias step and the figures of
 // the objective.  One workgroup, which rides along with the last column kernel.
@@ -500,6 +501,7 @@ struct DenseArgs {
     float *yhat, *a, *G, *q, *r;  // forward: nullable outputs; gradient alone: G and r are read
     int64_t gs, ss, as;           // floats between rows of G, of r, of a and q
     int32_t whole_rows;           // forward: packed aggregate rows [G | r | a | q | pad] go out whole
+    int32_t* aux_rows;            // forward into the handle's aggregates: takes whole_rows; nullable
     int32_t loss;
     float s;
     float* row_part;    // forward, nullable: [2 * nchunks] loss and sum of r per workgroup

@@ -278,6 +278,9 @@ __global__ __launch_bounds__(FM_BLOCK, L >= FM_WIDE_GROUP && is_refresh(MODE) ? 
         }
     }
 
+    if constexpr (!is_refresh(MODE)) {
+        if (A.aux_rows != nullptr && blockIdx.x == 0 && threadIdx.x == 0) *A.aux_rows = A.whole_rows;
+    }
     if (A.row_part != nullptr) {
         // l_i, r_i are non-zero only in lane 0 of a group: fixed-order block sums
         __shared__ float sh[2 * FM_WAVES];
@@ -398,8 +401,10 @@ int launch_rows_v(fm_matrix* m, int lanes, const RowArgs& A, bool refresh, hipSt
 }  // namespace
 
 namespace {
-__global__ void k_unpack_aux(const FmAux x, int64_t N, int32_t K, float* a, float* G, float* q, float* r)
+__global__ void k_unpack_aux(const FmAux planar, const FmAux rows, const int32_t* __restrict__ aux_rows, int64_t N, int32_t K,
+                             float* a, float* G, float* q, float* r)
 {
+    const FmAux x = *aux_rows != 0 ? rows : planar;
     const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     const int64_t per = K + 3;
     if (t >= N * per) return;
@@ -420,10 +425,11 @@ __global__ void k_unpack_aux(const FmAux x, int64_t N, int32_t K, float* a, floa
 namespace {
 // Caller-side dense r[N], G[N x K] into the packed aggregate rows [G | r | 0 | 0 | pad], one float4
 // per thread, whole rows written.
-__global__ void k_pack_aux(const FmAux x, int64_t N, int32_t K, const float* __restrict__ r,
+__global__ void k_pack_aux(const FmAux x, int32_t* __restrict__ aux_rows, int64_t N, int32_t K, const float* __restrict__ r,
                            const float* __restrict__ G)
 {
     const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (t == 0) *aux_rows = 1;
     const int64_t per = x.gs / 4;  // float4 per row
     if (t >= N * per) return;
     const int64_t i = t / per;
@@ -472,19 +478,21 @@ int fm_pack_aux(fm_matrix* m, const float* r, const float* G, hipStream_t st)
     if (total <= 0) return FM_OK;
     const int64_t grid = (total + 255) / 256;
     if (grid > 0x7fffffffLL) return fm_fail(m, FM_ERANGE, "aggregate copy too large");
-    hipLaunchKernelGGL(k_pack_aux, dim3((unsigned)grid), dim3(256), 0, st, x, m->N, m->wsK, r, G);
+    hipLaunchKernelGGL(k_pack_aux, dim3((unsigned)grid), dim3(256), 0, st, x, m->aux_rows, m->N, m->wsK, r, G);
     FM_HIP(m, hipGetLastError());
     return FM_OK;
 }
 
-int fm_unpack_aux(fm_matrix* m, float* a, float* G, float* q, float* r, hipStream_t st)
+// Each pass chooses its layout, and passes may run when a caller's graph is launched, in any order and long after they were
+// enqueued: which one the aggregates have is known where they are, in the word that a pass leaves beside them.
+int fm_unpack_aux(fm_matrix* m, bool rows_exist, float* a, float* G, float* q, float* r, hipStream_t st)
 {
     const int64_t total = m->N * (int64_t)(m->wsK + 3);
     if (total <= 0) return FM_OK;
     const int64_t grid = (total + 255) / 256;
     if (grid > 0x7fffffffLL) return fm_fail(m, FM_ERANGE, "aggregate copy too large");
-    hipLaunchKernelGGL(k_unpack_aux, dim3((unsigned)grid), dim3(256), 0, st, fm_aux_layout(m, m->wsK, m->aux_packed), m->N, m->wsK, a, G,
-                       q, r);
+    hipLaunchKernelGGL(k_unpack_aux, dim3((unsigned)grid), dim3(256), 0, st, fm_aux_layout(m, m->wsK, false),
+                       fm_aux_layout(m, m->wsK, rows_exist), (const int32_t*)m->aux_rows, m->N, m->wsK, a, G, q, r);
     FM_HIP(m, hipGetLastError());
     return FM_OK;
 }
@@ -552,6 +560,7 @@ void fm_dense_rows(const RowArgs& A, DenseArgs* E)
     E->ss = A.ss;
     E->as = A.as;
     E->whole_rows = A.whole_rows;
+    E->aux_rows = A.aux_rows;
     E->loss = A.loss;
     E->s = A.s;
     E->row_part = A.row_part;

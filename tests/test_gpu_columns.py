@@ -828,3 +828,55 @@ def test_panels_and_tiles_where_their_rules_change(N, K):
     assert_close(gw.cpu().numpy(), wgw, "grad_w")
     assert_close(gV.cpu().numpy().reshape(D, K), wgV, "grad_V")
     m.close()
+
+
+@pytest.mark.parametrize("captured", ["epoch", "strata", "batches"])
+def test_aggregates_of_a_replayed_pass_are_read_in_its_layout(captured):
+    """K = 16, 200,003 rows: full epochs keep packed rows, strata and batches planar ones.  What a pass leaves is read in that
+    pass's layout whichever call was enqueued last: a graph runs whenever it is launched, and a capture runs nothing."""
+    import torch
+    from paper_2004_13940_amd import binding as B
+    rng = np.random.default_rng(8400)
+    N, D, K, row = 200_003, 40, 16, 3
+    col = np.sort(np.argpartition(rng.random((N, D)), row, axis=1)[:, :row], axis=1).astype(np.int32).ravel()
+    val = rng.standard_normal(N * row).astype(np.float32)
+    rowptr = np.arange(N + 1, dtype=np.int64) * row
+    w, V = (rng.standard_normal(D) * 0.2).astype(np.float32), (rng.standard_normal((D, K)) * 0.1).astype(np.float32)
+    y = to_dev(np.where(rng.random(N) < 0.5, 1.0, -1.0).astype(np.float32))
+    p = B.make_params(K, O.LOSS_LOGISTIC, 0.0, 0.0, 0.0, 1.0 / N, 0)  # steps of length zero: G and r of the parameters as given
+    want = {}
+    X = O.make_matrix(N, D, rowptr, col, val)
+    for scale in (1.0, 2.0):
+        _, G, _, yhat = O.forward(X, 0.1 * scale, w * scale, V * scale)
+        want[scale] = (G, O.loss_multiplier(O.LOSS_LOGISTIC, 1.0 / N, yhat, y.cpu().numpy())[1])
+    m = B.Matrix(N, D, rowptr, col, val)
+    m.fm_build_csc()
+    m.fm_partition(3)
+    m.fm_partition_batches(3)
+    calls = dict(epoch=m.fm_sgd_epoch, strata=m.fm_stratified_epoch, batches=m.fm_minibatch_epoch)
+    one, two = (dev_params(np.float32(0.1 * s), w * s, V * s) for s in (1.0, 2.0))
+    G, r = torch.empty(N * K, device="cuda"), torch.empty(N, device="cuda")
+
+    def check(scale, what):
+        G.fill_(float("nan")), r.fill_(float("nan"))
+        m.fm_get_aux(K, G=G, r=r)
+        assert_close(G.cpu().numpy().reshape(N, K), want[scale][0], f"G {what}")
+        assert_close(r.cpu().numpy(), want[scale][1], f"r {what}")
+
+    for name in calls:
+        print("layouts under capture", captured, name, flush=True)
+        calls[captured](p, y, *two)  # the workspace is there before the capture
+        calls[name](p, y, *one)
+        torch.cuda.synchronize()
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g):
+            calls[captured](p, y, *two)
+        check(1.0, f"after {name}, {captured} only captured")
+        for turn in range(2):
+            g.replay()
+            check(2.0, f"after replay {turn} of {captured}")
+            calls[name](p, y, *one)
+            check(1.0, f"after {name} behind replay {turn} of {captured}")
+            g.replay()
+            check(2.0, f"after replay {turn} of {captured} behind {name}")
+    m.close()
