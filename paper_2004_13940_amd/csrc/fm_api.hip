@@ -555,7 +555,6 @@ static bool packed_exists(const fm_matrix* m, int32_t K) { return m->opt.aux != 
 // columns, 1e6 rows, strata K = 8 1066 / 873, K = 20 1979 / 1586, epochs 115 / 112, 118 / 112; 1e5 rows, strata K = 8 189 / 181, K =
 // 28 235 / 232, but K = 4 180 / 189).
 constexpr int64_t FM_PLANAR_ROWS = 200000;                   // full epochs, gradients
-constexpr int64_t FM_PACK_ROWS = 40000;                      // see fm_gradient
 constexpr int64_t FM_PLANAR_ROWS_BATCH = 400000;             // batches: their items are worked on in row order
 constexpr int64_t FM_PLANAR_ROWS_STRATA = int64_t(1) << 20;  // strata: the refresh gains by it too
 static bool take_packed(const fm_matrix* m, int32_t K, int64_t rows, int64_t planar_rows)
@@ -1002,12 +1001,15 @@ extern "C" int fm_gradient(fm_matrix* m, const fm_params* p, const float* r, con
     if (m->D == 0 || (grad_w == nullptr && grad_V == nullptr))
         return grad_w0 != nullptr ? fm_run_epilogue(m, E, st) : FM_OK;
     const bool dense = fm_dense_takes(m, p, m->N, FM_DENSE_GRADIENT);
-    // Planar, the caller's arrays are read as they are, and up to FM_PACK_ROWS rows the pass that packs them costs more than
-    // it gives at any K (packed / planar, us: uniform rows of 15, 2e4 rows, K = 8 15 / 12, K = 28 17 / 13; text-like 5e4 rows
-    // K = 8 32 / 28, K = 24 45 / 43, K = 28 45 / 48; 2e5 rows, K = 8 157 / 173, K = 24 196 / 200).  The dense kernels read
-    // either once, row by row.
-    const bool packed = !dense && (m->N > FM_PACK_ROWS || m->opt.aux == 2) && take_packed(m, p->K, m->N, FM_PLANAR_ROWS);
-    if (packed_exists(m, p->K)) m->aux_full = false;  // as packing leaves it, whichever path the call takes
+    const bool packed = !dense && take_packed(m, p->K, m->N, FM_PLANAR_ROWS);
+    if (packed_exists(m, p->K)) {
+        // Where packed rows exist the handle holds r and G of the call afterwards, for fm_get_aux.  Packed, one streaming pass
+        // makes every gather of the columns one request (and dense-ish columns can be staged through LDS); planar, the columns
+        // and the dense kernels read the caller's arrays as they are.
+        FM_TRY(fm_keep_aux(m, packed, r, G, st));
+        m->aux_held = true;
+        m->aux_full = false;
+    }
     ColArgs A;
     base_col_args(m, p, packed, A);
     if (grad_w0 != nullptr) A.epi = E;
@@ -1015,10 +1017,6 @@ extern "C" int fm_gradient(fm_matrix* m, const fm_params* p, const float* r, con
     A.row = m->crow;
     A.val = m->cval;
     if (packed) {
-        // one streaming pass puts r and G into packed aggregate rows, so that every gather of the
-        // column pass is one request (and dense-ish columns can be staged through LDS)
-        FM_TRY(fm_pack_aux(m, r, G, st));
-        m->aux_held = true;
         const FmAux x = fm_aux_layout(m, p->K, true);
         A.r = x.r;
         A.G = x.G;

@@ -364,7 +364,7 @@ int64_t fm_rows_max_grid(const fm_matrix* m, int64_t N, int32_t K);  // ... and 
 // once per device, with that device current: resolves the address of the static scratch array of
 // fm_forward_noalloc (fm_noalloc.hip); called when a handle is created
 int fm_noalloc_init_device(fm_matrix* m);
-int fm_pack_aux(fm_matrix* m, const float* r, const float* G, hipStream_t st);  // packed layout only
+int fm_keep_aux(fm_matrix* m, bool packed, const float* r, const float* G, hipStream_t st);  // the caller's; K a multiple of 4
 int fm_to_half(fm_matrix* m, const float* x, _Float16* out, int64_t n, hipStream_t st);  // round to nearest even
 // dense matrices (fm_dense.hip)
 bool fm_dense_fits(const fm_matrix* m, int32_t K);           // the dense kernels exist for this matrix and K

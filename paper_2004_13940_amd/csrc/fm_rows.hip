@@ -423,13 +423,13 @@ __global__ void k_unpack_aux(const FmAux planar, const FmAux rows, const int32_t
 }  // namespace
 
 namespace {
-// Caller-side dense r[N], G[N x K] into the packed aggregate rows [G | r | 0 | 0 | pad], one float4
-// per thread, whole rows written.
-__global__ void k_pack_aux(const FmAux x, int32_t* __restrict__ aux_rows, int64_t N, int32_t K, const float* __restrict__ r,
+// Caller-side dense r[N], G[N x K] into the aggregates, one float4 per thread: packed rows [G | r | 0 | 0 | pad], written
+// whole, or planar ones, as they come.
+__global__ void k_keep_aux(const FmAux x, int packed, int32_t* __restrict__ aux_rows, int64_t N, int32_t K, const float* __restrict__ r,
                            const float* __restrict__ G)
 {
     const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t == 0) *aux_rows = 1;
+    if (t == 0) *aux_rows = packed;
     const int64_t per = x.gs / 4;  // float4 per row
     if (t >= N * per) return;
     const int64_t i = t / per;
@@ -440,6 +440,7 @@ __global__ void k_pack_aux(const FmAux x, int32_t* __restrict__ aux_rows, int64_
     else if (o == K)
         z[0] = r[i];
     fm_store_vec<4>(x.G + i * x.gs + o, z);
+    if (!packed && o == 0) x.r[i] = r[i];
 }
 }  // namespace
 
@@ -471,14 +472,14 @@ int fm_to_half(fm_matrix* m, const float* x, _Float16* out, int64_t n, hipStream
     return FM_OK;
 }
 
-int fm_pack_aux(fm_matrix* m, const float* r, const float* G, hipStream_t st)
+int fm_keep_aux(fm_matrix* m, bool packed, const float* r, const float* G, hipStream_t st)
 {
-    const FmAux x = fm_aux_layout(m, m->wsK, true);
+    const FmAux x = fm_aux_layout(m, m->wsK, packed);
     const int64_t total = m->N * (x.gs / 4);
     if (total <= 0) return FM_OK;
     const int64_t grid = (total + 255) / 256;
     if (grid > 0x7fffffffLL) return fm_fail(m, FM_ERANGE, "aggregate copy too large");
-    hipLaunchKernelGGL(k_pack_aux, dim3((unsigned)grid), dim3(256), 0, st, x, m->aux_rows, m->N, m->wsK, r, G);
+    hipLaunchKernelGGL(k_keep_aux, dim3((unsigned)grid), dim3(256), 0, st, x, packed ? 1 : 0, m->aux_rows, m->N, m->wsK, r, G);
     FM_HIP(m, hipGetLastError());
     return FM_OK;
 }

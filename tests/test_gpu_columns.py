@@ -880,3 +880,31 @@ def test_aggregates_of_a_replayed_pass_are_read_in_its_layout(captured):
             g.replay()
             check(2.0, f"after replay {turn} of {captured} behind {name}")
     m.close()
+
+
+@pytest.mark.parametrize("N,D,row", [(1, 3, 2), (257, 9, 9), (40_000, 30, 3), (40_001, 30, 3), (200_001, 20, 2), (9_001, 20, 20)])
+@pytest.mark.parametrize("K,option", [(4, 0), (12, 0), (16, 0), (16, 2), (28, 0), (8, 1), (32, 0), (6, 0)])
+def test_gradient_leaves_what_it_was_given_in_the_aggregates(N, D, row, K, option):
+    """Where packed rows exist (K a multiple of four up to 28, not switched off), whichever layout and kernels the call takes."""
+    import torch
+    from paper_2004_13940_amd import binding as B
+    rng = np.random.default_rng(N + 100 * K + option)
+    col = np.sort(np.argpartition(rng.random((N, D)), row - 1, axis=1)[:, :row], axis=1).astype(np.int32).ravel()
+    m = B.Matrix(N, D, np.arange(N + 1, dtype=np.int64) * row, col, rng.standard_normal(N * row).astype(np.float32))
+    m.fm_set_option(B.FM_OPT_AUX_PLANAR, option)
+    m.fm_build_csc()
+    p = B.make_params(K, O.LOSS_SQUARED, 0.01, 0.02, 0.1)
+    _, w, V = dev_params(0.0, rng.standard_normal(D), rng.standard_normal((D, K)).ravel())
+    for turn in range(2):
+        r, G = to_dev(rng.standard_normal(N)), to_dev(rng.standard_normal(N * K))
+        m.fm_gradient(p, r, G, w, V, grad_w=torch.empty(D, device="cuda"), grad_V=torch.empty(D * K, device="cuda"))
+        gotr, gotG = torch.empty(N, device="cuda"), torch.empty(N * K, device="cuda")
+        if option == 1 or K % 4 or K > 28:
+            with pytest.raises(B.FMError):
+                m.fm_get_aux(K, G=gotG, r=gotr)
+            continue
+        m.fm_get_aux(K, G=gotG, r=gotr)
+        assert torch.equal(gotr, r) and torch.equal(gotG, G)
+        with pytest.raises(B.FMError):
+            m.fm_get_aux(K, a=gotr)
+    m.close()
