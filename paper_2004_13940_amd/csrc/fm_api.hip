@@ -643,10 +643,7 @@ static int ensure_ws(fm_matrix* m, int32_t K)
         fm_tile_shape(m, K, &shape[0], &shape[1], &shape[2]);
         if (memcmp(shape, m->lfull_shape, sizeof(shape)) != 0) {
             FM_HIP(m, hipDeviceSynchronize());
-            fm_unsettled(m);
             FM_TRY(fm_build_full_index(m, K, nullptr));
-            FM_TRY(fm_settle(m, nullptr));
-            FM_HIP(m, hipDeviceSynchronize());
         }
     }
     const size_t D = (size_t)m->D;

@@ -1112,6 +1112,26 @@ int fm_build_long_index(fm_matrix* m, const int64_t* ptr, const int32_t* ids, co
     return FM_OK;
 }
 
+// What a build allocates belongs to the handle once the build has settled; of one that fails (no memory, a launch refused)
+// nothing stays, and the handle is as it was before.
+struct BuildScope {
+    fm_matrix* m;
+    std::vector<FmAlloc> before;
+    bool done = false;
+    explicit BuildScope(fm_matrix* m_) : m(m_), before(m_->allocs) {}
+    ~BuildScope()
+    {
+        if (done) return;
+        (void)hipDeviceSynchronize();
+        fm_unsettled(m);
+        for (size_t i = m->allocs.size(); i-- > 0;) {
+            void* p = m->allocs[i].p;
+            const bool older = std::any_of(before.begin(), before.end(), [p](const FmAlloc& a) { return a.p == p; });
+            if (!older) fm_dev_free(m, p);
+        }
+    }
+};
+
 // Frees the device arrays of an index and resets it.
 static void free_long_index(fm_matrix* m, LongIndex* li)
 {
@@ -1163,16 +1183,29 @@ void fm_tile_shape(const fm_matrix* m, int32_t K, int* tile_rows, int* tile_min,
     *tile_seg = T.tile_seg > 0 ? T.tile_seg : seg;
 }
 
+static int build_full_index(fm_matrix* m, const FmTune& T, LongIndex* out, hipStream_t st);
+
 int fm_build_full_index(fm_matrix* m, int32_t K, hipStream_t st)
 {
-    LongIndex* out = &m->lfull;
-    free_long_index(m, out);
+    free_long_index(m, &m->lfull);
+    m->lfull_shape[0] = 0;  // no index has tiles of no rows: who finds it so builds one
     FmTune T = m->tune;
     if (T.seg <= 0) T.seg = fm_item_length(m->nnz, false);
     fm_tile_shape(m, K, &T.tile, &T.tile_min, &T.tile_seg);
+    BuildScope scope(m);
+    LongIndex built;
+    FM_TRY(build_full_index(m, T, &built, st));
+    FM_TRY(fm_settle(m, st));
+    m->lfull = built;
     m->lfull_shape[0] = T.tile;
     m->lfull_shape[1] = T.tile_min;
     m->lfull_shape[2] = T.tile_seg;
+    scope.done = true;
+    return FM_OK;
+}
+
+static int build_full_index(fm_matrix* m, const FmTune& T, LongIndex* out, hipStream_t st)
+{
     int64_t* tc = nullptr;
     FM_TRY(count_short_list(m, m->colptr, nullptr, m->D, 1, T.seg, out, &tc, st));
     out->nlong = out->nitems = 0;
@@ -1180,8 +1213,7 @@ int fm_build_full_index(fm_matrix* m, int32_t K, hipStream_t st)
     out->h_item_off.assign(2, 0);
     const int64_t D = m->D;
     if (D <= 0 || m->nnz == 0) {
-        FM_TRY(fm_settle(m, st));  // no columns with entries: none short
-        fm_spend(m, {tc});
+        fm_spend(m, {tc});  // no columns with entries: none short
         return FM_OK;
     }
     // 1. the long columns, in column order
@@ -1299,9 +1331,9 @@ extern "C" int fm_build_csc(fm_matrix* m, void* hip_stream)
     if (m == nullptr) return FM_EINVAL;
     hipStream_t st = (hipStream_t)hip_stream;
     if (m->has_csc) return FM_OK;
-    fm_unsettled(m);
+    BuildScope scope(m);
     const int64_t n = m->nnz;
-    FM_TRY(fm_dev_alloc(m, (void**)&m->colptr, (size_t)(m->D + 1) * sizeof(int64_t)));
+    FM_TRY(fm_dev_alloc(m, (void**)&m->colptr, (size_t)(m->D + 1) * sizeof(int64_t)));  // not read before has_csc is set
     FM_TRY(fm_dev_alloc(m, (void**)&m->crow, (size_t)(n + FM_ENTRY_PAD) * sizeof(int32_t)));
     FM_TRY(fm_dev_alloc(m, (void**)&m->cval, (size_t)(n + FM_ENTRY_PAD) * sizeof(float)));
     if (n == 0) {
@@ -1325,13 +1357,14 @@ extern "C" int fm_build_csc(fm_matrix* m, void* hip_stream)
         fm_spend(m, {row, key, t[0], t[1], t[2]});
     }
     FM_TRY(fm_build_full_index(m, 0, st));
-    FM_TRY(fm_settle(m, st));
+    scope.done = true;
     m->has_csc = true;
     fm_drop_workspace(m);
     return FM_OK;
 }
 
 static int partition_impl(fm_matrix* m, int32_t P, const int32_t* place, hipStream_t st);
+static int ensure_marks(fm_matrix* m, hipStream_t st);
 
 // One orientation of the per-stratum matrices: the entries in (stratum, major, minor) order, the list
 // of the (stratum, major) pairs that hold an entry with the offset of their first one, and where every
@@ -1346,7 +1379,8 @@ struct StrataSide {
     std::vector<int64_t> h_ent_off, h_list_off;  // [P + 1]
 };
 
-static int build_strata_side(fm_matrix* m, bool by_rows, hipStream_t st, StrataSide* out, int32_t P, bool batches = false)
+static int build_strata_side(fm_matrix* m, bool by_rows, const int32_t* place, hipStream_t st, StrataSide* out, int32_t P,
+                             bool batches = false)
 {
     const int64_t n = m->nnz;
     const int64_t nmajor = by_rows ? m->N : m->D;
@@ -1371,7 +1405,7 @@ static int build_strata_side(fm_matrix* m, bool by_rows, hipStream_t st, StrataS
     int64_t* hist = nullptr;
     FM_TRY(sort_hist(m, n, &hist));
     hipLaunchKernelGGL(k_stratum_keys, dim3((unsigned)sort_tiles(n)), dim3(RS_T), 0, st, major, nmajor, minor, n, m->N, m->D, P,
-                       batches ? 2 : (by_rows ? 1 : 0), batches ? nullptr : (const int32_t*)m->d_place, k0, j0, sort_bins(bits), hist,
+                       batches ? 2 : (by_rows ? 1 : 0), place, k0, j0, sort_bins(bits), hist,
                        sort_tiles(n));
     FM_HIP(m, hipGetLastError());
     const SortIn in = {k0, {reinterpret_cast<const uint32_t*>(minor), reinterpret_cast<const uint32_t*>(val), j0}};
@@ -1434,33 +1468,60 @@ static int partition_impl(fm_matrix* m, int32_t P, const int32_t* place, hipStre
     if (P < 1 || P > FM_MAXP) return fm_fail(m, FM_EINVAL, "P=%d outside 1..%d", P, FM_MAXP);
     if (m->P != 0) return fm_fail(m, FM_ESTATE, "matrix is already partitioned (P=%d)", m->P);
     if (m->N < 1 || m->D < 1) return fm_fail(m, FM_EINVAL, "cannot partition an empty matrix");
-    fm_unsettled(m);
-    m->P = P;
-    m->h_rb.resize(P + 1);
-    m->h_cb.resize(P + 1);
+    FM_TRY(fm_ensure_lazy(m, st));
+    FM_TRY(ensure_marks(m, st));
+    BuildScope scope(m);
+    std::vector<int64_t> h_rb((size_t)P + 1), h_cb((size_t)P + 1), h_cell_nnz;
     for (int32_t b = 0; b <= P; ++b) {
-        m->h_rb[b] = (int64_t)(((__int128)b * (__int128)m->N) / (__int128)P);
-        m->h_cb[b] = (int64_t)(((__int128)b * (__int128)m->D) / (__int128)P);
+        h_rb[b] = (int64_t)(((__int128)b * (__int128)m->N) / (__int128)P);
+        h_cb[b] = (int64_t)(((__int128)b * (__int128)m->D) / (__int128)P);
     }
     std::vector<float> h_rho((size_t)P);
-    for (int32_t b = 0; b < P; ++b) h_rho[b] = (float)((double)(m->h_rb[b + 1] - m->h_rb[b]) / (double)m->N);
-    FM_TRY(fm_dev_alloc(m, (void**)&m->d_rho, (size_t)P * sizeof(float)));
-    FM_TRY(fm_send(m, m->d_rho, h_rho.data(), (size_t)P * sizeof(float), st));
-    FM_TRY(fm_dev_alloc(m, (void**)&m->d_rb, (size_t)(P + 1) * sizeof(int64_t)));
-    FM_TRY(fm_send(m, m->d_rb, m->h_rb.data(), (size_t)(P + 1) * sizeof(int64_t), st));
-    FM_TRY(fm_ensure_lazy(m, st));
+    for (int32_t b = 0; b < P; ++b) h_rho[b] = (float)((double)(h_rb[b + 1] - h_rb[b]) / (double)m->N);
+    float* d_rho = nullptr;
+    int64_t* d_rb = nullptr;
+    int32_t* d_place = nullptr;
+    FM_TRY(fm_dev_alloc(m, (void**)&d_rho, (size_t)P * sizeof(float)));
+    FM_TRY(fm_send(m, d_rho, h_rho.data(), (size_t)P * sizeof(float), st));
+    FM_TRY(fm_dev_alloc(m, (void**)&d_rb, (size_t)(P + 1) * sizeof(int64_t)));
+    FM_TRY(fm_send(m, d_rb, h_rb.data(), (size_t)(P + 1) * sizeof(int64_t), st));
     if (place != nullptr) {
-        FM_TRY(fm_dev_alloc(m, (void**)&m->d_place, (size_t)m->D * sizeof(int32_t)));
-        FM_TRY(fm_send(m, m->d_place, place, (size_t)m->D * sizeof(int32_t), st));
+        FM_TRY(fm_dev_alloc(m, (void**)&d_place, (size_t)m->D * sizeof(int32_t)));
+        FM_TRY(fm_send(m, d_place, place, (size_t)m->D * sizeof(int32_t), st));
     }
-    FM_TRY(fm_dev_alloc(m, (void**)&m->col_mark, (size_t)m->D * sizeof(int32_t)));
-    FM_HIP(m, hipMemsetAsync(m->col_mark, 0, (size_t)m->D * sizeof(int32_t), st));
 
     StrataSide rows, cols;
-    FM_TRY(build_strata_side(m, true, st, &rows, P));
+    FM_TRY(build_strata_side(m, true, d_place, st, &rows, P));
     FM_TRY(fm_settle(m, st));  // its scratch serves the other side
-    FM_TRY(build_strata_side(m, false, st, &cols, P));
+    FM_TRY(build_strata_side(m, false, d_place, st, &cols, P));
     FM_TRY(fm_settle(m, st));
+
+    // cell table (row block, column block or worker the column started at)
+    if (P <= FM_MAXP_CELLS) {
+        h_cell_nnz.assign((size_t)P * P, 0);
+        if (m->nnz > 0) {
+            int64_t *d_cell = nullptr, *d_off = nullptr;
+            FM_TRY(fm_dev_alloc(m, (void**)&d_cell, (size_t)P * P * sizeof(int64_t)));
+            FM_TRY(fm_dev_alloc(m, (void**)&d_off, (size_t)(P + 1) * sizeof(int64_t)));
+            FM_TRY(fm_send(m, d_off, rows.h_list_off.data(), (size_t)(P + 1) * sizeof(int64_t), st));
+            hipLaunchKernelGGL(k_cell_table, dim3(blocks_for((int64_t)P * P, 256)), dim3(256), 0, st,
+                               (const int32_t*)rows.nz_major, (const int64_t*)rows.nz_beg, (const int64_t*)d_off,
+                               (const int64_t*)d_rb, P, d_cell);
+            FM_HIP(m, hipGetLastError());
+            FM_TRY(fm_read_later(m, h_cell_nnz.data(), d_cell, (size_t)P * P * sizeof(int64_t), st));
+            fm_spend(m, {d_cell, d_off});
+        }
+    }
+    LongIndex strata;
+    FM_TRY(fm_build_long_index(m, cols.nz_beg, cols.nz_major, cols.ind, cols.count, cols.h_list_off, P, &strata, st));
+    FM_TRY(fm_settle(m, st));
+    scope.done = true;
+    m->P = P;
+    m->h_rb = h_rb;
+    m->h_cb = h_cb;
+    m->d_rho = d_rho;
+    m->d_rb = d_rb;
+    m->d_place = d_place;
     m->s_col = rows.ind;
     m->s_val = rows.val;
     // the rows that have an entry in stratum s: its refresh visits only these (a row's entries end
@@ -1476,26 +1537,8 @@ static int partition_impl(fm_matrix* m, int32_t P, const int32_t* place, hipStre
     m->nncol = cols.count;
     m->h_ncol_off = cols.h_list_off;
     m->h_strat_nnz_off = cols.h_ent_off;
-
-    // cell table (row block, column block or worker the column started at)
-    m->h_cell_nnz.clear();
-    if (P <= FM_MAXP_CELLS) {
-        m->h_cell_nnz.assign((size_t)P * P, 0);
-        if (m->nnz > 0) {
-            int64_t *d_cell = nullptr, *d_off = nullptr;
-            FM_TRY(fm_dev_alloc(m, (void**)&d_cell, (size_t)P * P * sizeof(int64_t)));
-            FM_TRY(fm_dev_alloc(m, (void**)&d_off, (size_t)(P + 1) * sizeof(int64_t)));
-            FM_TRY(fm_send(m, d_off, m->h_touch_off.data(), (size_t)(P + 1) * sizeof(int64_t), st));
-            hipLaunchKernelGGL(k_cell_table, dim3(blocks_for((int64_t)P * P, 256)), dim3(256), 0, st,
-                               (const int32_t*)m->s_touched, (const int64_t*)m->s_touched_beg, (const int64_t*)d_off,
-                               (const int64_t*)m->d_rb, P, d_cell);
-            FM_HIP(m, hipGetLastError());
-            FM_TRY(fm_read_later(m, m->h_cell_nnz.data(), d_cell, (size_t)P * P * sizeof(int64_t), st));
-            fm_spend(m, {d_cell, d_off});
-        }
-    }
-    FM_TRY(fm_build_long_index(m, m->s_ncol_beg, m->s_ncol, m->s_row, m->nncol, m->h_ncol_off, P, &m->lstrat, st));
-    FM_TRY(fm_settle(m, st));
+    m->h_cell_nnz = std::move(h_cell_nnz);
+    m->lstrat = strata;
     fm_drop_workspace(m);
     return FM_OK;
 }
@@ -1509,6 +1552,16 @@ int fm_ensure_lazy(fm_matrix* m, hipStream_t st)
     return FM_OK;
 }
 
+static int ensure_marks(fm_matrix* m, hipStream_t st)
+{
+    if (m->col_mark != nullptr) return FM_OK;
+    int32_t* marks = nullptr;
+    FM_TRY(fm_dev_alloc(m, (void**)&marks, (size_t)m->D * sizeof(int32_t)));
+    FM_HIP(m, hipMemsetAsync(marks, 0, (size_t)m->D * sizeof(int32_t), st));  // the callers wait for the stream
+    m->col_mark = marks;
+    return FM_OK;
+}
+
 extern "C" int fm_partition_batches(fm_matrix* m, int32_t B, void* hip_stream)
 {
     if (m == nullptr) return FM_EINVAL;
@@ -1517,24 +1570,30 @@ extern "C" int fm_partition_batches(fm_matrix* m, int32_t B, void* hip_stream)
     if (B < 1 || B > FM_MAXP) return fm_fail(m, FM_EINVAL, "B=%d outside 1..%d", B, FM_MAXP);
     if (m->B != 0) return fm_fail(m, FM_ESTATE, "row batches are already built (B=%d)", m->B);
     if (m->N < 1 || m->D < 1) return fm_fail(m, FM_EINVAL, "cannot split an empty matrix");
-    fm_unsettled(m);
-    m->B = B;
-    m->h_bb.resize(B + 1);
-    std::vector<float> h_rho((size_t)B);
-    for (int32_t b = 0; b <= B; ++b) m->h_bb[b] = (int64_t)(((__int128)b * (__int128)m->N) / (__int128)B);
-    for (int32_t b = 0; b < B; ++b) h_rho[b] = (float)((double)(m->h_bb[b + 1] - m->h_bb[b]) / (double)m->N);
-    FM_TRY(fm_dev_alloc(m, (void**)&m->d_brho, (size_t)B * sizeof(float)));
-    FM_TRY(fm_send(m, m->d_brho, h_rho.data(), (size_t)B * sizeof(float), st));
-    FM_TRY(fm_dev_alloc(m, (void**)&m->d_bb, (size_t)(B + 1) * sizeof(int64_t)));
-    FM_TRY(fm_send(m, m->d_bb, m->h_bb.data(), (size_t)(B + 1) * sizeof(int64_t), st));
     FM_TRY(fm_ensure_lazy(m, st));
-    if (m->col_mark == nullptr) {
-        FM_TRY(fm_dev_alloc(m, (void**)&m->col_mark, (size_t)m->D * sizeof(int32_t)));
-        FM_HIP(m, hipMemsetAsync(m->col_mark, 0, (size_t)m->D * sizeof(int32_t), st));
-    }
+    FM_TRY(ensure_marks(m, st));
+    BuildScope scope(m);
+    std::vector<int64_t> h_bb((size_t)B + 1);
+    std::vector<float> h_rho((size_t)B);
+    for (int32_t b = 0; b <= B; ++b) h_bb[b] = (int64_t)(((__int128)b * (__int128)m->N) / (__int128)B);
+    for (int32_t b = 0; b < B; ++b) h_rho[b] = (float)((double)(h_bb[b + 1] - h_bb[b]) / (double)m->N);
+    float* d_rho = nullptr;
+    int64_t* d_bb = nullptr;
+    FM_TRY(fm_dev_alloc(m, (void**)&d_rho, (size_t)B * sizeof(float)));
+    FM_TRY(fm_send(m, d_rho, h_rho.data(), (size_t)B * sizeof(float), st));
+    FM_TRY(fm_dev_alloc(m, (void**)&d_bb, (size_t)(B + 1) * sizeof(int64_t)));
+    FM_TRY(fm_send(m, d_bb, h_bb.data(), (size_t)(B + 1) * sizeof(int64_t), st));
     StrataSide cols;
-    FM_TRY(build_strata_side(m, false, st, &cols, B, true));
+    FM_TRY(build_strata_side(m, false, nullptr, st, &cols, B, true));
     FM_TRY(fm_settle(m, st));
+    LongIndex batches;
+    FM_TRY(fm_build_long_index(m, cols.nz_beg, cols.nz_major, cols.ind, cols.count, cols.h_list_off, B, &batches, st));
+    FM_TRY(fm_settle(m, st));
+    scope.done = true;
+    m->B = B;
+    m->h_bb = h_bb;
+    m->d_brho = d_rho;
+    m->d_bb = d_bb;
     m->b_row = cols.ind;
     m->b_cval = cols.val;
     m->b_ncol = cols.nz_major;
@@ -1542,8 +1601,7 @@ extern "C" int fm_partition_batches(fm_matrix* m, int32_t B, void* hip_stream)
     m->nbcol = cols.count;
     m->h_bcol_off = cols.h_list_off;
     m->h_batch_nnz_off = cols.h_ent_off;
-    FM_TRY(fm_build_long_index(m, m->b_ncol_beg, m->b_ncol, m->b_row, m->nbcol, m->h_bcol_off, B, &m->lbatch, st));
-    FM_TRY(fm_settle(m, st));
+    m->lbatch = batches;
     fm_drop_workspace(m);
     return FM_OK;
 }
