@@ -655,8 +655,9 @@ static int ensure_ws(fm_matrix* m, int32_t K)
     // the dense kernels may be switched on and off: room for both paths
     const int64_t chunks = fm_dense_fits(m, K) ? fm_dense_chunks(m->N, m->D, K) : 0;
     const int64_t dense_items = chunks * 2;  // a batch of few rows has two to a column and workgroup
-    const int64_t items = std::max<int64_t>(std::max<int64_t>(m->lfull.nitems, m->lstrat.nitems),
-                                            std::max<int64_t>(m->lbatch.nitems, m->D * dense_items));
+    int64_t items = std::max<int64_t>(m->lfull.nitems, m->D * dense_items);
+    for (const LongIndex* li : {&m->lstrat, &m->lbatch})
+        for (size_t s = 0; s + 1 < li->h_item_off.size(); ++s) items = std::max(items, li->h_item_off[s + 1] - li->h_item_off[s]);
     FM_TRY(fm_dev_alloc(m, (void**)&m->part,
                         (size_t)std::max<int64_t>(items, 1) * (size_t)fm_part_stride(K) * sizeof(float)));
     FM_TRY(fm_dev_alloc(m, (void**)&m->row_part, (size_t)std::max<int64_t>(std::max<int64_t>(fm_rows_max_grid(m, m->N, K), chunks), 1) * 2 * sizeof(float)));
@@ -679,6 +680,7 @@ static void fill_long(const fm_matrix* m, ColArgs& A, const LongIndex& li, int32
     const int64_t i0 = strat ? li.h_item_off[s] : 0, i1 = strat ? li.h_item_off[s + 1] : li.nitems;
     A.nlong = l1 - l0;
     A.nitems = i1 - i0;
+    A.part = m->part - i0 * A.ps;  // this launch's items have the first rows: one stratum or batch is in flight at a time
     A.long_base = l0;
     A.item_base = i0;
     A.long_col = li.long_col;

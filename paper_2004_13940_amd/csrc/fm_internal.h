@@ -483,7 +483,7 @@ struct ColArgs {
     const int32_t* vlong;          // nullable: long columns finished by a whole workgroup
     int64_t nvlong;
     int32_t vlong_items;           // threshold that defines vlong
-    float* part;                    // rows [acc | gw | s2 | pad] of ps floats, indexed by absolute item id
+    float* part;                    // rows [acc | gw | s2 | pad] of ps floats, indexed by absolute item id: the rows from item_base on are there
     int64_t ps;
 };
 int fm_launch_cols(fm_matrix* m, const ColArgs& A, bool update, hipStream_t st);

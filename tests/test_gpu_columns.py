@@ -908,3 +908,41 @@ def test_gradient_leaves_what_it_was_given_in_the_aggregates(N, D, row, K, optio
         with pytest.raises(B.FMError):
             m.fm_get_aux(K, a=gotr)
     m.close()
+
+
+def test_partial_sums_of_one_stratum_or_batch_are_held_at_a_time():
+    """2,000 columns times strata of two items each where all columns have 65,000 as a whole: the workspace has rows for the
+    larger of one stratum's and the whole matrix's items, and strata that reuse the rows step like the oracle's."""
+    import torch
+    from types import SimpleNamespace
+    from paper_2004_13940_amd import binding as B
+    rng = np.random.default_rng(8500)
+    N, D, K, row, P = 200_000, 1_000, 64, 20, 96  # 2,083 rows to a block: not summed whole; 41 entries to a column and stratum
+    col = (np.arange(row) * (D // row) + rng.integers(0, D // row, (N, row))).astype(np.int32).ravel()
+    wl = SimpleNamespace(N=N, D=D, K=K, P=P, rowptr=np.arange(N + 1, dtype=np.int64) * row, col=col,
+                         val=rng.standard_normal(N * row).astype(np.float32),
+                         y=np.where(rng.random(N) < 0.5, 1.0, -1.0).astype(np.float32), w0=np.float32(0.1),
+                         w=(rng.standard_normal(D) * 0.2).astype(np.float32),
+                         V=(rng.standard_normal((D, K)) * 0.02).astype(np.float32), loss=O.LOSS_LOGISTIC,
+                         lambda_w=0.01, lambda_v=0.02, eta=0.5, loss_scale=1.0 / N, update_w0=1)
+    m = B.Matrix(N, D, wl.rowptr, col, wl.val)
+    m.fm_build_csc()
+    m.fm_partition(P)
+    m.fm_partition_batches(P)
+    dev = (*dev_params(wl.w0, wl.w, wl.V), to_dev(wl.y))
+    p = B.make_params(K, wl.loss, wl.lambda_w, wl.lambda_v, wl.eta, wl.loss_scale, 1)
+    X = O.make_matrix(N, D, wl.rowptr, col, wl.val)
+    torch.cuda.synchronize()
+    B.fm_trim()
+    free = torch.cuda.mem_get_info()[0]
+    print("partial sums of one stratum", flush=True)
+    host = run_stratified_epochs(B, wl, m, p, X, dev, (float(wl.w0), wl.w, wl.V), 1)
+    held = free - torch.cuda.mem_get_info()[0]
+    rows = N * (K + 3) * 4 + (row * N // 64 + D) * 96 * 4  # aggregates, and 96 floats for each item of the whole matrix
+    assert held <= rows + (16 << 20), (held, rows)  # rows for all strata would be 190,000 x 384 bytes
+    m.fm_minibatch_epoch(p, dev[3], *dev[:3])
+    host = O.minibatch_epoch(X, wl.y, *host, B=P, update_w0=True, reg_share=True, loss=wl.loss, s=wl.loss_scale,
+                             lambda_w=wl.lambda_w, lambda_v=wl.lambda_v, eta=wl.eta)[:3]
+    assert_close(dev[1].cpu().numpy(), host[1], "w after batches")
+    assert_close(dev[2].cpu().numpy().reshape(D, K), host[2], "V after batches")
+    m.close()
