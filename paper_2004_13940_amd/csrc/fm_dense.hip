@@ -123,7 +123,6 @@ __global__ __launch_bounds__(FM_BLOCK, dense_per_cu(DB, KB)) void k_dense(const 
             fm_reg_pair<FM_BLOCK>(A.w, A.D, A.V, A.D * (int64_t)A.K, A.regs, sh);
         return;
     }
-    if (FORWARD && A.aux_rows != nullptr && b == 0 && threadIdx.x == 0) *A.aux_rows = A.whole_rows;
     const int D = (int)A.D, K = A.K, gs = (int)A.gs;
     const int lane = threadIdx.x & (FM_WAVE - 1);
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / FM_WAVE);  // uniform, and so is all that follows from it
@@ -422,6 +421,7 @@ __global__ __launch_bounds__(FM_BLOCK, dense_per_cu(DB, KB)) void k_dense(const 
         }
     }
     if constexpr (FORWARD) {
+        if (b == 0 && threadIdx.x == 0 && A.aux_rows != nullptr) *A.aux_rows = A.whole_rows;
         if (want) {
             sum_lr = fm_group_sum<32>(sum_lr);
             if constexpr (!GRADIENT) sum_es = fm_group_sum<32>(sum_es);
