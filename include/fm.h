@@ -282,11 +282,12 @@ int fm_set_option(fm_matrix* m, int32_t option /*fm_option*/, int32_t value);
  * must be set before fm_build_csc (FM_ESTATE afterwards).  A value <= 0 keeps the current one.
  *   seg              entries per work item of a long column        (default 32 to 256, by the entries of
  *                    the matrix, 32 or 48 by those of a stratum or batch)
- *   panel            rows per panel of the L2-blocked traversal of heavy columns (default 32768)
+ *   panel            rows per panel, at most, of the L2-blocked traversal of heavy columns (default 32768)
  *   heavy_per_panel  a column is heavy if it averages this many entries per panel (default 16)
  *   vlong            columns with more items are summed by a whole workgroup      (default 128)
- *   min_panels       matrices with fewer panels use plain segments only (default: 24, and matrices of
- *                    fewer than 64,513 rows use plain segments)
+ *   min_panels       panels are halved until there are so many, and matrices with fewer use plain segments
+ *                    only (default: the same number of panels to each of the eight XCDs, at least three, and
+ *                    plain segments for matrices of fewer than 64,513 rows)
  * Results do not depend on these values beyond fp32 rounding. */
 int fm_set_tuning(fm_matrix* m, int32_t seg, int32_t panel, int32_t heavy_per_panel, int32_t vlong,
                   int32_t min_panels);

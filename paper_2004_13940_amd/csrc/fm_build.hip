@@ -1241,18 +1241,18 @@ static int build_full_index(fm_matrix* m, const FmTune& T, LongIndex* out, hipSt
                        (int64_t*)nullptr);
     FM_HIP(m, hipGetLastError());
     // 2. items per long column, then their first ids
-    // Panels shrink (down to 1024 rows) so that a matrix of moderate height still has
-    // min_panels of them to spread over the XCD lists; the density that makes a column
-    // heavy (heavy_per_panel / panel) is kept.
-    const int64_t min_panels = T.min_panels > 0 ? T.min_panels : FM_MIN_PANELS;
+    // With a number of panels asked for, they shrink (down to 1024 rows) until there are as many.
     int64_t panel = T.panel;
-    while (panel > 1024 && (m->N + panel - 1) / panel < min_panels) panel /= 2;
+    if (T.min_panels > 0)
+        while (panel > 1024 && (m->N + panel - 1) / panel < T.min_panels) panel /= 2;
+    else
+        panel = fm_panel_rows(m->N, T.panel);
     const int64_t npanels = (m->N + panel - 1) / panel;
+    const bool in_panels = T.min_panels > 0 ? npanels >= T.min_panels : m->N >= FM_PANEL_ROWS;
+    // the density that makes a column heavy does not depend on how tall the panels are
     const double heavy_density = (double)T.heavy_per_panel / (double)T.panel;
-    // the panel order pays off only when there are many more panels than XCDs
-    const int64_t heavy_min = npanels >= min_panels && (T.min_panels > 0 || m->N >= FM_PANEL_ROWS)
-                                  ? std::max<int64_t>((int64_t)(heavy_density * (double)m->N) + 1, (int64_t)T.seg + 1)
-                                  : INT64_MAX;
+    const int64_t heavy_min =
+        in_panels ? std::max<int64_t>((int64_t)(heavy_density * (double)m->N) + 1, (int64_t)T.seg + 1) : INT64_MAX;
     const int64_t maxpos = (npanels + FM_XCDS - 1) / FM_XCDS;
     // dense-ish columns (at least tile_min entries per row tile on average) go to the LDS-staged kernel
     const int64_t tile = T.tile;

@@ -11,6 +11,7 @@
 #include <vector>
 
 #include "fm.h"
+#include "fm_panels.h"
 
 constexpr int FM_WAVE = 64;
 constexpr int FM_BLOCK = 256;             // threads per workgroup of the pass kernels
@@ -18,14 +19,7 @@ constexpr int FM_WAVES = FM_BLOCK / FM_WAVE;
 constexpr int FM_MAXP = 1 << 20;       // row blocks / batches
 constexpr int FM_MAXP_CELLS = 4096;     // the P x P table of entries per cell is only kept up to this P
 constexpr int64_t FM_ENTRY_PAD = 16;      // entries by which the arrays of entries (index, value) are longer than they need be
-constexpr int FM_XCDS = 8;                // L2 domains; workgroup b runs on XCD b % 8
-// Panels are halved until a matrix has this many, three to an XCD.  Fewer and taller ones make longer items, and with that
-// fewer partial sums; what they bring is gone once an XCD's panel is far beyond its L2 or the lists get uneven.  Gradients in
-// us, LDS tiles off, with at least 64 / 32 / 24 / 16 panels: hashed rows, K = 64, 4e5 rows 1475 / 1341 / 1341 / -, 2.5e5
-// 949 / 855 / 826 / 832, 7e4 267 / 246 / 246 / 245; text-like 2e5 rows, K = 64 392 / 335 / 303 / -, 1.4e5, K = 16
-// 163 / 145 / 145 / 141; click-style 1.8e5 rows, K = 16 110 / 103 / 103 / 102.
-constexpr int FM_MIN_PANELS = 24;
-// Below, the aggregate rows of up to 128 bytes stay in the caches in any order (7e4 text-like rows, in panels / without, K = 8
+// Panels are for matrices of so many rows; below, the aggregate rows of up to 128 bytes stay in the caches in any order (7e4 text-like rows, in panels / without, K = 8
 // 61 / 53, K = 64 108 / 121; 5e4 rows, K = 16 44 / 35, K = 64 72 / 82; 1e5 rows, K = 16 56 / 59, K = 64 95 / 118).
 constexpr int64_t FM_PANEL_ROWS = 63 * 1024 + 1;
 
@@ -38,8 +32,8 @@ struct FmTune {
     int vlong = 128;           // columns with more items than this are finished by a whole workgroup (128 against 512,
                                // items of 128: mini-batch click epoch K=32 1.63 and 1.67 ms, stratified table K=64 934
                                // and 959 us, hashed epoch K=64 2.50 and 2.48 ms)
-    int min_panels = 0;        // the panel order is used only for matrices with at least this many panels; 0: FM_MIN_PANELS,
-                               // and only from FM_PANEL_ROWS rows on
+    int min_panels = 0;        // set: panels are halved until there are so many, and matrices with fewer have none; 0: see
+                               // fm_panel_rows, from FM_PANEL_ROWS rows on
     int tile = 0;              // rows per LDS tile of the kernel for dense-ish columns
     int tile_min = -1;         // a column is dense-ish if it averages this many entries per tile (0: none)
     int tile_seg = 0;          // entries per item inside a tile
