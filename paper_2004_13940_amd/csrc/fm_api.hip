@@ -693,6 +693,8 @@ static void fill_long(const fm_matrix* m, ColArgs& A, const LongIndex& li, int32
     A.ord_len = li.ord_len != nullptr ? li.ord_len + i0 : nullptr;
     for (int x = 0; x <= FM_XCDS; ++x) A.list_off[x] = li.list_off[x];
     for (int x = 0; x < FM_XCDS; ++x) A.list_mid[x] = li.list_mid[x];
+    // a single block or batch steps with the bits of the whole matrix
+    A.long_runs = m->lfull.in_panels && (!strat || A.P == 1) ? 1 : 0;
     A.tile_rows = li.tile_rows;
     A.ntiles = strat ? 0 : li.ntiles;
     A.tile_ptr = li.tile_ptr;

@@ -1249,6 +1249,7 @@ static int build_full_index(fm_matrix* m, const FmTune& T, LongIndex* out, hipSt
         panel = fm_panel_rows(m->N, T.panel);
     const int64_t npanels = (m->N + panel - 1) / panel;
     const bool in_panels = T.min_panels > 0 ? npanels >= T.min_panels : m->N >= FM_PANEL_ROWS;
+    out->in_panels = in_panels;
     // the density that makes a column heavy does not depend on how tall the panels are
     const double heavy_density = (double)T.heavy_per_panel / (double)T.panel;
     const int64_t heavy_min =

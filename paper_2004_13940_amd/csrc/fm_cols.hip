@@ -20,12 +20,14 @@
 namespace {
 
 // The multiplier of an entry of planar aggregates: x r, with r an array of its own.
+template <class SUM>
 struct OwnMultiplier {
     struct T {
         float r[1];
     };
     FmOwnArray<1> r;
-    float gw, s2;  // this lane's entries
+    SUM gw, s2;            // this lane's entries
+    float round_w, round_2;  // in fp64: those of the round
     template <int ADDR>
     __device__ __forceinline__ T load(int i) const
     {
@@ -36,27 +38,54 @@ struct OwnMultiplier {
     __device__ __forceinline__ float use(T t, float x)
     {
         const float xr = x * t.r[0];
-        gw += xr;
-        s2 += x * xr;
+        if constexpr (std::is_same_v<SUM, double>) {
+            round_w += xr;
+            round_2 += x * xr;
+        } else {
+            gw += xr;
+            s2 += x * xr;
+        }
         return xr;
+    }
+    __device__ __forceinline__ void end_round()
+    {
+        if constexpr (std::is_same_v<SUM, double>) {
+            gw += (double)round_w;
+            s2 += (double)round_2;
+            round_w = round_2 = 0.f;
+        }
     }
 };
 
+// How a run is added up.  Where columns are cut at panels a run is up to 256 entries long, and one chain of fp32 additions rounds
+// each at the size of all before it: a few entries (eight; 16 of packed rows, for the registers; four in wide groups) are added
+// in fp32, these sums in fp64, and the run is rounded once.  Sums of one sign over columns of 2e5 rows, 0.5 % and 5 % dense, items
+// of 128: share of results that are not the nearest float, one chain 0.27 and 0.14, fp32 sums of 16 0.14 and 0.05, now 0.08
+// and 0.02 (packed 0.13 and 0.04).  Costs 0 to 2 % of an epoch (text-like 2e5 rows, K = 16 181 -> 183 us; hashed 4e5 rows, K = 64 2210
+// -> 2240; click-style 1e7 rows nothing).  Elsewhere runs keep to fp32: those of strata and batches are of up to 48 entries unless
+// the caller sets their length (click-style 1.5e6 rows, K = 20, 32 strata 5802, with fp64 5932; 3e5 rows, K = 16 782, 796), those
+// of short matrices as long as the entries leave work for all compute units (2e4 text-like rows, K = 20 39.9, 41.0).
+enum { FM_LONG_RUNS = 0, FM_SHORT_RUNS = 1 };
+
 // Sums of the run of `len` entries from beg on: acc, this lane's latent slice; gw, s2 on every lane of the group.  All
 // groups of the wavefront call it together.
-template <int VEC, int L, int PACKED, int ADDR>
+template <int VEC, int L, int PACKED, int ADDR, int RUNS>
 __device__ __forceinline__ void walk_column(const ColArgs& A, int64_t beg, int len, int sub, int kbase, bool kact,
                                             float (&acc)[VEC], float& gw, float& s2)
 {
+    using Sum = std::conditional_t<RUNS == FM_SHORT_RUNS, float, double>;
+    Sum sum[VEC] = {}, sum_w = 0, sum_2 = 0;
     if constexpr (PACKED == FM_PACKED_LANE) {
         // lanes past the latent ones, at least the last of the group, read the scalars [r | a | q | pad]
-        fm_walk<VEC, L, FM_WALK_PACKED, ADDR>(A.row, A.val, beg, len, A.G, A.gs, sub, kact ? kbase : A.K, acc, gw, s2,
+        fm_walk<VEC, L, FM_WALK_PACKED, ADDR>(A.row, A.val, beg, len, A.G, A.gs, sub, kact ? kbase : A.K, sum, sum_w, sum_2,
                                               FmOwnNone());
+        gw = (float)sum_w;
+        s2 = (float)sum_2;
     } else if constexpr (L >= FM_WIDE_GROUP) {
         const float* __restrict__ r = A.r;
         const int64_t rs = A.rs;
         float g = 0.f, s = 0.f;
-        fm_walk_wide<VEC, L>(A.row, A.val, beg, beg + len, A.G, A.gs, sub, kact ? kbase : 0, acc, [&](int i, float x) {
+        fm_walk_wide<VEC, L>(A.row, A.val, beg, beg + len, A.G, A.gs, sub, kact ? kbase : 0, sum, [&](int i, float x) {
             const float xr = x * r[(int64_t)i * rs];
             g += xr;
             s += x * xr;
@@ -65,25 +94,26 @@ __device__ __forceinline__ void walk_column(const ColArgs& A, int64_t beg, int l
         gw = fm_group_sum<L>(g);
         s2 = fm_group_sum<L>(s);
     } else {
-        OwnMultiplier own{FmOwnArray<1>(A.r, A.rs), 0.f, 0.f};
-        float unused = 0.f;
-        fm_walk<VEC, L, FM_WALK_SUM, ADDR>(A.row, A.val, beg, len, A.G, A.gs, sub, kact ? kbase : 0, acc, unused, unused, own);
-        gw = fm_group_sum<L>(own.gw);
-        s2 = fm_group_sum<L>(own.s2);
+        OwnMultiplier<Sum> own{FmOwnArray<1>(A.r, A.rs), 0, 0, 0.f, 0.f};
+        fm_walk<VEC, L, FM_WALK_SUM, ADDR>(A.row, A.val, beg, len, A.G, A.gs, sub, kact ? kbase : 0, sum, sum_w, sum_2, own);
+        gw = fm_group_sum<L>((float)own.gw);
+        s2 = fm_group_sum<L>((float)own.s2);
     }
+#pragma unroll
+    for (int z = 0; z < VEC; ++z) acc[z] = (float)sum[z];
 }
 
 // once: the gathered rows are not used again soon
-template <int VEC, int L, int PACKED>
+template <int VEC, int L, int PACKED, int RUNS>
 __device__ __forceinline__ void accumulate_entries(const ColArgs& A, bool once, int64_t beg, int len, int sub, int kbase,
                                                    bool kact, float (&acc)[VEC], float& gw, float& s2)
 {
     if (L >= FM_WIDE_GROUP || A.big)
-        walk_column<VEC, L, PACKED, FM_ADDR_PTR>(A, beg, len, sub, kbase, kact, acc, gw, s2);
+        walk_column<VEC, L, PACKED, FM_ADDR_PTR, RUNS>(A, beg, len, sub, kbase, kact, acc, gw, s2);
     else if (once && A.nt)
-        walk_column<VEC, L, PACKED, FM_ADDR_BUF_NT>(A, beg, len, sub, kbase, kact, acc, gw, s2);
+        walk_column<VEC, L, PACKED, FM_ADDR_BUF_NT, RUNS>(A, beg, len, sub, kbase, kact, acc, gw, s2);
     else
-        walk_column<VEC, L, PACKED, FM_ADDR_BUF>(A, beg, len, sub, kbase, kact, acc, gw, s2);
+        walk_column<VEC, L, PACKED, FM_ADDR_BUF, RUNS>(A, beg, len, sub, kbase, kact, acc, gw, s2);
 }
 
 // The class of column j that decides which row block it meets in which stratum: its column block in
@@ -273,13 +303,9 @@ __device__ __forceinline__ void store_partial(const ColArgs& A, int64_t it, int 
 // With an order array, workgroup b takes its items from list b % FM_XCDS (the XCD it runs on).  Items of strata and batches are
 // in row order; with xcd_runs every XCD takes FM_RUN_BLOCKS workgroups of that order in a run, and the rows and multipliers
 // that the items of a run share are asked for by one L2.
-// FEW: four wavefronts to a SIMD and not the five that its registers leave room for, by naming a register that nothing uses
-// (LDS, the other means, is what k_cols_tile beside it lives on).  The items in panel order then have fewer panels' rows in
-// flight and find more of them in the L2: see few_wavefronts.
-template <int VEC, int L, bool UPDATE, int PACKED, bool FEW = false>
-__global__ __launch_bounds__(FM_BLOCK, L >= FM_WIDE_GROUP ? 8 : 1) void k_cols(const ColArgs A)
+template <int VEC, int L, bool UPDATE, int PACKED, int RUNS>
+__device__ __forceinline__ void cols_block(const ColArgs& A)
 {
-    if constexpr (FEW) asm volatile("" ::: "v103");
     constexpr int R = FM_WAVE / L;
     const int lane = threadIdx.x & (FM_WAVE - 1);
     const int wave = threadIdx.x / FM_WAVE;
@@ -347,12 +373,37 @@ __global__ __launch_bounds__(FM_BLOCK, L >= FM_WIDE_GROUP ? 8 : 1) void k_cols(c
         else
             len = 0;
     }
-    accumulate_entries<VEC, L, PACKED>(A, once, beg, len, sub, kbase, kact, acc, gw, s2);
+    accumulate_entries<VEC, L, PACKED, RUNS>(A, once, beg, len, sub, kbase, kact, acc, gw, s2);
     if (id < 0) return;
     if (items)
         store_partial<VEC, L>(A, id, sub, kbase, kact, acc, gw, s2);
     else
         finish_column<VEC, L, UPDATE>(A, id, sub, kbase, kact, acc, gw, s2, c);
+}
+
+// Wavefronts to a SIMD that the compiler must leave room for, where it would not by itself with the sums in fp64 and does
+// without spilling.
+constexpr int cols_waves(int vec, int l, int packed, bool update, bool few)
+{
+    if (l >= FM_WIDE_GROUP) return 8;
+    return vec == 4 && !few && ((packed == FM_PLANAR && l == 4) || (packed == FM_PACKED_LANE && l == 8 && update)) ? 5 : 1;
+}
+
+// FEW: four wavefronts to a SIMD and not the five that its registers leave room for, by naming a register that nothing uses
+// (LDS, the other means, is what k_cols_tile beside it lives on).  The items in panel order then have fewer panels' rows in
+// flight and find more of them in the L2: see few_wavefronts.
+template <int VEC, int L, bool UPDATE, int PACKED, bool FEW = false>
+__global__ __launch_bounds__(FM_BLOCK, cols_waves(VEC, L, PACKED, UPDATE, FEW)) void k_cols(const ColArgs A)
+{
+    if constexpr (FEW) asm volatile("" ::: "v103");
+    cols_block<VEC, L, UPDATE, PACKED, FM_LONG_RUNS>(A);
+}
+
+// Strata, batches and matrices without panels.
+template <int VEC, int L, bool UPDATE, int PACKED>
+__global__ __launch_bounds__(FM_BLOCK, L >= FM_WIDE_GROUP ? 8 : 1) void k_cols_part(const ColArgs A)
+{
+    cols_block<VEC, L, UPDATE, PACKED, FM_SHORT_RUNS>(A);
 }
 
 // Columns with nothing stored (in this matrix or stratum) only feel the regulariser; one group
@@ -762,7 +813,7 @@ __global__ __launch_bounds__(FM_BLOCK) void k_cols_whole(const ColArgs A)
 #pragma unroll
     for (int z = 0; z < VEC; ++z) acc[z] = 0.f;
     float gw = 0.f, s2 = 0.f;
-    accumulate_entries<VEC, L, PACKED>(A, false, beg, len, sub, kbase, kact, acc, gw, s2);
+    accumulate_entries<VEC, L, PACKED, FM_SHORT_RUNS>(A, false, beg, len, sub, kbase, kact, acc, gw, s2);
     if (whole) {
         double accd[VEC];
 #pragma unroll
@@ -1008,10 +1059,12 @@ int launch_cols_t(fm_matrix* m, const ColArgs& A, bool update, hipStream_t st)
             ProfScope ps(m, q, FMK_COLS);
             auto go = [&](auto few) {
                 constexpr bool F = decltype(few)::value;
-                if (update)
-                    hipLaunchKernelGGL((k_cols<VEC, L, true, PACKED, F>), dim3((unsigned)grid), dim3(FM_BLOCK), 0, q, B);
-                else
-                    hipLaunchKernelGGL((k_cols<VEC, L, false, PACKED, F>), dim3((unsigned)grid), dim3(FM_BLOCK), 0, q, B);
+                auto run = [&](auto kernel) { hipLaunchKernelGGL(kernel, dim3((unsigned)grid), dim3(FM_BLOCK), 0, q, B); };
+                if (F || B.long_runs) {
+                    if (update) run(&k_cols<VEC, L, true, PACKED, F>); else run(&k_cols<VEC, L, false, PACKED, F>);
+                } else {
+                    if (update) run(&k_cols_part<VEC, L, true, PACKED>); else run(&k_cols_part<VEC, L, false, PACKED>);
+                }
             };
             if constexpr (VEC == 4 && L == 8) {
                 if (few_wavefronts(B))

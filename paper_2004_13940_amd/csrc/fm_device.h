@@ -169,6 +169,12 @@ __device__ __forceinline__ int32_t fm_block_of(int64_t i, int64_t n, int32_t P)
     return b;
 }
 
+template <bool FIRST, class A, class B>
+__device__ __forceinline__ auto& fm_pick(A& a, B& b)
+{
+    if constexpr (FIRST) return a; else return b;
+}
+
 // Compile-time loop: f(std::integral_constant<int, I>) for I = 0..N-1.
 template <int I, int N, class F>
 __device__ __forceinline__ void fm_static_for(F&& f)
@@ -266,10 +272,10 @@ constexpr int FM_WIDE_GROUP = 16;
 // four, or odd from 9 on).  A group walks its run [beg,end) L entries to a round, four gathers at a time, at most 64
 // registers in all.  Latency-bound: the indices of the next round are on their way during this one, and the gathers of a
 // round are issued before the multipliers (own's own loads) are waited for.
-template <int VEC, int L, class Own>
+template <int VEC, int L, class Own, class SUM>
 __device__ __forceinline__ void fm_walk_wide(const int32_t* __restrict__ idx, const float* __restrict__ val, int64_t beg,
                                              int64_t end, const float* __restrict__ src, int64_t stride, int sub, int kb,
-                                             float (&acc)[VEC], Own&& own)
+                                             SUM (&acc)[VEC], Own&& own)
 {
     const int len = (int)(end - beg);
     if (len <= 0) return;
@@ -296,12 +302,18 @@ __device__ __forceinline__ void fm_walk_wide(const int32_t* __restrict__ idx, co
                 const int it = __shfl(i, t0 + u < nv ? t0 + u : nv - 1, L);
                 fm_load_vec<VEC>(sp + (int64_t)it * stride, g[u]);
             }
+            constexpr bool APART = std::is_same_v<SUM, double>;  // four entries in fp32, these sums in fp64
+            float sum[VEC];
+#pragma unroll
+            for (int z = 0; z < VEC; ++z) sum[z] = APART ? 0.f : (float)acc[z];
 #pragma unroll
             for (int u = 0; u < 4; ++u) {
                 const float m = __shfl(x, t0 + u, L);  // 0 where the run is over
 #pragma unroll
-                for (int z = 0; z < VEC; ++z) acc[z] += m * g[u][z];
+                for (int z = 0; z < VEC; ++z) sum[z] += m * g[u][z];
             }
+#pragma unroll
+            for (int z = 0; z < VEC; ++z) acc[z] = APART ? acc[z] + (SUM)sum[z] : (SUM)sum[z];
         }
         if (at >= len) break;
     }
@@ -340,12 +352,13 @@ enum { FM_WALK_SUM = 0, FM_WALK_PACKED = 1, FM_WALK_SCORE = 2 };
 
 // Per-entry work of the lane that holds the entry, besides the gathered row: load() asks for what the entry's index names
 // (a slot without an entry, index < 0, gets zeros), use() takes it and returns the multiplier.  Two steps, so that what it
-// asks for and the gathers of the round are on their way together.
+// asks for and the gathers of the round are on their way together.  end_round() after the entries that a lane holds of a round.
 struct FmOwnNone {
     struct T {};
     template <int ADDR>
     __device__ __forceinline__ T load(int) const { return T(); }
     __device__ __forceinline__ float use(T, float x) const { return x; }
+    __device__ __forceinline__ void end_round() const {}
 };
 
 // An array of W floats per index, read by load(): through a buffer descriptor, or with 64-bit addresses.
@@ -458,6 +471,17 @@ __device__ __forceinline__ void fm_slot_sums(const float (&mu)[U], const float (
     });
 }
 
+// Sums of the run in fp64: those of the batch in fp32, from zero, then added.
+template <int VEC, int L, int KIND, int S, int S0, int U>
+__device__ __forceinline__ void fm_slot_sums(const float (&mu)[U], const float (&g)[S][VEC], double (&acc)[VEC], double&, double&)
+{
+    static_assert(KIND == FM_WALK_SUM);
+    float a[VEC] = {}, b = 0.f, c = 0.f;
+    fm_slot_sums<VEC, L, KIND, S, S0>(mu, g, a, b, c);
+#pragma unroll
+    for (int z = 0; z < VEC; ++z) acc[z] += (double)a[z];
+}
+
 // The inner loop of the kernels for groups of up to eight lanes.  Every group of L lanes walks
 // its own run [beg,end) of one row or column, all groups of the wavefront in step: a round takes the next C entries of
 // every run, in batches of SMAX or four slots by the longest run left, so the choice is a scalar branch, and a group whose
@@ -474,13 +498,15 @@ __device__ __forceinline__ void fm_slot_sums(const float (&mu)[U], const float (
 // The refresh of a stratum, whose runs are mostly shorter than a round, takes rounds of four or eight in fours.
 // kb: offset of the lane's slice in a row, valid for every lane.
 // FIRST: see fm_slot_loads.
+// SUM: float, or double for long runs (see FM_SHORT_RUNS).
 // SP > 1: SP groups share a run, group `part` of them takes every SP-th stretch of C entries.
-template <int VEC, int L, int KIND, int ADDR, int C = 16, int SMAX = 8, int SP = 1, bool FIRST = false, class Own, class SRC>
+template <int VEC, int L, int KIND, int ADDR, int C = 16, int SMAX = 8, int SP = 1, bool FIRST = false, class Own, class SRC, class SUM>
 __device__ __forceinline__ void fm_walk(const int32_t* __restrict__ idx, const float* __restrict__ val, int64_t beg,
                                         int len, const SRC* __restrict__ src, int64_t stride, int sub, int kb,
-                                        float (&acc)[VEC], float& gw, float& s2, Own&& own, int part = 0)
+                                        SUM (&acc)[VEC], SUM& gw, SUM& s2, Own&& own, int part = 0)
 {
     constexpr int U = C / L;
+    constexpr bool APART = std::is_same_v<SUM, double> && KIND == FM_WALK_PACKED;
     static_assert(L < FM_WIDE_GROUP && C % L == 0 && ((SMAX == 8 && C == 16) || (SMAX == 4 && (C == 4 || C == 8))),
                   "rounds of whole batches");
     const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<SRC*>(src), 0, (int)FM_BUF_NONE, 0x20000);
@@ -531,8 +557,13 @@ __device__ __forceinline__ void fm_walk(const int32_t* __restrict__ idx, const f
         auto multipliers = [&] {
 #pragma unroll
             for (int u = 0; u < U; ++u) mu[u] = own.use(pre[u], mu[u]);
+            own.end_round();
         };
         if (at + part * C < len) {
+            [[maybe_unused]] float a[VEC] = {}, a_w = 0.f, a_2 = 0.f;  // packed rows: of the round
+            auto& to = fm_pick<APART>(a, acc);
+            auto& to_w = fm_pick<APART>(a_w, gw);
+            auto& to_2 = fm_pick<APART>(a_2, s2);
             bool done = false;
             if constexpr (SMAX == 8) {
                 if (left > 4) {
@@ -540,10 +571,10 @@ __device__ __forceinline__ void fm_walk(const int32_t* __restrict__ idx, const f
                     float g[8][VEC];
                     fm_slot_loads<VEC, L, ADDR, 8, 0, FIRST>(ix, rs, src, stride, kb, g);
                     multipliers();
-                    fm_slot_sums<VEC, L, KIND, 8, 0>(mu, g, acc, gw, s2);
+                    fm_slot_sums<VEC, L, KIND, 8, 0>(mu, g, to, to_w, to_2);
                     if (left > 8) {
                         fm_slot_loads<VEC, L, ADDR, 8, 8, FIRST>(ix, rs, src, stride, kb, g);
-                        fm_slot_sums<VEC, L, KIND, 8, 8>(mu, g, acc, gw, s2);
+                        fm_slot_sums<VEC, L, KIND, 8, 8>(mu, g, to, to_w, to_2);
                     }
                 }
             }
@@ -551,13 +582,19 @@ __device__ __forceinline__ void fm_walk(const int32_t* __restrict__ idx, const f
                 float g[4][VEC];
                 fm_slot_loads<VEC, L, ADDR, 4, 0, FIRST>(ix, rs, src, stride, kb, g);
                 multipliers();
-                fm_slot_sums<VEC, L, KIND, 4, 0>(mu, g, acc, gw, s2);
+                fm_slot_sums<VEC, L, KIND, 4, 0>(mu, g, to, to_w, to_2);
                 if constexpr (SMAX == 4 && C == 8) {
                     if (left > 4) {
                         fm_slot_loads<VEC, L, ADDR, 4, 4, FIRST>(ix, rs, src, stride, kb, g);
-                        fm_slot_sums<VEC, L, KIND, 4, 4>(mu, g, acc, gw, s2);
+                        fm_slot_sums<VEC, L, KIND, 4, 4>(mu, g, to, to_w, to_2);
                     }
                 }
+            }
+            if constexpr (APART) {
+#pragma unroll
+                for (int z = 0; z < VEC; ++z) acc[z] += (double)a[z];
+                gw += (double)a_w;
+                s2 += (double)a_2;
             }
         }
         if (!more) break;

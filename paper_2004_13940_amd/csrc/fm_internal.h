@@ -122,6 +122,7 @@ struct LongIndex {
     int32_t* ord_len = nullptr;
     int64_t list_off[FM_XCDS + 1] = {0};
     int64_t list_mid[FM_XCDS] = {0};  // in list x, positions from list_mid[x] on are not panel items
+    bool in_panels = false;         // the full matrix: heavy columns are cut at row panels
     // items of dense-ish columns: positions list_off[FM_XCDS]..nitems of `order`, sorted by row tile
     int64_t tile_rows = 0, ntiles = 0;
     int64_t* tile_ptr = nullptr;    // [ntiles+1] positions in `order`
@@ -465,6 +466,7 @@ struct ColArgs {
     int64_t lin_base, lin_count;   // positions of `order` that are taken in sequence (tile items that are not staged; all of a stratum or batch)
     int32_t xcd_runs;              // the lin items in runs of FM_RUN_BLOCKS workgroups to an XCD, not dealt out one after the other
     int64_t blk_lists, blk_lin, blk_short;  // workgroups of k_cols per role, in this order; then epi.nsums for the sums
+    int32_t long_runs;             // runs are added up in fp64 but for a few entries, see FM_LONG_RUNS
     int32_t nt;                    // gathers of rows that are not used again soon carry the non-temporal hint
     int32_t big;                   // the gathered array is larger than FM_BUF_BYTES
     FmEpilogue epi;

@@ -54,6 +54,7 @@ struct OwnScore {
         a += t.w[0] * x;
         return x;
     }
+    __device__ __forceinline__ void end_round() const {}
 };
 
 // Per-entry work of a refresh: the changes of w_j and of |v_j|^2.
@@ -76,6 +77,7 @@ struct OwnRefresh {
         q += t.d[1] * (x * x);
         return x;
     }
+    __device__ __forceinline__ void end_round() const {}
 };
 
 // Sum over the groups of L lanes that share a row of LS lanes, on every lane.

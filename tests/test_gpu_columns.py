@@ -946,3 +946,41 @@ def test_partial_sums_of_one_stratum_or_batch_are_held_at_a_time():
     assert_close(dev[1].cpu().numpy(), host[1], "w after batches")
     assert_close(dev[2].cpu().numpy().reshape(D, K), host[2], "V after batches")
     m.close()
+
+
+@pytest.mark.parametrize("N,density", [(200_000, 0.05), (200_000, 0.005), (131_072, 0.02), (400_001, 0.0025), (70_000, 0.3)])
+@pytest.mark.parametrize("K", [4, 8, 16, 28, 32, 60, 64, 128, 2])  # packed and planar rows, groups of up to eight lanes and wider ones
+def test_sums_of_long_columns_are_rounded_a_few_times(N, density, K):
+    """Sums of values of one sign whose products are exact: only additions round.  Items of n entries, at least 24 to a column (a
+    panel each, up to 128 entries), are added up in fp32 by at most 16 entries, in fp64 from there on, and rounded once.  With u
+    the rounding of one addition an item is off by u sqrt(1 + 16 / 3 / (n / 16)), the column by sqrt(items) less.  It shows in
+    the share of results that are not the nearest float: sqrt(2 / pi) times that error in units of the last place, where u is
+    0.31 of one (2^-23 / sqrt(12), on the average over the mantissas of partial and final sums).  Single chains of 128 would
+    be at 0.13 to 0.18 in the first case, where the bound is 0.06 to 0.08."""
+    import torch
+    from paper_2004_13940_amd import binding as B
+    rng = np.random.default_rng(N + K)
+    D = 48
+    cols = [np.sort(rng.choice(N, int(N * density), replace=False)) for _ in range(D)]
+    row = np.concatenate(cols)
+    col = np.repeat(np.arange(D, dtype=np.int32), [len(c) for c in cols])
+    order = np.argsort(row, kind="stable")
+    rowptr = np.concatenate([[0], np.cumsum(np.bincount(row, minlength=N))]).astype(np.int64)
+    m = B.Matrix(N, D, rowptr, col[order], np.ones(len(row), np.float32))
+    m.fm_set_tuning(seg=128)  # what matrices of 8e6 entries and more have
+    m.fm_build_csc()
+    G = (rng.random((N, K)) + 0.5).astype(np.float32)
+    zero = torch.zeros(D * K, device="cuda")
+    gV = torch.full((D * K,), float("nan"), device="cuda")
+    print("rounding of long columns", N, density, K, flush=True)
+    m.fm_gradient(B.make_params(K, O.LOSS_SQUARED, 0.0, 0.0, 0.1), torch.full((N,), 2.0 ** -10, device="cuda"), to_dev(G.ravel()),
+                  torch.zeros(D, device="cuda"), zero, grad_V=gV)
+    want = np.stack([G[c].astype(np.float64).sum(0) * 2.0 ** -10 for c in cols]).astype(np.float32)
+    share = float(np.mean(gV.cpu().numpy().reshape(D, K) != want))
+    items = 24 * -(-N * density // (24 * 128))
+    rounds = max(N * density / items / 16, 1.0)
+    want = np.sqrt(2 / np.pi) * 0.31 * np.sqrt((1 + 16 / 3 / rounds) / items)
+    bound = 1.5 * want + 3 * np.sqrt(want / (D * K))  # items are not all of one length; D K results are a sample
+    print("share", share, "bound", bound, flush=True)
+    assert share <= bound
+    m.close()

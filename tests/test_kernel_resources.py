@@ -66,3 +66,9 @@ def test_columns_of_large_aggregates_keep_to_four_wavefronts(kernels):
     few = {n: k[".vgpr_count"] for n, k in kernels.items() if re.search(r"k_colsILi4ELi8ELb[01]ELi[01]ELb1EE", n)}
     assert len(few) == 4, sorted(few)
     assert {n: v for n, v in few.items() if not 512 // 5 < (v + 7) // 8 * 8 <= 512 // 4} == {}
+
+
+def test_wide_groups_with_short_runs_leave_room_for_eight_wavefronts(kernels):
+    wide = {n: k[".vgpr_count"] for n, k in kernels.items() if re.search(r"k_cols_partILi[124]ELi(16|32|64)E", n)}
+    assert len(wide) == 18, sorted(wide)
+    assert {n: v for n, v in wide.items() if v > 64} == {}
