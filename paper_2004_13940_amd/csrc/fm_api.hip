@@ -541,22 +541,22 @@ static int no_half(fm_matrix* m, const fm_params* p)
 // is then a single request.  For larger K a row of G is one or more whole lines by itself.
 static bool packed_exists(const fm_matrix* m, int32_t K) { return m->opt.aux != 1 && K % 4 == 0 && K + 1 <= 32; }
 
-// Which layout a pass takes whose columns gather from so many rows (all of the matrix, a row block, a batch).  At K = 16 a
-// row of G is half a line and a packed row a whole one: planar moves half the bytes, and as long as the multipliers of the
-// rows (4 bytes each) stay in an XCD's L2 beside them, the second request for r is a cheap one.  Packed / planar, us, K = 16:
-// strata of click-style rows 4,700 rows to a block 601 / 519, 75,000 3540 / 2677, 156,250 32200 / 26100, 833,000 3691 / 3472,
-// 1e6 18384 / 16122, text-like 1,562 rows 558 / 493, 500,000 1439 / 1382; batches of 75,000 rows 767 / 684, 156,250 2900 /
-// 2400, 312,500 1175 / 1138, 625,000 1094 / 1099 and 2255 / 2180; full epochs text-like 5e4 rows 60 / 55, 2e5 257 / 239, hashed
-// 1e5 222 / 200, click-style 6e4 71 / 68, 1e5 99 / 112, 1.5e5 133 / 129, 1.8e5 150 / 147, 6e5 502 / 529, 1e7 7120 / 8300.  Any
-// other K packs better: a packed row up to K = 12 is half a line itself (click-style 6e5 rows, K = 8: full epoch 457 / 537,
-// batches 610 / 627, strata 1317 / 1256; K = 12 466 / 557, 652 / 700, 1413 / 1448), and from K = 20 on a planar row straddles
-// lines (K = 20 583 / 663, 870 / 914, 2119 / 2009; K = 28 623 / 753, 929 / 1009, 2113 / 2260).  Where every row stores every
-// column the rows are gathered one after the other, whole lines in any layout, and planar ones are the shorter (tables of 40
-// columns, 1e6 rows, strata K = 8 1066 / 873, K = 20 1979 / 1586, epochs 115 / 112, 118 / 112; 1e5 rows, strata K = 8 189 / 181, K =
-// 28 235 / 232, but K = 4 180 / 189).
-constexpr int64_t FM_PLANAR_ROWS = 200000;                   // full epochs, gradients
-constexpr int64_t FM_PLANAR_ROWS_BATCH = 400000;             // batches: their items are worked on in row order
-constexpr int64_t FM_PLANAR_ROWS_STRATA = int64_t(1) << 20;  // strata: the refresh gains by it too
+// Which layout a pass takes whose columns gather from so many rows (all of the matrix, a batch).  At K = 16 a row of G is half a
+// line and a packed row a whole one: planar moves half the bytes, and as long as the multipliers of the rows (4 bytes each) stay
+// in an XCD's L2 beside them, the second request for r is a cheap one.  Planar over packed, times, K = 16:
+//   full epochs  text-like 1e5 rows 0.93, 2e5 0.92, 3e5 0.90, 4e5 1.06; hashed 1e5 0.88, 2e5 0.92, 4e5 0.98; click-style 1e5 1.02, 1.5e5 0.96,
+//                1.8e5 0.99, 2e5 1.00, 2.2e5 1.06, 2.5e5 1.02, 3e5 1.00, 3.6e5 1.03, 6e5 1.09, 1e7 1.17
+//   batches      click-style 75,000 rows 0.89, 156,250 0.83, 312,500 0.97, 4e5 1.00, 5e5 1.01, 6.7e5 1.04, 1e6 1.05, 2.5e6 1.06; text-like 5e5 1.00, 1e6 1.01
+//   strata       the refresh, which reads and writes rows, gains by it too: click-style 4,700 rows to a block 0.86, 75,000 0.76, 156,250
+//                0.81, 1e6 0.97, 1.5e6 0.94 to 0.97, 3e6 0.98, 4e6 0.99, 5e6 0.99, text-like 1.5e6 0.96: on either side of any line.  A single
+//                block is like a batch: click-style 1.5e5 rows 0.93, 3e5 0.98, 6e5 1.05, 1e6 1.05, 3e6 1.07, text-like 1e5 0.93, 3e5 0.97
+// Other K mostly pack better: a packed row up to K = 12 is half a line itself, and from K = 20 on a planar row straddles lines
+// (click-style, full epochs of 6e5 rows, K = 8 1.18, 12 1.20, 20 1.14, 28 1.21; 16 strata of 1e5 and 6e5 rows and 4 of 2e6, K = 8 1.06, 0.99, 1.06,
+// K = 12 1.07, 1.06, 1.13, K = 20 1.02, 0.95, 1.05, K = 28 1.05, 1.09, 1.17; text-like 2e5 rows, 16 strata, K = 8 1.04, K = 20 0.97).  Where every
+// row stores every column the rows are gathered one after the other, whole lines in any layout, and planar ones are the
+// shorter (tables of 40 columns, 8 strata of 1e6 rows, K = 8 0.82, K = 20 0.80, of 2e5 0.97, K = 28 1.01, K = 4 0.99 to 1.05).
+constexpr int64_t FM_PLANAR_ROWS = 200000;        // full epochs, gradients
+constexpr int64_t FM_PLANAR_ROWS_BATCH = 400000;  // batches, a single block of strata: their items are worked on in row order
 static bool take_packed(const fm_matrix* m, int32_t K, int64_t rows, int64_t planar_rows)
 {
     if (!packed_exists(m, K)) return false;
@@ -1117,7 +1117,10 @@ extern "C" int fm_sgd_epoch(fm_matrix* m, const fm_params* p, const float* y, fl
 
 // All of the strata's calls ask for the layout here: a step goes on from aggregates that fm_stratified_begin left, now or in a
 // graph.
-static bool strata_packed(const fm_matrix* m, int32_t K) { return take_packed(m, K, m->N / m->P, FM_PLANAR_ROWS_STRATA); }
+static bool strata_packed(const fm_matrix* m, int32_t K)
+{
+    return take_packed(m, K, m->N, m->P == 1 ? FM_PLANAR_ROWS_BATCH : INT64_MAX);
+}
 
 extern "C" int fm_stratified_begin(fm_matrix* m, const fm_params* p, const float* y, const float* w0,
                                    const float* w, const float* V, void* hip_stream)
