@@ -1,91 +1,8 @@
-// Builds that fail halfway, on a runtime of which nothing is real: "device" memory is host memory, kernels do nothing, one value
-// read back from the device is 3, longer reads give what is there (zeros).  This program's definitions take the place of the
-// runtime's in the library.  From the call that `fail_from` counts down to on, everything that can fail does.  Prints one line
-// per check that fails, returns how many did.
-#include "fm.h"
+// Builds that fail halfway, on the stub of the runtime.  Prints one line per check that fails, returns how many did.
+#include "library_stub.h"
 
-#include <cstdint>
-#include <cstdio>
-#include <cstdlib>
-#include <cstring>
 #include <functional>
-#include <map>
 #include <vector>
-
-static long fail_from = -1, launches = 0, failed = 0;
-static std::map<void*, size_t> live;
-static int last = 0;
-
-static int can_fail()
-{
-    if (fail_from < 0 || --fail_from >= 0) return last = 0;
-    fail_from = 0;  // and every call from here on
-    ++failed;
-    return last = 2;
-}
-
-struct Dim3 {
-    uint32_t x, y, z;
-};
-extern "C" {
-int hipGetDevice(int* d) { return *d = 0; }
-int hipSetDevice(int) { return 0; }
-int hipGetLastError() { const int e = last; last = 0; return e; }
-const char* hipGetErrorString(int) { return "as the test wants"; }
-int hipMalloc(void** p, size_t n)
-{
-    if (can_fail()) return 2;
-    *p = calloc(n, 1);
-    live[*p] = n;
-    return 0;
-}
-int hipFree(void* p)
-{
-    if (live.erase(p) != 1) printf("freed twice\n"), abort();
-    free(p);
-    return 0;
-}
-int hipHostMalloc(void** p, size_t n, unsigned) { return (*p = calloc(n, 1)) == nullptr; }
-int hipHostFree(void* p) { free(p); return 0; }
-int hipMemcpy(void* d, const void* s, size_t n, int) { memcpy(d, s, n); return 0; }
-int hipMemcpyAsync(void* d, const void* s, size_t n, int kind, void*)
-{
-    if (can_fail()) return 2;
-    const int64_t three = 3;
-    memcpy(d, kind == 2 && n == 8 ? (const void*)&three : s, n);
-    return 0;
-}
-int hipMemsetAsync(void* d, int v, size_t n, void*)
-{
-    if (can_fail()) return 2;
-    memset(d, v, n);
-    return 0;
-}
-int hipDeviceSynchronize() { return 0; }
-int hipStreamSynchronize(void*) { return can_fail(); }
-int hipStreamIsCapturing(void*, int* s) { return *s = 0; }
-int hipFuncSetAttribute(const void*, int, int) { return 0; }
-int hipGetSymbolAddress(void** p, const void*)
-{
-    static char block[1 << 16];
-    *p = block;
-    return 0;
-}
-int __hipPushCallConfiguration(Dim3, Dim3, size_t, void*) { return 0; }
-int __hipPopCallConfiguration(Dim3* g, Dim3* b, size_t* s, void** st)
-{
-    *g = *b = Dim3{1, 1, 1};
-    *s = 0;
-    *st = nullptr;
-    return 0;
-}
-int hipLaunchKernel(const void*, Dim3, Dim3, void**, size_t, void*)
-{
-    if (can_fail()) return 2;
-    ++launches;
-    return 0;
-}
-}
 
 static size_t live_bytes()
 {

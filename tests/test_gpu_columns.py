@@ -252,7 +252,7 @@ def test_gradient_that_forks_for_its_empty_columns_replays_from_a_graph():
 
 
 @pytest.mark.parametrize("side_streams", [0, 1])
-@pytest.mark.parametrize("K,planar", [(4, 0), (4, 1), (8, 0), (12, 0), (12, 1), (16, 0), (16, 1), (20, 1), (28, 0), (60, 0),
+@pytest.mark.parametrize("K,planar", [(4, 0), (4, 1), (8, 0), (12, 0), (12, 1), (16, 0), (16, 1), (16, 2), (20, 1), (28, 0), (60, 0),
                                       (64, 0), (128, 0), (132, 0), (256, 0)])  # every lane count, K that idles lanes
 def test_columns_staged_in_tiles(K, planar, side_streams):
     """Dense-ish columns beside sparse ones over five tiles of 64 rows and a ragged one, through the LDS-staged kernel on the
@@ -290,8 +290,9 @@ def test_columns_staged_in_tiles(K, planar, side_streams):
     m.close()
 
 
-@pytest.mark.parametrize("K", [1, 2, 3, 4, 8, 12, 16, 28, 32])  # every lane count below 16, packed and planar rows
-def test_columns_and_refresh_with_64_bit_addresses(K, monkeypatch):
+@pytest.mark.parametrize("K,packed", [(1, 0), (2, 0), (3, 0), (4, 0), (8, 0), (12, 0), (16, 0), (28, 0), (32, 0),  # every lane count below 16
+                                      (4, 2), (8, 2), (12, 2), (16, 2), (28, 2)])  # packed rows also where planar ones are the default
+def test_columns_and_refresh_with_64_bit_addresses(K, packed, monkeypatch):
     """The same matrices through the form of the walk that large arrays take: slots without an entry read the run's last row
     again, empty runs row 0, and neither may count."""
     from paper_2004_13940_amd import binding as B
@@ -299,6 +300,7 @@ def test_columns_and_refresh_with_64_bit_addresses(K, monkeypatch):
 
     def wide(m, *a, **k):
         m.fm_set_option(B.FM_OPT_WIDE_ADDRESSES, 1)
+        m.fm_set_option(B.FM_OPT_AUX_PLANAR, packed)
         build(m, *a, **k)
 
     monkeypatch.setattr(B.Matrix, "fm_build_csc", wide)
@@ -346,11 +348,12 @@ def test_gathers_at_offsets_of_two_to_four_gigabytes(N, K):
 
 
 @pytest.mark.parametrize("N,D,K", [(1, 1, 1), (31, 5, 4), (32, 32, 32), (33, 33, 33), (127, 31, 28), (129, 64, 3),
-                                   (4097, 63, 17), (1000, 8, 64), (98_400, 33, 12), (99_000, 17, 40), (40_003, 64, 64)])
+                                   (4097, 63, 17), (1000, 8, 64), (98_400, 33, 12), (99_000, 17, 40), (40_003, 64, 64), (33, 9, 8), (70, 40, 20)])
 def test_dense_kernels_at_the_edges_of_their_tiles(N, D, K):
     """Tables whose rows, columns and latent dimensions end just before, at and after a tile of 32, one tile to a wavefront
     and more than eight (where its sums are set aside); packed and planar aggregates.  Forward, metrics, gradient, an epoch
-    and a mini-batch epoch against the oracle; without the dense kernels the same entry points meet it too."""
+    and a mini-batch epoch against the oracle; without the dense kernels, and with packed rows where planar ones are the default
+    (K = 8 and more), the same entry points meet it too."""
     import torch
     from paper_2004_13940_amd import binding as B
     rng = np.random.default_rng(7900 + N + 100 * D + K)
@@ -365,10 +368,11 @@ def test_dense_kernels_at_the_edges_of_their_tiles(N, D, K):
     l, r = O.loss_multiplier(O.LOSS_LOGISTIC, 1.0 / N, yhat, y)
     want = dict(yhat=yhat, a=a, G=G, q=q, r=r)
     batches = min(N, 3)
-    for dense in (1, 0):
-        print("dense tiles", N, D, K, dense, flush=True)
+    for dense, packed in ((1, 0), (0, 0)) + (((1, 2), (0, 2)) if K % 4 == 0 and 8 <= K <= 28 else ()):
+        print("dense tiles", N, D, K, dense, packed, flush=True)
         m = B.Matrix(N, D, rowptr, col, val)
         m.fm_set_option(B.FM_OPT_DENSE_ROWS, dense)
+        m.fm_set_option(B.FM_OPT_AUX_PLANAR, packed)
         p = B.make_params(K, O.LOSS_LOGISTIC, 0.01, 0.02, 0.5, 1.0 / N)
         d_w0, d_w, d_V = dev_params(w0, w, V)
         d_y = to_dev(y)
@@ -983,4 +987,43 @@ def test_sums_of_long_columns_are_rounded_a_few_times(N, density, K):
     bound = 1.5 * want + 3 * np.sqrt(want / (D * K))  # items are not all of one length; D K results are a sample
     print("share", share, "bound", bound, flush=True)
     assert share <= bound
+    m.close()
+
+
+@pytest.mark.parametrize("call,N,parts", [("batches", 400_000, 1), ("batches", 400_001, 1), ("strata", 400_000, 1), ("strata", 400_001, 1),
+                                          ("strata", 2_200_000, 2)])
+def test_layouts_where_their_rules_change(call, N, parts):
+    """K = 16: batches and a single block of strata of up to 400,000 rows planar, larger ones packed; several blocks planar at any size."""
+    import torch
+    from paper_2004_13940_amd import binding as B
+    rng = np.random.default_rng(N)
+    D, K, row = 30, 16, 2
+    col = (np.arange(row) * (D // row) + rng.integers(0, D // row, (N, row))).astype(np.int32).ravel()
+    rowptr, val = np.arange(N + 1, dtype=np.int64) * row, rng.standard_normal(N * row).astype(np.float32)
+    y = np.where(rng.random(N) < 0.5, 1.0, -1.0).astype(np.float32)
+    w, V = (rng.standard_normal(D) * 0.2).astype(np.float32), (rng.standard_normal((D, K)) * 0.1).astype(np.float32)
+    m = B.Matrix(N, D, rowptr, col, val)
+    m.fm_build_csc()
+    p = B.make_params(K, O.LOSS_LOGISTIC, 0.01, 0.02, 0.5, 1.0 / N, 1)
+    kw = dict(loss=O.LOSS_LOGISTIC, s=1.0 / N, lambda_w=0.01, lambda_v=0.02, eta=0.5)
+    X = O.make_matrix(N, D, rowptr, col, val)
+    dev, d_y = dev_params(np.float32(0.1), w, V), to_dev(y)
+    print("layouts at their lines", call, N, parts, flush=True)
+    if call == "batches":
+        m.fm_partition_batches(parts)
+        m.fm_minibatch_epoch(p, d_y, *dev)
+        _, G, _, yhat = O.forward(X, 0.1, w, V)  # one batch: the aggregates that the only step was taken from
+        host = O.minibatch_epoch(X, y, 0.1, w, V, B=parts, update_w0=True, reg_share=True, **kw)[:3]
+    else:
+        m.fm_partition(parts)
+        m.fm_stratified_epoch(p, d_y, *dev)
+        held = {}  # the aggregates as the last stratum refreshed them
+        host = O.stratified_epoch(X, y, 0.1, w, V, P=parts, update_w0=True, final_objective=False,
+                                  on_stratum=lambda s, st: held.update(G=st["G"].copy()), **kw)[:3]
+        G = held["G"]
+    G_dev = torch.full((N * K,), float("nan"), device="cuda")
+    m.fm_get_aux(K, G=G_dev)
+    assert_close(G_dev.cpu().numpy().reshape(N, K), G, "G")
+    assert_close(dev[1].cpu().numpy(), host[1], "w")
+    assert_close(dev[2].cpu().numpy().reshape(D, K), host[2], "V")
     m.close()

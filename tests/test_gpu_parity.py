@@ -736,8 +736,9 @@ def test_every_option_gives_the_oracle_result(options, idx, scale):
     host = _run_stratified_epochs(B, wl, m, p, X, dev, host, 2)
     # switching the aggregate layout on a live handle: the next pass allocates the other layout
     if "FM_OPT_AUX_PLANAR" in options:
-        m.fm_set_option(B.FM_OPT_AUX_PLANAR, 0)
-        host = _run_stratified_epochs(B, wl, m, p, X, dev, host, 1)
+        for layout in (0, 2, 1):  # as the sizes say (planar here), packed, planar
+            m.fm_set_option(B.FM_OPT_AUX_PLANAR, layout)
+            host = _run_stratified_epochs(B, wl, m, p, X, dev, host, 1)
     m.close()
     m2, _, _ = _run_minibatch_epochs(B, wl, 5, 1, update_w0=bool(wl.update_w0), setup=setup)
     m2.close()
@@ -790,9 +791,9 @@ def test_random_shapes_through_every_epoch_kind():
 
 
 def test_replayed_stratified_epochs_stay_correct_between_other_work():
-    """With P >= 16 and small strata fm_stratified_epoch is captured once per set of arguments and
-    replayed; every replay is checked against the oracle, with other calls of the library (another
-    handle's epoch, a forward of this handle, a synchronisation) between the replays."""
+    """With FM_OPT_GRAPH 2 fm_stratified_epoch is captured once per set of arguments and replayed; every replay is checked
+    against the oracle, with other calls of the library (another handle's epoch, a forward of this handle, a synchronisation)
+    between the replays.  That a graph is used at all is seen on the stub of the runtime (graph_check)."""
     import torch
     B = _B()
     wl = make_config(3, scale=0.1)
@@ -806,7 +807,7 @@ def test_replayed_stratified_epochs_stay_correct_between_other_work():
     m = B.Matrix(wl.N, wl.D, wl.rowptr, wl.col, wl.val)
     m.fm_build_csc()
     m.fm_partition(wl.P)
-    assert wl.P >= 16
+    m.fm_set_option(B.FM_OPT_GRAPH, 2)
     p = B.make_params(wl.K, wl.loss, wl.lambda_w, wl.lambda_v, wl.eta, wl.loss_scale, 1)
     d_w0, d_w, d_V = dev_params(wl.w0, wl.w, wl.V)
     d_y = to_dev(wl.y)
