@@ -47,16 +47,13 @@ def csrc_sha256():
 
 def column_classes(N, K, nnz):
     """(seg, tile_rows, tile_min, tile_seg) by the rules of the library (fm_item_length, fm_tile_shape)."""
+    fill = 8 * 16 * 256
     seg = 32
-    while seg < 256 and nnz // (2 * seg) >= 8 * 16 * 256:
+    while seg < 256 and nnz // (2 * seg) >= (fill if seg < 128 else 2 * fill):
         seg *= 2
     if K % 4 == 0 and K <= 16 and N >= 1 << 21:
         return seg, 1024, 12, 512
-    if N < 1 << 17:
-        return seg, 128, 0, 128
-    if N < 1 << 18:
-        return seg, 256, 4, 256
-    return seg, 512, 8, 256
+    return seg, 512, 0 if N < 360_000 else 8, 256
 
 
 def algorithmic_bytes(N, D, K, counts):

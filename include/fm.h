@@ -228,8 +228,9 @@ int fm_stratified_step(fm_matrix* m, const fm_params* p, int32_t s, const float*
 int fm_stratified_end(fm_matrix* m, const fm_params* p, float* w0, void* hip_stream);
 
 /* Copy the aggregates the handle holds (after fm_sgd_epoch, fm_minibatch_epoch or any stratified
- * call; a and q only after a stratified call; nothing after fm_evaluate: FM_ESTATE) into caller
- * DEVICE arrays; any may be NULL. */
+ * call; after fm_gradient with K a multiple of 4 up to 28, unless FM_OPT_AUX_PLANAR is 1: the r and G it was
+ * given; a and q only after a stratified call; nothing after fm_evaluate: FM_ESTATE) into caller
+ * DEVICE arrays; any may be NULL.  In a captured call: those that are held when the graph runs. */
 int fm_get_aux(const fm_matrix* m, float* a /*N*/, float* G /*N*K*/, float* q /*N*/, float* r /*N*/,
                void* hip_stream);
 
@@ -258,8 +259,8 @@ int fm_profile_read(fm_matrix* m, int64_t* launches /*HOST nk*/, double* total_m
  *                        differ by the part eta lambda of the parameters that those steps are, in the
  *                        scores, not only by rounding.
  *   FM_OPT_GRAPH         fm_stratified_epoch replayed from a captured HIP graph, which takes one call of the host
- *                        instead of two or three a stratum: 2 always; 1 (default) where the replay is the faster
- *                        one, which it is nowhere; 0 never.
+ *                        instead of two or three a stratum: 2; 0 and 1 (default): enqueued directly, which was the
+ *                        faster way wherever both were measured.
  *   FM_OPT_DENSE_ROWS    1: a matrix in which every row stores all D columns (D and K up to 64) takes dense
  *                        kernels on the matrix cores for fm_forward, fm_evaluate, fm_gradient, fm_sgd_epoch and
  *                        fm_minibatch_epoch (G = XV and X^T(r.G) as fp32 contractions; the column indices are

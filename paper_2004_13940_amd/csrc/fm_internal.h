@@ -44,7 +44,7 @@ struct FmOptions {
     int aux = 0;               // layout of the aggregates: 0 as take_packed chooses, 1 planar, 2 packed where that exists
     bool side_streams = true;  // column kernels that touch disjoint columns overlap on internal side streams
     bool lazy_reg = true;      // regulariser-only steps of a stratified or mini-batch epoch are postponed
-    int graph = 1;             // stratified epoch from a captured graph: 2 always; 0, 1 never (nowhere the faster one)
+    int graph = 1;             // stratified epoch from a captured graph: 2; directly: 0, 1
     int dense_rows = 2;        // matrices that store every column in every row take the dense (MFMA) kernels: 0 never, 1 always,
                                // 2 where fm_dense_takes says that they are the faster ones
     bool wide_addresses = false;  // gathers take 64-bit addresses at any size
@@ -99,7 +99,7 @@ constexpr int32_t FM_WHOLE_WAVE = 256;
 
 // Work items for columns longer than `seg` entries (of one matrix, or of all strata
 // concatenated).  Offsets in item_beg are global offsets into the entry arrays.  Items of
-// a column are numbered consecutively (long_first); partial sums live at the item id.
+// a column are numbered consecutively (long_first); partial sums live at the item id, counted from the launch's first item.
 struct LongIndex {
     int64_t nlong = 0, nitems = 0;
     int32_t* long_col = nullptr;    // [nlong] column id
@@ -216,10 +216,11 @@ struct fm_matrix {
     bool is_dense = false;
     float* dV = nullptr;    // [D*K] last step's change of V
     float2* dwn = nullptr;  // [D] (change of w_j, change of |v_j|^2)
-    float* part = nullptr;      // [max items * part_stride(K)] partial sums of the items, see fm_part_stride
+    float* part = nullptr;      // [items of the largest launch * part_stride(K)] partial sums, see fm_part_stride
     float* row_part = nullptr;  // [2 * row blocks]: loss, sum r
     double* scal = nullptr;     // device scalars: 0 loss, 1 sum r, 2 |w|^2, 3 |V|^2
-    double* h_scal = nullptr;   // pinned: 8 doubles that mirror scal, then one FmCheck per workgroup of k_check_csr
+    double* h_scal = nullptr;   // pinned: 8 doubles that mirror scal, then one FmCheck per workgroup of k_check_csr, what
+                                // fm_evaluate's workgroups leave, or what a build moves (fm_read_later, fm_send)
     bool aux_full = false;      // a, q valid (not only G, r)
     bool aux_held = false;      // the aggregate rows hold the result of a pass (fm_get_aux may read them)
     int32_t* aux_rows = nullptr;  // device, behind scal: 1 where they are packed rows, 0 where planar; see fm_unpack_aux
