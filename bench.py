@@ -300,7 +300,7 @@ def traffic_from(fetch_csv, write_csv, name):
         sys.exit("no k_probe_copy dispatch in the counter file: run bench.py with --copy-calibration")
     f_scale = (COPY_BYTES / 1024.0) / fetch[copy[0]]
     w_scale = (COPY_BYTES / 1024.0) / write[copy[0]]
-    groups = {"rows_forward": r"^k_rows<\d+, \d+, 0, \d+>", "cols": r"^k_cols(_empty)?<", "cols_tile": r"^k_cols_tile<",
+    groups = {"rows_forward": r"^k_rows<\d+, \d+, 0, \d+>", "cols": r"^k_cols(_empty|_part)?<", "cols_tile": r"^k_cols_tile<",
               "cols_finish": r"^k_cols_finish<", "reduce": r"^k_(reduce|reg|epi)_"}
     out = {"_kind": TRAFFIC_KIND, "_csrc_sha256": csrc_sha256(), "_fetch_scale": f_scale, "_write_scale": w_scale,
            "_copy_reads_KiB": fetch[copy[0]], "_copy_writes_KiB": write[copy[0]]}
