@@ -564,6 +564,11 @@ static bool take_packed(const fm_matrix* m, int32_t K, int64_t rows, int64_t pla
     return m->is_dense && K >= 8 ? false : K != 16 || rows > planar_rows;
 }
 
+// Both layouts may come up on this handle: a forward pass then leaves the one it took in the word that fm_get_aux reads.  Options
+// that change the answer, and another K, drop the aggregates with it.
+static bool packed_possible(const fm_matrix* m, int32_t K) { return take_packed(m, K, 1, 0); }
+static int32_t* layout_word(const fm_matrix* m, int32_t K) { return packed_possible(m, K) ? m->aux_rows : nullptr; }
+
 static int64_t packed_stride(int32_t K) { return ((int64_t)K + 3 + 15) / 16 * 16; }
 
 static int64_t whole_lines(int64_t floats) { return (floats + 31) / 32 * 32; }
@@ -722,7 +727,7 @@ static void aux_outputs(fm_matrix* m, int32_t K, RowArgs& A, bool with_aq, bool 
 {
     const FmAux x = fm_aux_layout(m, K, packed);
     A.whole_rows = packed ? 1 : 0;  // never leave a line partly written
-    A.aux_rows = m->aux_rows;
+    A.aux_rows = layout_word(m, K);
     A.G = x.G;
     A.gs = x.gs;
     A.ss = x.ss;
@@ -1431,6 +1436,7 @@ extern "C" int fm_minibatch_epoch(fm_matrix* m, const fm_params* p, const float*
     };
     int vec = 0, lanes = 0;
     (void)fm_shape_for_K(p->K, &vec, &lanes);  // checked with the parameters
+    int32_t* word = layout_word(m, p->K);        // the first pass writes it for all
     for (int32_t b = 0; b < m->B; ++b) {
         const int64_t r0 = m->h_bb[b], nb = m->h_bb[b + 1] - r0;
         RowArgs R;
@@ -1453,7 +1459,8 @@ extern "C" int fm_minibatch_epoch(fm_matrix* m, const fm_params* p, const float*
             R.as = x.as;
             R.r = x.r + r0 * x.ss;
             R.whole_rows = packed ? 1 : 0;
-            R.aux_rows = m->aux_rows;
+            R.aux_rows = word;
+            word = nullptr;
             R.row_part = p->update_w0 ? m->row_part : nullptr;
             R.loss = p->loss;
             R.s = p->loss_scale;
@@ -1510,7 +1517,7 @@ extern "C" int fm_get_aux(const fm_matrix* m, float* a, float* G, float* q, floa
     if ((a != nullptr || q != nullptr) && !m->aux_full)
         return fm_fail(mm, FM_ESTATE, "a and q are only held after a stratified call");
     hipStream_t st = (hipStream_t)hip_stream;
-    FM_TRY(fm_unpack_aux(mm, packed_exists(m, m->wsK), a, G, q, r, st));
+    FM_TRY(fm_unpack_aux(mm, packed_possible(m, m->wsK), a, G, q, r, st));
     return FM_OK;
 }
 

@@ -223,7 +223,7 @@ struct fm_matrix {
                                 // fm_evaluate's workgroups leave, or what a build moves (fm_read_later, fm_send)
     bool aux_full = false;      // a, q valid (not only G, r)
     bool aux_held = false;      // the aggregate rows hold the result of a pass (fm_get_aux may read them)
-    int32_t* aux_rows = nullptr;  // device, behind scal: 1 where they are packed rows, 0 where planar; see fm_unpack_aux
+    int32_t* aux_rows = nullptr;  // device, behind scal: 1 where they are packed rows, 0 where planar; see layout_word
     // side streams so that the LDS-bound and the memory-bound column kernels overlap
     hipStream_t side1 = nullptr, side2 = nullptr;
     hipEvent_t ev_fork = nullptr, ev_join1 = nullptr, ev_join2 = nullptr;
@@ -466,8 +466,8 @@ struct ColArgs {
     const int64_t* tile_ptr;
     int64_t lin_base, lin_count;   // positions of `order` that are taken in sequence (tile items that are not staged; all of a stratum or batch)
     int32_t xcd_runs;              // the lin items in runs of FM_RUN_BLOCKS workgroups to an XCD, not dealt out one after the other
-    int64_t blk_lists, blk_lin, blk_short;  // workgroups of k_cols per role, in this order; then epi.nsums for the sums
     int32_t long_runs;             // runs are added up in fp64 but for a few entries, see FM_LONG_RUNS
+    int64_t blk_lists, blk_lin, blk_short;  // workgroups of k_cols per role, in this order; then epi.nsums for the sums
     int32_t nt;                    // gathers of rows that are not used again soon carry the non-temporal hint
     int32_t big;                   // the gathered array is larger than FM_BUF_BYTES
     FmEpilogue epi;
@@ -498,8 +498,8 @@ struct DenseArgs {
     float *yhat, *a, *G, *q, *r;  // forward: nullable outputs; gradient alone: G and r are read
     int64_t gs, ss, as;           // floats between rows of G, of r, of a and q
     int32_t whole_rows;           // forward: packed aggregate rows [G | r | a | q | pad] go out whole
-    int32_t* aux_rows;            // forward into the handle's aggregates: takes whole_rows; nullable
     int32_t loss;
+    int32_t* aux_rows;            // forward into the handle's aggregates: takes whole_rows; nullable
     float s;
     float* row_part;    // forward, nullable: [2 * nchunks] loss and sum of r per workgroup
     double* eval_part;  // forward alone, nullable: [3 * nchunks] sums of losses, squared errors and correct signs

@@ -914,6 +914,39 @@ def test_gradient_leaves_what_it_was_given_in_the_aggregates(N, D, row, K, optio
     m.close()
 
 
+@pytest.mark.parametrize("N,batches", [(3, 5), (3, 1), (700, 3)])
+@pytest.mark.parametrize("K", [4, 8, 32])
+@pytest.mark.parametrize("dense", [0, 1])
+def test_batches_of_a_table_leave_their_layout(N, batches, K, dense):
+    """K = 4: gradients of the dense kernels keep planar rows, batches packed ones, and the first pass over rows writes the word
+    for all, which is not the first batch's where that is empty.  K = 8 and 32: planar always, no word."""
+    import torch
+    from paper_2004_13940_amd import binding as B
+    rng = np.random.default_rng(8500 + N + K)
+    D = 5
+    rowptr, col = np.arange(N + 1, dtype=np.int64) * D, np.tile(np.arange(D, dtype=np.int32), N)
+    val = rng.standard_normal(N * D).astype(np.float32)
+    y = rng.standard_normal(N).astype(np.float32)
+    w, V = (rng.standard_normal(D) * 0.2).astype(np.float32), (rng.standard_normal((D, K)) * 0.1).astype(np.float32)
+    _, wantG, _, yhat = O.forward(O.make_matrix(N, D, rowptr, col, val), 0.1, w, V)
+    wantr = O.loss_multiplier(O.LOSS_SQUARED, 1.0 / N, yhat, y)[1]
+    m = B.Matrix(N, D, rowptr, col, val)
+    m.fm_set_option(B.FM_OPT_DENSE_ROWS, dense)
+    m.fm_build_csc()
+    m.fm_partition_batches(batches)
+    p = B.make_params(K, O.LOSS_SQUARED, 0.0, 0.0, 0.0, 1.0 / N, 0)  # steps of length zero
+    for turn in range(2):
+        params = dev_params(np.float32(0.1), w, V)
+        m.fm_gradient(p, to_dev(rng.standard_normal(N)), to_dev(rng.standard_normal(N * K)), *params[1:],
+                      grad_w=torch.empty(D, device="cuda"), grad_V=torch.empty(D * K, device="cuda"))
+        m.fm_minibatch_epoch(p, to_dev(y), *params)
+        G, r = torch.empty(N * K, device="cuda"), torch.empty(N, device="cuda")
+        m.fm_get_aux(K, G=G, r=r)
+        assert_close(G.cpu().numpy().reshape(N, K), wantG, "G")
+        assert_close(r.cpu().numpy(), wantr, "r")
+    m.close()
+
+
 def test_partial_sums_of_one_stratum_or_batch_are_held_at_a_time():
     """2,000 columns times strata of two items each where all columns have 65,000 as a whole: the workspace has rows for the
     larger of one stratum's and the whole matrix's items, and strata that reuse the rows step like the oracle's."""
